@@ -24,6 +24,7 @@
 //
 // f32: a plain LDS-tiled FMA kernel (small shapes).
 #include "dass_internal.h"
+#include "tile_order.h"
 
 #include <type_traits>
 
@@ -370,8 +371,7 @@ template <int ACT, int EPI>
 __global__ __launch_bounds__(256) void calib_pipe64_kernel(
     const uint16_t *__restrict__ X, int64_t T, int64_t ldx, const uint16_t *__restrict__ Wg,
     const uint16_t *__restrict__ Wu, int64_t ldw, int64_t d, int64_t d_int,
-    float *__restrict__ sumsq, uint16_t *__restrict__ out, int64_t ldo, int64_t tiles_t, int64_t tiles_n,
-    int super_rows)
+    float *__restrict__ sumsq, uint16_t *__restrict__ out, int64_t ldo, const TileOrder order)
 {
     constexpr int BM = P_BM, BN = P_BN, BK = 64, WN = 2;
     constexpr int BN_TILE = EPI == kEpiGemm ? 2 * BN : BN;   // rows of W (output columns) per tile
@@ -383,29 +383,10 @@ __global__ __launch_bounds__(256) void calib_pipe64_kernel(
 
     extern __shared__ __attribute__((aligned(1024))) char lds64[];   // P64_LDS bytes
 
-    // ---- tile assignment.  Consecutive workgroup ids go to different XCDs (8 of them, each
-    // with its own L2).  The tile grid is cut into patches of 4 token tiles x 8 neuron tiles; an
-    // XCD's 32 concurrent workgroups take one patch, so its L2 serves all but 3/16 of their reads.
-    // Patches are dealt round-robin to the XCDs from a list ordered so that the 8 patches in
-    // flight share data through the memory-side cache:
-    //   super_rows = 1: token-major.  The 8 patches lie in one row of patches: X is fetched
-    //     from HBM by one XCD and found in the cache by the others, and the weights stay
-    //     cached from one row to the next as long as both matrices fit (measured: +5 % over
-    //     giving each XCD its own band of neurons).
-    //   super_rows = R > 1, for weights too large to stay cached: rows of patches are taken R
-    //     at a time, and inside such a super-row the patch columns are outermost.  The 8 patches
-    //     share one patch column of the weights, fetched once per super-row, and the super-row's
-    //     X (R x 8 MB at d = 4096) stays cached while the columns sweep past.
-    constexpr int PT = 4, PN = 8;
-    const int64_t np_n = (tiles_n + PN - 1) / PN;
-    const int64_t idx = blockIdx.x / 8, within = idx % (PT * PN);
-    const int64_t patch = (idx / (PT * PN)) * 8 + blockIdx.x % 8;
-    const int64_t sr = patch / (np_n * super_rows), rem = patch % (np_n * super_rows);
-    const int64_t prow = sr * super_rows + rem % super_rows, pcol = rem / super_rows;
-    const int64_t tile_t = prow * PT + within / PN, tile_n = pcol * PN + within % PN;
-    if (tile_t >= tiles_t || tile_n >= tiles_n)
+    uint32_t tile_t, tile_n;   // tile_order.h
+    if (!tile_of_block(order, blockIdx.x, tile_t, tile_n))
         return;
-    const int64_t t0 = tile_t * BM, n0 = tile_n * BN_TILE;
+    const int64_t t0 = (int64_t)tile_t * BM, n0 = (int64_t)tile_n * BN_TILE;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -806,50 +787,41 @@ static void launch_mfma(int act, dim3 grid, hipStream_t stream, const uint16_t *
 }
 
 template <int ACT, int EPI>
-static hipError_t launch_pipe64_act(dim3 grid, hipStream_t stream, const uint16_t *X, int64_t T, int64_t ldx,
+static hipError_t launch_pipe64_act(hipStream_t stream, const uint16_t *X, int64_t T, int64_t ldx,
                                     const uint16_t *Wg, const uint16_t *Wu, int64_t ldw, int64_t d, int64_t d_int,
-                                    float *sumsq, uint16_t *out, int64_t ldo, int64_t tiles_t, int64_t tiles_n,
-                                    int super_rows)
+                                    float *sumsq, uint16_t *out, int64_t ldo, const TileOrder &order)
 {
     // the kernel's ring takes all 160 KB of LDS, more than a launch gets without asking
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(calib_pipe64_kernel<ACT, EPI>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, P64_LDS);
     if (e != hipSuccess)
         return e;
-    hipLaunchKernelGGL((calib_pipe64_kernel<ACT, EPI>), grid, dim3(256), P64_LDS, stream, X, T, ldx, Wg, Wu, ldw, d,
-                       d_int, sumsq, out, ldo, tiles_t, tiles_n, super_rows);
+    hipLaunchKernelGGL((calib_pipe64_kernel<ACT, EPI>), dim3(order.blocks), dim3(256), P64_LDS, stream, X, T, ldx, Wg,
+                       Wu, ldw, d, d_int, sumsq, out, ldo, order);
     return hipSuccess;
 }
 
 template <int EPI>
-static hipError_t launch_pipe64(int act, dim3 grid, hipStream_t stream, const uint16_t *X, int64_t T, int64_t ldx,
+static hipError_t launch_pipe64(int act, hipStream_t stream, const uint16_t *X, int64_t T, int64_t ldx,
                                 const uint16_t *Wg, const uint16_t *Wu, int64_t ldw, int64_t d, int64_t d_int,
-                                float *sumsq, uint16_t *out, int64_t ldo, int64_t tiles_t, int64_t tiles_n,
-                                int super_rows)
+                                float *sumsq, uint16_t *out, int64_t ldo, const TileOrder &order)
 {
     switch (act) {
     case DASS_ACT_SILU:
-        return launch_pipe64_act<DASS_ACT_SILU, EPI>(grid, stream, X, T, ldx, Wg, Wu, ldw, d, d_int, sumsq, out, ldo,
-                                                     tiles_t, tiles_n, super_rows);
+        return launch_pipe64_act<DASS_ACT_SILU, EPI>(stream, X, T, ldx, Wg, Wu, ldw, d, d_int, sumsq, out, ldo, order);
     case DASS_ACT_GELU_TANH:
-        return launch_pipe64_act<DASS_ACT_GELU_TANH, EPI>(grid, stream, X, T, ldx, Wg, Wu, ldw, d, d_int, sumsq, out,
-                                                          ldo, tiles_t, tiles_n, super_rows);
+        return launch_pipe64_act<DASS_ACT_GELU_TANH, EPI>(stream, X, T, ldx, Wg, Wu, ldw, d, d_int, sumsq, out, ldo, order);
     case DASS_ACT_GELU_ERF:
-        return launch_pipe64_act<DASS_ACT_GELU_ERF, EPI>(grid, stream, X, T, ldx, Wg, Wu, ldw, d, d_int, sumsq, out,
-                                                         ldo, tiles_t, tiles_n, super_rows);
+        return launch_pipe64_act<DASS_ACT_GELU_ERF, EPI>(stream, X, T, ldx, Wg, Wu, ldw, d, d_int, sumsq, out, ldo, order);
     default:
-        return launch_pipe64_act<DASS_ACT_RELU, EPI>(grid, stream, X, T, ldx, Wg, Wu, ldw, d, d_int, sumsq, out, ldo,
-                                                     tiles_t, tiles_n, super_rows);
+        return launch_pipe64_act<DASS_ACT_RELU, EPI>(stream, X, T, ldx, Wg, Wu, ldw, d, d_int, sumsq, out, ldo, order);
     }
 }
 
-// Grid of the pipelined kernels: whole 4 x 8 patches of tiles dealt to the 8 XCDs, rows of
-// patches in groups of `super_rows`.  Returns 0 when one launch cannot hold it.
-static int64_t pipe_grid(int64_t tiles_t, int64_t tiles_n, int super_rows)
+// Whether `matrices` bf16 matrices of this size stay in the 256 MB memory-side cache.
+static bool fits_memory_cache(int64_t matrices, int64_t rows, int64_t cols)
 {
-    const int64_t patches = ((tiles_t + 3) / 4 + super_rows - 1) / super_rows * super_rows * ((tiles_n + 7) / 8);
-    const int64_t blocks = (patches + 7) / 8 * 8 * 32;
-    return blocks > 0x7fffffffLL ? 0 : blocks;
+    return matrices * rows * cols * 2 <= (256LL << 20);
 }
 
 }  // namespace dass
@@ -898,12 +870,11 @@ extern "C" dass_status dass_calib_norms(const void *X, int64_t T, int64_t ldx, c
     const int64_t tiles_t = bf16 ? (T + BM - 1) / BM : (T + F_BM - 1) / F_BM;
     const int64_t tiles_n = bf16 ? (d_int + BN - 1) / BN : (d_int + F_BN - 1) / F_BN;
     // calib_pipe64_kernel: d a multiple of its 64-column slab, and 32-bit byte offsets inside a
-    // tile's rows.  Its grid is whole 4 x 8 patches of tiles dealt to the 8 XCDs, rows of patches in
-    // groups of 8 when Wgate + Wup exceed the 256 MB memory-side cache (see the kernel).
+    // tile's rows.
     const bool pipe64 = bf16 && d % 64 == 0 && (int64_t)BM * ldx * 2 < 0x7fffffffLL &&
                         (int64_t)BN * ldw * 2 < 0x7fffffffLL;
-    const int super_rows = 2 * d_int * d * 2 > (256LL << 20) ? 8 : 1;
-    const int64_t blocks = pipe64 ? pipe_grid(tiles_t, tiles_n, super_rows)
+    const TileOrder order = make_tile_order(tiles_t, tiles_n, fits_memory_cache(2, d_int, d));
+    const int64_t blocks = pipe64 ? order.blocks
                            : bf16 ? (tiles_t * tiles_n + 7) / 8 * 8
                                   : tiles_t * tiles_n;
     if (blocks <= 0 || blocks > 0x7fffffffLL)
@@ -918,11 +889,10 @@ extern "C" dass_status dass_calib_norms(const void *X, int64_t T, int64_t ldx, c
             return s;
     }
     if (pipe64) {
-        const hipError_t e = launch_pipe64<kEpiNorms>((int)act, dim3((unsigned)blocks), stream,
-                                                      static_cast<const uint16_t *>(X), T, ldx,
+        const hipError_t e = launch_pipe64<kEpiNorms>((int)act, stream, static_cast<const uint16_t *>(X), T, ldx,
                                                       static_cast<const uint16_t *>(Wgate),
                                                       static_cast<const uint16_t *>(Wup), ldw, d, d_int, sumsq,
-                                                      nullptr, 0, tiles_t, tiles_n, super_rows);
+                                                      nullptr, 0, order);
         if (e != hipSuccess)
             return fail(DASS_ERR_HIP, "%s: cannot reserve %d bytes of LDS: %s", fn, P64_LDS, hipGetErrorString(e));
     } else if (bf16) {
@@ -997,15 +967,13 @@ extern "C" dass_status dass_mlp_forward(const void *X, int64_t T, int64_t ldx, c
     // Eq. 2: y = act(X Wgate^T) * (X Wup^T), tiles of 256 tokens x 128 neurons
     {
         const int64_t tiles_n = (d_int + P_BN - 1) / P_BN;
-        const int super_rows = 2 * d_int * d * 2 > (256LL << 20) ? 8 : 1;
-        const int64_t blocks = pipe_grid(tiles_t, tiles_n, super_rows);
-        if (blocks == 0)
+        const TileOrder order = make_tile_order(tiles_t, tiles_n, fits_memory_cache(2, d_int, d));
+        if (order.blocks == 0)
             return fail(DASS_ERR_SHAPE, "%s: too many tiles for one launch; split the tokens", fn);
-        const hipError_t e = launch_pipe64<kEpiGlu>((int)act, dim3((unsigned)blocks), stream,
-                                                    static_cast<const uint16_t *>(X), T, ldx,
+        const hipError_t e = launch_pipe64<kEpiGlu>((int)act, stream, static_cast<const uint16_t *>(X), T, ldx,
                                                     static_cast<const uint16_t *>(Wgate),
                                                     static_cast<const uint16_t *>(Wup), ldw, d, d_int, nullptr, Y,
-                                                    d_int, tiles_t, tiles_n, super_rows);
+                                                    d_int, order);
         if (e != hipSuccess)
             return fail(DASS_ERR_HIP, "%s: cannot reserve %d bytes of LDS: %s", fn, P64_LDS, hipGetErrorString(e));
         const dass_status s = check_launch("GLU kernel");
@@ -1015,13 +983,12 @@ extern "C" dass_status dass_mlp_forward(const void *X, int64_t T, int64_t ldx, c
     // Eq. 3: out = y Wdown^T, tiles of 256 tokens x 256 output features, K = d_int
     {
         const int64_t tiles_n = (d + 2 * P_BN - 1) / (2 * P_BN);
-        const int super_rows = d * d_int * 2 > (256LL << 20) ? 8 : 1;
-        const int64_t blocks = pipe_grid(tiles_t, tiles_n, super_rows);
-        if (blocks == 0)
+        const TileOrder order = make_tile_order(tiles_t, tiles_n, fits_memory_cache(1, d_int, d));
+        if (order.blocks == 0)
             return fail(DASS_ERR_SHAPE, "%s: too many tiles for one launch; split the tokens", fn);
         const hipError_t e = launch_pipe64_act<DASS_ACT_RELU, kEpiGemm>(
-            dim3((unsigned)blocks), stream, Y, T, d_int, static_cast<const uint16_t *>(Wdown), nullptr, ldd, d_int, d,
-            nullptr, static_cast<uint16_t *>(out), ldo, tiles_t, tiles_n, super_rows);
+            stream, Y, T, d_int, static_cast<const uint16_t *>(Wdown), nullptr, ldd, d_int, d,
+            nullptr, static_cast<uint16_t *>(out), ldo, order);
         if (e != hipSuccess)
             return fail(DASS_ERR_HIP, "%s: cannot reserve %d bytes of LDS: %s", fn, P64_LDS, hipGetErrorString(e));
         return check_launch("down-projection kernel");

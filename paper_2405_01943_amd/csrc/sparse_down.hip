@@ -16,6 +16,7 @@
 // a lane fetches 16 bytes of them, not 4.  Rows are XOR-swizzled in 16-byte chunks so that the fragment reads spread
 // over the banks.  One barrier per slab; the loads of slab s + 2 are issued right after it.
 #include "dass_internal.h"
+#include "tile_order.h"
 
 #include <type_traits>
 
@@ -64,20 +65,14 @@ __device__ __forceinline__ uint32_t bf16_pair(float lo, float hi)
 __global__ __launch_bounds__(256) void down_sparse24_kernel(
     const uint16_t *__restrict__ Y, int64_t T, int64_t ldy, const uint16_t *__restrict__ values, int64_t ldv,
     const uint8_t *__restrict__ meta, int64_t ldm, int64_t d, int64_t d_int, uint16_t *__restrict__ out,
-    int64_t ldo, int64_t tiles_t, int64_t tiles_f)
+    int64_t ldo, const TileOrder order)
 {
     extern __shared__ __attribute__((aligned(1024))) char lds[];   // kLds bytes
 
-    // ---- tile assignment: patches of 4 token tiles x 8 feature tiles, dealt to the 8 XCDs
-    // (workgroup b runs on XCD b % 8), as in the calibration kernel
-    constexpr int PT = 4, PF = 8;
-    const int64_t np_f = (tiles_f + PF - 1) / PF;
-    const int64_t idx = blockIdx.x / 8, within = idx % (PT * PF);
-    const int64_t patch = (idx / (PT * PF)) * 8 + blockIdx.x % 8;
-    const int64_t tile_t = (patch / np_f) * PT + within / PF, tile_f = (patch % np_f) * PF + within % PF;
-    if (tile_t >= tiles_t || tile_f >= tiles_f)
+    uint32_t tile_t, tile_f;   // tile_order.h
+    if (!tile_of_block(order, blockIdx.x, tile_t, tile_f))
         return;
-    const int64_t t0 = tile_t * kTN, f0 = tile_f * kFM;
+    const int64_t t0 = (int64_t)tile_t * kTN, f0 = (int64_t)tile_f * kFM;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -325,17 +320,16 @@ extern "C" dass_status dass_down_proj_sparse24(const void *Y, int64_t T, int64_t
         (int64_t)sp::kFM * ldm >= 0x7fffffffLL)
         return fail(DASS_ERR_SHAPE, "%s: rows too long for the tile addressing", fn);
     const int64_t tiles_t = (T + sp::kTN - 1) / sp::kTN, tiles_f = (d + sp::kFM - 1) / sp::kFM;
-    const int64_t patches = (tiles_t + 3) / 4 * ((tiles_f + 7) / 8);
-    const int64_t blocks = (patches + 7) / 8 * 8 * 32;
-    if (blocks > 0x7fffffffLL)
+    const TileOrder order = make_tile_order(tiles_t, tiles_f, true);
+    if (order.blocks == 0)
         return fail(DASS_ERR_SHAPE, "%s: too many tiles for one launch; split the tokens", fn);
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(sp::down_sparse24_kernel),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, sp::kLds);
     if (e != hipSuccess)
         return fail(DASS_ERR_HIP, "%s: cannot reserve %d bytes of LDS: %s", fn, sp::kLds, hipGetErrorString(e));
-    hipLaunchKernelGGL(sp::down_sparse24_kernel, dim3((unsigned)blocks), dim3(256), sp::kLds, stream,
+    hipLaunchKernelGGL(sp::down_sparse24_kernel, dim3(order.blocks), dim3(256), sp::kLds, stream,
                        static_cast<const uint16_t *>(Y), T, ldy, static_cast<const uint16_t *>(values), ldv, meta, ldm,
-                       d, d_int, static_cast<uint16_t *>(out), ldo, tiles_t, tiles_f);
+                       d, d_int, static_cast<uint16_t *>(out), ldo, order);
     return check_launch("sparse down-projection kernel");
 }

@@ -1,0 +1,98 @@
+// Which output tile a workgroup of the matrix-core kernels (calib.hip, sparse_down.hip) computes.
+//
+// Consecutive workgroup ids go to different XCDs (8 of them, each with its own L2), and an XCD
+// runs about 32 of these workgroups at a time, one per compute unit.  Tiles that share rows of X
+// or of W should therefore run on one XCD at one time, and every XCD should get the same number of
+// tiles.  Two orders:
+//
+//   runs (band > 0)   every XCD takes one contiguous run of ceil(N / 8) tiles of a list in which the
+//       token tiles are cut into bands of at most 4 and a band's tiles are listed column of tiles by
+//       column of tiles, so 32 neighbours of the list are about a 4 x 8 patch.  The XCDs get equal
+//       shares whatever the shape of the grid.
+//   patches (band = 0)   the grid is cut into patches of 4 token tiles x 8 column tiles, each taken
+//       by one XCD (its L2 serves 13/16 of their reads), and the patches are dealt round-robin from a
+//       list whose neighbours share data in the memory-side cache:
+//         super_rows = 1: token-major.  The 8 patches in flight lie in one row of patches: X is
+//           fetched from HBM by one XCD and found in that cache by the others, and the weights stay
+//           cached from one row to the next as long as they fit (+5 % over one band of columns per XCD).
+//         super_rows = R > 1, for weights too large to stay cached: R rows of patches at a time, the
+//           patch columns outermost.  The patches in flight share a column of the weights, fetched
+//           once per super-row, whose X (R x 8 MB at d = 4096) stays cached meanwhile (+7 % at 8192
+//           x 28672).  The rows of patches are split evenly over the super-rows: a last super-row of
+//           one or two rows left most XCDs without work.
+//       A whole patch is a whole round of an XCD, so a grid of few patches leaves XCDs idle.
+#pragma once
+
+#include <cstdint>
+
+namespace dass {
+
+struct TileOrder {
+    uint32_t tiles_t, tiles_n;   // the grid of tiles
+    uint32_t band;               // > 0: runs, bands of this many token tiles; 0: patches
+    uint32_t per_xcd;            // runs: tiles of one XCD
+    uint32_t super_rows;         // patches: rows of patches taken together
+    uint32_t blocks;             // workgroups to launch; 0: more than one launch can hold
+};
+
+constexpr uint32_t kPatchT = 4, kPatchN = 8, kXcds = 8, kXcdSlots = kPatchT * kPatchN;
+
+// False: this workgroup has no tile.
+__device__ __forceinline__ bool tile_of_block(const TileOrder &o, uint32_t block, uint32_t &tile_t, uint32_t &tile_n)
+{
+    const uint32_t xcd = block % kXcds, idx = block / kXcds;
+    if (o.band > 0) {
+        const uint32_t lin = xcd * o.per_xcd + idx;
+        if (lin >= o.tiles_t * o.tiles_n)
+            return false;
+        const uint32_t per_band = o.band * o.tiles_n, b = lin / per_band, rem = lin - b * per_band;
+        const uint32_t left = o.tiles_t - b * o.band, rows = left < o.band ? left : o.band;
+        tile_n = rem / rows;
+        tile_t = b * o.band + (rem - tile_n * rows);
+        return true;
+    }
+    const uint32_t np_t = (o.tiles_t + kPatchT - 1) / kPatchT, np_n = (o.tiles_n + kPatchN - 1) / kPatchN;
+    const uint32_t patch = idx / kXcdSlots * kXcds + xcd, within = idx % kXcdSlots;
+    const uint32_t per_super = np_n * o.super_rows, sr = patch / per_super, rem = patch - sr * per_super;
+    if (sr * o.super_rows >= np_t)
+        return false;
+    const uint32_t left = np_t - sr * o.super_rows, rows = left < o.super_rows ? left : o.super_rows;
+    const uint32_t pcol = rem / rows, prow = sr * o.super_rows + (rem - pcol * rows);
+    tile_t = prow * kPatchT + within / kPatchN;
+    tile_n = pcol * kPatchN + within % kPatchN;
+    return pcol < np_n && tile_t < o.tiles_t && tile_n < o.tiles_n;
+}
+
+// Runs up to this many tiles (16 rounds of the chip).  Measured on calib_pipe64_kernel, patches -> runs:
+// 6 x 192 tiles 1390 us (super-rows of 8: two of the eight XCDs had work) -> 345, 366 with even
+// super-rows; 2 x 86 tiles 87 -> 75 us, 4 x 86 170 -> 157; the plain product with 4 x 16 tiles 251 -> 207 us.
+// From about 4000 tiles on either order is within 1 % (22 x the chip: patches 0.5 % ahead), with one
+// exception: an even number of patch columns of which the last is not whole gives the XCDs of one
+// parity all the short patches (12 column tiles, 128 token tiles: 4.6 ms against 3.6).
+constexpr int64_t kRunTiles = 4096;
+
+// weights_cached: the operand that the column tiles read fits the 256 MB memory-side cache.
+inline TileOrder make_tile_order(int64_t tiles_t, int64_t tiles_n, bool weights_cached)
+{
+    TileOrder o = {0, 0, 0, 0, 0, 0};
+    const int64_t np_t = (tiles_t + kPatchT - 1) / kPatchT, np_n = (tiles_n + kPatchN - 1) / kPatchN;
+    const int64_t patches = np_t * np_n, patch_blocks = (patches + kXcds - 1) / kXcds * kXcds * kXcdSlots;
+    if (patch_blocks > 0x7fffffffLL)
+        return o;
+    o.tiles_t = (uint32_t)tiles_t;
+    o.tiles_n = (uint32_t)tiles_n;
+    const int64_t n = tiles_t * tiles_n;
+    const bool short_patches_meet = weights_cached && tiles_n % kPatchN != 0 && np_n % 2 == 0;
+    if (n <= kRunTiles || short_patches_meet) {
+        o.band = (uint32_t)((tiles_t + np_t - 1) / np_t);   // even bands of at most kPatchT
+        o.per_xcd = (uint32_t)((n + kXcds - 1) / kXcds);
+        o.blocks = o.per_xcd * kXcds;
+    } else {
+        const int64_t supers = weights_cached ? np_t : (np_t + 7) / 8;
+        o.super_rows = (uint32_t)((np_t + supers - 1) / supers);
+        o.blocks = (uint32_t)patch_blocks;
+    }
+    return o;
+}
+
+}  // namespace dass

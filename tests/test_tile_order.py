@@ -1,0 +1,67 @@
+"""csrc/tile_order.h on the CPU: every tile of a grid belongs to exactly one workgroup, and no XCD
+(workgroup id mod 8) is given much more than its share of the tiles."""
+import os
+import subprocess
+
+import pytest
+
+HEADER = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2405_01943_amd", "csrc",
+                      "tile_order.h")
+
+DRIVER = r"""
+#include <cstdio>
+#include <cstdlib>
+#include <vector>
+#define __device__
+#define __forceinline__ inline
+#include HEADER
+using namespace dass;
+int main(int, char **argv)
+{
+    const uint32_t tt = atoi(argv[1]), tn = atoi(argv[2]);
+    const TileOrder o = make_tile_order(tt, tn, atoi(argv[3]) != 0);
+    std::vector<int> seen((size_t)tt * tn, 0);
+    uint32_t per_xcd[8] = {0}, worst = 0;
+    for (uint32_t b = 0; b < o.blocks; ++b) {
+        uint32_t t, n;
+        if (!tile_of_block(o, b, t, n))
+            continue;
+        if (t >= tt || n >= tn)
+            return printf("tile %u,%u outside\n", t, n), 1;
+        ++seen[(size_t)t * tn + n];
+        ++per_xcd[b % 8];
+    }
+    for (size_t i = 0; i < seen.size(); ++i)
+        if (seen[i] != 1)
+            return printf("tile %zu taken %d times\n", i, seen[i]), 1;
+    for (uint32_t x : per_xcd)
+        worst = x > worst ? x : worst;
+    printf("%u %u\n", worst, o.band);
+    return 0;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    d = tmp_path_factory.mktemp("tile_order")
+    src, exe = d / "driver.cpp", d / "driver"
+    src.write_text(DRIVER)
+    subprocess.run(["g++", "-O1", "-std=c++17", f'-DHEADER="{HEADER}"', "-o", str(exe), str(src)], check=True)
+    return str(exe)
+
+
+@pytest.mark.parametrize("cached", [0, 1])
+@pytest.mark.parametrize("tiles_t,tiles_n", [
+    (1, 1), (1, 86), (3, 7), (5, 9), (6, 192), (8, 16), (13, 43),   # small grids, ragged bands
+    (64, 64), (64, 65), (47, 88),                                   # either side of the change of order (4096 tiles)
+    (37, 192), (36, 192), (100, 97), (1024, 86), (1024, 12)])       # patches; super-rows that do not divide; short columns
+def test_every_tile_once_and_evenly(driver, tiles_t, tiles_n, cached):
+    out = subprocess.run([driver, str(tiles_t), str(tiles_n), str(cached)], capture_output=True, text=True)
+    assert out.returncode == 0, out.stdout
+    worst, band = (int(v) for v in out.stdout.split())
+    n = tiles_t * tiles_n
+    if band:
+        assert worst == (n + 7) // 8
+    else:   # whole patches of 32 dealt to the XCDs
+        assert worst <= n / 8 * 1.1 + 64
