@@ -2,9 +2,11 @@
 // quantity that the Down-Proj score of Eq. 5 is built like and the paper's main comparison
 // system scores every layer with.  sumsq[j] (+)= sum_t X[t, j]^2, norms = sqrt(sumsq).
 //
-// The pass is bound by reading X once (HBM).  Two kernels, no atomics, so the result does not
-// depend on the order in which workgroups finish:
-//   input_partial_kernel  a thread owns the 16 bytes of one column slot (8 bf16 / 4 f32
+// The pass is bound by reading X once (HBM).  No atomics, so the result does not depend on the
+// order in which workgroups finish.
+//   input_strip_kernel    few tokens: one launch.  A workgroup owns the 64-byte strip of 32 bf16 / 16
+//                         f32 columns and all rows, so nothing has to be added up across workgroups.
+//   input_partial_kernel  many tokens: a thread owns the 16 bytes of one column slot (8 bf16 / 4 f32
 //                         columns) and the rows of one row block; it adds the squares in f32
 //                         and writes its sums to partial[row block][column].
 //   input_reduce_kernel   adds the row blocks' partial sums of a column in f64, in a fixed order,
@@ -14,12 +16,106 @@
 namespace dass {
 
 constexpr int kInBlock = 256;     // threads = column slots per workgroup
-constexpr int kInRows = 512;      // rows per row block
 constexpr int kInUnroll = 8;      // rows in flight per thread
+constexpr int kInMaxRows = 512;   // rows per row block, at most (a multiple of kInUnroll)
+
+// The last step of either path: sumsq (+)= total, norm = sqrt(sumsq).
+__device__ __forceinline__ void finish_column(double total, int64_t j, float *__restrict__ sumsq, int accumulate,
+                                              float *__restrict__ norms)
+{
+    if (accumulate)
+        total += (double)sumsq[j];
+    const float s32 = (float)total;
+    sumsq[j] = s32;
+    if (norms)
+        norms[j] = (float)sqrt((double)s32);
+}
+
+constexpr int kStripThreads = 1024;
+constexpr int kStripSlots = 4;                                // 16-byte slots of a strip: half a memory line
+constexpr int kStripRows = kStripThreads / kStripSlots;       // rows read at once
+
+template <int DT>
+__global__ __launch_bounds__(kStripThreads) void input_strip_kernel(
+    const void *__restrict__ Xv, int64_t T, int64_t ldx, int64_t d, float *__restrict__ sumsq, int accumulate,
+    float *__restrict__ norms)
+{
+    constexpr int EPV = DT == DASS_BF16 ? 8 : 4;
+    constexpr int EB = DT == DASS_BF16 ? 2 : 4;
+    constexpr int COLS = kStripSlots * EPV;
+    __shared__ float part[kStripThreads / 64][COLS];
+    // workgroup b runs on XCD b % 8: the two strips of a 128-byte line go to one XCD, whose L2
+    // then fetches the line once
+    const int64_t xcd = blockIdx.x % 8, i = blockIdx.x / 8;
+    const int64_t strip = (i / 2 * 8 + xcd) * 2 + i % 2;
+    const int64_t c0 = strip * COLS;
+    if (c0 >= d)
+        return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int slot = tid % kStripSlots;
+    const int64_t c = c0 + slot * EPV;
+    float acc[EPV];
+#pragma unroll
+    for (int e = 0; e < EPV; ++e)
+        acc[e] = 0.0f;
+    if (c < d) {
+        const char *X = static_cast<const char *>(Xv) + c * EB;
+        int64_t r = tid / kStripSlots;
+        for (; r + (kInUnroll - 1) * kStripRows < T; r += kInUnroll * kStripRows) {
+            u32x4 v[kInUnroll];
+#pragma unroll
+            for (int k = 0; k < kInUnroll; ++k)
+                v[k] = *reinterpret_cast<const u32x4 *>(X + (r + k * kStripRows) * ldx * EB);
+#pragma unroll
+            for (int k = 0; k < kInUnroll; ++k)
+#pragma unroll
+                for (int e = 0; e < EPV; ++e) {
+                    const float x = elem_of<DT>(v[k], e);
+                    acc[e] = fmaf(x, x, acc[e]);
+                }
+        }
+        // up to kInUnroll - 1 rows left: all loads first, a row past the end repeats row r and adds nothing
+        u32x4 v[kInUnroll - 1];
+#pragma unroll
+        for (int k = 0; k < kInUnroll - 1; ++k)
+            if (r + k * kStripRows < T)
+                v[k] = *reinterpret_cast<const u32x4 *>(X + (r + k * kStripRows) * ldx * EB);
+#pragma unroll
+        for (int k = 0; k < kInUnroll - 1; ++k)
+            if (r + k * kStripRows < T) {
+#pragma unroll
+                for (int e = 0; e < EPV; ++e) {
+                    const float x = elem_of<DT>(v[k], e);
+                    acc[e] = fmaf(x, x, acc[e]);
+                }
+            }
+    }
+    // 16 lanes of a wavefront hold rows of the same slot
+#pragma unroll
+    for (int e = 0; e < EPV; ++e) {
+#pragma unroll
+        for (int s = kStripSlots; s < 64; s *= 2)
+            acc[e] += __shfl_xor(acc[e], s, 64);
+    }
+    if (lane < kStripSlots) {
+#pragma unroll
+        for (int e = 0; e < EPV; ++e)
+            part[wave][lane * EPV + e] = acc[e];
+    }
+    __syncthreads();
+    if (tid < COLS && c0 + tid < d) {
+        double total = 0.0;
+#pragma unroll
+        for (int w = 0; w < kStripThreads / 64; ++w)
+            total += (double)part[w][tid];
+        finish_column(total, c0 + tid, sumsq, accumulate, norms);
+    }
+}
 
 template <int DT>
 __global__ __launch_bounds__(kInBlock) void input_partial_kernel(
-    const void *__restrict__ Xv, int64_t T, int64_t ldx, int64_t d, float *__restrict__ partial)
+    const void *__restrict__ Xv, int64_t T, int64_t ldx, int64_t d, int64_t rows_per_block,
+    float *__restrict__ partial)
 {
     constexpr int EPV = DT == DASS_BF16 ? 8 : 4;
     constexpr int EB = DT == DASS_BF16 ? 2 : 4;
@@ -29,8 +125,8 @@ __global__ __launch_bounds__(kInBlock) void input_partial_kernel(
     const int64_t slot = (int64_t)bx * kInBlock + threadIdx.x;
     if (slot >= slots)
         return;
-    const int64_t r0 = (int64_t)rb * kInRows;
-    const int64_t r1 = r0 + kInRows < T ? r0 + kInRows : T;
+    const int64_t r0 = (int64_t)rb * rows_per_block;
+    const int64_t r1 = r0 + rows_per_block < T ? r0 + rows_per_block : T;
     const char *X = static_cast<const char *>(Xv) + slot * 16;
 
     float acc[EPV];
@@ -70,42 +166,60 @@ __global__ __launch_bounds__(kInBlock) void input_partial_kernel(
     }
 }
 
-// A workgroup owns 64 columns; wavefront w adds the partial sums of every 4th row block
-// (w, w + 4, ...) in f64, then the four are added in a fixed order.
-__global__ __launch_bounds__(256) void input_reduce_kernel(
+// A workgroup owns 64 columns; wavefront w adds the partial sums of every kReduceWaves-th row block
+// (w, w + kReduceWaves, ...) in f64, then the wavefronts' sums are added in a fixed order.
+constexpr int kReduceWaves = 16;
+__global__ __launch_bounds__(64 * kReduceWaves) void input_reduce_kernel(
     const float *__restrict__ partial, int64_t n_row_blocks, int64_t d, float *__restrict__ sumsq,
     int accumulate, float *__restrict__ norms)
 {
-    __shared__ double part[4][64];
+    __shared__ double part[kReduceWaves][64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int64_t j = (int64_t)blockIdx.x * 64 + lane;
     double s = 0.0;
     if (j < d) {
         int64_t b = w;
-        for (; b + 12 < n_row_blocks; b += 16) {   // four loads in flight
-            const float x0 = partial[b * d + j], x1 = partial[(b + 4) * d + j], x2 = partial[(b + 8) * d + j],
-                        x3 = partial[(b + 12) * d + j];
+        for (; b + 3 * kReduceWaves < n_row_blocks; b += 4 * kReduceWaves) {   // four loads in flight
+            const float x0 = partial[b * d + j], x1 = partial[(b + kReduceWaves) * d + j],
+                        x2 = partial[(b + 2 * kReduceWaves) * d + j], x3 = partial[(b + 3 * kReduceWaves) * d + j];
             s += (double)x0;
             s += (double)x1;
             s += (double)x2;
             s += (double)x3;
         }
-        for (; b < n_row_blocks; b += 4)
+        for (; b < n_row_blocks; b += kReduceWaves)
             s += (double)partial[b * d + j];
     }
     part[w][lane] = s;
     __syncthreads();
     if (w == 0 && j < d) {
-        double total = accumulate ? (double)sumsq[j] : 0.0;
-        total += part[0][lane];
-        total += part[1][lane];
-        total += part[2][lane];
-        total += part[3][lane];
-        const float s32 = (float)total;
-        sumsq[j] = s32;
-        if (norms)
-            norms[j] = (float)sqrt((double)s32);
+        double total = 0.0;
+#pragma unroll
+        for (int i = 0; i < kReduceWaves; ++i)
+            total += part[i][lane];
+        finish_column(total, j, sumsq, accumulate, norms);
     }
+}
+
+// Rows per row block of input_partial_kernel: about 1024 wavefronts (one per SIMD) whatever the
+// shape, each with as long a run of rows as that leaves, between 32 (below, the reduction of the
+// partial sums is the longer part) and 512 (f32 sums).  With 512 rows always, a batch of a few thousand
+// tokens ran on 8 workgroups: bf16, d = 4096, 2048 / 8192 / 16384 / 65536 tokens took 50 / 51 / 52 / 78 us;
+// 12 / 15 / 24 / 78 us with this rule (4.4, 5.7 and 6.9 TB/s for the last three).
+static int64_t input_rows_per_block(int64_t T, int64_t d)
+{
+    const int64_t waves = (d / 8 + 63) / 64;   // of a row, bf16
+    const int64_t rows = ((T * waves + 1023) / 1024 + kInUnroll - 1) / kInUnroll * kInUnroll;
+    return rows < 32 ? 32 : rows > kInMaxRows ? kInMaxRows : rows;
+}
+
+// Few tokens take input_strip_kernel: its workgroups read 64 bytes of every row, so its time grows with
+// T whatever d is, but there is no second launch to wait for.  bf16, us a call, strips against row blocks
+// (both bound by the host's launches below 11 us): 2048 tokens 8.8 against 11.7 (d = 4096), 10.9 against
+// 11.5 (8192); 4096 tokens 9.7 against 11.6 (d = 2048), but 16.6 against 11.5 (4096).
+static bool input_by_strips(int64_t T, int64_t row_bytes)
+{
+    return T <= 2048 || (T <= 4096 && row_bytes <= 4096);
 }
 
 }  // namespace dass
@@ -114,7 +228,7 @@ extern "C" size_t dass_input_norms_workspace_bytes(int64_t T, int64_t d)
 {
     if (T <= 0 || d <= 0)
         return 0;
-    const int64_t n_row_blocks = (T + dass::kInRows - 1) / dass::kInRows;
+    const int64_t rows = dass::input_rows_per_block(T, d), n_row_blocks = (T + rows - 1) / rows;
     return dass::round_up((size_t)n_row_blocks * (size_t)d * sizeof(float), 256);
 }
 
@@ -146,23 +260,34 @@ extern "C" dass_status dass_input_norms(const void *X, int64_t T, int64_t ldx, i
     if (!aligned16(workspace))
         return fail(DASS_ERR_ALIGN, "%s: workspace must be 16-byte aligned", fn);
 
-    const int64_t n_row_blocks = (T + kInRows - 1) / kInRows;
+    const int64_t rows = input_rows_per_block(T, d), n_row_blocks = (T + rows - 1) / rows;
     const int64_t slots = d / vec_elems(dt);
     const int64_t nbx = (slots + kInBlock - 1) / kInBlock;
     if (nbx * n_row_blocks > 0x7fffffffLL)
         return fail(DASS_ERR_SHAPE, "%s: too many tokens for one launch; split them", fn);
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    if (input_by_strips(T, d * elem_bytes(dt))) {
+        const int64_t n_strips = (slots + kStripSlots - 1) / kStripSlots;
+        const unsigned grid = (unsigned)((n_strips + 15) / 16 * 16);
+        if (dt == DASS_BF16)
+            hipLaunchKernelGGL(input_strip_kernel<DASS_BF16>, dim3(grid), dim3(kStripThreads), 0, stream, X, T, ldx, d,
+                               sumsq, accumulate, norms_out);
+        else
+            hipLaunchKernelGGL(input_strip_kernel<DASS_F32>, dim3(grid), dim3(kStripThreads), 0, stream, X, T, ldx, d,
+                               sumsq, accumulate, norms_out);
+        return check_launch("input-norm kernel");
+    }
     float *partial = static_cast<float *>(workspace);
     if (dt == DASS_BF16)
         hipLaunchKernelGGL(input_partial_kernel<DASS_BF16>, dim3((unsigned)(nbx * n_row_blocks)), dim3(kInBlock), 0,
-                           stream, X, T, ldx, d, partial);
+                           stream, X, T, ldx, d, rows, partial);
     else
         hipLaunchKernelGGL(input_partial_kernel<DASS_F32>, dim3((unsigned)(nbx * n_row_blocks)), dim3(kInBlock), 0,
-                           stream, X, T, ldx, d, partial);
+                           stream, X, T, ldx, d, rows, partial);
     dass_status s = check_launch("input-norm kernel");
     if (s != DASS_OK)
         return s;
-    hipLaunchKernelGGL(input_reduce_kernel, dim3((unsigned)((d + 63) / 64)), dim3(256), 0, stream,
+    hipLaunchKernelGGL(input_reduce_kernel, dim3((unsigned)((d + 63) / 64)), dim3(64 * kReduceWaves), 0, stream,
                        (const float *)partial, n_row_blocks, d, sumsq, accumulate, norms_out);
     return check_launch("input-norm reduction");
 }

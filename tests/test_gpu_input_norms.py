@@ -43,6 +43,29 @@ def test_input_norms_small_and_ragged(gpu_device, dtype, T, d, pad):
         assert torch.all(base[:, d:] == 7.0)
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("T,d", [
+    (2047, 32), (2048, 1032), (2049, 72),                   # either side of strips / row blocks (wide rows)
+    (4096, 1024), (4097, 1024), (4096, 2056),               # the same for rows of up to 4096 bytes
+    (1793, 40), (257, 4096),                                # strips: every length of the last batch of rows, a short strip
+    (33000, 1032), (40000, 8)])                             # row blocks that are no power of two, one column slot
+def test_input_norms_paths(gpu_device, dtype, T, d):
+    """Strips and row blocks at the edges of their ranges, added to what is there; the same bits twice."""
+    g = torch.Generator(device=gpu_device).manual_seed(T * 131 + d)
+    X = (torch.randn((T, d), generator=g, device=gpu_device) * (torch.rand(d, generator=g, device=gpu_device) * 4 + 0.01)).to(dtype)
+    start = torch.rand(d, generator=g, device=gpu_device) * T
+    got = []
+    for _ in range(2):
+        sumsq, norms = start.clone(), torch.full((d,), -1.0, device=gpu_device)
+        dass.input_norms(X, sumsq, accumulate=True, norms_out=norms)
+        torch.cuda.synchronize()
+        got.append((sumsq, norms))
+    want = oracle.input_sumsq(to_np32(X)) + start.cpu().numpy().astype(np.float64)
+    assert _rel_err(got[0][0].cpu().numpy(), want) <= TOL
+    assert _rel_err(got[0][1].cpu().numpy(), oracle.norms(want)) <= TOL
+    assert all(torch.equal(a.view(torch.int32), b.view(torch.int32)) for a, b in zip(*got))
+
+
 def test_input_norms_chunks_accumulate_and_zero_columns(gpu_device):
     T, d = 1500, 512
     g = torch.Generator(device="cpu").manual_seed(5)
