@@ -7,15 +7,17 @@
 //
 // Two families of kernels:
 //   nm_half_*   the patterns the paper uses, n_keep = m / 2 for m = 2, 4, 8, with
-//               alpha in {0, 0.5, 1}: the factor is computed in the kernel; a group
+//               alpha in {0, 0.5, 1}: the factor is computed in the kernel (any other
+//               alpha: factor vector from a helper kernel); a group
 //               is decided by its cut (the m / 2-th largest leading term, from a
 //               min/max network) whenever the leading terms decide it, else by
 //               pairwise comparison of exact two-term f32 scores, bit-sliced over
 //               the thread's groups; accesses are non-temporal and every thread
 //               makes a single pass (many small workgroups keep HBM busier than a
 //               resident grid that loops).
-//   nm_*        every other (n_keep, m, alpha): factor vector from a helper kernel,
-//               scores as f64 products, selection by counting wins per lane.
+//   nm_*        every other (n_keep, m): factor vector from a helper kernel; groups of
+//               4 and 8 by their cut from a sorting network where it decides them, the
+//               rest by f64 products and counting wins per lane.
 #include "select.h"
 
 #include <cstdio>
@@ -23,12 +25,31 @@
 
 #include <type_traits>
 
-#include <mutex>
-
 namespace dass {
 
 constexpr int kBlock = 256;
 constexpr int kHalfColsRows = 4;   // 16-byte vectors per thread of nm_half_cols_kernel
+constexpr int kGeneralColsRows = 4;   // rows per thread of nm_cols_kernel
+
+// 16-byte accesses.  Non-temporal where a wavefront's access is contiguous; where a thread owns
+// several vectors of a row (NV > 1) the lanes of one access are 16 NV bytes apart and the caches
+// have to put the lines together: f32 8:16 along the rows of 13824 x 5120 259 us non-temporal, 145
+// so; f32 4:8 with factors across the groups 142 and 110 us.
+template <int NV>
+__device__ __forceinline__ u32x4 load_vec(const char *p)
+{
+    if constexpr (NV == 1)
+        return __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
+    return *reinterpret_cast<const u32x4 *>(p);
+}
+template <int NV>
+__device__ __forceinline__ void store_vec(char *p, const u32x4 &v)
+{
+    if constexpr (NV == 1)
+        __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(p));
+    else
+        *reinterpret_cast<u32x4 *>(p) = v;
+}
 
 // ---------------------------------------------------------------------------
 // n_keep = m / 2, factor computed in the kernel
@@ -311,8 +332,7 @@ __device__ __forceinline__ void nm_half_cols_body(
         if (by * RB + k < rows) {
 #pragma unroll
             for (int j = 0; j < NV; ++j)
-                v[k][j] = __builtin_nontemporal_load(
-                    reinterpret_cast<const u32x4 *>(W + ((by * RB + k) * ld + c0) * EB + 16 * j));
+                v[k][j] = load_vec<NV>(W + ((by * RB + k) * ld + c0) * EB + 16 * j);
         }
 
     bool fast_ok = true;
@@ -382,7 +402,7 @@ __device__ __forceinline__ void nm_half_cols_body(
                 if (active) {
 #pragma unroll
                     for (int j = 0; j < NV; ++j)
-                        __builtin_nontemporal_store(v[k][j], reinterpret_cast<u32x4 *>(W + (r * ld + c0) * EB + 16 * j));
+                        store_vec<NV>(W + (r * ld + c0) * EB + 16 * j, v[k][j]);
                 }
                 if constexpr (WITH_MASK) {
                     if constexpr (UW >= 8) {
@@ -405,8 +425,7 @@ __device__ __forceinline__ void nm_half_cols_body(
             if (k < rows_here) {
 #pragma unroll
                 for (int j = 0; j < NV; ++j)
-                    v[k][j] = __builtin_nontemporal_load(
-                        reinterpret_cast<const u32x4 *>(W + ((by * RB + k) * ld + c0) * EB + 16 * j));
+                    v[k][j] = load_vec<NV>(W + ((by * RB + k) * ld + c0) * EB + 16 * j);
             }
     }
 
@@ -474,7 +493,7 @@ __device__ __forceinline__ void nm_half_cols_body(
                         v[k][j][i] &= m[j * 4 + i];
                 }
                 if (active)
-                    __builtin_nontemporal_store(v[k][j], reinterpret_cast<u32x4 *>(W + (r * ld + c0) * EB + 16 * j));
+                    store_vec<NV>(W + (r * ld + c0) * EB + 16 * j, v[k][j]);
             }
             if constexpr (WITH_MASK) {
 #pragma unroll
@@ -545,190 +564,281 @@ __global__ __launch_bounds__(kBlock) void nm_half_batched_kernel(const NmBatch b
 }
 
 // ---------------------------------------------------------------------------
-// Groups run along a row (contiguous in memory): Down-Proj.
-// A thread owns UW = max(8, M) consecutive columns and walks down rows, so the
-// factors of its columns are loaded once.  Rows are taken RB at a time so RB
-// 16-byte loads per thread are in flight before the first is used.
+// A thread owns UW = max(8, M) consecutive columns (groups along the row: Down-Proj) or 8 columns
+// of one or more groups of M rows (groups down the columns: Gate-Proj, Up-Proj), in one pass of
+// many small workgroups with non-temporal accesses like the nm_half_* kernels.
+//
+// With CUT every group is first decided in f32 by its cut (select.h: one sorting network instead
+// of M (M - 1) / 2 comparisons of f64 products); a wavefront with a group whose leading terms tie
+// at the cut, or a factor or product outside the fast range, fetches its weights again and
+// compares f64 products.  The arithmetic of the f64 comparison bounded this path: 2:8 of 13824 x
+// 5120 bf16 with mask took 86 us down the rows and 68 us along them that way, 53 and 52 us by the cut.
 // ---------------------------------------------------------------------------
-template <int DT, int M, bool NORM_COLS>
-__global__ __launch_bounds__(kBlock) void nm_cols_kernel(
-    void *__restrict__ Wv, int64_t rows, int64_t cols, int64_t ld, const float *__restrict__ f,
-    int min_wins, uint8_t *__restrict__ mask, int64_t nbx, int64_t nby)
+
+// The cut of one group of weights x[0..M) with scaled factors fs[0..M): kept[a] is x[a] or +0.
+template <int M>
+__device__ __forceinline__ uint32_t cut_group(const float *x, const float *fs, int n_keep, uint32_t *kept, bool &undecided,
+                                              float &top_all)
 {
-    constexpr int UW = M > 8 ? M : 8;
-    constexpr int NW = words_for<DT>(UW);  // words per thread per row
-    constexpr int NV = NW / 4;             // 16-byte vectors per thread per row
-    constexpr int RB = 4;
-    constexpr int EB = DT == DASS_BF16 ? 2 : 4;
-
-    const int64_t bx = blockIdx.x % nbx, by = blockIdx.x / nbx;
-    const int64_t slot = bx * kBlock + threadIdx.x;
-    if (slot >= cols / UW)
-        return;
-    const int64_t c0 = slot * UW;
-    char *W = static_cast<char *>(Wv);
-
-    double fc[UW];
-    if constexpr (NORM_COLS) {
+    float p[M];
 #pragma unroll
-        for (int v = 0; v < UW / 4; ++v) {
-            const Vec16 q = load16(f + c0 + 4 * v);
+    for (int a = 0; a < M; ++a)
+        p[a] = fabsf(x[a]) * fs[a];
+    float cut, next, top;
+    group_rank_cut<M>(p, n_keep, cut, next, top);
+    undecided |= next == cut;
+    top_all = fmaxf(top_all, top);
+    uint32_t bits = 0;
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
-                fc[4 * v + k] = (double)__uint_as_float(q.w[k]);
-        }
+    for (int a = 0; a < M; ++a) {
+        const bool keep = p[a] >= cut;
+        kept[a] = keep ? __float_as_uint(x[a]) : 0u;
+        bits |= keep ? 1u << a : 0u;
     }
+    return bits;
+}
 
-    for (int64_t rb = by * RB; rb < rows; rb += nby * RB) {
-        uint32_t words[RB][NW];
+// The same by f64 products.
+template <int M>
+__device__ __forceinline__ uint32_t exact_group(const float *x, const float *f, int n_keep, uint32_t *kept)
+{
+    double s[M];
 #pragma unroll
-        for (int k = 0; k < RB; ++k) {
-            if (rb + k < rows) {
+    for (int a = 0; a < M; ++a)
+        s[a] = (double)fabsf(x[a]) * (double)f[a];
+    uint32_t bits = nm_keep_bits<M>(s, M - n_keep);
+    asm volatile("" : "+v"(bits));   // else the comparisons sink below and every group's products stay live
 #pragma unroll
-                for (int v = 0; v < NV; ++v) {
-                    const Vec16 q = load16(W + ((rb + k) * ld + c0) * EB + 16 * v);
+    for (int a = 0; a < M; ++a)
+        kept[a] = ((bits >> a) & 1u) ? __float_as_uint(x[a]) : 0u;
+    return bits;
+}
+
+// Eight kept elements (f32 bits) back into their 16-byte vector or vectors.
+template <int DT>
+__device__ __forceinline__ void pack8(u32x4 *v, const uint32_t *kept)
+{
 #pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        words[k][4 * v + j] = q.w[j];
-                }
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < RB; ++k) {
-            if (rb + k < rows) {
-                double fr = 0.0;
-                if constexpr (!NORM_COLS)
-                    fr = (double)f[rb + k];
-                uint32_t kept = 0;
-#pragma unroll
-                for (int g = 0; g < UW / M; ++g) {
-                    double s[M];
-#pragma unroll
-                    for (int a = 0; a < M; ++a)
-                        s[a] = (double)abs_elem<DT>(words[k], g * M + a) *
-                               (NORM_COLS ? fc[g * M + a] : fr);
-                    const uint32_t bits = nm_keep_bits<M>(s, min_wins);
-#pragma unroll
-                    for (int a = 0; a < M; ++a)
-                        if (!((bits >> a) & 1u))
-                            zero_elem<DT>(words[k], g * M + a);
-                    kept |= bits << (g * M);
-                }
-#pragma unroll
-                for (int v = 0; v < NV; ++v) {
-                    Vec16 q;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        q.w[j] = words[k][4 * v + j];
-                    store16(W + ((rb + k) * ld + c0) * EB + 16 * v, q);
-                }
-                if (mask) {
-#pragma unroll
-                    for (int b = 0; b < UW / 8; ++b)
-                        mask[(rb + k) * (cols / 8) + c0 / 8 + b] = (uint8_t)(kept >> (8 * b));
-                }
-            }
+    for (int j = 0; j < 4; ++j) {
+        if constexpr (DT == DASS_BF16) {
+            v[0][j] = pack_bf16_pair(kept[2 * j], kept[2 * j + 1]);
+        } else {
+            v[0][j] = kept[j];
+            v[1][j] = kept[4 + j];
         }
     }
 }
 
-// ---------------------------------------------------------------------------
-// Groups run down a column (stride ld): Gate-Proj and Up-Proj.
-// A thread owns 8 consecutive columns and takes GB row-groups (GB * M rows) at a
-// time; each row is one 16-byte access per 8 bf16 columns, contiguous across the
-// lanes of a wavefront.  With the factor per row (DaSS), all lanes of a
-// wavefront read the same M factors.
-// ---------------------------------------------------------------------------
-template <int DT, int M, bool NORM_ROWS>
-__global__ __launch_bounds__(kBlock) void nm_rows_kernel(
+template <int DT, int M, bool NORM_COLS, bool CUT>
+__global__ __launch_bounds__(kBlock) void nm_cols_kernel(
     void *__restrict__ Wv, int64_t rows, int64_t cols, int64_t ld, const float *__restrict__ f,
-    int min_wins, uint8_t *__restrict__ mask, int64_t nbx, int64_t nby)
+    int n_keep, uint8_t *__restrict__ mask, uint32_t nbx)
 {
-    constexpr int NW = words_for<DT>(8);
-    constexpr int NV = NW / 4;
-    constexpr int GB = M >= 8 ? 1 : 8 / M;
+    constexpr int EPV = DT == DASS_BF16 ? 8 : 4;
+    constexpr int UW = M > 8 ? M : 8, NV = UW / EPV, RB = kGeneralColsRows;
     constexpr int EB = DT == DASS_BF16 ? 2 : 4;
 
     const int64_t bx = blockIdx.x % nbx, by = blockIdx.x / nbx;
-    const int64_t slot = bx * kBlock + threadIdx.x;
-    if (slot >= cols / 8)
+    const int64_t slot = bx * blockDim.x + threadIdx.x;
+    if (slot >= cols / UW)
         return;
-    const int64_t c0 = slot * 8;
-    const int64_t n_groups = rows / M;
-    char *W = static_cast<char *>(Wv);
+    const int64_t c0 = slot * UW;
+    const int rows_here = rows - by * RB < RB ? (int)(rows - by * RB) : RB;   // uniform in the workgroup
+    char *W = static_cast<char *>(Wv) + (by * RB * ld + c0) * EB;
 
-    double fc[8];
-    if constexpr (!NORM_ROWS) {
+    u32x4 v[RB][NV];
+    auto fetch = [&]() {
 #pragma unroll
-        for (int v = 0; v < 2; ++v) {
-            const Vec16 q = load16(f + c0 + 4 * v);
+        for (int k = 0; k < RB; ++k)
+            if (k < rows_here) {
+#pragma unroll
+                for (int j = 0; j < NV; ++j)
+                    v[k][j] = load_vec<NV>(W + k * ld * EB + 16 * j);
+            }
+    };
+    fetch();
+    float fc[UW];
+    if constexpr (NORM_COLS) {
+#pragma unroll
+        for (int i = 0; i < UW / 4; ++i) {
+            const u32x4 q = *reinterpret_cast<const u32x4 *>(f + c0 + 4 * i);
 #pragma unroll
             for (int k = 0; k < 4; ++k)
-                fc[4 * v + k] = (double)__uint_as_float(q.w[k]);
+                fc[4 * i + k] = __uint_as_float(q[k]);
         }
     }
 
-    for (int64_t gb = by * GB; gb < n_groups; gb += nby * GB) {
-        uint32_t words[GB][M][NW];
+    uint32_t kept_row[RB];
+    // The rows through `decide`, which takes a group's weights, their first column and the row.
+    auto select_rows = [&](auto decide) {
 #pragma unroll
-        for (int g = 0; g < GB; ++g) {
-            if (gb + g < n_groups) {
+        for (int k = 0; k < RB; ++k) {
+            kept_row[k] = 0;
+            if (k >= rows_here)
+                break;
+            uint32_t kept[UW];
 #pragma unroll
-                for (int a = 0; a < M; ++a) {
-                    const int64_t r = (gb + g) * M + a;
-#pragma unroll
-                    for (int v = 0; v < NV; ++v) {
-                        const Vec16 q = load16(W + (r * ld + c0) * EB + 16 * v);
-#pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            words[g][a][4 * v + j] = q.w[j];
-                    }
-                }
-            }
-        }
-#pragma unroll
-        for (int g = 0; g < GB; ++g) {
-            if (gb + g < n_groups) {
-                const int64_t r0 = (gb + g) * M;
-                double fr[M];
-                if constexpr (NORM_ROWS) {
-#pragma unroll
-                    for (int a = 0; a < M; ++a)
-                        fr[a] = (double)f[r0 + a];
-                }
-                uint32_t kept[M];
+            for (int g = 0; g < UW / M; ++g) {
+                float x[M];
 #pragma unroll
                 for (int a = 0; a < M; ++a)
-                    kept[a] = 0;
+                    x[a] = elem_of<DT>(v[k][(g * M + a) / EPV], (g * M + a) % EPV);
+                kept_row[k] |= decide(x, g * M, k, kept + g * M) << (g * M);
+                __builtin_amdgcn_sched_barrier(0);   // one group at a time keeps the register count down
+            }
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    double s[M];
+            for (int u = 0; u < UW / 8; ++u)
+                pack8<DT>(v[k] + u * 8 / EPV, kept + u * 8);
+        }
+    };
+    bool exact = true;
+    if constexpr (CUT) {
+        bool undecided = false, ok = true;
+        float top_all = 0.0f, fs[UW];
 #pragma unroll
-                    for (int a = 0; a < M; ++a)
-                        s[a] = (double)abs_elem<DT>(words[g][a], e) * (NORM_ROWS ? fr[a] : fc[e]);
-                    const uint32_t bits = nm_keep_bits<M>(s, min_wins);
+        for (int e = 0; e < UW; ++e) {
+            ok &= factor_in_fast_range(fc[e]);
+            fs[e] = fc[e] * kFactorScale;
+        }
+        select_rows([&](const float *x, int e, int, uint32_t *kept) {
+            return cut_group<M>(x, fs + e, n_keep, kept, undecided, top_all);
+        });
+        exact = __builtin_amdgcn_ballot_w64(undecided || !ok || !(top_all < INFINITY)) != 0;
+        if (exact)
+            fetch();
+    }
+    if (exact)
+        select_rows([&](const float *x, int e, int k, uint32_t *kept) {
+            float fg[M];
 #pragma unroll
-                    for (int a = 0; a < M; ++a) {
-                        if (!((bits >> a) & 1u))
-                            zero_elem<DT>(words[g][a], e);
-                        kept[a] |= ((bits >> a) & 1u) << e;
-                    }
-                }
+            for (int a = 0; a < M; ++a)
+                fg[a] = NORM_COLS ? fc[e + a] : f[by * RB + k];
+            return exact_group<M>(x, fg, n_keep, kept);
+        });
+
 #pragma unroll
-                for (int a = 0; a < M; ++a) {
+    for (int k = 0; k < RB; ++k) {
+        if (k >= rows_here)
+            break;
 #pragma unroll
-                    for (int v = 0; v < NV; ++v) {
-                        Vec16 q;
+        for (int j = 0; j < NV; ++j)
+            store_vec<NV>(W + k * ld * EB + 16 * j, v[k][j]);
+        if (mask) {
 #pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            q.w[j] = words[g][a][4 * v + j];
-                        store16(W + ((r0 + a) * ld + c0) * EB + 16 * v, q);
-                    }
-                    if (mask)
-                        mask[(r0 + a) * (cols / 8) + slot] = (uint8_t)kept[a];
-                }
+            for (int b = 0; b < UW / 8; ++b)
+                mask[(by * RB + k) * (cols / 8) + c0 / 8 + b] = (uint8_t)(kept_row[k] >> (8 * b));
+        }
+    }
+}
+
+// One group of M rows per thread: a second one would only lengthen the pass.
+template <int DT, int M, bool NORM_ROWS, bool CUT>
+__global__ __launch_bounds__(kBlock) void nm_rows_kernel(
+    void *__restrict__ Wv, int64_t rows, int64_t cols, int64_t ld, const float *__restrict__ f,
+    int n_keep, uint8_t *__restrict__ mask, uint32_t nbx)
+{
+    constexpr int EPV = DT == DASS_BF16 ? 8 : 4, NV = 8 / EPV;
+    constexpr int EB = DT == DASS_BF16 ? 2 : 4;
+
+    const int64_t bx = blockIdx.x % nbx, by = blockIdx.x / nbx;
+    const int64_t slot = bx * blockDim.x + threadIdx.x;
+    if (slot >= cols / 8)
+        return;
+    const int64_t c0 = slot * 8, r0 = by * M;
+    char *W = static_cast<char *>(Wv) + (r0 * ld + c0) * EB;
+
+    u32x4 v[M][NV];
+    auto fetch = [&]() {
+#pragma unroll
+        for (int a = 0; a < M; ++a)
+#pragma unroll
+            for (int j = 0; j < NV; ++j)
+                v[a][j] = load_vec<NV>(W + a * ld * EB + 16 * j);
+    };
+    fetch();
+    float fr[M], fc[8];   // the factors of the group's rows, or of the thread's columns
+#pragma unroll
+    for (int a = 0; a < M; ++a)
+        fr[a] = NORM_ROWS ? f[r0 + a] : 0.0f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+        fc[e] = NORM_ROWS ? 0.0f : f[c0 + e];
+
+    uint32_t kept_cols[M];
+    auto select_cols = [&](auto decide) {
+#pragma unroll
+        for (int a = 0; a < M; ++a)
+            kept_cols[a] = 0;
+        constexpr int EPW = DT == DASS_BF16 ? 2 : 1;   // elements per 32-bit word
+#pragma unroll
+        for (int w = 0; w < 8 / EPW; ++w) {
+            uint32_t kept[EPW][M];
+#pragma unroll
+            for (int h = 0; h < EPW; ++h) {
+                const int e = w * EPW + h;
+                float x[M];
+#pragma unroll
+                for (int a = 0; a < M; ++a)
+                    x[a] = elem_of<DT>(v[a][e / EPV], e % EPV);
+                const uint32_t bits = decide(x, e, kept[h]);
+#pragma unroll
+                for (int a = 0; a < M; ++a)
+                    kept_cols[a] |= ((bits >> a) & 1u) << e;
+                __builtin_amdgcn_sched_barrier(0);   // one column at a time keeps the register count down
+            }
+#pragma unroll
+            for (int a = 0; a < M; ++a) {
+                if constexpr (DT == DASS_BF16)
+                    v[a][0][w] = pack_bf16_pair(kept[0][a], kept[1][a]);
+                else
+                    v[a][w / 4][w % 4] = kept[0][a];
             }
         }
+    };
+    bool exact = true;
+    if constexpr (CUT) {
+        bool undecided = false, ok = true;
+        float top_all = 0.0f, fs[M];
+#pragma unroll
+        for (int a = 0; a < M; ++a) {
+            ok &= factor_in_fast_range(fr[a]);
+            fs[a] = fr[a] * kFactorScale;
+        }
+        select_cols([&](const float *x, int, uint32_t *kept) {
+            return cut_group<M>(x, fs, n_keep, kept, undecided, top_all);
+        });
+        exact = __builtin_amdgcn_ballot_w64(undecided || !ok || !(top_all < INFINITY)) != 0;
+        if (exact)
+            fetch();
+    }
+    if (exact) {
+#pragma unroll
+        for (int a = 0; a < M; ++a)
+            kept_cols[a] = 0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            double s[M];
+#pragma unroll
+            for (int a = 0; a < M; ++a)
+                s[a] = (double)fabsf(elem_of<DT>(v[a][e / EPV], e % EPV)) * (double)(NORM_ROWS ? fr[a] : fc[e]);
+            uint32_t bits = nm_keep_bits<M>(s, M - n_keep);
+            asm volatile("" : "+v"(bits));   // else the comparisons sink below and every column's products stay live
+#pragma unroll
+            for (int a = 0; a < M; ++a) {
+                zero_lane_if<DT>(v[a][e / EPV], e % EPV, !((bits >> a) & 1u));
+                kept_cols[a] |= ((bits >> a) & 1u) << e;
+            }
+            __builtin_amdgcn_sched_barrier(0);   // one column at a time keeps the register count down
+        }
+    }
+
+#pragma unroll
+    for (int a = 0; a < M; ++a) {
+#pragma unroll
+        for (int j = 0; j < NV; ++j)
+            store_vec<NV>(W + a * ld * EB + 16 * j, v[a][j]);
+        if (mask)
+            mask[(r0 + a) * (cols / 8) + slot] = (uint8_t)kept_cols[a];
     }
 }
 
@@ -736,49 +846,28 @@ __global__ __launch_bounds__(kBlock) void nm_rows_kernel(
 // Host side
 // ---------------------------------------------------------------------------
 
-// Blocks of `kernel` that fit on the device at once (CUs x blocks per CU).
-static int64_t resident_blocks(const void *kernel)
-{
-    static std::mutex mu;
-    static int n_cu = 0;
-    std::lock_guard<std::mutex> lock(mu);
-    if (n_cu == 0) {
-        int dev = 0;
-        hipDeviceProp_t prop;
-        if (hipGetDevice(&dev) != hipSuccess || hipGetDeviceProperties(&prop, dev) != hipSuccess)
-            return 0;
-        n_cu = prop.multiProcessorCount;
-    }
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kBlock, 0) != hipSuccess ||
-        per_cu <= 0)
-        return 0;
-    return (int64_t)n_cu * per_cu;
-}
+using nm_kernel_t = void (*)(void *, int64_t, int64_t, int64_t, const float *, int, uint8_t *, uint32_t);
 
-using nm_kernel_t = void (*)(void *, int64_t, int64_t, int64_t, const float *, int, uint8_t *,
-                             int64_t, int64_t);
-
+// Groups of 4 and 8 whose factors run along the group are decided by their cut first; the others
+// (16 positions, or one factor for the whole group: bf16 magnitudes tie all the time, see
+// pick_half_kernel) by f64 products straight away.
 template <int DT, int M>
 static nm_kernel_t pick_kernel(int group_axis, int norm_axis)
 {
     if (group_axis == DASS_AXIS_COLS)
-        return norm_axis == DASS_AXIS_COLS ? nm_cols_kernel<DT, M, true>
-                                           : nm_cols_kernel<DT, M, false>;
-    return norm_axis == DASS_AXIS_ROWS ? nm_rows_kernel<DT, M, true>
-                                       : nm_rows_kernel<DT, M, false>;
+        return norm_axis == DASS_AXIS_COLS ? nm_cols_kernel<DT, M, true, M <= 8> : nm_cols_kernel<DT, M, false, false>;
+    return norm_axis == DASS_AXIS_ROWS ? nm_rows_kernel<DT, M, true, M <= 8> : nm_rows_kernel<DT, M, false, false>;
 }
 
 template <int DT>
 static nm_kernel_t pick_kernel_m(int m, int group_axis, int norm_axis)
 {
     switch (m) {
-    case 2: return pick_kernel<DT, 2>(group_axis, norm_axis);
     case 4: return pick_kernel<DT, 4>(group_axis, norm_axis);
     case 8: return pick_kernel<DT, 8>(group_axis, norm_axis);
     case 16: return pick_kernel<DT, 16>(group_axis, norm_axis);
     }
-    return nullptr;
+    return nullptr;   // 1:2 is a half pattern
 }
 
 using nm_half_kernel_t = void (*)(void *, int64_t, int64_t, int64_t, const float *, int, uint8_t *,
@@ -855,6 +944,16 @@ struct HalfGeometry {
     int block;
     int64_t nbx, batches;
 };
+// Workgroup width: the widest of 256, 128, 64 that leaves the fewest idle lanes in the last
+// workgroup of a row (e.g. 1376 slots: 6 x 256 idles 10 %, 11 x 128 only 2 %).
+static HalfGeometry one_pass_geometry(int64_t slots, int64_t batches)
+{
+    int block = kBlock;
+    for (int cand = kBlock / 2; cand >= 64; cand /= 2)
+        if ((slots + cand - 1) / cand * cand < (slots + block - 1) / block * block)
+            block = cand;
+    return {block, (slots + block - 1) / block, batches};
+}
 static HalfGeometry half_geometry(int64_t rows, int64_t cols, int dt, int group_axis, int m)
 {
     const int epv = vec_elems(dt);
@@ -868,18 +967,15 @@ static HalfGeometry half_geometry(int64_t rows, int64_t cols, int dt, int group_
         const int gb = m >= 4 ? 1 : 2;
         batches = (rows / m + gb - 1) / gb;
     }
-    // Workgroup width: the widest of 256, 128, 64 that leaves the fewest idle lanes in the
-    // last workgroup of a row (e.g. 1376 slots: 6 x 256 idles 10 %, 11 x 128 only 2 %).
-    int block = kBlock;
-    for (int cand = kBlock / 2; cand >= 64; cand /= 2)
-        if ((slots + cand - 1) / cand * cand < (slots + block - 1) / block * block)
-            block = cand;
-    return {block, (slots + block - 1) / block, batches};
+    return one_pass_geometry(slots, batches);
 }
 
+static bool half_pattern(int n_keep, int m) { return 2 * n_keep == m && m <= 8; }
+
+// The exponents whose factor has an exact f32 recipe, which the nm_half_* kernels evaluate themselves.
 static bool half_path(double alpha, int n_keep, int m)
 {
-    return 2 * n_keep == m && m <= 8 && (alpha == 0.0 || alpha == 0.5 || alpha == 1.0);
+    return half_pattern(n_keep, m) && (alpha == 0.0 || alpha == 0.5 || alpha == 1.0);
 }
 
 }  // namespace dass
@@ -927,55 +1023,42 @@ extern "C" dass_status dass_score_mask_nm(void *W, int64_t rows, int64_t cols, i
 
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
 
-    // The paper's patterns with an exponent whose factor has an exact f32 recipe: one kernel.
-    if (half_path(alpha, n_keep, m)) {
-        const int fmode = alpha == 0.0 ? kFactorOne : alpha == 1.0 ? kFactorNorm : kFactorSqrt;
+    // The factor vector of an exponent without an exact f32 recipe, or of a pattern whose kernels
+    // read the factors ready-made.
+    const bool own_factor = half_path(alpha, n_keep, m);
+    float *f = static_cast<float *>(workspace);
+    if (!own_factor) {
+        st = launch_factor(norms, norm_axis == DASS_AXIS_ROWS ? rows : cols, alpha, f, stream);
+        if (st != DASS_OK)
+            return st;
+    }
+
+    // The paper's patterns.  With any other exponent the factor vector takes the norms' place and
+    // counts as a norm of exponent 1: the kernel's scores are |w| f either way.  4:8 of 13824 x
+    // 5120 bf16 with mask, alpha = 0.25: 87 us by f64 products, 47 us + the factors so.
+    if (half_pattern(n_keep, m)) {
+        const int fmode = !own_factor ? kFactorNorm : alpha == 0.0 ? kFactorOne : alpha == 1.0 ? kFactorNorm : kFactorSqrt;
         const bool varying = norm_axis == group_axis && alpha != 0.0;
         nm_half_kernel_t kernel =
             dt == DASS_BF16 ? pick_half_kernel_mask<DASS_BF16>(mask_out != nullptr, m, group_axis, norm_axis, varying)
                             : pick_half_kernel_mask<DASS_F32>(mask_out != nullptr, m, group_axis, norm_axis, varying);
         const HalfGeometry g = half_geometry(rows, cols, dt, group_axis, m);
-        const int block = g.block;
-        const int64_t nbx = g.nbx, batches = g.batches;
-        if (nbx * batches > 0x7fffffffLL)
+        if (g.nbx * g.batches > 0x7fffffffLL)
             return fail(DASS_ERR_SHAPE, "%s: matrix too large for one launch", fn);
-        hipLaunchKernelGGL(kernel, dim3((unsigned)(nbx * batches)), dim3(block), 0, stream, W, rows, cols, ld,
-                           norms, fmode, mask_out, (uint32_t)nbx);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(g.nbx * g.batches)), dim3(g.block), 0, stream, W, rows, cols, ld,
+                           own_factor ? norms : (const float *)f, fmode, mask_out, (uint32_t)g.nbx);
         return check_launch("N:M kernel");
     }
 
-    float *f = static_cast<float *>(workspace);
-    const int64_t n_norm = norm_axis == DASS_AXIS_ROWS ? rows : cols;
-    st = launch_factor(norms, n_norm, alpha, f, stream);
-    if (st != DASS_OK)
-        return st;
-
     nm_kernel_t kernel = dt == DASS_BF16 ? pick_kernel_m<DASS_BF16>(m, group_axis, norm_axis)
                                          : pick_kernel_m<DASS_F32>(m, group_axis, norm_axis);
-    // Work items along x: column slots; along y: row batches, grid-strided so
-    // that the whole grid is resident at once and every block does equal work.
-    int64_t slots, batches;
-    if (group_axis == DASS_AXIS_COLS) {
-        slots = cols / (m > 8 ? m : 8);
-        batches = (rows + 3) / 4;
-    } else {
-        slots = cols / 8;
-        const int gb = m >= 8 ? 1 : 8 / m;
-        batches = (rows / m + gb - 1) / gb;
-    }
-    const int64_t nbx = (slots + kBlock - 1) / kBlock;
-    int64_t resident = resident_blocks(reinterpret_cast<const void *>(kernel));
-    if (resident <= 0)
-        resident = 1024;
-    int64_t nby = resident / nbx;
-    if (nby < 1)
-        nby = 1;
-    if (nby > batches)
-        nby = batches;
-    if (nbx * nby > 0x7fffffffLL)
-        return fail(DASS_ERR_SHAPE, "%s: matrix too wide for one launch", fn);
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(nbx * nby)), dim3(kBlock), 0, stream, W, rows, cols,
-                       ld, (const float *)f, m - n_keep, mask_out, nbx, nby);
+    const HalfGeometry g = group_axis == DASS_AXIS_COLS
+                               ? one_pass_geometry(cols / (m > 8 ? m : 8), (rows + kGeneralColsRows - 1) / kGeneralColsRows)
+                               : one_pass_geometry(cols / 8, rows / m);
+    if (g.nbx * g.batches > 0x7fffffffLL)
+        return fail(DASS_ERR_SHAPE, "%s: matrix too large for one launch", fn);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(g.nbx * g.batches)), dim3(g.block), 0, stream, W, rows, cols, ld,
+                       (const float *)f, n_keep, mask_out, (uint32_t)g.nbx);
     return check_launch("N:M kernel");
 }
 

@@ -209,6 +209,41 @@ __device__ __forceinline__ void group_cut(const float *p, float &cut, float &nex
     }
 }
 
+// The same for any number of kept positions, 0 < n_keep < M: `cut` is the n_keep-th largest leading
+// term, `next` the one below it, from the sorted group.  n_keep is uniform: its selects are scalar.
+template <int M>
+__device__ __forceinline__ void group_rank_cut(const float *p, int n_keep, float &cut, float &next, float &top)
+{
+    static_assert(M == 4 || M == 8, "sorting networks of 4 and 8");
+    float s[M];
+#pragma unroll
+    for (int a = 0; a < M; ++a)
+        s[a] = p[a];
+    sort4(s[0], s[1], s[2], s[3]);
+    if constexpr (M == 8) {
+        sort4(s[4], s[5], s[6], s[7]);
+        // against the other half in descending order: the four smallest and the four largest, both bitonic
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            sort2(s[i], s[7 - i]);
+#pragma unroll
+        for (int h = 0; h < M; h += 4) {
+            sort2(s[h], s[h + 2]);
+            sort2(s[h + 1], s[h + 3]);
+            sort2(s[h], s[h + 1]);
+            sort2(s[h + 2], s[h + 3]);
+        }
+    }
+    top = s[M - 1];
+    cut = s[M - 1];
+    next = s[M - 2];
+#pragma unroll
+    for (int k = 2; k < M; ++k) {
+        cut = n_keep == k ? s[M - k] : cut;
+        next = n_keep == k ? s[M - k - 1] : next;
+    }
+}
+
 // Two bf16 elements, each held as f32 bits with the low half clear, packed into one word:
 // `lo` becomes the low half, `hi` the high half.
 __device__ __forceinline__ uint32_t pack_bf16_pair(uint32_t lo, uint32_t hi)

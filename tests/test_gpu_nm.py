@@ -151,6 +151,34 @@ def test_nm_near_ties_decided_below_f32_precision(gpu_device, dtype, axes, n_kee
     assert np.array_equal(mask.cpu().numpy(), want_mask)
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("axes", [("rows", "rows"), ("cols", "cols")])
+@pytest.mark.parametrize("n_keep,m,alpha", [(1, 4, 1.0), (3, 4, 0.25), (2, 8, 0.5), (7, 8, 1.0), (3, 16, 0.5), (2, 4, 0.75),
+                                            (4, 8, 1.01)])
+def test_nm_cut_and_exact_groups_side_by_side(gpu_device, dtype, axes, n_keep, m, alpha):
+    """Wavefronts that the leading terms decide next to ones that need exact products: a third of the
+    columns has zeros that tie at the cut (negative zeros among them), some factors lie below and above
+    the fast range; the last workgroup and the last row batch are not full."""
+    rows, cols = 16 * 9, 16 * 67
+    if axes[0] == "cols":
+        rows = 37
+    g = torch.Generator(device="cpu").manual_seed(31 * m + n_keep)
+    W = torch.randn((rows, cols), generator=g) * 0.02
+    W[:, : cols // 3] *= (torch.rand((rows, cols // 3), generator=g) < 0.4).to(torch.float32)
+    W = W.to(dtype).to(gpu_device)
+    nrm = synth.make_norms(rows if axes[0] == "rows" else cols, "cpu", 5)
+    n = nrm.numel()
+    nrm[n // 2 : n // 2 + 3] = torch.tensor([0.0, 1e-30, 3e37])
+    nrm = nrm.to(gpu_device)
+    want, want_mask = oracle.mask_nm(to_np32(W), nrm.cpu().numpy(), axes[0], axes[1], alpha, n_keep, m,
+                                     want_mask=True)
+    mask = torch.full((rows, cols // 8), 0x55, dtype=torch.uint8, device=gpu_device)
+    dass.score_mask_nm(W, nrm, axes[0], axes[1], alpha, n_keep, m, mask_out=mask)
+    torch.cuda.synchronize()
+    assert bits_equal(W, want), first_mismatch(W, want)
+    assert np.array_equal(mask.cpu().numpy(), want_mask)
+
+
 def test_nm_tiny_config_all_three_matrices(gpu_device):
     """Config 'tiny' (f32, d=256, d_int=688): Gate, Up with alpha 0.5 down rows; Down with alpha 1."""
     cfg = synth.CONFIGS["tiny"]
