@@ -22,7 +22,7 @@
 //   calib_mfma_kernel  any other d (a multiple of 8): register-staged,
 //                      double-buffered; the K tail is masked.
 //
-// f32: a plain LDS-tiled FMA kernel (small shapes).
+// f32: calib_f32_kernel, the f32 matrix instruction on fragments straight from global memory.
 #include "dass_internal.h"
 #include "tile_order.h"
 
@@ -680,83 +680,157 @@ __global__ __launch_bounds__(256) void calib_pipe64_kernel(
     }
 }
 
-// ------------------------------------------------------------------ f32 tiled --
-constexpr int F_BM = 64, F_BN = 64, F_BK = 16, F_PAD = 4;
+// ------------------------------------------------------------------- f32 MFMA --
+// v_mfma_f32_16x16x4_f32 on fragments that come straight from global memory.  A wavefront owns 32
+// tokens x 32 neurons x {gate, up}: 8 accumulator blocks, and per 16 columns of K 6 fragments of 16
+// rows x 64 bytes.  Lane l holds columns 4 (l / 16) .. + 3 of row l % 16 of a fragment as one 16-byte
+// load, and the i-th of its four floats goes into the i-th MFMA of the chunk: that MFMA then covers
+// columns i, 4 + i, 8 + i, 12 + i, the same ones of both operands.  The f32 matrix rate is 256 flop
+// a clock and CU, so 6 KB for 1024 clocks of a SIMD is within what L1 and L2 deliver; there is no LDS
+// and no barrier in the loop, and kDepth - 1 chunks per wavefront are in flight.  (An LDS-tiled kernel
+// of vector FMAs took 823 us for 4096 tokens of 1024 x 4096 and 32 us for 512 of 256 x 688; this one
+// 688 and 19, launches included.)
+//   KSPLIT = 1   a workgroup is 2 x 2 wavefront tiles (64 tokens x 64 neurons) that share rows in L1.
+//   KSPLIT = 4   a workgroup is one wavefront tile; its four wavefronts take every fourth chunk and
+//                add up through LDS.  Four times the workgroups, each a quarter as long.
+constexpr int F_WT = 32;      // tokens and neurons of a wavefront tile
+constexpr int F_KC = 16;      // columns of a chunk
 
+template <int KSPLIT>
 __global__ __launch_bounds__(256) void calib_f32_kernel(
     const float *__restrict__ X, int64_t T, int64_t ldx, const float *__restrict__ Wg,
     const float *__restrict__ Wu, int64_t ldw, int64_t d, int64_t d_int, int act,
-    float *__restrict__ sumsq, int64_t tiles_n)
+    float *__restrict__ sumsq, const TileOrder order)
 {
-    __shared__ float xs[F_BK][F_BM + F_PAD];
-    __shared__ float gs[F_BK][F_BN + F_PAD];
-    __shared__ float us[F_BK][F_BN + F_PAD];
-    __shared__ float red[16][F_BN];
+    constexpr int kDepth = 4;
+    constexpr int WGT = KSPLIT == 1 ? 2 * F_WT : F_WT;   // tokens and neurons of a workgroup
 
-    const int64_t tile_t = blockIdx.x / tiles_n, tile_n = blockIdx.x % tiles_n;
-    const int64_t t0 = tile_t * F_BM, n0 = tile_n * F_BN;
-    const int tid = threadIdx.x, tx = tid % 16, ty = tid / 16;
-    const int lr = tid / 4, lk = (tid % 4) * 4;  // staging: row lr, columns lk..lk+3
+    uint32_t tile_t, tile_n;   // tile_order.h
+    if (!tile_of_block(order, blockIdx.x, tile_t, tile_n))
+        return;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int fr = lane & 15, fc = lane >> 4;
+    const int64_t t0 = (int64_t)tile_t * WGT + (KSPLIT == 1 ? wave / 2 * F_WT : 0);
+    const int64_t n0 = (int64_t)tile_n * WGT + (KSPLIT == 1 ? wave % 2 * F_WT : 0);
 
-    float ag[4][4], au[4][4];
+    // Rows past the end are clamped to the last one; the epilogue drops what they give.
+    const float *row[6];   // X, X + 16 rows, Wgate, + 16, Wup, + 16
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int h = 0; h < 2; ++h) {
+        const int64_t t = t0 + 16 * h + fr, n = n0 + 16 * h + fr;
+        row[h] = X + (t < T ? t : T - 1) * ldx;
+        row[2 + h] = Wg + (n < d_int ? n : d_int - 1) * ldw;
+        row[4 + h] = Wu + (n < d_int ? n : d_int - 1) * ldw;
+    }
+    f32x4 frag[kDepth][6];
+    auto load_chunk = [&](int buf, int64_t chunk) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            ag[i][j] = au[i][j] = 0.0f;
+        for (int q = 0; q < 6; ++q)
+            frag[buf][q] = *reinterpret_cast<const f32x4 *>(row[q] + chunk * F_KC + 4 * fc);
+    };
 
-    for (int64_t k0 = 0; k0 < d; k0 += F_BK) {
-        const bool k_ok = k0 + lk < d;  // d is a multiple of 4
-        float4 xv = make_float4(0.f, 0.f, 0.f, 0.f), gv = xv, uv = xv;
-        if (k_ok && t0 + lr < T)
-            xv = *reinterpret_cast<const float4 *>(X + (t0 + lr) * ldx + k0 + lk);
-        if (k_ok && n0 + lr < d_int) {
-            gv = *reinterpret_cast<const float4 *>(Wg + (n0 + lr) * ldw + k0 + lk);
-            uv = *reinterpret_cast<const float4 *>(Wu + (n0 + lr) * ldw + k0 + lk);
+    f32x4 acc_g[2][2], acc_u[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                acc_g[i][j][r] = acc_u[i][j][r] = 0.0f;
+
+    auto multiply = [&](int buf) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    acc_g[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(frag[buf][i][k], frag[buf][2 + j][k], acc_g[i][j], 0, 0, 0);
+                    acc_u[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(frag[buf][i][k], frag[buf][4 + j][k], acc_u[i][j], 0, 0, 0);
+                }
+    };
+    const int64_t chunks = d / F_KC;   // whole ones
+    const int64_t first = KSPLIT == 1 ? 0 : wave;
+#pragma unroll
+    for (int b = 0; b < kDepth - 1; ++b)
+        if (first + b * KSPLIT < chunks)
+            load_chunk(b, first + b * KSPLIT);
+    int64_t c = first;
+    for (; c + (2 * kDepth - 2) * KSPLIT < chunks; c += kDepth * KSPLIT) {
+#pragma unroll
+        for (int b = 0; b < kDepth; ++b) {
+            load_chunk((b + kDepth - 1) % kDepth, c + (b + kDepth - 1) * KSPLIT);
+            multiply(b);
+            __builtin_amdgcn_sched_barrier(0);   // the loads stay ahead of these MFMAs
         }
-        __syncthreads();  // previous slab fully consumed
-        xs[lk + 0][lr] = xv.x; xs[lk + 1][lr] = xv.y; xs[lk + 2][lr] = xv.z; xs[lk + 3][lr] = xv.w;
-        gs[lk + 0][lr] = gv.x; gs[lk + 1][lr] = gv.y; gs[lk + 2][lr] = gv.z; gs[lk + 3][lr] = gv.w;
-        us[lk + 0][lr] = uv.x; us[lk + 1][lr] = uv.y; us[lk + 2][lr] = uv.z; us[lk + 3][lr] = uv.w;
-        __syncthreads();
+    }
+    for (; c < chunks; c += kDepth * KSPLIT) {   // the last one or two rounds
 #pragma unroll
-        for (int k = 0; k < F_BK; ++k) {
-            float a[4], g[4], u[4];
+        for (int b = 0; b < kDepth; ++b) {
+            if (c + (b + kDepth - 1) * KSPLIT < chunks)
+                load_chunk((b + kDepth - 1) % kDepth, c + (b + kDepth - 1) * KSPLIT);
+            if (c + b * KSPLIT < chunks)
+                multiply(b);
+        }
+    }
+    if (d % F_KC != 0 && (KSPLIT == 1 || chunks % KSPLIT == wave)) {
+        // Columns past d (a multiple of 4) read column 0 and become 0.
+        const int64_t k = chunks * F_KC + 4 * fc;
+        const bool in = k < d;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                a[i] = xs[k][ty * 4 + i];
-                g[i] = gs[k][tx * 4 + i];
-                u[i] = us[k][tx * 4 + i];
-            }
+        for (int q = 0; q < 6; ++q) {
+            const f32x4 v = *reinterpret_cast<const f32x4 *>(row[q] + (in ? k : 0));
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    ag[i][j] = fmaf(a[i], g[j], ag[i][j]);
-                    au[i][j] = fmaf(a[i], u[j], au[i][j]);
-                }
+                frag[0][q][i] = in ? v[i] : 0.0f;
         }
+        multiply(0);
     }
-    // tokens past T were staged as zero rows: g = u = 0 gives y = 0
+
+    // Register r of lane l of a block is token 4 (l / 16) + r and neuron l % 16.
+    auto column_sum = [&](const f32x4 &g, const f32x4 &u, int64_t t_block) {
+        float part = 0.0f;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        float s = 0.0f;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float y = glu_act_precise(ag[i][j], act) * au[i][j];
-            s = fmaf(y, y, s);
+        for (int r = 0; r < 4; ++r) {
+            const float y = glu_act_precise(g[r], act) * u[r];
+            part = fmaf(t_block + 4 * fc + r < T ? y : 0.0f, y, part);
         }
-        red[ty][tx * 4 + j] = s;
+        return part;
+    };
+    // All tokens of the workgroup are added up before the one atomic per neuron.
+    __shared__ float halves[2][WGT];   // [token half][neuron of the workgroup]
+    auto column_total = [&](float part, int half, int col) {
+        part += __shfl_xor(part, 16, 64);
+        part += __shfl_xor(part, 32, 64);
+        if (fc == 0)
+            halves[half][col + fr] = part;
+    };
+    if constexpr (KSPLIT == 1) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+            column_total(column_sum(acc_g[0][j], acc_u[0][j], t0) + column_sum(acc_g[1][j], acc_u[1][j], t0 + 16), wave / 2,
+                         wave % 2 * F_WT + 16 * j);
+    } else {
+        __shared__ __attribute__((aligned(16))) f32x4 sums[KSPLIT][2][4][64];   // [wavefront][gate, up][block][lane]
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            sums[wave][0][q][lane] = acc_g[q / 2][q % 2];
+            sums[wave][1][q][lane] = acc_u[q / 2][q % 2];
+        }
+        __syncthreads();
+        f32x4 g = sums[0][0][wave][lane], u = sums[0][1][wave][lane];   // each wavefront finishes one block
+#pragma unroll
+        for (int w = 1; w < KSPLIT; ++w) {
+            g += sums[w][0][wave][lane];
+            u += sums[w][1][wave][lane];
+        }
+        column_total(column_sum(g, u, t0 + 16 * (wave / 2)), wave / 2, 16 * (wave % 2));
     }
     __syncthreads();
-    if (tid < F_BN) {
-        float s = 0.0f;
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-            s += red[r][tid];
-        if (n0 + tid < d_int)
-            atomicAdd(sumsq + n0 + tid, s);
-    }
+    const int64_t n = (int64_t)tile_n * WGT + threadIdx.x;
+    if (threadIdx.x < WGT && n < d_int)
+        atomicAdd(sumsq + n, halves[0][threadIdx.x] + halves[1][threadIdx.x]);
 }
 
 // ------------------------------------------------------------------ host side --
@@ -818,6 +892,15 @@ static hipError_t launch_pipe64(int act, hipStream_t stream, const uint16_t *X, 
     }
 }
 
+// Whether a wavefront tile gets a workgroup of its own (calib_f32_kernel, KSPLIT = 4): when the 64 x 64
+// tiles are no more than the 256 compute units.  Whole calls, split and not: 512 tokens, 256 x 688 (88
+// tiles) 18.9 and 21.2 us, 128 tokens, 1024 x 4096 (128) 34 and 54 us; 1024 tokens, 512 x 2048 (512) 66 and
+// 58 us, 4096 tokens, 1024 x 4096 738 and 688 us (100 TFLOP/s).
+static bool split_f32(int64_t T, int64_t d_int)
+{
+    return ((T + 2 * F_WT - 1) / (2 * F_WT)) * ((d_int + 2 * F_WT - 1) / (2 * F_WT)) <= 256;
+}
+
 // Whether `matrices` bf16 matrices of this size stay in the 256 MB memory-side cache.
 static bool fits_memory_cache(int64_t matrices, int64_t rows, int64_t cols)
 {
@@ -867,16 +950,16 @@ extern "C" dass_status dass_calib_norms(const void *X, int64_t T, int64_t ldx, c
     // ---- launch plan; every size check comes before the first launch
     constexpr int BM = P_BM, BN = P_BN, BK = 64;
     const bool bf16 = dt == DASS_BF16;
-    const int64_t tiles_t = bf16 ? (T + BM - 1) / BM : (T + F_BM - 1) / F_BM;
-    const int64_t tiles_n = bf16 ? (d_int + BN - 1) / BN : (d_int + F_BN - 1) / F_BN;
+    const bool f32_split = !bf16 && split_f32(T, d_int);
+    const int f_tile = f32_split ? F_WT : 2 * F_WT;
+    const int64_t tiles_t = bf16 ? (T + BM - 1) / BM : (T + f_tile - 1) / f_tile;
+    const int64_t tiles_n = bf16 ? (d_int + BN - 1) / BN : (d_int + f_tile - 1) / f_tile;
     // calib_pipe64_kernel: d a multiple of its 64-column slab, and 32-bit byte offsets inside a
     // tile's rows.
     const bool pipe64 = bf16 && d % 64 == 0 && (int64_t)BM * ldx * 2 < 0x7fffffffLL &&
                         (int64_t)BN * ldw * 2 < 0x7fffffffLL;
     const TileOrder order = make_tile_order(tiles_t, tiles_n, fits_memory_cache(2, d_int, d));
-    const int64_t blocks = pipe64 ? order.blocks
-                           : bf16 ? (tiles_t * tiles_n + 7) / 8 * 8
-                                  : tiles_t * tiles_n;
+    const int64_t blocks = pipe64 || !bf16 ? order.blocks : (tiles_t * tiles_n + 7) / 8 * 8;
     if (blocks <= 0 || blocks > 0x7fffffffLL)
         return fail(DASS_ERR_SHAPE, "%s: too many tiles for one launch; split the tokens", fn);
 
@@ -900,9 +983,10 @@ extern "C" dass_status dass_calib_norms(const void *X, int64_t T, int64_t ldx, c
                                          T, ldx, static_cast<const uint16_t *>(Wgate),
                                          static_cast<const uint16_t *>(Wup), ldw, d, d_int, sumsq, tiles_t, tiles_n);
     } else {
-        hipLaunchKernelGGL(calib_f32_kernel, dim3((unsigned)blocks), dim3(256), 0, stream,
+        const auto kernel = f32_split ? calib_f32_kernel<4> : calib_f32_kernel<1>;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, stream,
                            static_cast<const float *>(X), T, ldx, static_cast<const float *>(Wgate),
-                           static_cast<const float *>(Wup), ldw, d, d_int, (int)act, sumsq, tiles_n);
+                           static_cast<const float *>(Wup), ldw, d, d_int, (int)act, sumsq, order);
     }
     dass_status s = check_launch("calibration kernel");
     if (s != DASS_OK)

@@ -95,6 +95,16 @@ def test_calib_other_widths(gpu_device, act, d):
     _check(X, Wg, Wu, act, gpu_device, chunks=[T - 100, 100])
 
 
+@pytest.mark.parametrize("d", [4, 12, 16, 60, 76, 112, 256, 340])
+@pytest.mark.parametrize("T,I", [(1, 1), (33, 95), (1100, 970)])
+def test_calib_f32_chunks_and_tiles(gpu_device, T, I, d):
+    """f32: K chunks of 16 columns, none to a whole round of the pipeline and remainders of 4, 8 and 12
+    columns; one row, ragged tiles with the K split over wavefronts, and 288 tiles without it.  The
+    products are f32 with f32 sums, so the tolerance of f32 inputs holds."""
+    X, Wg, Wu = _inputs(T, d, I, torch.float32, gpu_device, seed=7 + d)
+    _check(X, Wg, Wu, "silu", gpu_device)
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_calib_several_tiles_both_ways(gpu_device, dtype):
     X, Wg, Wu = _inputs(700, 320, 400, dtype, gpu_device, seed=2)
