@@ -422,7 +422,7 @@ __global__ __launch_bounds__(kUBlock) void unstructured_rows_kernel(
 
 
 // ===========================================================================
-// Line-resident kernels, alpha in {0, 0.5, 1}: a 1024-thread workgroup holds up to 8 lines in its
+// Line-resident kernels: a 1024-thread workgroup holds up to 8 lines in its
 // registers (131072 bf16 / 65536 f32 weights in all), so the weights are read once and written
 // once; all selection passes run on the registers.  Column lines: up to 16384 (bf16) / 8192 (f32)
 // rows; row lines: any length below 65536 whose factors fit LDS beside the histograms (8, 4, 2 or
@@ -1265,7 +1265,22 @@ static dass_status score_mask_unstructured_impl(const char *fn, void *W, int64_t
     const uint32_t *gate = nullptr;   // set: the launches below run only where the word(s) it points to are nonzero
     uint32_t gate_rows = 0;           // 0: one word for the whole matrix; else one word per block of so many rows
 
-    // Column lines in the DaSS configuration (the factor varies along the line, exponent 0.5 or 1):
+    // Exponents without an exact f32 recipe: the factor vector (f64 power, rounded once) is written
+    // first and every path below takes it as norms with exponent 1, whose factor is the norm itself.
+    // The multi-pass kernels, which alone took such exponents before, read the matrix eleven times:
+    // two 11008 x 4096 bf16 down the rows with alpha 0.25 and one 4096 x 11008 along them with 0.75, copies
+    // of the dense weights included, 2997 -> 335 us; 2048 x 512 f32 (0.25 and 2.0, mask) 474 -> 95 us.
+    float *const f = static_cast<float *>(workspace);
+    const bool swept = alpha != 0.0 && alpha != 0.5 && alpha != 1.0;
+    if (swept) {
+        s = launch_factor(norms, norm_axis == DASS_AXIS_ROWS ? rows : cols, alpha, f, stream);
+        if (s != DASS_OK)
+            return s;
+        norms = f;
+        alpha = 1.0;
+    }
+
+    // Column lines in the DaSS configuration (the factor varies along the line, exponent not 0):
     // streaming passes over 64-column tiles.  They decide every ordinary matrix; for what they do
     // not decide they leave W untouched and set the flag, and the launches below, which then run
     // behind that flag, redo the matrix.
@@ -1297,9 +1312,8 @@ static dass_status score_mask_unstructured_impl(const char *fn, void *W, int64_t
         }
     }
 
-    // Lines that fit the registers of one workgroup, exponent with an exact f32 factor: the
-    // weights are read once.
-    if ((alpha == 0.0 || alpha == 0.5 || alpha == 1.0) && len <= 0xFFFF && n_keep > 0 && n_keep < (uint32_t)len) {
+    // Lines that fit the registers of one workgroup: the weights are read once.
+    if (len <= 0xFFFF && n_keep > 0 && n_keep < (uint32_t)len) {
         const int fmode = alpha == 0.0 ? kFactorOne : alpha == 1.0 ? kFactorNorm : kFactorSqrt;
         const bool along = norm_axis == group_axis;
         const bool col_lines = group_axis == DASS_AXIS_ROWS;
@@ -1331,10 +1345,11 @@ static dass_status score_mask_unstructured_impl(const char *fn, void *W, int64_t
         }
     }
 
-    float *f = static_cast<float *>(workspace);
-    s = launch_factor(norms, norm_axis == DASS_AXIS_ROWS ? rows : cols, alpha, f, stream);
-    if (s != DASS_OK)
-        return s;
+    if (!swept) {
+        s = launch_factor(norms, norm_axis == DASS_AXIS_ROWS ? rows : cols, alpha, f, stream);
+        if (s != DASS_OK)
+            return s;
+    }
 
     const dim3 grid((unsigned)blocks), block(kUBlock);
     if (group_axis == DASS_AXIS_COLS) {

@@ -18,7 +18,7 @@ struct TiledPlan {
     size_t bytes;        // size of the region
 };
 
-// Column lines of W [rows, cols] with the factor varying along the line, exponent 0.5 or 1.
+// Column lines of W [rows, cols] with the factor varying along the line (fmode: factor = norm or its square root).
 // mask_out: NULL, or where the keep bits go; a mask that is not made of whole aligned 32-bit words
 // does not take this path (its bits are corrected with 32-bit atomics).
 TiledPlan plan_tiled(int64_t rows, int64_t cols, int64_t ld, int dt, const uint8_t *mask_out = nullptr);
@@ -44,7 +44,7 @@ struct RowlinesPlan {
     size_t todo_bytes;   // one word per block in the caller's workspace
 };
 
-// Row lines of W [rows, cols] with the factor varying along the line, exponent 0.5 or 1.
+// Row lines of W [rows, cols] with the factor varying along the line (fmode: factor = norm or its square root).
 RowlinesPlan plan_rowlines(int64_t rows, int64_t cols, int64_t ld, int dt, const uint8_t *mask_out = nullptr);
 
 // Enqueue the kernel.  todo[b] is written for every block b of kRowlinesBlock rows: 0 if the

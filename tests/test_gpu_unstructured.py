@@ -499,6 +499,34 @@ def test_unstructured_calls_overlap_on_several_streams(gpu_device):
             assert bits_equal(W, ref), f"round {rep}, call {k}: {first_mismatch(W, ref)}"
 
 
+@pytest.mark.parametrize("dtype,rows,cols,axes", [
+    (torch.bfloat16, 2056, 1032, ("rows", "rows")),    # passes over column tiles
+    (torch.float32, 1040, 2048, ("cols", "cols")),     # whole rows per workgroup
+    (torch.float32, 688, 72, ("rows", "rows")),        # line-resident, column lines
+    (torch.bfloat16, 72, 696, ("cols", "cols")),       # line-resident, row lines
+    (torch.bfloat16, 136, 264, ("rows", "cols")),      # line-resident, one factor per line
+    (torch.bfloat16, 16392, 72, ("rows", "rows")),     # transposed copy (without mask), multi-pass (with it)
+])
+def test_unstructured_other_exponents(gpu_device, dtype, rows, cols, axes):
+    """Exponents other than 0, 0.5 and 1 run every path on the factor vector: ordinary ones, and ones
+    whose factors leave the range of the two-term score (f64 products) or underflow to equal zeros."""
+    nrm = synth.make_norms(rows if axes[0] == "rows" else cols, "cpu", 9)
+    length = rows if axes[1] == "rows" else cols
+    g = torch.Generator(device="cpu").manual_seed(rows + cols)
+    W0 = (torch.randn((rows, cols), generator=g) * 0.02).to(dtype)
+    for alpha, n_prune, masked in ((0.25, length // 2, True), (0.75, length // 3, False), (2.0, length - 1, True),
+                                   (12.0, length // 2, False), (60.0, length // 2, True)):
+        W = padded(W0.to(gpu_device), 8)
+        n = nrm * 1e-2 if alpha > 10 else nrm
+        mask = torch.zeros((rows, cols // 8), dtype=torch.uint8, device=gpu_device) if masked else None
+        want, want_mask = oracle.mask_unstructured(to_np32(W), n.numpy(), axes[0], axes[1], alpha, n_prune, want_mask=True)
+        dass.score_mask_unstructured(W, n.to(gpu_device), axes[0], axes[1], alpha, n_prune, mask_out=mask)
+        torch.cuda.synchronize()
+        assert bits_equal(W, want), f"alpha={alpha}: {first_mismatch(W, want)}"
+        assert not masked or np.array_equal(mask.cpu().numpy(), want_mask), alpha
+        assert torch.all(W._base[:, cols:] == 7.0)
+
+
 def test_unstructured_argument_errors(gpu_device):
     W = torch.ones((8, 16), dtype=torch.bfloat16, device=gpu_device)
     nrm = torch.ones(16, device=gpu_device)
