@@ -319,6 +319,13 @@ __device__ __forceinline__ void wait_vmcnt()
     __builtin_amdgcn_s_waitcnt(0x0f70 | (N & 15) | ((N >> 4) << 14));
 }
 
+// One wave-load of 16 bytes a lane from a buffer straight into LDS.  (Not a template: with arguments that
+// depend on one, the compiler's host pass rejects the builtin and drops the kernel's stub without a word.)
+__device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t r, char *dst, uint32_t lane_off, int off)
+{
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr_t)dst, 16, lane_off, off, 0, 0);
+}
+
 // Workgroup barrier that the compiler may not move LDS traffic across (the
 // direct-to-LDS loads are invisible to its alias analysis).
 __device__ __forceinline__ void block_barrier()
@@ -328,7 +335,7 @@ __device__ __forceinline__ void block_barrier()
     asm volatile("" ::: "memory");
 }
 
-// Workgroup tile of calib_pipe64_kernel, shared with the host-side checks.
+// Largest workgroup tile of calib_pipe64_kernel, shared with the host-side checks.
 constexpr int P_BM = 256, P_BN = 128;
 
 // ------------------------------------------------- bf16 MFMA, 128-byte rows --
@@ -367,19 +374,25 @@ __device__ __forceinline__ uint32_t bf16_pair(float lo, float hi)
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{lo, hi}, bf16x2_t));
 }
 
-template <int ACT, int EPI>
+//
+// The tile is MI x NI blocks of 16 x 16 per wavefront and {gate, up}: 8 x 4 is the one described above;
+// 4 x 4 (128 tokens) and 4 x 2 (128 tokens x 64 neurons) are for grids that leave compute units idle,
+// where a slab's time is that of its loads on one compute unit (tile_shape() chooses).  They keep the
+// ring's five units and its schedule, with units partly filled.
+template <int ACT, int EPI, int MI, int NI>
 __global__ __launch_bounds__(256) void calib_pipe64_kernel(
     const uint16_t *__restrict__ X, int64_t T, int64_t ldx, const uint16_t *__restrict__ Wg,
     const uint16_t *__restrict__ Wu, int64_t ldw, int64_t d, int64_t d_int,
     float *__restrict__ sumsq, uint16_t *__restrict__ out, int64_t ldo, const TileOrder order)
 {
-    constexpr int BM = P_BM, BN = P_BN, BK = 64, WN = 2;
+    constexpr int BM = 32 * MI, BN = 32 * NI, BK = 64, WN = 2;
+    static_assert(BM <= P_BM && BN <= P_BN && MI % 2 == 0, "the tile fits the ring's units");
     constexpr int BN_TILE = EPI == kEpiGemm ? 2 * BN : BN;   // rows of W (output columns) per tile
-    constexpr int TM = 128, TN = 64, MI = 8, NI = 4;   // wavefront tile in 16 x 16 MFMA blocks
+    constexpr int TM = 16 * MI, TN = 16 * NI;   // wavefront tile
     constexpr int CH = BK / 8;               // 16-byte chunks per tile row
     constexpr int UNIT = 32768;              // A part, or gate half + up half of the B part
-    constexpr int B_HALF = BN * BK * 2;      // 16 KB
-    constexpr int A_WL = 8, B_WL = 4;        // wave-loads (8 rows x 128 B) per wavefront per slab: 8 + 4 + 4
+    constexpr int B_HALF = BN * BK * 2;      // 16 KB at most
+    constexpr int A_WL = MI, B_WL = NI;      // wave-loads (8 rows x 128 B) per wavefront per slab: MI + NI + NI
 
     extern __shared__ __attribute__((aligned(1024))) char lds64[];   // P64_LDS bytes
 
@@ -428,19 +441,16 @@ __global__ __launch_bounds__(256) void calib_pipe64_kernel(
     const __amdgpu_buffer_rsrc_t ru =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(up_rows), 0, span_u, kRawBuffer);
 
-    // q-th of this wavefront's 8 loads of an A part (slab at byte offset kb) into ring unit `unit`
+    // q-th of this wavefront's A_WL loads of an A part (slab at byte offset kb) into ring unit `unit`
     auto issue_a = [&](int unit, int kb, int q) {
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_ptr_t)(lds64 + unit * UNIT + (wave * A_WL + q) * 1024), 16,
-                                                 a_off[q], kb, 0, 0);
+        load_to_lds(rx, lds64 + unit * UNIT + (wave * A_WL + q) * 1024, a_off[q], kb);
     };
-    // q-th of its 8 loads of a B part: 4 of Wgate, then 4 of Wup
+    // q-th of its 2 B_WL loads of a B part: B_WL of Wgate, then B_WL of Wup
     auto issue_b = [&](int unit, int kb, int q) {
         if (q < B_WL)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rg, (lds_ptr_t)(lds64 + unit * UNIT + (wave * B_WL + q) * 1024), 16,
-                                                     b_off[q], kb, 0, 0);
+            load_to_lds(rg, lds64 + unit * UNIT + (wave * B_WL + q) * 1024, b_off[q], kb);
         else
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                ru, (lds_ptr_t)(lds64 + unit * UNIT + B_HALF + (wave * B_WL + q - B_WL) * 1024), 16, b_off[q - B_WL], kb, 0, 0);
+            load_to_lds(ru, lds64 + unit * UNIT + B_HALF + (wave * B_WL + q - B_WL) * 1024, b_off[q - B_WL], kb);
     };
 
     f32x4 acc_g[MI][NI], acc_u[MI][NI];
@@ -459,9 +469,9 @@ __global__ __launch_bounds__(256) void calib_pipe64_kernel(
     struct Frags {
         bf16x8 a[MI], g[NI], u[NI];
     };
-    constexpr int N_READS = MI + 2 * NI;   // 16 fragment reads per K step
+    constexpr int N_READS = MI + 2 * NI;   // fragment reads per K step (16)
     // q-th fragment of K step kk of the slab in units (ua, ub), in the order the MFMAs need them:
-    // a0 a1 g0 u0 g1 u1 g2 u2 g3 u3 a2 .. a7
+    // a0 a1 g0 u0 g1 u1 .. a2 a3 ..
     auto read_one = [&](Frags &f, int ua, int ub, int kk, int q) {
         const char *pa = lds64 + ua * UNIT + (a_frag0 ^ (kk * 64)), *pb = lds64 + ub * UNIT + (b_frag0 ^ (kk * 64));
         if (q < 2) {
@@ -477,7 +487,7 @@ __global__ __launch_bounds__(256) void calib_pipe64_kernel(
             f.a[i] = *reinterpret_cast<const bf16x8 *>(pa + i * 2048);
         }
     };
-    constexpr int N_PAIRS = MI * NI;   // 32 pairs of MFMAs per K step
+    constexpr int N_PAIRS = MI * NI, N_HALF = N_PAIRS / 2;   // pairs of MFMAs per K step (32)
     // Pair q of a K step.  The order is a Gray code over the operands: every MFMA shares one operand
     // with the one before, (a0, g) (a1, g) (a1, u) (a0, u) for g = g_0 .. g_3 with its u, then the next
     // two A blocks.  Measured against A-block-major order (a_i with g_0 u_0 g_1 u_1 ..): +1.5 %.
@@ -496,22 +506,22 @@ __global__ __launch_bounds__(256) void calib_pipe64_kernel(
     // ---- prologue: A0 B0 A1 B1 A2 fill the five units
     const int S = (int)(d / BK);   // slabs; the host guarantees d % 64 == 0
 #pragma unroll
-    for (int q = 0; q < 8; ++q)
+    for (int q = 0; q < A_WL; ++q)
         issue_a(0, 0, q);
 #pragma unroll
-    for (int q = 0; q < 8; ++q)
+    for (int q = 0; q < 2 * B_WL; ++q)
         issue_b(1, 0, q);
     if (S > 1) {
 #pragma unroll
-        for (int q = 0; q < 8; ++q)
+        for (int q = 0; q < A_WL; ++q)
             issue_a(2, BK * 2, q);
 #pragma unroll
-        for (int q = 0; q < 8; ++q)
+        for (int q = 0; q < 2 * B_WL; ++q)
             issue_b(3, BK * 2, q);
     }
     if (S > 2) {
 #pragma unroll
-        for (int q = 0; q < 8; ++q)
+        for (int q = 0; q < A_WL; ++q)
             issue_a(4, 2 * BK * 2, q);
     }
 #pragma unroll
@@ -524,9 +534,9 @@ __global__ __launch_bounds__(256) void calib_pipe64_kernel(
                 acc_u[i][j][r] = 0.0f;
             }
     if (S > 2)
-        wait_vmcnt<24>();   // slab 0 has landed
+        wait_vmcnt<2 * A_WL + 2 * B_WL>();   // slab 0 has landed
     else if (S > 1)
-        wait_vmcnt<16>();
+        wait_vmcnt<A_WL + 2 * B_WL>();
     else
         wait_vmcnt<0>();
     block_barrier();
@@ -535,8 +545,8 @@ __global__ __launch_bounds__(256) void calib_pipe64_kernel(
     for (int q = 0; q < N_READS; ++q)
         read_one(f0, 0, 1, 0, q);
 
-    // ---- main loop.  One slab = 2 K steps of 32 gate/up MFMA pairs, the first on f0, the second
-    // on f1.  During K step 0 a wavefront reads the fragments of K step 1 (one read every second
+    // ---- main loop.  One slab = 2 K steps of N_PAIRS gate/up MFMA pairs, the first on f0, the second
+    // on f1.  (The spacings below are those of the 8 x 4 tile.)  During K step 0 a wavefront reads the fragments of K step 1 (one read every second
     // pair); during the second half of K step 1, after the slab's one barrier, those of K step 0
     // of the next slab (one read a pair).  One global->LDS wave-load goes out every fourth pair:
     // the rest of the B part of slab s + 1 (first half of K step 0), then the A part of slab s + 2
@@ -545,6 +555,8 @@ __global__ __launch_bounds__(256) void calib_pipe64_kernel(
     // whether these parts exist and were not issued by the prologue; NEXT: whether a slab follows.
     // All four are compile-time, so the steady state has no branch between its MFMAs.
     int ua = 0, ub = 1;   // ring units of slab s
+    constexpr int A_GAP = N_HALF / (A_WL / 2), B_GAP = N_HALF / B_WL;   // MFMA pairs per wave-load (4)
+    static_assert(N_HALF % (A_WL / 2) == 0 && N_HALF % B_WL == 0 && A_WL < 16, "every load has its place");
     auto slab_body = [&](int s, auto b1_tag, auto a2_tag, auto b2_tag, auto next_tag) {
         constexpr bool B1 = decltype(b1_tag)::value, A2 = decltype(a2_tag)::value, B2 = decltype(b2_tag)::value,
                        NEXT = decltype(next_tag)::value;
@@ -553,36 +565,40 @@ __global__ __launch_bounds__(256) void calib_pipe64_kernel(
         const int k1 = (s + 1) * BK * 2, k2 = (s + 2) * BK * 2;
 #pragma unroll
         for (int q = 0; q < N_PAIRS; ++q) {   // K step 0
-            if (B1 && q < N_PAIRS / 2 && (q & 3) == 0)
-                issue_b(uam, k1, 4 + (q >> 2));
-            if (A2 && q >= N_PAIRS / 2 && (q & 3) == 0)
-                issue_a(ubm, k2, (q - N_PAIRS / 2) >> 2);
-            if ((q & 1) == 0)
-                read_one(f1, ua, ub, 1, q >> 1);
+            if (B1 && q < N_HALF && q % B_GAP == 0)
+                issue_b(uam, k1, B_WL + q / B_GAP);
+            if (A2 && q >= N_HALF && (q - N_HALF) % A_GAP == 0)
+                issue_a(ubm, k2, (q - N_HALF) / A_GAP);
+#pragma unroll
+            for (int x = (q * N_READS + N_PAIRS - 1) / N_PAIRS; x < ((q + 1) * N_READS + N_PAIRS - 1) / N_PAIRS; ++x)
+                read_one(f1, ua, ub, 1, x);
             mfma_pair(f0, q);
             __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
-        for (int q = 0; q < N_PAIRS / 2; ++q) {   // K step 1, first half
-            if (A2 && (q & 3) == 0)
-                issue_a(ubm, k2, 4 + (q >> 2));
+        for (int q = 0; q < N_HALF; ++q) {   // K step 1, first half
+            if (A2 && q % A_GAP == 0)
+                issue_a(ubm, k2, A_WL / 2 + q / A_GAP);
             mfma_pair(f1, q);
             __builtin_amdgcn_sched_barrier(0);
         }
-        // Slab s + 1 has landed (only the A part of slab s + 2, the last 8 loads, may be in
-        // flight) and this wavefront holds its last fragments of slab s: vmcnt(8 or 0), lgkmcnt(0).
+        // Slab s + 1 has landed (only the A part of slab s + 2, the last A_WL loads, may be in
+        // flight) and this wavefront holds its last fragments of slab s: vmcnt(A_WL or 0), lgkmcnt(0).
         if (A2)
-            __builtin_amdgcn_s_waitcnt(0x0078);
+            __builtin_amdgcn_s_waitcnt(0x0070 | A_WL);
         else
             __builtin_amdgcn_s_waitcnt(0x0070);
         block_barrier();
 #pragma unroll
-        for (int q = N_PAIRS / 2; q < N_PAIRS; ++q) {   // K step 1, second half; the units of slab s are free
-            if (B2 && (q & 3) == 0)
-                issue_b(ua, k2, (q - N_PAIRS / 2) >> 2);
-            if (NEXT)
-                read_one(f0, ua1, ub1, 0, q - N_PAIRS / 2);
-            mfma_pair(f1, q);
+        for (int q = 0; q < N_HALF; ++q) {   // K step 1, second half; the units of slab s are free
+            if (B2 && q % B_GAP == 0)
+                issue_b(ua, k2, q / B_GAP);
+            if (NEXT) {
+#pragma unroll
+                for (int x = (q * N_READS + N_HALF - 1) / N_HALF; x < ((q + 1) * N_READS + N_HALF - 1) / N_HALF; ++x)
+                    read_one(f0, ua1, ub1, 0, x);
+            }
+            mfma_pair(f1, N_HALF + q);
             __builtin_amdgcn_sched_barrier(0);
         }
         ua = ua1;
@@ -860,35 +876,79 @@ static void launch_mfma(int act, dim3 grid, hipStream_t stream, const uint16_t *
     }
 }
 
-template <int ACT, int EPI>
-static hipError_t launch_pipe64_act(hipStream_t stream, const uint16_t *X, int64_t T, int64_t ldx,
-                                    const uint16_t *Wg, const uint16_t *Wu, int64_t ldw, int64_t d, int64_t d_int,
-                                    float *sumsq, uint16_t *out, int64_t ldo, const TileOrder &order)
+// The tile of calib_pipe64_kernel for T tokens and n output columns (of each of two matrices for the gated
+// forms, so their tiles are half as wide in columns).  A workgroup fills a compute unit, and on grids that
+// do not run for many rounds a slab takes about as long as its rows take to load, so a shape's time goes as
+// rounds x rows of a tile's slab.  Large tiles load least in all and win wherever they fill the chip; small
+// ones win where large ones leave compute units idle.  256 x 256 against the tile chosen here, whole calls:
+// dass_mlp_forward 128 tokens of 1024 x 4096 98 -> 49 us, 1024 of 4096 x 11008 (64 tiles in the down
+// projection) 397 -> 293, 2048 of it (128 tiles) 451 -> 439; dass_calib_norms 300 of 4096 x 1024 73 -> 36.
+struct TileShape {
+    int which;              // 0: 8 x 4, 1: 4 x 4, 2: 4 x 2
+    int64_t tiles_t, tiles_n;
+};
+static TileShape tile_shape(int64_t T, int64_t n, bool gated)
+{
+    constexpr int kTokens[3] = {256, 128, 128}, kCols[3] = {256, 256, 128};
+    TileShape best{};
+    int64_t best_cost = 0;
+    for (int k = 0; k < 3; ++k) {
+        const int cols = gated ? kCols[k] / 2 : kCols[k];
+        const TileShape s{k, (T + kTokens[k] - 1) / kTokens[k], (n + cols - 1) / cols};
+        const int64_t cost = (s.tiles_t * s.tiles_n + 255) / 256 * (kTokens[k] + kCols[k]);
+        if (k == 0 || cost < best_cost) {
+            best = s;
+            best_cost = cost;
+        }
+    }
+    return best;
+}
+
+template <int ACT, int EPI, int MI, int NI>
+static hipError_t launch_pipe64_tile(hipStream_t stream, const uint16_t *X, int64_t T, int64_t ldx,
+                                     const uint16_t *Wg, const uint16_t *Wu, int64_t ldw, int64_t d, int64_t d_int,
+                                     float *sumsq, uint16_t *out, int64_t ldo, const TileOrder &order)
 {
     // the kernel's ring takes all 160 KB of LDS, more than a launch gets without asking
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(calib_pipe64_kernel<ACT, EPI>),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(calib_pipe64_kernel<ACT, EPI, MI, NI>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, P64_LDS);
     if (e != hipSuccess)
         return e;
-    hipLaunchKernelGGL((calib_pipe64_kernel<ACT, EPI>), dim3(order.blocks), dim3(256), P64_LDS, stream, X, T, ldx, Wg,
-                       Wu, ldw, d, d_int, sumsq, out, ldo, order);
+    hipLaunchKernelGGL((calib_pipe64_kernel<ACT, EPI, MI, NI>), dim3(order.blocks), dim3(256), P64_LDS, stream, X, T, ldx,
+                       Wg, Wu, ldw, d, d_int, sumsq, out, ldo, order);
     return hipSuccess;
 }
 
+template <int ACT, int EPI>
+static hipError_t launch_pipe64_act(const TileShape &shape, hipStream_t stream, const uint16_t *X, int64_t T, int64_t ldx,
+                                    const uint16_t *Wg, const uint16_t *Wu, int64_t ldw, int64_t d, int64_t d_int,
+                                    float *sumsq, uint16_t *out, int64_t ldo, const TileOrder &order)
+{
+    if (shape.which == 0)
+        return launch_pipe64_tile<ACT, EPI, 8, 4>(stream, X, T, ldx, Wg, Wu, ldw, d, d_int, sumsq, out, ldo, order);
+    if (shape.which == 1)
+        return launch_pipe64_tile<ACT, EPI, 4, 4>(stream, X, T, ldx, Wg, Wu, ldw, d, d_int, sumsq, out, ldo, order);
+    return launch_pipe64_tile<ACT, EPI, 4, 2>(stream, X, T, ldx, Wg, Wu, ldw, d, d_int, sumsq, out, ldo, order);
+}
+
 template <int EPI>
-static hipError_t launch_pipe64(int act, hipStream_t stream, const uint16_t *X, int64_t T, int64_t ldx,
+static hipError_t launch_pipe64(int act, const TileShape &shape, hipStream_t stream, const uint16_t *X, int64_t T, int64_t ldx,
                                 const uint16_t *Wg, const uint16_t *Wu, int64_t ldw, int64_t d, int64_t d_int,
                                 float *sumsq, uint16_t *out, int64_t ldo, const TileOrder &order)
 {
     switch (act) {
     case DASS_ACT_SILU:
-        return launch_pipe64_act<DASS_ACT_SILU, EPI>(stream, X, T, ldx, Wg, Wu, ldw, d, d_int, sumsq, out, ldo, order);
+        return launch_pipe64_act<DASS_ACT_SILU, EPI>(shape, stream, X, T, ldx, Wg, Wu, ldw, d, d_int, sumsq, out, ldo,
+                                                         order);
     case DASS_ACT_GELU_TANH:
-        return launch_pipe64_act<DASS_ACT_GELU_TANH, EPI>(stream, X, T, ldx, Wg, Wu, ldw, d, d_int, sumsq, out, ldo, order);
+        return launch_pipe64_act<DASS_ACT_GELU_TANH, EPI>(shape, stream, X, T, ldx, Wg, Wu, ldw, d, d_int, sumsq, out, ldo,
+                                                         order);
     case DASS_ACT_GELU_ERF:
-        return launch_pipe64_act<DASS_ACT_GELU_ERF, EPI>(stream, X, T, ldx, Wg, Wu, ldw, d, d_int, sumsq, out, ldo, order);
+        return launch_pipe64_act<DASS_ACT_GELU_ERF, EPI>(shape, stream, X, T, ldx, Wg, Wu, ldw, d, d_int, sumsq, out, ldo,
+                                                         order);
     default:
-        return launch_pipe64_act<DASS_ACT_RELU, EPI>(stream, X, T, ldx, Wg, Wu, ldw, d, d_int, sumsq, out, ldo, order);
+        return launch_pipe64_act<DASS_ACT_RELU, EPI>(shape, stream, X, T, ldx, Wg, Wu, ldw, d, d_int, sumsq, out, ldo,
+                                                         order);
     }
 }
 
@@ -952,13 +1012,15 @@ extern "C" dass_status dass_calib_norms(const void *X, int64_t T, int64_t ldx, c
     const bool bf16 = dt == DASS_BF16;
     const bool f32_split = !bf16 && split_f32(T, d_int);
     const int f_tile = f32_split ? F_WT : 2 * F_WT;
-    const int64_t tiles_t = bf16 ? (T + BM - 1) / BM : (T + f_tile - 1) / f_tile;
-    const int64_t tiles_n = bf16 ? (d_int + BN - 1) / BN : (d_int + f_tile - 1) / f_tile;
     // calib_pipe64_kernel: d a multiple of its 64-column slab, and 32-bit byte offsets inside a
     // tile's rows.
     const bool pipe64 = bf16 && d % 64 == 0 && (int64_t)BM * ldx * 2 < 0x7fffffffLL &&
                         (int64_t)BN * ldw * 2 < 0x7fffffffLL;
-    const TileOrder order = make_tile_order(tiles_t, tiles_n, fits_memory_cache(2, d_int, d));
+    const TileShape shape = pipe64 ? tile_shape(T, d_int, true) : TileShape{};
+    const int64_t tiles_t = pipe64 ? shape.tiles_t : bf16 ? (T + BM - 1) / BM : (T + f_tile - 1) / f_tile;
+    const int64_t tiles_n = pipe64 ? shape.tiles_n : bf16 ? (d_int + BN - 1) / BN : (d_int + f_tile - 1) / f_tile;
+    const TileOrder order = make_tile_order(tiles_t, tiles_n, fits_memory_cache(2, d_int, d),
+                                            pipe64 && shape.which == 1 ? 8 : kPatchT);
     const int64_t blocks = pipe64 || !bf16 ? order.blocks : (tiles_t * tiles_n + 7) / 8 * 8;
     if (blocks <= 0 || blocks > 0x7fffffffLL)
         return fail(DASS_ERR_SHAPE, "%s: too many tiles for one launch; split the tokens", fn);
@@ -972,7 +1034,7 @@ extern "C" dass_status dass_calib_norms(const void *X, int64_t T, int64_t ldx, c
             return s;
     }
     if (pipe64) {
-        const hipError_t e = launch_pipe64<kEpiNorms>((int)act, stream, static_cast<const uint16_t *>(X), T, ldx,
+        const hipError_t e = launch_pipe64<kEpiNorms>((int)act, shape, stream, static_cast<const uint16_t *>(X), T, ldx,
                                                       static_cast<const uint16_t *>(Wgate),
                                                       static_cast<const uint16_t *>(Wup), ldw, d, d_int, sumsq,
                                                       nullptr, 0, order);
@@ -1047,14 +1109,14 @@ extern "C" dass_status dass_mlp_forward(const void *X, int64_t T, int64_t ldx, c
 
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     uint16_t *Y = static_cast<uint16_t *>(workspace);
-    const int64_t tiles_t = (T + P_BM - 1) / P_BM;
-    // Eq. 2: y = act(X Wgate^T) * (X Wup^T), tiles of 256 tokens x 128 neurons
+    // Eq. 2: y = act(X Wgate^T) * (X Wup^T), tiles of up to 256 tokens x 128 neurons
     {
-        const int64_t tiles_n = (d_int + P_BN - 1) / P_BN;
-        const TileOrder order = make_tile_order(tiles_t, tiles_n, fits_memory_cache(2, d_int, d));
+        const TileShape shape = tile_shape(T, d_int, true);
+        const TileOrder order = make_tile_order(shape.tiles_t, shape.tiles_n, fits_memory_cache(2, d_int, d),
+                                                shape.which == 1 ? 8 : kPatchT);
         if (order.blocks == 0)
             return fail(DASS_ERR_SHAPE, "%s: too many tiles for one launch; split the tokens", fn);
-        const hipError_t e = launch_pipe64<kEpiGlu>((int)act, stream, static_cast<const uint16_t *>(X), T, ldx,
+        const hipError_t e = launch_pipe64<kEpiGlu>((int)act, shape, stream, static_cast<const uint16_t *>(X), T, ldx,
                                                     static_cast<const uint16_t *>(Wgate),
                                                     static_cast<const uint16_t *>(Wup), ldw, d, d_int, nullptr, Y,
                                                     d_int, order);
@@ -1064,14 +1126,15 @@ extern "C" dass_status dass_mlp_forward(const void *X, int64_t T, int64_t ldx, c
         if (s != DASS_OK || eq2_only)
             return s;
     }
-    // Eq. 3: out = y Wdown^T, tiles of 256 tokens x 256 output features, K = d_int
+    // Eq. 3: out = y Wdown^T, tiles of up to 256 tokens x 256 output features, K = d_int
     {
-        const int64_t tiles_n = (d + 2 * P_BN - 1) / (2 * P_BN);
-        const TileOrder order = make_tile_order(tiles_t, tiles_n, fits_memory_cache(1, d_int, d));
+        const TileShape shape = tile_shape(T, d, false);
+        const TileOrder order = make_tile_order(shape.tiles_t, shape.tiles_n, fits_memory_cache(1, d_int, d),
+                                                shape.which == 1 ? 8 : kPatchT);
         if (order.blocks == 0)
             return fail(DASS_ERR_SHAPE, "%s: too many tiles for one launch; split the tokens", fn);
         const hipError_t e = launch_pipe64_act<DASS_ACT_RELU, kEpiGemm>(
-            stream, Y, T, d_int, static_cast<const uint16_t *>(Wdown), nullptr, ldd, d_int, d,
+            shape, stream, Y, T, d_int, static_cast<const uint16_t *>(Wdown), nullptr, ldd, d_int, d,
             nullptr, static_cast<uint16_t *>(out), ldo, order);
         if (e != hipSuccess)
             return fail(DASS_ERR_HIP, "%s: cannot reserve %d bytes of LDS: %s", fn, P64_LDS, hipGetErrorString(e));

@@ -30,23 +30,37 @@ typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 typedef __attribute__((address_space(3))) void *lds_ptr_t;
 
-constexpr int kFM = 256, kTN = 256, kBK = 64;          // features, tokens per tile; dense K per slab
-constexpr int kABytes = kFM * (kBK / 2) * 2;           // 16 KB of values
-constexpr int kBBytes = kTN * kBK * 2;                 // 32 KB of y
-constexpr int kStage = kABytes + kBBytes;              // 48 KB
+constexpr int kFM = 256, kTN = 256, kBK = 64;          // features, tokens of the largest tile; dense K per slab
 constexpr int kStages = 3;
-constexpr int kMBlock = kFM * 16;                      // codes of two slabs (128 dense K): 16 B a row, 4 KB
-constexpr int kMBase = kStages * kStage;               // two such blocks behind the ring
-constexpr int kLds = kMBase + 2 * kMBlock;             // 152 KB
-// wave-loads a wavefront issues for slab s: 4 of values, 8 of y, and with every even slab the
-// codes of that slab and the next
-constexpr int kLoadsOdd = 12, kLoadsEven = 13;
+// The tile of a workgroup is FB x NB blocks of 32 x 32 per wavefront (4 x 4: the one described above).
+template <int FB, int NB>
+struct Tile {
+    static constexpr int kFM = 64 * FB, kTN = 64 * NB;
+    static constexpr int kABytes = kFM * (kBK / 2) * 2;           // 16 KB of values
+    static constexpr int kBBytes = kTN * kBK * 2;                 // 32 KB of y
+    static constexpr int kStage = kABytes + kBBytes;              // 48 KB
+    // codes of two slabs (128 dense K): 16 B a row, 4 KB.  A wave-load is 64 rows, so 128 features
+    // are two: wavefronts 2 and 3 then load the same rows into a copy that nobody reads, so that every
+    // wavefront waits for the same number of loads.
+    static constexpr int kMBlock = 4 * 1024;
+    static constexpr int kMBase = kStages * kStage;               // two such blocks behind the ring
+    static constexpr int kLds = kMBase + 2 * kMBlock;             // 152 KB
+    // wave-loads a wavefront issues for slab s: FB of values, 2 NB of y, and with every even slab the
+    // codes of that slab and the next
+    static constexpr int kLoadsOdd = FB + 2 * NB, kLoadsEven = kLoadsOdd + 1;
+};
 
 template <int N>
 __device__ __forceinline__ void wait_vmcnt()
 {
     static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
     __builtin_amdgcn_s_waitcnt(0x0f70 | (N & 15) | ((N >> 4) << 14));
+}
+// One wave-load of 16 bytes a lane from a buffer straight into LDS.  (Not a template: with arguments that
+// depend on one, the compiler's host pass rejects the builtin and drops the kernel's stub without a word.)
+__device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t r, char *dst, uint32_t lane_off, int off)
+{
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr_t)dst, 16, lane_off, off, 0, 0);
 }
 __device__ __forceinline__ void block_barrier()
 {
@@ -62,12 +76,16 @@ __device__ __forceinline__ uint32_t bf16_pair(float lo, float hi)
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{lo, hi}, bf16x2_t));
 }
 
+template <int FB, int NB>
 __global__ __launch_bounds__(256) void down_sparse24_kernel(
     const uint16_t *__restrict__ Y, int64_t T, int64_t ldy, const uint16_t *__restrict__ values, int64_t ldv,
     const uint8_t *__restrict__ meta, int64_t ldm, int64_t d, int64_t d_int, uint16_t *__restrict__ out,
     int64_t ldo, const TileOrder order)
 {
-    extern __shared__ __attribute__((aligned(1024))) char lds[];   // kLds bytes
+    using P = Tile<FB, NB>;
+    constexpr int kFM = P::kFM, kTN = P::kTN, kABytes = P::kABytes, kStage = P::kStage, kMBlock = P::kMBlock,
+                  kMBase = P::kMBase, kLoadsOdd = P::kLoadsOdd, kLoadsEven = P::kLoadsEven;
+    extern __shared__ __attribute__((aligned(1024))) char lds[];   // P::kLds bytes
 
     uint32_t tile_t, tile_f;   // tile_order.h
     if (!tile_of_block(order, blockIdx.x, tile_t, tile_f))
@@ -90,32 +108,29 @@ __global__ __launch_bounds__(256) void down_sparse24_kernel(
     const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint16_t *>(Y + t0 * ldy), 0, (int)((rows_t - 1) * ldy * 2 + d_int * 2), kRawBuffer);
     // values: a wave-load is 16 rows x 64 B; lane l fills slot l % 4 of row l / 4 with chunk slot ^ (row / 4 & 3)
-    uint32_t a_off[4], m_off, b_off[8];
+    uint32_t a_off[FB], m_off, b_off[2 * NB];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int r = (wave * 4 + q) * 16 + (lane >> 2);
+    for (int q = 0; q < FB; ++q) {
+        const int r = (wave * FB + q) * 16 + (lane >> 2);
         a_off[q] = (uint32_t)((int64_t)r * ldv * 2 + (((lane & 3) ^ ((r >> 2) & 3)) * 16));
     }
     // codes: a wave-load is 64 rows x 16 B (two slabs), one row a lane
-    m_off = (uint32_t)((int64_t)(wave * 64 + lane) * ldm);
+    m_off = (uint32_t)((int64_t)((wave * 64 + lane) % kFM) * ldm);
     // y: a wave-load is 8 rows x 128 B; lane l fills slot l % 8 of row l / 8 with chunk slot ^ (row / 2 & 7)
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        const int r = (wave * 8 + q) * 8 + (lane >> 3);
+    for (int q = 0; q < 2 * NB; ++q) {
+        const int r = (wave * 2 * NB + q) * 8 + (lane >> 3);
         b_off[q] = (uint32_t)((int64_t)r * ldy * 2 + (((lane & 7) ^ ((r >> 1) & 7)) * 16));
     }
-    // q-th wave-load of slab s: 0..3 values, 4..11 y, 12 (even slabs only) the codes of slabs s, s + 1
+    // q-th wave-load of slab s: FB of values, 2 NB of y, the last (even slabs only) the codes of slabs s, s + 1
     auto load_one = [&](int s, int q) {
         char *st = lds + (s % kStages) * kStage;
-        if (q < 4)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rv, (lds_ptr_t)(st + (wave * 4 + q) * 1024), 16, a_off[q], s * kBK, 0,
-                                                     0);
-        else if (q < 12)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(ry, (lds_ptr_t)(st + kABytes + (wave * 8 + q - 4) * 1024), 16,
-                                                     b_off[q - 4], s * kBK * 2, 0, 0);
+        if (q < FB)
+            load_to_lds(rv, st + (wave * FB + q) * 1024, a_off[q], s * kBK);
+        else if (q < kLoadsOdd)
+            load_to_lds(ry, st + kABytes + (wave * 2 * NB + q - FB) * 1024, b_off[q - FB], s * kBK * 2);
         else
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rm, (lds_ptr_t)(lds + kMBase + ((s >> 1) & 1) * kMBlock + wave * 1024),
-                                                     16, m_off, (s >> 1) * 16, 0, 0);
+            load_to_lds(rm, lds + kMBase + ((s >> 1) & 1) * kMBlock + wave * 1024, m_off, (s >> 1) * 16);
     };
     auto issue_slab = [&](int s) {   // prologue only
 #pragma unroll
@@ -126,54 +141,57 @@ __global__ __launch_bounds__(256) void down_sparse24_kernel(
     };
 
     // ---- LDS -> registers
-    int a_row[4], b_row[4];
+    int a_row[FB], b_row[NB];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-        a_row[i] = wm * 128 + i * 32 + fr;
+    for (int i = 0; i < FB; ++i)
+        a_row[i] = wm * (kFM / 2) + i * 32 + fr;
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-        b_row[j] = wn * 128 + j * 32 + fr;
+    for (int j = 0; j < NB; ++j)
+        b_row[j] = wn * (kTN / 2) + j * 32 + fr;
+    constexpr int kReads = FB + 2 * NB;   // fragment reads of a K step: FB sparse, 2 NB dense halves
     struct Frags {
-        bf16x8 a[4], lo[4], hi[4];   // the dense operand of block j is lo[j] followed by hi[j]
+        bf16x8 a[FB], lo[NB], hi[NB];   // the dense operand of block j is lo[j] followed by hi[j]
     };
-    // q-th of the 12 fragment reads of K step kk of the slab in stage st: 4 sparse, 8 dense halves
+    // q-th of the fragment reads of K step kk of the slab in stage st
     auto read_one = [&](Frags &f, const char *st, int kk, int q) {
-        if (q < 4) {
+        if (q < FB) {
             const int r = a_row[q];
             f.a[q] = *reinterpret_cast<const bf16x8 *>(st + (r * 4 + ((2 * kk + fc) ^ ((r >> 2) & 3))) * 16);
         } else {
-            const int j = (q - 4) >> 1, r = b_row[j];
+            const int j = (q - FB) >> 1, r = b_row[j];
             const char *row = st + kABytes + r * 128;
             const int sw = (r >> 1) & 7;
-            if ((q & 1) == 0)
+            if (((q - FB) & 1) == 0)
                 f.lo[j] = *reinterpret_cast<const bf16x8 *>(row + (((4 * kk + fc) ^ sw) * 16));
             else
                 f.hi[j] = *reinterpret_cast<const bf16x8 *>(row + (((4 * kk + 2 + fc) ^ sw) * 16));
         }
     };
-    u32x2 codes[4], codes_next[4];   // the 16 nibbles of a slab of each of this lane's four rows
+    u32x2 codes[FB], codes_next[FB];   // the 16 nibbles of a slab of each of this lane's FB rows
     auto read_codes = [&](u32x2 *c, int s, int i) {   // slab s: half s % 2 of the row's 16 bytes in block s / 2
         c[i] = *reinterpret_cast<const u32x2 *>(lds + kMBase + ((s >> 1) & 1) * kMBlock + a_row[i] * 16 + (s & 1) * 8);
     };
 
-    f32x16 acc[4][4];
+    f32x16 acc[FB][NB];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < FB; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < NB; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r)
                 acc[i][j][r] = 0.0f;
     auto mfma = [&](const Frags &f, const u32x2 *c, int kk, int q) {
-        const int i = q >> 2, j = q & 3;
+        const int i = q / NB, j = q % NB;
         const bf16x16 b = __builtin_shufflevector(f.lo[j], f.hi[j], 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15);
         acc[i][j] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(f.a[i], b, acc[i][j], (int)(c[i][kk] >> (16 * fc)), 0, 0);
     };
 
-    // ---- main loop.  A slab is two K steps of 16 sparse MFMAs.  Under the MFMAs of K step 0 go
+    constexpr int kMfmas = FB * NB;
+
+    // ---- main loop.  A slab is two K steps of FB NB sparse MFMAs (16).  Under the MFMAs of K step 0 go
     // the fragment reads of K step 1; then one barrier - slab s + 1 has landed, nobody reads slab
     // s from LDS any more, so its stage takes slab s + 3 - and under the MFMAs of K step 1 go those
-    // 14 loads and the fragment reads of K step 0 of slab s + 1.
+    // loads and the fragment reads of K step 0 of slab s + 1.
     const int S = (int)(d_int / kBK);   // the host guarantees d_int % 64 == 0
     issue_slab(0);
     if (S > 1)
@@ -189,10 +207,10 @@ __global__ __launch_bounds__(256) void down_sparse24_kernel(
     block_barrier();
     Frags fa, fb;
 #pragma unroll
-    for (int q = 0; q < 12; ++q)
+    for (int q = 0; q < kReads; ++q)
         read_one(fa, lds, 0, q);
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < FB; ++i)
         read_codes(codes, 0, i);
     // MORE: a slab follows; LOAD: slab s + 3 exists; AHEAD: slab s + 2 exists (it may be in flight
     // at the barrier).  All three are compile-time: the steady state has no branch between MFMAs.
@@ -207,9 +225,10 @@ __global__ __launch_bounds__(256) void down_sparse24_kernel(
         constexpr int kIssue = PAR == 1 ? kLoadsEven : kLoadsOdd;                    // loads of slab s + 3
         const char *st = lds + (s % kStages) * kStage, *st_next = lds + ((s + 1) % kStages) * kStage;
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {   // K step 0
-            if (q < 12)
-                read_one(fb, st, 1, q);
+        for (int q = 0; q < kMfmas; ++q) {   // K step 0
+#pragma unroll
+            for (int x = q; x < kReads; x += kMfmas)
+                read_one(fb, st, 1, x);
             mfma(fa, codes, 0, q);
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -221,23 +240,29 @@ __global__ __launch_bounds__(256) void down_sparse24_kernel(
             __builtin_amdgcn_s_waitcnt(0x0070);
         block_barrier();
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {   // K step 1
-            if (LOAD && q < kIssue)
-                load_one(s + 3, q);
-            if (LOAD && PAR == 2 && q == kLoadsOdd && ((s + 3) & 1) == 0)   // uniform
+        for (int q = 0; q < kMfmas; ++q) {   // K step 1
+            if (LOAD) {
+#pragma unroll
+                for (int x = q; x < kIssue; x += kMfmas)
+                    load_one(s + 3, x);
+            }
+            if (LOAD && PAR == 2 && q == kLoadsOdd % kMfmas && ((s + 3) & 1) == 0)   // uniform
                 load_one(s + 3, kLoadsOdd);
             if (MORE) {
-                if (q < 12)
-                    read_one(fa, st_next, 0, q);
-                else
-                    read_codes(codes_next, s + 1, q - 12);
+#pragma unroll
+                for (int x = q; x < kReads + FB; x += kMfmas) {
+                    if (x < kReads)
+                        read_one(fa, st_next, 0, x);
+                    else
+                        read_codes(codes_next, s + 1, x - kReads);
+                }
             }
             mfma(fb, codes, 1, q);
             __builtin_amdgcn_sched_barrier(0);
         }
         if (MORE) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < FB; ++i)
                 codes[i] = codes_next[i];
         }
     };
@@ -264,14 +289,14 @@ __global__ __launch_bounds__(256) void down_sparse24_kernel(
     // of one token: 8-byte writes.
     block_barrier();   // every wavefront is done with the last slab
     constexpr int SROW = kFM * 2 + 16;
-    static_assert(kTN * SROW <= kLds, "the tile fits in the ring");
+    static_assert(kTN * SROW <= P::kLds, "the tile fits in the ring");
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < FB; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < NB; ++j)
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
-                const int token = wn * 128 + j * 32 + fr, feature = wm * 128 + i * 32 + 8 * g + 4 * fc;
+                const int token = wn * (kTN / 2) + j * 32 + fr, feature = wm * (kFM / 2) + i * 32 + 8 * g + 4 * fc;
                 u32x2 w;
                 w[0] = bf16_pair(acc[i][j][4 * g], acc[i][j][4 * g + 1]);
                 w[1] = bf16_pair(acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
@@ -286,6 +311,21 @@ __global__ __launch_bounds__(256) void down_sparse24_kernel(
             __builtin_nontemporal_store(*reinterpret_cast<const u32x4 *>(lds + row * SROW + cc * 16),
                                         reinterpret_cast<u32x4 *>(out + t * ldo + f));   // streamed: not read again from L2
     }
+}
+
+template <int FB, int NB>
+static hipError_t launch_tile(hipStream_t stream, const uint16_t *Y, int64_t T, int64_t ldy, const uint16_t *values,
+                              int64_t ldv, const uint8_t *meta, int64_t ldm, int64_t d, int64_t d_int, uint16_t *out,
+                              int64_t ldo, const TileOrder &order)
+{
+    constexpr int kLds = Tile<FB, NB>::kLds;
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(down_sparse24_kernel<FB, NB>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+    if (e != hipSuccess)
+        return e;
+    hipLaunchKernelGGL((down_sparse24_kernel<FB, NB>), dim3(order.blocks), dim3(256), kLds, stream, Y, T, ldy, values, ldv,
+                       meta, ldm, d, d_int, out, ldo, order);
+    return hipSuccess;
 }
 
 }  // namespace sp
@@ -319,17 +359,32 @@ extern "C" dass_status dass_down_proj_sparse24(const void *Y, int64_t T, int64_t
     if ((int64_t)sp::kTN * ldy * 2 >= 0x7fffffffLL || (int64_t)sp::kFM * ldv * 2 >= 0x7fffffffLL ||
         (int64_t)sp::kFM * ldm >= 0x7fffffffLL)
         return fail(DASS_ERR_SHAPE, "%s: rows too long for the tile addressing", fn);
-    const int64_t tiles_t = (T + sp::kTN - 1) / sp::kTN, tiles_f = (d + sp::kFM - 1) / sp::kFM;
-    const TileOrder order = make_tile_order(tiles_t, tiles_f, true);
+    // A workgroup fills a compute unit and a slab takes about as long as its rows take to load, so a tile's
+    // time goes as rounds x bytes of a slab (64 a feature, 128 a token): small tiles where large ones leave
+    // compute units idle.  256 x 256 against the tile chosen here: 2048 tokens of 4096 x 11008 (128 tiles)
+    // 176 -> 128 us; with the compression 1024 tokens 219 -> 103, 128 tokens of 1024 x 4096 65 -> 33 us;
+    // 4096 tokens (256 tiles) and more stay with 256 x 256.
+    constexpr int kFeatures[3] = {256, 256, 128}, kTokens[3] = {256, 128, 128};
+    int which = 0;
+    int64_t tiles_t = 0, tiles_f = 0, cost = 0;
+    for (int k = 0; k < 3; ++k) {
+        const int64_t nt = (T + kTokens[k] - 1) / kTokens[k], nf = (d + kFeatures[k] - 1) / kFeatures[k];
+        const int64_t c = (nt * nf + 255) / 256 * (kFeatures[k] + 2 * kTokens[k]);
+        if (k == 0 || c < cost) {
+            which = k;
+            tiles_t = nt;
+            tiles_f = nf;
+            cost = c;
+        }
+    }
+    const TileOrder order = make_tile_order(tiles_t, tiles_f, true, which == 1 ? 8 : kPatchT);
     if (order.blocks == 0)
         return fail(DASS_ERR_SHAPE, "%s: too many tiles for one launch; split the tokens", fn);
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(sp::down_sparse24_kernel),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, sp::kLds);
+    const auto launch = which == 0 ? sp::launch_tile<4, 4> : which == 1 ? sp::launch_tile<4, 2> : sp::launch_tile<2, 2>;
+    const hipError_t e = launch(stream, static_cast<const uint16_t *>(Y), T, ldy, static_cast<const uint16_t *>(values), ldv,
+                                meta, ldm, d, d_int, static_cast<uint16_t *>(out), ldo, order);
     if (e != hipSuccess)
-        return fail(DASS_ERR_HIP, "%s: cannot reserve %d bytes of LDS: %s", fn, sp::kLds, hipGetErrorString(e));
-    hipLaunchKernelGGL(sp::down_sparse24_kernel, dim3(order.blocks), dim3(256), sp::kLds, stream,
-                       static_cast<const uint16_t *>(Y), T, ldy, static_cast<const uint16_t *>(values), ldv, meta, ldm,
-                       d, d_int, static_cast<uint16_t *>(out), ldo, order);
+        return fail(DASS_ERR_HIP, "%s: cannot reserve the ring's LDS: %s", fn, hipGetErrorString(e));
     return check_launch("sparse down-projection kernel");
 }

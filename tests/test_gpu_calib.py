@@ -74,7 +74,9 @@ def test_calib_activations_ragged_shapes(gpu_device, dtype, act):
 
 
 @pytest.mark.parametrize("act", ACTS)
-@pytest.mark.parametrize("T,d,I", [(300, 64, 150), (515, 192, 257), (1100, 448, 130)])
+@pytest.mark.parametrize("T,d,I", [(300, 64, 150), (515, 192, 257), (1100, 448, 130),
+                                     # tiles of 128 tokens x 128 neurons, then of 256 x 128
+                                     (4225, 192, 530), (16700, 64, 530)])
 def test_calib_pipelined_kernel_every_activation(gpu_device, act, T, d, I):
     """bf16 with d a multiple of 64: the direct-to-LDS kernel (1, 3 and 7 K slabs, so the prologue,
     the steady state and the peeled last slabs all run), ragged T and d_int, every activation's

@@ -38,7 +38,9 @@ def _sparse_weights(d, d_int, seed):
 
 
 @pytest.mark.parametrize("T,d,d_int,pad", [(300, 192, 320, 0), (513, 264, 448, 8), (256, 256, 64, 0), (70, 8, 704, 16),
-                                           (1, 520, 128, 0)])
+                                           (1, 520, 128, 0),
+                                           # tiles of 256 features x 128 tokens, then of 256 x 256
+                                           (8200, 520, 192, 8), (4225, 1032, 576, 0), (33100, 512, 128, 0)])
 def test_sparse_down_small_shapes(gpu_device, T, d, d_int, pad):
     W = _sparse_weights(d, d_int, T + d)
     # the compressed form comes from the oracle, so the test does not lean on the GPU's compressor

@@ -19,7 +19,7 @@ using namespace dass;
 int main(int, char **argv)
 {
     const uint32_t tt = atoi(argv[1]), tn = atoi(argv[2]);
-    const TileOrder o = make_tile_order(tt, tn, atoi(argv[3]) != 0);
+    const TileOrder o = make_tile_order(tt, tn, atoi(argv[3]) != 0, atoi(argv[4]));
     std::vector<int> seen((size_t)tt * tn, 0);
     uint32_t per_xcd[8] = {0}, worst = 0;
     for (uint32_t b = 0; b < o.blocks; ++b) {
@@ -51,17 +51,19 @@ def driver(tmp_path_factory):
     return str(exe)
 
 
+@pytest.mark.parametrize("max_band", [4, 8])
 @pytest.mark.parametrize("cached", [0, 1])
 @pytest.mark.parametrize("tiles_t,tiles_n", [
     (1, 1), (1, 86), (3, 7), (5, 9), (6, 192), (8, 16), (13, 43),   # small grids, ragged bands
     (64, 64), (64, 65), (47, 88),                                   # either side of the change of order (4096 tiles)
     (37, 192), (36, 192), (100, 97), (1024, 86), (1024, 12)])       # patches; super-rows that do not divide; short columns
-def test_every_tile_once_and_evenly(driver, tiles_t, tiles_n, cached):
-    out = subprocess.run([driver, str(tiles_t), str(tiles_n), str(cached)], capture_output=True, text=True)
+def test_every_tile_once_and_evenly(driver, tiles_t, tiles_n, cached, max_band):
+    out = subprocess.run([driver, str(tiles_t), str(tiles_n), str(cached), str(max_band)], capture_output=True, text=True)
     assert out.returncode == 0, out.stdout
     worst, band = (int(v) for v in out.stdout.split())
     n = tiles_t * tiles_n
     if band:
+        assert band <= max_band
         assert worst == (n + 7) // 8
     else:   # whole patches of 32 dealt to the XCDs
         assert worst <= n / 8 * 1.1 + 64
