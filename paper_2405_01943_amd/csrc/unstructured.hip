@@ -1280,11 +1280,16 @@ static dass_status score_mask_unstructured_impl(const char *fn, void *W, int64_t
         alpha = 1.0;
     }
 
+    // Lines of up to 1024 weights take the wavefront-per-line kernel whatever the size of the matrix (1024
+    // x 8192 bf16, the three of a block: 127 us by the streaming passes, 119 so); lines of up to 2048 where
+    // the streaming passes, which are ahead on large matrices (2048 x 4096: 115 against 166), do not apply.
+    const bool short_first = short_lines_fit(rows, cols, group_axis == DASS_AXIS_ROWS, 1024);
+
     // Column lines in the DaSS configuration (the factor varies along the line, exponent not 0):
     // streaming passes over 64-column tiles.  They decide every ordinary matrix; for what they do
     // not decide they leave W untouched and set the flag, and the launches below, which then run
     // behind that flag, redo the matrix.
-    if ((alpha == 0.5 || alpha == 1.0) && group_axis == DASS_AXIS_ROWS && norm_axis == DASS_AXIS_ROWS && n_keep > 0 &&
+    if (!short_first && (alpha == 0.5 || alpha == 1.0) && group_axis == DASS_AXIS_ROWS && norm_axis == DASS_AXIS_ROWS && n_keep > 0 &&
         n_keep < (uint32_t)len) {
         const TiledPlan tp = plan_tiled(rows, cols, ld, dt, mask_out);
         if (tp.fits && region_bytes >= tp.bytes) {
@@ -1298,7 +1303,7 @@ static dass_status score_mask_unstructured_impl(const char *fn, void *W, int64_t
     }
     // Row lines in the DaSS configuration: one launch in which a workgroup owns 8 whole rows; blocks of
     // rows it does not decide are marked and redone by the launches below.
-    if ((alpha == 0.5 || alpha == 1.0) && group_axis == DASS_AXIS_COLS && norm_axis == DASS_AXIS_COLS && n_keep > 0 &&
+    if (!short_first && (alpha == 0.5 || alpha == 1.0) && group_axis == DASS_AXIS_COLS && norm_axis == DASS_AXIS_COLS && n_keep > 0 &&
         n_keep < (uint32_t)len) {
         const RowlinesPlan rp = plan_rowlines(rows, cols, ld, dt, mask_out);
         if (rp.fits && region_bytes >= rp.todo_bytes) {
@@ -1317,6 +1322,8 @@ static dass_status score_mask_unstructured_impl(const char *fn, void *W, int64_t
         const int fmode = alpha == 0.0 ? kFactorOne : alpha == 1.0 ? kFactorNorm : kFactorSqrt;
         const bool along = norm_axis == group_axis;
         const bool col_lines = group_axis == DASS_AXIS_ROWS;
+        if (!gate && short_lines_fit(rows, cols, col_lines, 2048))
+            return launch_short_lines(fn, W, rows, cols, ld, dt, norms, col_lines, along, fmode, n_keep, mask_out, stream);
         const ResidentPlan p = plan_resident(rows, cols, ld, dt, col_lines, along);
         if (p.fits)
             return launch_resident(fn, p, W, rows, cols, ld, dt, norms, col_lines, along, fmode, n_keep, mask_out, gate,

@@ -1,6 +1,6 @@
 // Unstructured selection by streaming passes: column lines over 64-column tiles
-// (unstructured_tiled.hip), row lines by workgroups that own whole rows (unstructured_rows.hip);
-// called from the entry points in unstructured.hip.
+// (unstructured_tiled.hip), row lines by workgroups that own whole rows (unstructured_rows.hip); and
+// short lines by wavefronts that own one (unstructured_short.hip); called from the entry points in unstructured.hip.
 #pragma once
 
 #include "dass_internal.h"
@@ -52,5 +52,14 @@ RowlinesPlan plan_rowlines(int64_t rows, int64_t cols, int64_t ld, int dt, const
 dass_status launch_rowlines(const char *fn, const RowlinesPlan &p, void *W, int64_t rows, int64_t cols, int64_t ld, int dt,
                             const float *norms, int fmode, uint32_t n_keep, uint8_t *mask_out, uint32_t *todo,
                             hipStream_t stream);
+
+// ---- lines of at most 2048 weights (unstructured_short.hip): one launch, a wavefront per line ----
+// Whether the lines are at most `longest` (<= 2048) weights long and the launch is possible.
+bool short_lines_fit(int64_t rows, int64_t cols, bool col_lines, int64_t longest);
+
+// 0 < n_keep < the line's length; norms of the line's positions (along) or one per line.
+dass_status launch_short_lines(const char *fn, void *W, int64_t rows, int64_t cols, int64_t ld, int dt, const float *norms,
+                               bool col_lines, bool along, int fmode, uint32_t n_keep, uint8_t *mask_out,
+                               hipStream_t stream);
 
 }  // namespace dass

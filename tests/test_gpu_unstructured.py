@@ -527,6 +527,24 @@ def test_unstructured_other_exponents(gpu_device, dtype, rows, cols, axes):
         assert torch.all(W._base[:, cols:] == 7.0)
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("group_axis", ["rows", "cols"])
+@pytest.mark.parametrize("length", [2, 8, 63, 512, 520, 1024, 1025, 1032, 1536, 2048, 2056])
+def test_unstructured_short_lines(gpu_device, dtype, group_axis, length):
+    """Lines of a wavefront's registers: edges of every count of positions per lane, both sides of the
+    limits, one wanted position and all but one, ties, a factor per line, quotas and padding."""
+    if group_axis == "cols" and length % 8:
+        pytest.skip("row lines are multiples of 8 long")
+    rows, cols = (length, 72) if group_axis == "rows" else (19, length)
+    axes = (group_axis, group_axis)
+    _run_case(gpu_device, rows, cols, dtype, axes, 0.5, length // 2, seed=5, pad=8)
+    _run_case(gpu_device, rows, cols, dtype, axes, 1.0, length - 1, seed=6)
+    _run_case(gpu_device, rows, cols, dtype, axes, 1.0, 1, seed=7, ties=True)
+    _run_case(gpu_device, rows, cols, dtype, axes, 0.0, length // 2, seed=8, ties=True)
+    _run_case(gpu_device, rows, cols, dtype, ("cols" if group_axis == "rows" else "rows", group_axis), 0.5, length // 2,
+              seed=9, pad=8)
+
+
 def test_unstructured_argument_errors(gpu_device):
     W = torch.ones((8, 16), dtype=torch.bfloat16, device=gpu_device)
     nrm = torch.ones(16, device=gpu_device)
