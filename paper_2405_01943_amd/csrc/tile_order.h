@@ -86,7 +86,10 @@ inline TileOrder make_tile_order(int64_t tiles_t, int64_t tiles_n, bool weights_
     o.tiles_n = (uint32_t)tiles_n;
     const int64_t n = tiles_t * tiles_n;
     const bool short_patches_meet = weights_cached && tiles_n % kPatchN != 0 && np_n % 2 == 0;
-    if (n <= kRunTiles || short_patches_meet) {
+    // Whole patches that go round evenly leave no XCD idle, and from some rounds on their order is ahead
+    // (down projection of 32768 tokens of 4096 x 14336, 128 x 16 tiles: dass_mlp_forward 7.59 -> 7.52 ms).
+    const bool even_patches = n > 1024 && tiles_t % kPatchT == 0 && tiles_n % kPatchN == 0 && patches % kXcds == 0;
+    if ((n <= kRunTiles && !even_patches) || short_patches_meet) {
         const int64_t bands = (tiles_t + max_band - 1) / max_band;
         o.band = (uint32_t)((tiles_t + bands - 1) / bands);   // even bands of at most max_band
         o.per_xcd = (uint32_t)((n + kXcds - 1) / kXcds);

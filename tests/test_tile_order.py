@@ -55,7 +55,7 @@ def driver(tmp_path_factory):
 @pytest.mark.parametrize("cached", [0, 1])
 @pytest.mark.parametrize("tiles_t,tiles_n", [
     (1, 1), (1, 86), (3, 7), (5, 9), (6, 192), (8, 16), (13, 43),   # small grids, ragged bands
-    (64, 64), (64, 65), (47, 88),                                   # either side of the change of order (4096 tiles)
+    (64, 64), (128, 16), (64, 65), (47, 88),                                   # either side of the change of order (4096 tiles)
     (37, 192), (36, 192), (100, 97), (1024, 86), (1024, 12)])       # patches; super-rows that do not divide; short columns
 def test_every_tile_once_and_evenly(driver, tiles_t, tiles_n, cached, max_band):
     out = subprocess.run([driver, str(tiles_t), str(tiles_n), str(cached), str(max_band)], capture_output=True, text=True)
