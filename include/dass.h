@@ -187,9 +187,12 @@ dass_status dass_score_mask_nm_batched(const dass_nm_task *tasks, int64_t n_task
  *   X      [T, d] row stride ldx, dtype dt, read only; d a multiple of 8
  *   sumsq  f32[d]; overwritten, or added to when accumulate != 0 (token chunks)
  *   norms_out  NULL or f32[d]
- *   workspace  device scratch of at least dass_input_norms_workspace_bytes()
- *          bytes, 16-byte aligned (per-row-block partial sums; the result does
- *          not depend on scheduling)
+ *   workspace  device scratch of dass_input_norms_workspace_bytes() bytes, 16-byte
+ *          aligned (per-row-block partial sums; the result does not depend on
+ *          scheduling).  The size does not decrease in T: a workspace for the
+ *          longest chunk serves every shorter one.  Less is taken down to
+ *          ceil(T / 512) * d floats (rounded up to 256 bytes): longer row
+ *          blocks, slower for a few thousand tokens.
  * Squares and block sums are f32, the sum over blocks f64.
  */
 size_t dass_input_norms_workspace_bytes(int64_t T, int64_t d);

@@ -206,11 +206,25 @@ __global__ __launch_bounds__(64 * kReduceWaves) void input_reduce_kernel(
 // partial sums is the longer part) and 512 (f32 sums).  With 512 rows always, a batch of a few thousand
 // tokens ran on 8 workgroups: bf16, d = 4096, 2048 / 8192 / 16384 / 65536 tokens took 50 / 51 / 52 / 78 us;
 // 12 / 15 / 24 / 78 us with this rule (4.4, 5.7 and 6.9 TB/s for the last three).
-static int64_t input_rows_per_block(int64_t T, int64_t d)
+// A workspace with room for fewer than that rule's blocks, but at least `blocks_fit` >= T / 512 of them, gets
+// longer ones.
+static int64_t input_rows_per_block(int64_t T, int64_t d, int64_t blocks_fit)
 {
     const int64_t waves = (d / 8 + 63) / 64;   // of a row, bf16
-    const int64_t rows = ((T * waves + 1023) / 1024 + kInUnroll - 1) / kInUnroll * kInUnroll;
+    const int64_t rule = (T * waves + 1023) / 1024, room = (T + blocks_fit - 1) / blocks_fit;
+    const int64_t rows = ((rule > room ? rule : room) + kInUnroll - 1) / kInUnroll * kInUnroll;
     return rows < 32 ? 32 : rows > kInMaxRows ? kInMaxRows : rows;
+}
+
+// The most row blocks that input_rows_per_block() makes of T or fewer tokens when it has the room:
+// blocks of 32 rows up to 1024 wavefronts, then 1024 wavefronts, then blocks of 512 rows.  It does not
+// decrease in T, so that a workspace for the longest chunk of a stream serves the shorter ones.
+static int64_t input_most_blocks(int64_t T, int64_t d)
+{
+    const int64_t waves = (d / 8 + 63) / 64;
+    const int64_t small = (T + 31) / 32, full = (1024 + waves - 1) / (waves > 0 ? waves : 1), large = (T + kInMaxRows - 1) / kInMaxRows;
+    const int64_t blocks = small < full ? small : full;
+    return blocks > large ? blocks : large;
 }
 
 // Few tokens take input_strip_kernel: its workgroups read 64 bytes of every row, so its time grows with
@@ -228,8 +242,7 @@ extern "C" size_t dass_input_norms_workspace_bytes(int64_t T, int64_t d)
 {
     if (T <= 0 || d <= 0)
         return 0;
-    const int64_t rows = dass::input_rows_per_block(T, d), n_row_blocks = (T + rows - 1) / rows;
-    return dass::round_up((size_t)n_row_blocks * (size_t)d * sizeof(float), 256);
+    return dass::round_up((size_t)dass::input_most_blocks(T, d) * (size_t)d * sizeof(float), 256);
 }
 
 extern "C" dass_status dass_input_norms(const void *X, int64_t T, int64_t ldx, int64_t d, dass_dtype dt,
@@ -253,14 +266,16 @@ extern "C" dass_status dass_input_norms(const void *X, int64_t T, int64_t ldx, i
     if (ldx % vec_elems(dt) != 0)
         return fail(DASS_ERR_ALIGN, "%s: ldx=%lld must be a multiple of %d elements", fn, (long long)ldx,
                     vec_elems(dt));
-    const size_t need = dass_input_norms_workspace_bytes(T, d);
+    // partial sums of blocks of 512 rows have to fit; room for more of them only makes the call faster
+    const size_t need = round_up((size_t)((T + kInMaxRows - 1) / kInMaxRows) * (size_t)d * sizeof(float), 256);
     if (!workspace || workspace_bytes < need)
         return fail(DASS_ERR_WORKSPACE, "%s: workspace of %zu bytes needed, %zu given", fn, need,
                     workspace ? workspace_bytes : (size_t)0);
     if (!aligned16(workspace))
         return fail(DASS_ERR_ALIGN, "%s: workspace must be 16-byte aligned", fn);
 
-    const int64_t rows = input_rows_per_block(T, d), n_row_blocks = (T + rows - 1) / rows;
+    const int64_t rows = input_rows_per_block(T, d, (int64_t)(workspace_bytes / ((size_t)d * sizeof(float))));
+    const int64_t n_row_blocks = (T + rows - 1) / rows;
     const int64_t slots = d / vec_elems(dt);
     const int64_t nbx = (slots + kInBlock - 1) / kInBlock;
     if (nbx * n_row_blocks > 0x7fffffffLL)

@@ -66,6 +66,30 @@ def test_input_norms_paths(gpu_device, dtype, T, d):
     assert all(torch.equal(a.view(torch.int32), b.view(torch.int32)) for a, b in zip(*got))
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_input_norms_one_workspace_for_every_chunk(gpu_device, dtype):
+    """Chunks of a stream in the workspace of the longest one, and every chunk in room for no more than
+    blocks of 512 rows (the least the call takes): the same sums, in longer blocks."""
+    d, chunks = 1032, (4097, 4096, 3000, 2048, 700, 8200, 1)
+    g = torch.Generator(device=gpu_device).manual_seed(3)
+    X = torch.randn((sum(chunks), d), generator=g, device=gpu_device).to(dtype)
+    want = oracle.input_sumsq(to_np32(X))
+    longest = torch.empty(dass.input_norms_workspace_bytes(max(chunks), d), dtype=torch.uint8, device=gpu_device)
+    for room in ("longest", "least"):
+        sumsq, lo = torch.zeros(d, device=gpu_device), 0
+        for T in chunks:
+            need = -(-(-(-T // 512) * d * 4) // 256) * 256
+            guarded = torch.full((need + 4096,), 0x5A, dtype=torch.uint8, device=gpu_device)
+            ws = longest if room == "longest" else guarded[:need]
+            dass.input_norms(X[lo:lo + T], sumsq, accumulate=True, workspace=ws)
+            lo += T
+            torch.cuda.synchronize()
+            assert torch.all(guarded[need:] == 0x5A)
+        assert _rel_err(sumsq.cpu().numpy(), want) <= TOL, room
+    with pytest.raises(dass.DassError):
+        dass.input_norms(X[:4097], sumsq, workspace=longest[:9 * d * 4 - 16])
+
+
 def test_input_norms_chunks_accumulate_and_zero_columns(gpu_device):
     T, d = 1500, 512
     g = torch.Generator(device="cpu").manual_seed(5)

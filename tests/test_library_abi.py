@@ -175,6 +175,16 @@ def test_input_norms_rejections(lib):
     assert lib.dass_input_norms_workspace_bytes(0, 4096) == 0
 
 
+@pytest.mark.parametrize("d", [8, 520, 3072, 4096, 8192, 28672, 1 << 20])
+def test_input_norms_workspace_serves_shorter_chunks(lib, d):
+    """A workspace sized for the longest chunk of a stream serves every shorter one: the size does not
+    decrease in T (the row blocks change length at 33, 2049, 4097, 16385, 32769 .. tokens)."""
+    near = {v + k for e in range(20) for v in (1 << e,) for k in (-1, 0, 1)} | set(range(1, 5000)) | set(range(5000, 300000, 997))
+    sizes = [lib.dass_input_norms_workspace_bytes(T, d) for T in sorted(near - {0})]
+    assert all(a <= b for a, b in zip(sizes, sizes[1:]))
+    assert all(lib.dass_input_norms_workspace_bytes(T, d) >= -(-T // 512) * d * 4 for T in (1, 512, 513, 262144))
+
+
 def _fwd(lib, X=FAKE, T=256, ldx=128, Wg=FAKE, Wu=FAKE, ldw=128, Wd=FAKE, ldd=192, d=128, d_int=192, dt=1, act=0,
          out=FAKE, ldo=128, ws=FAKE, wsb=1 << 20):
     return lib.dass_status_string(lib.dass_mlp_forward(X, T, ldx, Wg, Wu, ldw, Wd, ldd, d, d_int, dt, act, out, ldo,
