@@ -74,7 +74,7 @@ __global__ __launch_bounds__(kStripThreads) void input_strip_kernel(
                     acc[e] = fmaf(x, x, acc[e]);
                 }
         }
-        // up to kInUnroll - 1 rows left: all loads first, a row past the end repeats row r and adds nothing
+        // up to kInUnroll - 1 rows left: all loads first; a row past the end is neither loaded nor added
         u32x4 v[kInUnroll - 1];
 #pragma unroll
         for (int k = 0; k < kInUnroll - 1; ++k)
@@ -227,13 +227,15 @@ static int64_t input_most_blocks(int64_t T, int64_t d)
     return blocks > large ? blocks : large;
 }
 
-// Few tokens take input_strip_kernel: its workgroups read 64 bytes of every row, so its time grows with
-// T whatever d is, but there is no second launch to wait for.  bf16, us a call, strips against row blocks
-// (both bound by the host's launches below 11 us): 2048 tokens 8.8 against 11.7 (d = 4096), 10.9 against
-// 11.5 (8192); 4096 tokens 9.7 against 11.6 (d = 2048), but 16.6 against 11.5 (4096).
+// Few tokens take input_strip_kernel: its workgroups read 64 bytes of every row, so there is no second
+// launch to wait for, but its time grows with T whatever d is, and with the rounds of workgroups that a long
+// row takes.  us a call, strips against row blocks: bf16, 4096 tokens 6.8 and 9.8 (d = 1024), 7.3 and 10.6
+// (2048), 17.6 and 11.3 (4096); 2048 tokens 6.6 and 10.3 (4096), 11.8 and 10.8 (8192); f32, 2048 tokens 10.8
+// and 10.5 (4096), 63.6 and 42.2 (28672), 1024 tokens 6.7 and 10.1 (5120), 11.1 and 11.2 (8192).  The two
+// meet at 24 to 32 MB of X.
 static bool input_by_strips(int64_t T, int64_t row_bytes)
 {
-    return T <= 2048 || (T <= 4096 && row_bytes <= 4096);
+    return (T <= 2048 || (T <= 4096 && row_bytes <= 4096)) && row_bytes <= (24LL << 20) / T;
 }
 
 }  // namespace dass

@@ -47,6 +47,7 @@ def test_input_norms_small_and_ragged(gpu_device, dtype, T, d, pad):
 @pytest.mark.parametrize("T,d", [
     (2047, 32), (2048, 1032), (2049, 72),                   # either side of strips / row blocks (wide rows)
     (4096, 1024), (4097, 1024), (4096, 2056),               # the same for rows of up to 4096 bytes
+    (2000, 6288), (1500, 8384), (96, 131080),               # either side of 24 MiB of X in each type; long rows
     (1793, 40), (257, 4096),                                # strips: every length of the last batch of rows, a short strip
     (33000, 1032), (40000, 8)])                             # row blocks that are no power of two, one column slot
 def test_input_norms_paths(gpu_device, dtype, T, d):
