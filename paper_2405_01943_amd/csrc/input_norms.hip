@@ -18,6 +18,7 @@ namespace dass {
 constexpr int kInBlock = 256;     // threads = column slots per workgroup
 constexpr int kInUnroll = 8;      // rows in flight per thread
 constexpr int kInMaxRows = 512;   // rows per row block, at most (a multiple of kInUnroll)
+constexpr int64_t kReduceCols = 1 << 27;   // columns of one reduction launch, at most: a grid has fewer than 2^32 threads
 
 // The last step of either path: sumsq (+)= total, norm = sqrt(sumsq).
 __device__ __forceinline__ void finish_column(double total, int64_t j, float *__restrict__ sumsq, int accumulate,
@@ -170,12 +171,12 @@ __global__ __launch_bounds__(kInBlock) void input_partial_kernel(
 // (w, w + kReduceWaves, ...) in f64, then the wavefronts' sums are added in a fixed order.
 constexpr int kReduceWaves = 16;
 __global__ __launch_bounds__(64 * kReduceWaves) void input_reduce_kernel(
-    const float *__restrict__ partial, int64_t n_row_blocks, int64_t d, float *__restrict__ sumsq,
+    const float *__restrict__ partial, int64_t n_row_blocks, int64_t d, int64_t j0, float *__restrict__ sumsq,
     int accumulate, float *__restrict__ norms)
 {
     __shared__ double part[kReduceWaves][64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int64_t j = (int64_t)blockIdx.x * 64 + lane;
+    const int64_t j = j0 + (int64_t)blockIdx.x * 64 + lane;
     double s = 0.0;
     if (j < d) {
         int64_t b = w;
@@ -304,7 +305,13 @@ extern "C" dass_status dass_input_norms(const void *X, int64_t T, int64_t ldx, i
     dass_status s = check_launch("input-norm kernel");
     if (s != DASS_OK)
         return s;
-    hipLaunchKernelGGL(input_reduce_kernel, dim3((unsigned)((d + 63) / 64)), dim3(64 * kReduceWaves), 0, stream,
-                       (const float *)partial, n_row_blocks, d, sumsq, accumulate, norms_out);
-    return check_launch("input-norm reduction");
+    for (int64_t j0 = 0; j0 < d; j0 += kReduceCols) {
+        const int64_t n = d - j0 < kReduceCols ? d - j0 : kReduceCols;
+        hipLaunchKernelGGL(input_reduce_kernel, dim3((unsigned)((n + 63) / 64)), dim3(64 * kReduceWaves), 0, stream,
+                           (const float *)partial, n_row_blocks, d, j0, sumsq, accumulate, norms_out);
+        s = check_launch("input-norm reduction");
+        if (s != DASS_OK)
+            return s;
+    }
+    return DASS_OK;
 }

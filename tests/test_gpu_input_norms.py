@@ -142,6 +142,18 @@ def test_input_norms_full_size_and_wanda_masks(gpu_device):
     assert bits_equal(W, want_w), first_mismatch(W, want_w)
 
 
+def test_input_norms_more_columns_than_one_reduction(gpu_device):
+    """A reduction launch of 16 threads a column holds fewer than 2^28 columns."""
+    d = (1 << 28) + 64
+    X = torch.ones((1, d), dtype=torch.bfloat16, device=gpu_device)
+    X[0, :64] = X[0, -64:] = torch.arange(64, device=gpu_device)
+    X[0, (1 << 27) - 8:(1 << 27) + 8] = 3.0
+    sumsq = torch.full((d,), -1.0, device=gpu_device)
+    dass.input_norms(X, sumsq)
+    torch.cuda.synchronize()
+    assert torch.equal(sumsq, X[0].float().square())   # squares of bf16 are exact
+
+
 def test_input_norms_argument_errors(gpu_device):
     X = torch.ones((16, 12), dtype=torch.bfloat16, device=gpu_device)    # 12 features: not a multiple of 8
     with pytest.raises(dass.DassError):
