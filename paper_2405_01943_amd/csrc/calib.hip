@@ -809,8 +809,9 @@ __global__ __launch_bounds__(256) void calib_f32_kernel(
         float part = 0.0f;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const float y = glu_act_precise(g[r], act) * u[r];
-            part = fmaf(t_block + 4 * fc + r < T ? y : 0.0f, y, part);
+            // a row past the end is a copy of the last token: its y may be infinite, and 0 times that a NaN
+            const float y = t_block + 4 * fc + r < T ? glu_act_precise(g[r], act) * u[r] : 0.0f;
+            part = fmaf(y, y, part);
         }
         return part;
     };

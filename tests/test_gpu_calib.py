@@ -108,6 +108,23 @@ def test_calib_f32_chunks_and_tiles(gpu_device, T, I, d):
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("T,I", [(1, 40), (33, 70), (1100, 970)])   # f32: K split over wavefronts, and not
+def test_calib_overflow_of_the_last_token(gpu_device, dtype, T, I):
+    """A last token whose y overflows makes the norms of its neurons infinite, not NaN, however much of
+    the last tile of tokens is filled; the other neurons keep theirs."""
+    d = 64
+    X, Wg, Wu = _inputs(T, d, I, dtype, gpu_device, seed=11)
+    X[-1] = 1e19
+    Wg[::2], Wu[::2] = 1e6, 1e6        # y = (64e25)^2: beyond f32
+    Wg[1::2, :], Wu[1::2, :] = -1.0, 1e-3   # silu of a large negative number: 0
+    sumsq, norms = torch.zeros(I, device=gpu_device), torch.zeros(I, device=gpu_device)
+    dass.calib_norms(X, Wg, Wu, "silu", sumsq, norms_out=norms)
+    torch.cuda.synchronize()
+    assert torch.all(torch.isposinf(sumsq[::2])) and torch.all(torch.isposinf(norms[::2]))
+    assert torch.all(torch.isfinite(sumsq[1::2]))
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_calib_several_tiles_both_ways(gpu_device, dtype):
     X, Wg, Wu = _inputs(700, 320, 400, dtype, gpu_device, seed=2)
     _check(X, Wg, Wu, "silu", gpu_device)
