@@ -16,8 +16,8 @@
 //               makes a single pass (many small workgroups keep HBM busier than a
 //               resident grid that loops).
 //   nm_*        every other (n_keep, m): factor vector from a helper kernel; groups of
-//               4 and 8 by their cut from a sorting network where it decides them, the
-//               rest by f64 products and counting wins per lane.
+//               4 and 8 by their cut from a sorting network, groups of 16 by f64 products
+//               and counting wins per lane.
 #include "select.h"
 
 #include <cstdio>
@@ -568,17 +568,20 @@ __global__ __launch_bounds__(kBlock) void nm_half_batched_kernel(const NmBatch b
 // of one or more groups of M rows (groups down the columns: Gate-Proj, Up-Proj), in one pass of
 // many small workgroups with non-temporal accesses like the nm_half_* kernels.
 //
-// With CUT every group is first decided in f32 by its cut (select.h: one sorting network instead
-// of M (M - 1) / 2 comparisons of f64 products); a wavefront with a group whose leading terms tie
-// at the cut, or a factor or product outside the fast range, fetches its weights again and
-// compares f64 products.  The arithmetic of the f64 comparison bounded this path: 2:8 of 13824 x
-// 5120 bf16 with mask took 86 us down the rows and 68 us along them that way, 53 and 52 us by the cut.
+// With CUT every group is decided in f32 by its cut (select.h: one sorting network instead of M (M - 1) / 2
+// comparisons of f64 products), with the error terms where leading terms tie there; a wavefront with a
+// factor or product outside the fast range fetches its weights again and compares f64 products.  bf16 with
+// mask, us down the rows and along them, f64 products against the cut: 13824 x 5120 2:8 88.6 and 68.0 ->
+// 51.9 and 52.0, 1:4 63.0 and 57.7 -> 49.9 and 52.7; with half of the weights 0, so that some group of every
+// wavefront ties, 2:8 88.4 and 68.4 -> 57.4 and 52.2, 1:4 61.8 and 57.4 -> 54.6 and 54.5.  (Ties left to f64
+// products after a second fetch took 83.2 and 82.5, 59.0 and 73.2: slower along the rows than f64 alone.)
 // ---------------------------------------------------------------------------
 
-// The cut of one group of weights x[0..M) with scaled factors fs[0..M): kept[a] is x[a] or +0.
+// One group of weights x[0..M) with scaled factors fs[0..M) by its cut: kept[a] is x[a] or +0, bit a of the
+// result says which.  Leading terms that tie at the cut are settled by their error terms and then by the
+// index (the order of the exact scores, select.h).
 template <int M>
-__device__ __forceinline__ uint32_t cut_group(const float *x, const float *fs, int n_keep, uint32_t *kept, bool &undecided,
-                                              float &top_all)
+__device__ __forceinline__ uint32_t cut_group(const float *x, const float *fs, int n_keep, uint32_t *kept, float &top_all)
 {
     float p[M];
 #pragma unroll
@@ -586,15 +589,57 @@ __device__ __forceinline__ uint32_t cut_group(const float *x, const float *fs, i
         p[a] = fabsf(x[a]) * fs[a];
     float cut, next, top;
     group_rank_cut<M>(p, n_keep, cut, next, top);
-    undecided |= next == cut;
     top_all = fmaxf(top_all, top);
     uint32_t bits = 0;
+    if (__builtin_amdgcn_ballot_w64(next == cut) == 0) {
 #pragma unroll
-    for (int a = 0; a < M; ++a) {
-        const bool keep = p[a] >= cut;
-        kept[a] = keep ? __float_as_uint(x[a]) : 0u;
-        bits |= keep ? 1u << a : 0u;
+        for (int a = 0; a < M; ++a) {
+            const bool keep = p[a] >= cut;
+            kept[a] = keep ? __float_as_uint(x[a]) : 0u;
+            bits |= keep ? 1u << a : 0u;
+        }
+        return bits;
     }
+    if (__builtin_amdgcn_ballot_w64(next == cut && cut != 0.0f) == 0) {
+        // Scores of exactly 0 tie (sparse weights): all that is dropped is the last of them.  (In the
+        // lanes without a tie the M - n_keep positions below the cut are, whatever the order.)
+        uint32_t low = 0;
+#pragma unroll
+        for (int a = 0; a < M; ++a)
+            low |= p[a] > next ? 0u : 1u << a;
+        bits = (1u << M) - 1;
+        for (int k = n_keep; k < M; ++k) {   // uniform
+            const uint32_t last = low ? 0x80000000u >> __clz((int)low) : 0u;   // 0: a product overflowed
+            bits ^= last;
+            low ^= last;
+        }
+    } else {
+        float q[M];
+        int wanted = n_keep;   // of the positions that tie at the cut
+#pragma unroll
+        for (int a = 0; a < M; ++a) {
+            q[a] = fmaf(fabsf(x[a]), fs[a], -p[a]);
+            wanted -= p[a] > cut ? 1 : 0;
+        }
+        int above[M];
+#pragma unroll
+        for (int a = 0; a < M; ++a)
+            above[a] = 0;
+#pragma unroll
+        for (int a = 0; a < M; ++a)
+#pragma unroll
+            for (int b = a + 1; b < M; ++b) {
+                const bool b_first = q[b] > q[a];   // equal: the lower index
+                above[a] += p[b] == cut && b_first ? 1 : 0;
+                above[b] += p[a] == cut && !b_first ? 1 : 0;
+            }
+#pragma unroll
+        for (int a = 0; a < M; ++a)
+            bits |= p[a] > cut || (p[a] == cut && above[a] < wanted) ? 1u << a : 0u;
+    }
+#pragma unroll
+    for (int a = 0; a < M; ++a)
+        kept[a] = ((bits >> a) & 1u) ? __float_as_uint(x[a]) : 0u;
     return bits;
 }
 
@@ -693,7 +738,7 @@ __global__ __launch_bounds__(kBlock) void nm_cols_kernel(
     };
     bool exact = true;
     if constexpr (CUT) {
-        bool undecided = false, ok = true;
+        bool ok = true;
         float top_all = 0.0f, fs[UW];
 #pragma unroll
         for (int e = 0; e < UW; ++e) {
@@ -701,9 +746,9 @@ __global__ __launch_bounds__(kBlock) void nm_cols_kernel(
             fs[e] = fc[e] * kFactorScale;
         }
         select_rows([&](const float *x, int e, int, uint32_t *kept) {
-            return cut_group<M>(x, fs + e, n_keep, kept, undecided, top_all);
+            return cut_group<M>(x, fs + e, n_keep, kept, top_all);
         });
-        exact = __builtin_amdgcn_ballot_w64(undecided || !ok || !(top_all < INFINITY)) != 0;
+        exact = __builtin_amdgcn_ballot_w64(!ok || !(top_all < INFINITY)) != 0;
         if (exact)
             fetch();
     }
@@ -797,7 +842,7 @@ __global__ __launch_bounds__(kBlock) void nm_rows_kernel(
     };
     bool exact = true;
     if constexpr (CUT) {
-        bool undecided = false, ok = true;
+        bool ok = true;
         float top_all = 0.0f, fs[M];
 #pragma unroll
         for (int a = 0; a < M; ++a) {
@@ -805,9 +850,9 @@ __global__ __launch_bounds__(kBlock) void nm_rows_kernel(
             fs[a] = fr[a] * kFactorScale;
         }
         select_cols([&](const float *x, int, uint32_t *kept) {
-            return cut_group<M>(x, fs, n_keep, kept, undecided, top_all);
+            return cut_group<M>(x, fs, n_keep, kept, top_all);
         });
-        exact = __builtin_amdgcn_ballot_w64(undecided || !ok || !(top_all < INFINITY)) != 0;
+        exact = __builtin_amdgcn_ballot_w64(!ok || !(top_all < INFINITY)) != 0;
         if (exact)
             fetch();
     }

@@ -121,7 +121,7 @@ def test_nm_extreme_magnitudes(gpu_device, dtype, axes, n_keep, m):
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("axes", [("rows", "rows"), ("cols", "cols")])
-@pytest.mark.parametrize("n_keep,m", [(2, 4), (4, 8)])
+@pytest.mark.parametrize("n_keep,m", [(2, 4), (4, 8), (1, 4), (3, 4), (2, 8), (5, 8)])
 def test_nm_near_ties_decided_below_f32_precision(gpu_device, dtype, axes, n_keep, m):
     """Groups whose scores agree to f32 precision and differ only below it: weight k of a group
     is 1 + k/128 and its norm is fl32(P / weight), so all m products are P up to an f32 rounding
