@@ -29,7 +29,10 @@ namespace dass {
 
 constexpr int kBlock = 256;
 constexpr int kHalfColsRows = 4;   // 16-byte vectors per thread of nm_half_cols_kernel
-constexpr int kGeneralColsRows = 4;   // rows per thread of nm_cols_kernel
+// Rows per thread of nm_cols_kernel: four 16-byte vectors for groups of up to 8, whichever the type.  f32
+// with four rows kept 67 MB matrices from the rate they had: 8:16 of 4096 x 4096 with mask 49 us, 43 with
+// two (13824 x 5120 150 and 142), 1:4 32 and 30.
+constexpr int general_cols_rows(int dt) { return dt == DASS_BF16 ? 4 : 2; }
 
 // 16-byte accesses.  Non-temporal where a wavefront's access is contiguous; where a thread owns
 // several vectors of a row (NV > 1) the lanes of one access are 16 NV bytes apart and the caches
@@ -680,7 +683,7 @@ __global__ __launch_bounds__(kBlock) void nm_cols_kernel(
     int n_keep, uint8_t *__restrict__ mask, uint32_t nbx)
 {
     constexpr int EPV = DT == DASS_BF16 ? 8 : 4;
-    constexpr int UW = M > 8 ? M : 8, NV = UW / EPV, RB = kGeneralColsRows;
+    constexpr int UW = M > 8 ? M : 8, NV = UW / EPV, RB = general_cols_rows(DT);
     constexpr int EB = DT == DASS_BF16 ? 2 : 4;
 
     const int64_t bx = blockIdx.x % nbx, by = blockIdx.x / nbx;
@@ -1098,7 +1101,7 @@ extern "C" dass_status dass_score_mask_nm(void *W, int64_t rows, int64_t cols, i
     nm_kernel_t kernel = dt == DASS_BF16 ? pick_kernel_m<DASS_BF16>(m, group_axis, norm_axis)
                                          : pick_kernel_m<DASS_F32>(m, group_axis, norm_axis);
     const HalfGeometry g = group_axis == DASS_AXIS_COLS
-                               ? one_pass_geometry(cols / (m > 8 ? m : 8), (rows + kGeneralColsRows - 1) / kGeneralColsRows)
+                               ? one_pass_geometry(cols / (m > 8 ? m : 8), (rows + general_cols_rows(dt) - 1) / general_cols_rows(dt))
                                : one_pass_geometry(cols / 8, rows / m);
     if (g.nbx * g.batches > 0x7fffffffLL)
         return fail(DASS_ERR_SHAPE, "%s: matrix too large for one launch", fn);
