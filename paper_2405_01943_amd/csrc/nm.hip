@@ -7,8 +7,8 @@
 //
 // Two families of kernels:
 //   nm_half_*   the patterns the paper uses, n_keep = m / 2 for m = 2, 4, 8, with
-//               alpha in {0, 0.5, 1}: the factor is computed in the kernel (any other
-//               alpha: factor vector from a helper kernel); a group
+//               alpha in {0, 0.5, 1}: the factor is computed in the kernel; with any other
+//               alpha they read it from a helper kernel's vector (bf16 4:8 along the rows goes to nm_*); a group
 //               is decided by its cut (the m / 2-th largest leading term, from a
 //               min/max network) whenever the leading terms decide it, else by
 //               pairwise comparison of exact two-term f32 scores, bit-sliced over
@@ -580,10 +580,12 @@ __global__ __launch_bounds__(kBlock) void nm_half_batched_kernel(const NmBatch b
 // products after a second fetch took 83.2 and 82.5, 59.0 and 73.2: slower along the rows than f64 alone.)
 // ---------------------------------------------------------------------------
 
+enum { kNoCut = 0, kAnyCut = 1, kHalfCut = 2 };   // kHalfCut: n_keep = M / 2, whose network is the shorter one
+
 // One group of weights x[0..M) with scaled factors fs[0..M) by its cut: kept[a] is x[a] or +0, bit a of the
 // result says which.  Leading terms that tie at the cut are settled by their error terms and then by the
 // index (the order of the exact scores, select.h).
-template <int M>
+template <int M, int CUT>
 __device__ __forceinline__ uint32_t cut_group(const float *x, const float *fs, int n_keep, uint32_t *kept, float &top_all)
 {
     float p[M];
@@ -591,10 +593,13 @@ __device__ __forceinline__ uint32_t cut_group(const float *x, const float *fs, i
     for (int a = 0; a < M; ++a)
         p[a] = fabsf(x[a]) * fs[a];
     float cut, next, top;
-    group_rank_cut<M>(p, n_keep, cut, next, top);
+    if constexpr (CUT == kHalfCut)
+        group_cut<M>(p, cut, next, top);
+    else
+        group_rank_cut<M>(p, n_keep, cut, next, top);
     top_all = fmaxf(top_all, top);
     uint32_t bits = 0;
-    if (__builtin_amdgcn_ballot_w64(next == cut) == 0) {
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(next == cut) == 0, 1)) {
 #pragma unroll
         for (int a = 0; a < M; ++a) {
             const bool keep = p[a] >= cut;
@@ -677,7 +682,7 @@ __device__ __forceinline__ void pack8(u32x4 *v, const uint32_t *kept)
     }
 }
 
-template <int DT, int M, bool NORM_COLS, bool CUT>
+template <int DT, int M, bool NORM_COLS, int CUT>
 __global__ __launch_bounds__(kBlock) void nm_cols_kernel(
     void *__restrict__ Wv, int64_t rows, int64_t cols, int64_t ld, const float *__restrict__ f,
     int n_keep, uint8_t *__restrict__ mask, uint32_t nbx)
@@ -740,7 +745,7 @@ __global__ __launch_bounds__(kBlock) void nm_cols_kernel(
         }
     };
     bool exact = true;
-    if constexpr (CUT) {
+    if constexpr (CUT != kNoCut) {
         bool ok = true;
         float top_all = 0.0f, fs[UW];
 #pragma unroll
@@ -749,7 +754,7 @@ __global__ __launch_bounds__(kBlock) void nm_cols_kernel(
             fs[e] = fc[e] * kFactorScale;
         }
         select_rows([&](const float *x, int e, int, uint32_t *kept) {
-            return cut_group<M>(x, fs + e, n_keep, kept, top_all);
+            return cut_group<M, CUT>(x, fs + e, n_keep, kept, top_all);
         });
         exact = __builtin_amdgcn_ballot_w64(!ok || !(top_all < INFINITY)) != 0;
         if (exact)
@@ -780,7 +785,7 @@ __global__ __launch_bounds__(kBlock) void nm_cols_kernel(
 }
 
 // One group of M rows per thread: a second one would only lengthen the pass.
-template <int DT, int M, bool NORM_ROWS, bool CUT>
+template <int DT, int M, bool NORM_ROWS, int CUT>
 __global__ __launch_bounds__(kBlock) void nm_rows_kernel(
     void *__restrict__ Wv, int64_t rows, int64_t cols, int64_t ld, const float *__restrict__ f,
     int n_keep, uint8_t *__restrict__ mask, uint32_t nbx)
@@ -844,7 +849,7 @@ __global__ __launch_bounds__(kBlock) void nm_rows_kernel(
         }
     };
     bool exact = true;
-    if constexpr (CUT) {
+    if constexpr (CUT != kNoCut) {
         bool ok = true;
         float top_all = 0.0f, fs[M];
 #pragma unroll
@@ -853,7 +858,7 @@ __global__ __launch_bounds__(kBlock) void nm_rows_kernel(
             fs[a] = fr[a] * kFactorScale;
         }
         select_cols([&](const float *x, int, uint32_t *kept) {
-            return cut_group<M>(x, fs, n_keep, kept, top_all);
+            return cut_group<M, CUT>(x, fs, n_keep, kept, top_all);
         });
         exact = __builtin_amdgcn_ballot_w64(!ok || !(top_all < INFINITY)) != 0;
         if (exact)
@@ -900,20 +905,24 @@ using nm_kernel_t = void (*)(void *, int64_t, int64_t, int64_t, const float *, i
 // (16 positions, or one factor for the whole group: bf16 magnitudes tie all the time, see
 // pick_half_kernel) by f64 products straight away.
 template <int DT, int M>
-static nm_kernel_t pick_kernel(int group_axis, int norm_axis)
+static nm_kernel_t pick_kernel(int group_axis, int norm_axis, int n_keep)
 {
+    constexpr int kCut = M <= 8 ? kAnyCut : kNoCut;
+    if constexpr (DT == DASS_BF16 && M == 8)   // the one half pattern that comes here
+        if (n_keep == M / 2 && group_axis == DASS_AXIS_COLS && norm_axis == DASS_AXIS_COLS)
+            return nm_cols_kernel<DT, M, true, kHalfCut>;
     if (group_axis == DASS_AXIS_COLS)
-        return norm_axis == DASS_AXIS_COLS ? nm_cols_kernel<DT, M, true, M <= 8> : nm_cols_kernel<DT, M, false, false>;
-    return norm_axis == DASS_AXIS_ROWS ? nm_rows_kernel<DT, M, true, M <= 8> : nm_rows_kernel<DT, M, false, false>;
+        return norm_axis == DASS_AXIS_COLS ? nm_cols_kernel<DT, M, true, kCut> : nm_cols_kernel<DT, M, false, kNoCut>;
+    return norm_axis == DASS_AXIS_ROWS ? nm_rows_kernel<DT, M, true, kCut> : nm_rows_kernel<DT, M, false, kNoCut>;
 }
 
 template <int DT>
-static nm_kernel_t pick_kernel_m(int m, int group_axis, int norm_axis)
+static nm_kernel_t pick_kernel_m(int m, int group_axis, int norm_axis, int n_keep)
 {
     switch (m) {
-    case 4: return pick_kernel<DT, 4>(group_axis, norm_axis);
-    case 8: return pick_kernel<DT, 8>(group_axis, norm_axis);
-    case 16: return pick_kernel<DT, 16>(group_axis, norm_axis);
+    case 4: return pick_kernel<DT, 4>(group_axis, norm_axis, n_keep);
+    case 8: return pick_kernel<DT, 8>(group_axis, norm_axis, n_keep);
+    case 16: return pick_kernel<DT, 16>(group_axis, norm_axis, n_keep);
     }
     return nullptr;   // 1:2 is a half pattern
 }
@@ -1082,14 +1091,21 @@ extern "C" dass_status dass_score_mask_nm(void *W, int64_t rows, int64_t cols, i
     }
 
     // The paper's patterns.  With any other exponent the factor vector takes the norms' place and
-    // counts as a norm of exponent 1: the kernel's scores are |w| f either way.  4:8 of 13824 x
-    // 5120 bf16 with mask, alpha = 0.25: 87 us by f64 products, 47 us + the factors so.
-    if (half_pattern(n_keep, m)) {
+    // counts as a norm of exponent 1: the kernel's scores are |w| f either way.  Such groups compare pairs
+    // straight away, which costs nothing on dense weights and no second fetch on sparse ones, except in bf16
+    // 4:8, whose pairs are bound by their arithmetic: cut first down the rows, the kernel of the other
+    // patterns along them.  13824 x 5120 with mask, alpha = 0.25, us down the rows and along them, dense and
+    // with half of the weights 0: bf16 1:2 pairs 51 51, 51 51, cut first 54 54, 72 71; 2:4 pairs 51 51, 51 51,
+    // cut first 52 53, 52 71; f32 2:4 pairs 92 95, 92 95, cut first 96 100, 96 159; f32 4:8 pairs 96 112, 95 111,
+    // cut first 101 110, 101 126; bf16 4:8 cut first 51 53, 76 75, nm_rows / nm_cols 51 52, 55 52, pairs 62 56,
+    // 62 55, f64 products 88 70, 87 70 (down the rows nm_rows takes 1 us more a matrix back to back).
+    const bool half_kernel = own_factor || m < 8 || dt == DASS_F32 || group_axis == DASS_AXIS_ROWS || norm_axis == DASS_AXIS_ROWS;
+    if (half_pattern(n_keep, m) && half_kernel) {
         const int fmode = !own_factor ? kFactorNorm : alpha == 0.0 ? kFactorOne : alpha == 1.0 ? kFactorNorm : kFactorSqrt;
-        const bool varying = norm_axis == group_axis && alpha != 0.0;
+        const bool cut_first = norm_axis == group_axis && alpha != 0.0 && (own_factor || (m == 8 && dt == DASS_BF16));
         nm_half_kernel_t kernel =
-            dt == DASS_BF16 ? pick_half_kernel_mask<DASS_BF16>(mask_out != nullptr, m, group_axis, norm_axis, varying)
-                            : pick_half_kernel_mask<DASS_F32>(mask_out != nullptr, m, group_axis, norm_axis, varying);
+            dt == DASS_BF16 ? pick_half_kernel_mask<DASS_BF16>(mask_out != nullptr, m, group_axis, norm_axis, cut_first)
+                            : pick_half_kernel_mask<DASS_F32>(mask_out != nullptr, m, group_axis, norm_axis, cut_first);
         const HalfGeometry g = half_geometry(rows, cols, dt, group_axis, m);
         if (g.nbx * g.batches > 0x7fffffffLL)
             return fail(DASS_ERR_SHAPE, "%s: matrix too large for one launch", fn);
@@ -1098,8 +1114,8 @@ extern "C" dass_status dass_score_mask_nm(void *W, int64_t rows, int64_t cols, i
         return check_launch("N:M kernel");
     }
 
-    nm_kernel_t kernel = dt == DASS_BF16 ? pick_kernel_m<DASS_BF16>(m, group_axis, norm_axis)
-                                         : pick_kernel_m<DASS_F32>(m, group_axis, norm_axis);
+    nm_kernel_t kernel = dt == DASS_BF16 ? pick_kernel_m<DASS_BF16>(m, group_axis, norm_axis, n_keep)
+                                         : pick_kernel_m<DASS_F32>(m, group_axis, norm_axis, n_keep);
     const HalfGeometry g = group_axis == DASS_AXIS_COLS
                                ? one_pass_geometry(cols / (m > 8 ? m : 8), (rows + general_cols_rows(dt) - 1) / general_cols_rows(dt))
                                : one_pass_geometry(cols / 8, rows / m);
