@@ -1000,31 +1000,43 @@ static nm_batched_kernel_t pick_batched_kernel_m(int m, int group_axis, int norm
 struct HalfGeometry {
     int block;
     int64_t nbx, batches;
+    int64_t rows_per_batch;
 };
 // Workgroup width: the widest of 256, 128, 64 that leaves the fewest idle lanes in the last
 // workgroup of a row (e.g. 1376 slots: 6 x 256 idles 10 %, 11 x 128 only 2 %).
-static HalfGeometry one_pass_geometry(int64_t slots, int64_t batches)
+static HalfGeometry one_pass_geometry(int64_t slots, int64_t rows, int64_t rows_per_batch)
 {
     int block = kBlock;
     for (int cand = kBlock / 2; cand >= 64; cand /= 2)
         if ((slots + cand - 1) / cand * cand < (slots + block - 1) / block * block)
             block = cand;
-    return {block, (slots + block - 1) / block, batches};
+    return {block, (slots + block - 1) / block, (rows + rows_per_batch - 1) / rows_per_batch, rows_per_batch};
+}
+
+// Calls launch(first row, rows, workgroups) for the whole matrix, or for one range of rows after the other
+// where its grid would have 2^32 threads or more (a thread covers little of a narrow matrix: 8 columns
+// leave 63 of 64 lanes idle).
+template <typename Launch>
+static dass_status for_row_ranges(const HalfGeometry &g, int64_t rows, Launch launch)
+{
+    const int64_t most = 0xffffffffLL / (g.nbx * g.block), step = (most < 1 ? 1 : most) * g.rows_per_batch;
+    for (int64_t r0 = 0; r0 < rows; r0 += step) {
+        const int64_t n = rows - r0 < step ? rows - r0 : step;
+        launch(r0, n, (unsigned)(g.nbx * ((n + g.rows_per_batch - 1) / g.rows_per_batch)));
+        const dass_status st = check_launch("N:M kernel");
+        if (st != DASS_OK)
+            return st;
+    }
+    return DASS_OK;
 }
 static HalfGeometry half_geometry(int64_t rows, int64_t cols, int dt, int group_axis, int m)
 {
     const int epv = vec_elems(dt);
-    int64_t slots, batches;
     if (group_axis == DASS_AXIS_COLS) {
-        const int uw = m > epv ? m : epv, rb = kHalfColsRows / (uw / epv);
-        slots = cols / uw;
-        batches = (rows + rb - 1) / rb;
-    } else {
-        slots = cols / epv;
-        const int gb = m >= 4 ? 1 : 2;
-        batches = (rows / m + gb - 1) / gb;
+        const int uw = m > epv ? m : epv;
+        return one_pass_geometry(cols / uw, rows, kHalfColsRows / (uw / epv));
     }
-    return one_pass_geometry(slots, batches);
+    return one_pass_geometry(cols / epv, rows, m >= 4 ? m : 2 * m);
 }
 
 static bool half_pattern(int n_keep, int m) { return 2 * n_keep == m && m <= 8; }
@@ -1090,6 +1102,11 @@ extern "C" dass_status dass_score_mask_nm(void *W, int64_t rows, int64_t cols, i
             return st;
     }
 
+    // where row r0 of the matrix, of its mask bits and of a vector along the norm axis begins
+    auto W_from = [&](int64_t r0) -> void * { return static_cast<char *>(W) + r0 * ld * elem_bytes(dt); };
+    auto mask_from = [&](int64_t r0) { return mask_out ? mask_out + r0 * (cols / 8) : nullptr; };
+    auto norms_from = [&](const float *v, int64_t r0) { return norm_axis == DASS_AXIS_ROWS ? v + r0 : v; };
+
     // The paper's patterns.  With any other exponent the factor vector takes the norms' place and
     // counts as a norm of exponent 1: the kernel's scores are |w| f either way.  Such groups compare pairs
     // straight away, which costs nothing on dense weights and no second fetch on sparse ones, except in bf16
@@ -1107,23 +1124,22 @@ extern "C" dass_status dass_score_mask_nm(void *W, int64_t rows, int64_t cols, i
             dt == DASS_BF16 ? pick_half_kernel_mask<DASS_BF16>(mask_out != nullptr, m, group_axis, norm_axis, cut_first)
                             : pick_half_kernel_mask<DASS_F32>(mask_out != nullptr, m, group_axis, norm_axis, cut_first);
         const HalfGeometry g = half_geometry(rows, cols, dt, group_axis, m);
-        if (g.nbx * g.batches > 0x7fffffffLL)
+        if (own_factor && g.nbx * g.batches > 0x7fffffffLL)
             return fail(DASS_ERR_SHAPE, "%s: matrix too large for one launch", fn);
-        hipLaunchKernelGGL(kernel, dim3((unsigned)(g.nbx * g.batches)), dim3(g.block), 0, stream, W, rows, cols, ld,
-                           own_factor ? norms : (const float *)f, fmode, mask_out, (uint32_t)g.nbx);
-        return check_launch("N:M kernel");
+        return for_row_ranges(g, rows, [&](int64_t r0, int64_t n, unsigned grid) {
+            hipLaunchKernelGGL(kernel, dim3(grid), dim3(g.block), 0, stream, W_from(r0), n, cols, ld,
+                               norms_from(own_factor ? norms : f, r0), fmode, mask_from(r0), (uint32_t)g.nbx);
+        });
     }
 
     nm_kernel_t kernel = dt == DASS_BF16 ? pick_kernel_m<DASS_BF16>(m, group_axis, norm_axis, n_keep)
                                          : pick_kernel_m<DASS_F32>(m, group_axis, norm_axis, n_keep);
-    const HalfGeometry g = group_axis == DASS_AXIS_COLS
-                               ? one_pass_geometry(cols / (m > 8 ? m : 8), (rows + general_cols_rows(dt) - 1) / general_cols_rows(dt))
-                               : one_pass_geometry(cols / 8, rows / m);
-    if (g.nbx * g.batches > 0x7fffffffLL)
-        return fail(DASS_ERR_SHAPE, "%s: matrix too large for one launch", fn);
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(g.nbx * g.batches)), dim3(g.block), 0, stream, W, rows, cols, ld,
-                       (const float *)f, n_keep, mask_out, (uint32_t)g.nbx);
-    return check_launch("N:M kernel");
+    const HalfGeometry g = group_axis == DASS_AXIS_COLS ? one_pass_geometry(cols / (m > 8 ? m : 8), rows, general_cols_rows(dt))
+                                                        : one_pass_geometry(cols / 8, rows, m);
+    return for_row_ranges(g, rows, [&](int64_t r0, int64_t n, unsigned grid) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(g.block), 0, stream, W_from(r0), n, cols, ld, norms_from(f, r0), n_keep,
+                           mask_from(r0), (uint32_t)g.nbx);
+    });
 }
 
 extern "C" size_t dass_nm_batched_workspace_bytes(const dass_nm_task *tasks, int64_t n_tasks)

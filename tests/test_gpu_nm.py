@@ -179,6 +179,27 @@ def test_nm_cut_and_exact_groups_side_by_side(gpu_device, dtype, axes, n_keep, m
     assert np.array_equal(mask.cpu().numpy(), want_mask)
 
 
+@pytest.mark.parametrize("axes", [("rows", "rows"), ("cols", "cols")])
+@pytest.mark.parametrize("n_keep,m", [(1, 4), (2, 4)])
+def test_nm_narrow_matrix_of_many_rows(gpu_device, axes, n_keep, m):
+    """2^28 rows of 8 columns, whose one grid would have 2^32 threads: other exponents take any number of
+    rows.  The rows repeat, so that one period against the oracle says what all of them have to be."""
+    period, repeat = 4096, 1 << 16
+    g = torch.Generator(device="cpu").manual_seed(m + n_keep)
+    base = (torch.randn((period, 8), generator=g) * 0.02).to(torch.bfloat16)
+    nrm = synth.make_norms(period if axes[0] == "rows" else 8, "cpu", 5)
+    want, want_mask = oracle.mask_nm(to_np32(base), nrm.numpy(), axes[0], axes[1], 0.25, n_keep, m, want_mask=True)
+    W = base.to(gpu_device).repeat(repeat, 1)
+    norms = nrm.to(gpu_device).repeat(repeat) if axes[0] == "rows" else nrm.to(gpu_device)
+    mask = torch.full((W.shape[0], 1), 0x55, dtype=torch.uint8, device=gpu_device)
+    dass.score_mask_nm(W, norms, axes[0], axes[1], 0.25, n_keep, m, mask_out=mask)
+    torch.cuda.synchronize()
+    assert bits_equal(W[:period], want), first_mismatch(W[:period], want)
+    assert torch.equal(W.view(torch.int16).view(repeat, -1), W[:period].view(torch.int16).reshape(1, -1).expand(repeat, -1))
+    assert np.array_equal(mask[-period:].cpu().numpy(), want_mask)
+    assert torch.equal(mask.view(repeat, -1), mask[:period].reshape(1, -1).expand(repeat, -1))
+
+
 def test_nm_tiny_config_all_three_matrices(gpu_device):
     """Config 'tiny' (f32, d=256, d_int=688): Gate, Up with alpha 0.5 down rows; Down with alpha 1."""
     cfg = synth.CONFIGS["tiny"]
