@@ -1230,6 +1230,25 @@ extern "C" size_t dass_unstructured_workspace_bytes(int64_t rows, int64_t cols, 
 
 namespace dass {
 
+// The longest lines that the wavefront-per-line kernel takes from the line-resident kernel.  Measured back
+// to back, us, line-resident and wavefronts (2 to 5 times fewer on weights that are half 0):
+//   row lines                  128 x 32768 lines bf16 335 38, 1024 x 8192 99 27, 2048 x 4096 58 32, f32 52 34
+//     bf16, one factor         1536 x 4096 64 57, 2048 x 2048 38 40, 2048 x 4096 67 73: equal scores (bf16
+//                              magnitudes tie all the time) cost a second and a third search
+//   column lines               bf16 512 x 2048 24 12, 1000 x 8192 71 40, 1536 x 4096 47 47, 2048 x 4096 53 72;
+//                              f32 1536 x 4096 55 38, 2048 x 4096 67 72
+//     f32, one factor a line   2048 x 1024 29 25, 2048 x 8192 123 88
+//     bf16, one factor         512 x 2048 23 22, 688 x 2048 24 31, 1000 x 4096 46 46, 1000 x 8192 85 81, 1032 x
+//                              8192 87 155
+static int64_t short_line_limit(int dt, bool col_lines, bool along, bool one_factor, int64_t lines)
+{
+    if (!col_lines)
+        return dt == DASS_BF16 && one_factor ? 1536 : 2048;
+    if (dt == DASS_BF16 && one_factor)
+        return lines >= 4096 ? 1024 : 512;
+    return dt == DASS_F32 && !along ? 2048 : 1536;
+}
+
 // The selection itself, shared by the two entry points.  `workspace_needed` is what the caller's
 // contract asks for; a workspace that holds the factor vector but not the transposed copy sends
 // long column lines to the multi-pass kernels.
@@ -1280,10 +1299,13 @@ static dass_status score_mask_unstructured_impl(const char *fn, void *W, int64_t
         alpha = 1.0;
     }
 
-    // Lines of up to 1024 weights take the wavefront-per-line kernel whatever the size of the matrix (1024
-    // x 8192 bf16, the three of a block: 127 us by the streaming passes, 119 so); lines of up to 2048 where
-    // the streaming passes, which are ahead on large matrices (2048 x 4096: 115 against 166), do not apply.
-    const bool short_first = short_lines_fit(rows, cols, group_axis == DASS_AXIS_ROWS, 1024);
+    // Short lines take the wavefront-per-line kernel, ahead of the streaming passes up to 1024 weights.  Of the
+    // column lines that those take, 1024 long and more, it keeps up to 8192 of 1024 (us, wavefronts and
+    // passes: bf16 1024 x 4096 25 36, x 8192 40 40, x 32768 126 86; f32 28 35, 42 42, 155 114).
+    const bool col_lines = group_axis == DASS_AXIS_ROWS, along = norm_axis == group_axis, one_factor = !along || alpha == 0.0;
+    const int64_t short_limit = short_line_limit(dt, col_lines, along, one_factor, lines);
+    const bool short_first = short_lines_fit(rows, cols, col_lines, short_limit < 1024 ? short_limit : 1024) &&
+                             !(col_lines && !one_factor && rows == 1024 && cols > 8192);
 
     // Column lines in the DaSS configuration (the factor varies along the line, exponent not 0):
     // streaming passes over 64-column tiles.  They decide every ordinary matrix; for what they do
@@ -1320,9 +1342,7 @@ static dass_status score_mask_unstructured_impl(const char *fn, void *W, int64_t
     // Lines that fit the registers of one workgroup: the weights are read once.
     if (len <= 0xFFFF && n_keep > 0 && n_keep < (uint32_t)len) {
         const int fmode = alpha == 0.0 ? kFactorOne : alpha == 1.0 ? kFactorNorm : kFactorSqrt;
-        const bool along = norm_axis == group_axis;
-        const bool col_lines = group_axis == DASS_AXIS_ROWS;
-        if (!gate && short_lines_fit(rows, cols, col_lines, 2048))
+        if (!gate && short_lines_fit(rows, cols, col_lines, short_limit))
             return launch_short_lines(fn, W, rows, cols, ld, dt, norms, col_lines, along, fmode, n_keep, mask_out, stream);
         const ResidentPlan p = plan_resident(rows, cols, ld, dt, col_lines, along);
         if (p.fits)

@@ -1,4 +1,4 @@
-// Unstructured selection on lines of at most 2048 weights (Sec. 3 "Pruning Granularity"): one wavefront
+// Unstructured selection on short lines, of at most 2048 weights (Sec. 3 "Pruning Granularity"): one wavefront
 // per line, the whole line's scores in its registers.
 //
 // What bounds such calls is not memory (a 688 x 256 matrix is 0.7 MB) but the chain of dependent steps.
@@ -8,9 +8,9 @@
 // search ends at the first bit at which the count is the wanted one (about 20 of 31 bits).  Ties at the
 // threshold go on with the error terms and then the indexes in the same way.
 // Three matrices a call each, copies of the dense weights and the host's calls included, against the
-// workgroup-wide kernel (the streaming passes for 1024): f32 256 x 688 with mask 63 -> 43 us, 256 x 2048
-// 83 -> 75; bf16 8192 x 1000 261 -> 125, 2048 x 1024 78 -> 51, 1000 x 2000 89 -> 82.  A bit's cost grows
-// with the line: at 4096 the other kernels are ahead (256 x 4096 112 -> 144, 4096 x 4096 161 -> 425).
+// workgroup-wide kernel: f32 256 x 688 with mask 63 -> 43 us; bf16 8192 x 1000 261 -> 125.  A bit's cost grows
+// with the line: at 4096 the other kernels are ahead (256 x 4096 112 -> 144, 4096 x 4096 161 -> 425).  Which
+// lines come here is decided in unstructured.hip.
 //
 // Order of positions: (A, B, 0xFFFF - index) as in unstructured.hip, A and B the two-term f32 score or, in a
 // line with a factor or product outside its range, the two words of the f64 product.

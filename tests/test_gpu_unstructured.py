@@ -545,6 +545,25 @@ def test_unstructured_short_lines(gpu_device, dtype, group_axis, length):
               seed=9, pad=8)
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("rows,cols,alpha,mask_at", [
+    (1024, 8192, 0.5, 0), (1024, 8200, 0.5, 0), (1024, 8200, 0.0, 0),   # wavefronts, then passes over column tiles
+    (1024, 8200, 0.5, 1),                                               # a mask that the passes refuse
+    (1536, 2048, 0.5, 1), (1544, 2048, 0.5, 1), (2048, 72, 0.5, 0),     # wavefronts and the line-resident kernel
+    (512, 72, 0.0, 0), (520, 72, 0.0, 0), (1000, 4088, 0.0, 0), (1000, 4096, 0.0, 0)])   # the same under one factor
+def test_unstructured_limits_of_short_column_lines(gpu_device, dtype, rows, cols, alpha, mask_at):
+    """Column lines on either side of the lengths and numbers at which another kernel takes them."""
+    W = _weights(rows, cols, dtype, gpu_device, rows + cols, False)
+    nrm = _norms(rows, gpu_device, 3, False)
+    want, want_mask = oracle.mask_unstructured(to_np32(W), nrm.cpu().numpy(), "rows", "rows", alpha, rows // 2, want_mask=True)
+    mask = torch.zeros(rows * (cols // 8) + 1, dtype=torch.uint8, device=gpu_device)[mask_at:]
+    mask = mask[:rows * (cols // 8)].view(rows, cols // 8)
+    dass.score_mask_unstructured(W, nrm, "rows", "rows", alpha, rows // 2, mask_out=mask)
+    torch.cuda.synchronize()
+    assert bits_equal(W, want), first_mismatch(W, want)
+    assert np.array_equal(mask.cpu().numpy(), want_mask)
+
+
 def test_unstructured_argument_errors(gpu_device):
     W = torch.ones((8, 16), dtype=torch.bfloat16, device=gpu_device)
     nrm = torch.ones(16, device=gpu_device)
