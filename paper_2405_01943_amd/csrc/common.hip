@@ -1,7 +1,7 @@
 // Status strings, the thread-local error text, argument checks shared by the
 // stage-2 entry points, and the factor kernel f = norm^alpha (Sec. 3 Eq. 4 with
 // exponent alpha, Eq. 5 with exponent 1).
-#include "dass_internal.h"
+#include "select.h"
 
 namespace dass {
 
@@ -52,30 +52,38 @@ dass_status check_score_args(const char *fn, const void *W, int64_t rows, int64_
 // sqrt of an f32 is never closer than 2^-51 (relative) to the midpoint of two
 // adjacent f32 values, far more than the f64 routine's error.
 __global__ void factor_kernel(const float *__restrict__ norms, int64_t n, int mode, double alpha,
-                              float *__restrict__ f)
+                              float *__restrict__ f, uint8_t *__restrict__ out_of_range)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n)
-        return;
-    const double x = (double)norms[i];
-    double v;
-    if (mode == 0)
-        v = 1.0;
-    else if (mode == 1)
-        v = x;
-    else if (mode == 2)
-        v = sqrt(x);
-    else
-        v = pow(x, alpha);
-    f[i] = (float)v;
+    bool bad = false;
+    if (i < n) {
+        const double x = (double)norms[i];
+        double v;
+        if (mode == 0)
+            v = 1.0;
+        else if (mode == 1)
+            v = x;
+        else if (mode == 2)
+            v = sqrt(x);
+        else
+            v = pow(x, alpha);
+        f[i] = (float)v;
+        bad = !factor_in_fast_range((float)v);
+    }
+    if (out_of_range) {   // uniform
+        const int any = __syncthreads_or(bad);
+        if (threadIdx.x == 0)
+            out_of_range[blockIdx.x] = any ? 1 : 0;
+    }
 }
 
-dass_status launch_factor(const float *norms, int64_t n, double alpha, float *f, hipStream_t stream)
+dass_status launch_factor(const float *norms, int64_t n, double alpha, float *f, hipStream_t stream,
+                          uint8_t *out_of_range)
 {
     const int mode = alpha == 0.0 ? 0 : alpha == 1.0 ? 1 : alpha == 0.5 ? 2 : 3;
-    const int block = 256;
+    const int block = kFactorBlock;
     const unsigned grid = (unsigned)((n + block - 1) / block);
-    hipLaunchKernelGGL(factor_kernel, dim3(grid), dim3(block), 0, stream, norms, n, mode, alpha, f);
+    hipLaunchKernelGGL(factor_kernel, dim3(grid), dim3(block), 0, stream, norms, n, mode, alpha, f, out_of_range);
     return check_launch("factor kernel");
 }
 

@@ -51,7 +51,10 @@ dass_status check_score_args(const char *fn, const void *W, int64_t rows, int64_
                              double alpha, const void *workspace, size_t workspace_bytes,
                              size_t workspace_needed);
 
-// Enqueue f[i] = norms[i]^alpha (see include/dass.h for the special cases).
-dass_status launch_factor(const float *norms, int64_t n, double alpha, float *f, hipStream_t stream);
+// Enqueue f[i] = norms[i]^alpha (see include/dass.h for the special cases).  With `out_of_range`, its byte k
+// says whether a factor k * kFactorBlock .. is outside the range of the two-term score (select.h).
+constexpr int kFactorBlock = 256;
+dass_status launch_factor(const float *norms, int64_t n, double alpha, float *f, hipStream_t stream,
+                          uint8_t *out_of_range = nullptr);
 
 }  // namespace dass

@@ -446,7 +446,8 @@ constexpr int kLrLines = 8;
 constexpr int kLrPasses = 8;
 constexpr int kLrThreads = 1024;
 constexpr int kLrVecs = 16;   // 16-byte vectors held by a thread
-constexpr size_t kFlagBytes = 256;   // the block of the workspace that holds the flag word of the tiled passes
+constexpr size_t kFlagBytes = 256;   // the block of the workspace that holds the flag word of the tiled passes and
+                                     // launch_factor()'s bytes for up to 65536 factors
 constexpr int kLrTies = 64;   // scores of the threshold's bin that are listed and ranked directly, per line
 
 struct LrState {
@@ -1284,6 +1285,20 @@ static dass_status score_mask_unstructured_impl(const char *fn, void *W, int64_t
     const uint32_t *gate = nullptr;   // set: the launches below run only where the word(s) it points to are nonzero
     uint32_t gate_rows = 0;           // 0: one word for the whole matrix; else one word per block of so many rows
 
+    // Short lines take the wavefront-per-line kernel, ahead of the streaming passes up to 1024 weights.  Of the
+    // column lines that those take, 1024 long and more, it keeps up to 8192 of 1024 (us, wavefronts and
+    // passes: bf16 1024 x 4096 25 36, x 8192 40 40, x 32768 126 86; f32 28 35, 42 42, 155 114).
+    const bool col_lines = group_axis == DASS_AXIS_ROWS, along = norm_axis == group_axis, one_factor = !along || alpha == 0.0;
+    const int64_t short_limit = short_line_limit(dt, col_lines, along, one_factor, lines);
+    const bool short_first = short_lines_fit(rows, cols, col_lines, short_limit < 1024 ? short_limit : 1024) &&
+                             !(col_lines && !one_factor && rows == 1024 && cols > 8192);
+    // The DaSS configuration (the factor varies along the line): streaming passes, where they fit.
+    const bool streaming = !short_first && !one_factor && n_keep > 0 && n_keep < (uint32_t)len;
+    const TiledPlan tp = streaming && col_lines ? plan_tiled(rows, cols, ld, dt, mask_out) : TiledPlan{};
+    const RowlinesPlan rp = streaming && !col_lines ? plan_rowlines(rows, cols, ld, dt, mask_out) : RowlinesPlan{};
+    const bool tiled = tp.fits && region_bytes >= tp.bytes, rowlines = rp.fits && region_bytes >= rp.todo_bytes;
+    uint32_t *const flag = reinterpret_cast<uint32_t *>(static_cast<char *>(workspace) + f_bytes);
+
     // Exponents without an exact f32 recipe: the factor vector (f64 power, rounded once) is written
     // first and every path below takes it as norms with exponent 1, whose factor is the norm itself.
     // The multi-pass kernels, which alone took such exponents before, read the matrix eleven times:
@@ -1292,55 +1307,49 @@ static dass_status score_mask_unstructured_impl(const char *fn, void *W, int64_t
     float *const f = static_cast<float *>(workspace);
     const bool swept = alpha != 0.0 && alpha != 0.5 && alpha != 1.0;
     if (swept) {
-        s = launch_factor(norms, norm_axis == DASS_AXIS_ROWS ? rows : cols, alpha, f, stream);
+        s = launch_factor(norms, norm_axis == DASS_AXIS_ROWS ? rows : cols, alpha, f, stream,
+                          tiled || rowlines ? reinterpret_cast<uint8_t *>(flag) : nullptr);
         if (s != DASS_OK)
             return s;
         norms = f;
         alpha = 1.0;
     }
 
-    // Short lines take the wavefront-per-line kernel, ahead of the streaming passes up to 1024 weights.  Of the
-    // column lines that those take, 1024 long and more, it keeps up to 8192 of 1024 (us, wavefronts and
-    // passes: bf16 1024 x 4096 25 36, x 8192 40 40, x 32768 126 86; f32 28 35, 42 42, 155 114).
-    const bool col_lines = group_axis == DASS_AXIS_ROWS, along = norm_axis == group_axis, one_factor = !along || alpha == 0.0;
-    const int64_t short_limit = short_line_limit(dt, col_lines, along, one_factor, lines);
-    const bool short_first = short_lines_fit(rows, cols, col_lines, short_limit < 1024 ? short_limit : 1024) &&
-                             !(col_lines && !one_factor && rows == 1024 && cols > 8192);
-
-    // Column lines in the DaSS configuration (the factor varies along the line, exponent not 0):
-    // streaming passes over 64-column tiles.  They decide every ordinary matrix; for what they do
+    // Column lines: passes over 64-column tiles.  They decide every ordinary matrix; for what they do
     // not decide they leave W untouched and set the flag, and the launches below, which then run
     // behind that flag, redo the matrix.
-    if (!short_first && (alpha == 0.5 || alpha == 1.0) && group_axis == DASS_AXIS_ROWS && norm_axis == DASS_AXIS_ROWS && n_keep > 0 &&
-        n_keep < (uint32_t)len) {
-        const TiledPlan tp = plan_tiled(rows, cols, ld, dt, mask_out);
-        if (tp.fits && region_bytes >= tp.bytes) {
-            uint32_t *flag = reinterpret_cast<uint32_t *>(static_cast<char *>(workspace) + f_bytes);
-            s = launch_tiled(fn, tp, W, rows, cols, ld, dt, norms, alpha == 1.0 ? kFactorNorm : kFactorSqrt, n_keep,
-                             mask_out, flag, region, stream);
-            if (s != DASS_OK)
-                return s;
-            gate = flag;
-        }
+    if (tiled) {
+        s = launch_tiled(fn, tp, W, rows, cols, ld, dt, norms, alpha == 1.0 ? kFactorNorm : kFactorSqrt, n_keep,
+                         mask_out, flag, swept, region, stream);
+        if (s != DASS_OK)
+            return s;
+        gate = flag;
     }
-    // Row lines in the DaSS configuration: one launch in which a workgroup owns 8 whole rows; blocks of
-    // rows it does not decide are marked and redone by the launches below.
-    if (!short_first && (alpha == 0.5 || alpha == 1.0) && group_axis == DASS_AXIS_COLS && norm_axis == DASS_AXIS_COLS && n_keep > 0 &&
-        n_keep < (uint32_t)len) {
-        const RowlinesPlan rp = plan_rowlines(rows, cols, ld, dt, mask_out);
-        if (rp.fits && region_bytes >= rp.todo_bytes) {
-            uint32_t *todo = reinterpret_cast<uint32_t *>(region);
-            s = launch_rowlines(fn, rp, W, rows, cols, ld, dt, norms, alpha == 1.0 ? kFactorNorm : kFactorSqrt, n_keep,
-                                mask_out, todo, stream);
-            if (s != DASS_OK)
-                return s;
-            gate = todo;
-            gate_rows = kRowlinesBlock;
-        }
+    // Row lines: one launch in which a workgroup owns 8 whole rows; blocks of rows it does not decide are
+    // marked and redone by the launches below.
+    if (rowlines) {
+        uint32_t *todo = reinterpret_cast<uint32_t *>(region);
+        s = launch_rowlines(fn, rp, W, rows, cols, ld, dt, norms, alpha == 1.0 ? kFactorNorm : kFactorSqrt, n_keep,
+                            mask_out, todo, swept ? reinterpret_cast<const uint8_t *>(flag) : nullptr, stream);
+        if (s != DASS_OK)
+            return s;
+        gate = todo;
+        gate_rows = kRowlinesBlock;
     }
 
+    // A matrix whose factor vector is there already goes to the multi-pass kernels where these are ahead of the
+    // line-resident kernel.  What the passes leave: row lines, and column lines of wide matrices (many
+    // workgroups).  Whole calls without the passes' early exits, alpha = 0.25 and half of the weights 0, us,
+    // line-resident and multi-pass: bf16 along the rows 4096 x 11008 878 720, 28672 x 2048 2114 870; down them
+    // 2048 x 28672 1640 877, 4096 x 14336 1262 986, 4096 x 11008 1031 952, 8192 x 8192 1324 1545, 11008 x 4096 915
+    // 2061; f32 8192 x 8192 1563 1508, 11008 x 4096 1061 1846.  With them the first three take 663, 768 and 685,
+    // and the multi-pass kernels alone 617, 724 and 626.  Row lines of matrices too small for the passes: 256 x
+    // 4096 210 38, dense 37 29, but 64 x 28672 dense 66 98.
+    const bool multi_pass = swept && (gate ? !col_lines || cols >= (bf16 ? 12288 : 8192)
+                                           : !col_lines && along && len > short_limit && cols <= 8192);
+
     // Lines that fit the registers of one workgroup: the weights are read once.
-    if (len <= 0xFFFF && n_keep > 0 && n_keep < (uint32_t)len) {
+    if (len <= 0xFFFF && n_keep > 0 && n_keep < (uint32_t)len && !multi_pass) {
         const int fmode = alpha == 0.0 ? kFactorOne : alpha == 1.0 ? kFactorNorm : kFactorSqrt;
         if (!gate && short_lines_fit(rows, cols, col_lines, short_limit))
             return launch_short_lines(fn, W, rows, cols, ld, dt, norms, col_lines, along, fmode, n_keep, mask_out, stream);

@@ -28,8 +28,10 @@ TiledPlan plan_tiled(int64_t rows, int64_t cols, int64_t ld, int dt, const uint8
 // or product outside the range of the two-term f32 score, a threshold outside the sampled window,
 // more equal leading terms at the threshold than a list holds).  When it is set, W has not been
 // written: the caller's next launches, gated on the flag, redo the whole matrix.
+// early: launch_factor()'s bytes for `norms` begin at `flag`; the passes stop as soon as these or the samples
+// say that they will not decide the matrix, for a caller whose other kernels are not much slower.
 dass_status launch_tiled(const char *fn, const TiledPlan &p, void *W, int64_t rows, int64_t cols, int64_t ld, int dt,
-                         const float *norms, int fmode, uint32_t n_keep, uint8_t *mask_out, uint32_t *flag,
+                         const float *norms, int fmode, uint32_t n_keep, uint8_t *mask_out, uint32_t *flag, bool early,
                          void *region, hipStream_t stream);
 
 // ---- row lines (unstructured_rows.hip): one launch, a workgroup owns kRowlinesBlock whole rows ----
@@ -48,10 +50,11 @@ struct RowlinesPlan {
 RowlinesPlan plan_rowlines(int64_t rows, int64_t cols, int64_t ld, int dt, const uint8_t *mask_out = nullptr);
 
 // Enqueue the kernel.  todo[b] is written for every block b of kRowlinesBlock rows: 0 if the
-// block's rows are done, 1 if they were left for the caller's next launch, gated per block.
+// block's rows are done, 1 if they were left for the caller's next launch, gated per block.  out_of_range: NULL,
+// or launch_factor()'s bytes for `norms`; then a block is left as soon as these or its samples say that it will be.
 dass_status launch_rowlines(const char *fn, const RowlinesPlan &p, void *W, int64_t rows, int64_t cols, int64_t ld, int dt,
                             const float *norms, int fmode, uint32_t n_keep, uint8_t *mask_out, uint32_t *todo,
-                            hipStream_t stream);
+                            const uint8_t *out_of_range, hipStream_t stream);
 
 // ---- lines of at most 2048 weights (unstructured_short.hip): one launch, a wavefront per line ----
 // Whether the lines are at most `longest` (<= 2048) weights long and the launch is possible.

@@ -50,7 +50,7 @@ constexpr int kWinCols = 8;             // columns per workgroup of the window k
 constexpr uint32_t kInfBits = 0x7f800000u;
 // Bits of the flag word: why the passes left the matrix to the caller's other kernels.
 enum : uint32_t {
-    kWhyRange = 1,      // a factor or a product outside the range of the two-term score
+    kWhyRange = 1,      // a factor or a product outside the range of the two-term score (or launch_factor's byte for it)
     kWhyWindow = 2,     // a column's threshold lies outside its sampled window
     kWhyBin = 4,        // the threshold's bin holds more scores than a list
     kWhyList = 8,       // a list overflowed
@@ -89,17 +89,21 @@ __device__ __forceinline__ uint32_t sample_row(uint32_t k, uint32_t rows)
 // Blocks [0, win_blocks): 8 columns each, one wavefront per 2 columns.  Blocks after those: the
 // scaled factor vector, 256 rows each.  Block 0 clears the flag and every window block the
 // list counters of its columns.
+// early: launch_factor() has set or cleared the flag, for its first four blocks of factors; block 0 adds what it
+// found in the others, and every window block whether its samples hold at least as many exact zeros as are to be
+// pruned (a threshold of 0 is a tie of thousands).
 template <int DT>
 __global__ __launch_bounds__(256) void window_kernel(const void *__restrict__ Wv, uint32_t rows, uint32_t cols,
                                                      int64_t ld, const float *__restrict__ norms, int fmode,
                                                      uint32_t n_keep, uint32_t win_blocks, float *__restrict__ fs,
                                                      Window *__restrict__ win, uint32_t *__restrict__ cnt,
-                                                     uint32_t *__restrict__ flag)
+                                                     uint32_t *__restrict__ flag, int early)
 {
     constexpr int EPV = DT == DASS_BF16 ? 8 : 4;
     constexpr int EB = DT == DASS_BF16 ? 2 : 4;
     constexpr int VPR = kWinCols / EPV;   // vectors per sampled row
     __shared__ uint32_t smp[kWinCols][kSamples + 1];
+    __shared__ uint32_t zeros;
     const int tid = threadIdx.x;
     if (blockIdx.x >= win_blocks) {
         const uint32_t i = (blockIdx.x - win_blocks) * 256u + tid;
@@ -107,8 +111,14 @@ __global__ __launch_bounds__(256) void window_kernel(const void *__restrict__ Wv
             fs[i] = factor_of(norms[i], fmode) * kFactorScale;
         return;
     }
-    if (blockIdx.x == 0 && tid == 0)
-        *flag = 0;
+    if (blockIdx.x == 0) {
+        if (!early && tid == 0)
+            *flag = 0;
+        if (early && tid > 3 && (uint32_t)tid * kFactorBlock < rows && reinterpret_cast<const uint8_t *>(flag)[tid])
+            atomicOr(flag, kWhyRange);
+    }
+    if (tid == 0)
+        zeros = 0;
     const uint32_t c0 = blockIdx.x * kWinCols;
     const char *W = static_cast<const char *>(Wv);
     for (int v = tid; v < kSamples * VPR; v += 256) {
@@ -138,6 +148,11 @@ __global__ __launch_bounds__(256) void window_kernel(const void *__restrict__ Wv
         if (c >= cols)
             break;   // uniform inside the wavefront
         const uint32_t s0 = smp[cl][lane], s1 = smp[cl][lane + 64];
+        if (early) {
+            const int n = __popcll(__ballot(s0 == 0)) + __popcll(__ballot(s1 == 0));
+            if (lane == 0)
+                atomicAdd(&zeros, (uint32_t)n);
+        }
         // the r-th largest sample, cut to its bits 30 .. 19 (a sixteenth of a binade): the largest T with r samples >= T
         auto order_stat = [&](int r) {
             uint32_t t = 0;
@@ -161,6 +176,12 @@ __global__ __launch_bounds__(256) void window_kernel(const void *__restrict__ Wv
             cnt[c] = 0;
         }
     }
+    if (early) {   // uniform
+        __syncthreads();
+        const uint32_t taken = (cols - c0 < (uint32_t)kWinCols ? cols - c0 : (uint32_t)kWinCols) * kSamples;
+        if (tid == 0 && (uint64_t)zeros * rows >= (uint64_t)(rows - n_keep) * taken)
+            atomicOr(flag, kWhyBin);
+    }
 }
 
 // Per-thread view of a tile: LPR lanes cover the 64 columns of a row with one 16-byte vector
@@ -180,12 +201,20 @@ __global__ __launch_bounds__(kThreads) void hist_kernel(const void *__restrict__
                                                         int64_t ld, const float *__restrict__ fs,
                                                         const Window *__restrict__ win, uint32_t groups,
                                                         uint32_t slab_rows, uint32_t *__restrict__ part,
-                                                        uint32_t *__restrict__ flag)
+                                                        uint32_t *__restrict__ flag, int early)
 {
     using TL = Tile<DT>;
     constexpr int EPV = TL::EPV, EB = TL::EB, LPR = TL::LPR, RPI = TL::RPI, U = TL::UNROLL;
     extern __shared__ uint32_t hist[];   // [kCols][kStride]: more than a launch gets without asking
     const int tid = threadIdx.x;
+    if (early) {   // uniform
+        __shared__ uint32_t stop;   // as one thread read it: the same answer for the whole workgroup
+        if (tid == 0)
+            stop = *flag;
+        __syncthreads();
+        if (stop)
+            return;
+    }
     const uint32_t g = blockIdx.x % groups, slab = blockIdx.x / groups;
     const uint32_t piece = tid % LPR, r_in = tid / LPR;
     const uint32_t c0 = g * kCols + piece * EPV;
@@ -252,11 +281,11 @@ __global__ __launch_bounds__(kThreads) void hist_kernel(const void *__restrict__
 // lanes counts from the top.
 __global__ __launch_bounds__(256) void scan_kernel(const uint16_t *__restrict__ part, const Window *__restrict__ win,
                                                    uint32_t cols, uint32_t groups, uint32_t slabs, uint32_t n_keep,
-                                                   Select *__restrict__ sel, uint32_t *__restrict__ flag)
+                                                   Select *__restrict__ sel, uint32_t *__restrict__ flag, int early)
 {
     const int lane = threadIdx.x & 63;
     const uint32_t c = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (c >= cols)
+    if (c >= cols || (early && *flag))   // set: there may be no counts, and nobody will look at what is found
         return;
     const size_t col_stride = kSlots, slab_stride = (size_t)groups * kCols * kSlots;
     const uint16_t *p = part + (size_t)c * col_stride;
@@ -617,7 +646,7 @@ TiledPlan plan_tiled(int64_t rows, int64_t cols, int64_t ld, int dt, const uint8
 }
 
 dass_status launch_tiled(const char *fn, const TiledPlan &p, void *W, int64_t rows, int64_t cols, int64_t ld, int dt,
-                         const float *norms, int fmode, uint32_t n_keep, uint8_t *mask_out, uint32_t *flag,
+                         const float *norms, int fmode, uint32_t n_keep, uint8_t *mask_out, uint32_t *flag, bool early,
                          void *region, hipStream_t stream)
 {
     using namespace tiled;
@@ -635,16 +664,18 @@ dass_status launch_tiled(const char *fn, const TiledPlan &p, void *W, int64_t ro
     const dim3 tiles(groups * slabs), per_col((c32 + 3) / 4);
 
     hipLaunchKernelGGL(bf16 ? window_kernel<DASS_BF16> : window_kernel<DASS_F32>, dim3(win_blocks + fs_blocks), dim3(256),
-                       0, stream, (const void *)W, r32, c32, ld, norms, fmode, n_keep, win_blocks, fs, win, cnt, flag);
+                       0, stream, (const void *)W, r32, c32, ld, norms, fmode, n_keep, win_blocks, fs, win, cnt, flag,
+                       (int)early);
     constexpr size_t hist_lds = (size_t)kCols * kStride * sizeof(uint32_t);
     auto hk = bf16 ? hist_kernel<DASS_BF16> : hist_kernel<DASS_F32>;
     if (hipFuncSetAttribute(reinterpret_cast<const void *>(hk), hipFuncAttributeMaxDynamicSharedMemorySize, (int)hist_lds) !=
         hipSuccess)
         return fail(DASS_ERR_HIP, "%s: cannot reserve %zu bytes of LDS", fn, hist_lds);
     hipLaunchKernelGGL(hk, tiles, dim3(kThreads), hist_lds, stream,
-                       (const void *)W, r32, c32, ld, (const float *)fs, (const Window *)win, groups, slab_rows, part, flag);
+                       (const void *)W, r32, c32, ld, (const float *)fs, (const Window *)win, groups, slab_rows, part, flag,
+                       (int)early);
     hipLaunchKernelGGL(scan_kernel, per_col, dim3(256), 0, stream, (const uint16_t *)part, (const Window *)win, c32, groups,
-                       slabs, n_keep, sel, flag);
+                       slabs, n_keep, sel, flag, (int)early);
     const uint32_t rows_per_block = kApplyTrips * kApplyThreads / (bf16 ? 8 : 16);
     auto ak = bf16 ? (mask_out ? apply_kernel<DASS_BF16, true> : apply_kernel<DASS_BF16, false>)
                    : (mask_out ? apply_kernel<DASS_F32, true> : apply_kernel<DASS_F32, false>);

@@ -527,6 +527,34 @@ def test_unstructured_other_exponents(gpu_device, dtype, rows, cols, axes):
         assert torch.all(W._base[:, cols:] == 7.0)
 
 
+@pytest.mark.parametrize("dtype,rows,cols,group_axis", [
+    (torch.bfloat16, 1040, 2056, "rows"), (torch.float32, 1032, 8200, "rows"),     # redone in the registers of a workgroup; by the multi-pass kernels
+    (torch.bfloat16, 1032, 12296, "rows"),
+    (torch.bfloat16, 1030, 2056, "cols"), (torch.float32, 201, 11272, "cols")])    # row lines, one chunk of factors and two
+@pytest.mark.parametrize("undecided", ["zeros", "some zeros", "range", "neither"])
+def test_unstructured_other_exponents_undecided(gpu_device, dtype, rows, cols, group_axis, undecided):
+    """What the streaming passes leave with other exponents: thresholds that tie at 0, in all lines or in
+    some, and factors outside the range of the two-term score."""
+    length = rows if group_axis == "rows" else cols
+    g = torch.Generator(device="cpu").manual_seed(rows + cols)
+    W0 = torch.randn((rows, cols), generator=g) * 0.02
+    if undecided == "zeros":
+        W0 *= (torch.rand((rows, cols), generator=g) < 0.4).to(torch.float32)
+    elif undecided == "some zeros":     # lines 40 .. 59
+        block = W0[:, 40:60] if group_axis == "rows" else W0[40:60]
+        block *= (torch.rand(block.shape, generator=g) < 0.4).to(torch.float32)
+    nrm = synth.make_norms(length, "cpu", 9)
+    if undecided == "range":
+        nrm[length // 3] = 1e30
+    W, n_prune = W0.to(dtype).to(gpu_device), length // 2
+    want, want_mask = oracle.mask_unstructured(to_np32(W), nrm.numpy(), group_axis, group_axis, 0.75, n_prune, want_mask=True)
+    mask = torch.full((rows, cols // 8), 0x55, dtype=torch.uint8, device=gpu_device)
+    dass.score_mask_unstructured(W, nrm.to(gpu_device), group_axis, group_axis, 0.75, n_prune, mask_out=mask)
+    torch.cuda.synchronize()
+    assert bits_equal(W, want), first_mismatch(W, want)
+    assert np.array_equal(mask.cpu().numpy(), want_mask)
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("group_axis", ["rows", "cols"])
 @pytest.mark.parametrize("length", [2, 8, 63, 512, 520, 1024, 1025, 1032, 1536, 2048, 2056])
