@@ -75,7 +75,9 @@ constexpr int64_t kRunTiles = 4096;
 // max_band: token tiles of a band (runs).  8 for tiles half as high as they are wide, so that 32 neighbours
 // stay a square: down projection of 2048 tokens of 4096 x 11008 by 128 x 256 tiles 451 -> 439 us (whole
 // dass_mlp_forward), by the sparse kernel 169 -> 162 us with the compression.
-inline TileOrder make_tile_order(int64_t tiles_t, int64_t tiles_n, bool weights_cached, int64_t max_band = kPatchT)
+// run_tiles: runs up to so many tiles.
+inline TileOrder make_tile_order(int64_t tiles_t, int64_t tiles_n, bool weights_cached, int64_t max_band = kPatchT,
+                                 int64_t run_tiles = kRunTiles)
 {
     TileOrder o = {0, 0, 0, 0, 0, 0};
     const int64_t np_t = (tiles_t + kPatchT - 1) / kPatchT, np_n = (tiles_n + kPatchN - 1) / kPatchN;
@@ -89,7 +91,7 @@ inline TileOrder make_tile_order(int64_t tiles_t, int64_t tiles_n, bool weights_
     // Whole patches that go round evenly leave no XCD idle, and from some rounds on their order is ahead
     // (down projection of 32768 tokens of 4096 x 14336, 128 x 16 tiles: dass_mlp_forward 7.59 -> 7.52 ms).
     const bool even_patches = n > 1024 && tiles_t % kPatchT == 0 && tiles_n % kPatchN == 0 && patches % kXcds == 0;
-    if ((n <= kRunTiles && !even_patches) || short_patches_meet) {
+    if ((n <= run_tiles && !even_patches) || short_patches_meet) {
         const int64_t bands = (tiles_t + max_band - 1) / max_band;
         o.band = (uint32_t)((tiles_t + bands - 1) / bands);   // even bands of at most max_band
         o.per_xcd = (uint32_t)((n + kXcds - 1) / kXcds);

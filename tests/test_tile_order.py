@@ -16,10 +16,11 @@ DRIVER = r"""
 #define __forceinline__ inline
 #include HEADER
 using namespace dass;
-int main(int, char **argv)
+int main(int argc, char **argv)
 {
     const uint32_t tt = atoi(argv[1]), tn = atoi(argv[2]);
-    const TileOrder o = make_tile_order(tt, tn, atoi(argv[3]) != 0, atoi(argv[4]));
+    const TileOrder o = argc > 5 ? make_tile_order(tt, tn, atoi(argv[3]) != 0, atoi(argv[4]), atoi(argv[5]))
+                                 : make_tile_order(tt, tn, atoi(argv[3]) != 0, atoi(argv[4]));
     std::vector<int> seen((size_t)tt * tn, 0);
     uint32_t per_xcd[8] = {0}, worst = 0;
     for (uint32_t b = 0; b < o.blocks; ++b) {
@@ -67,3 +68,16 @@ def test_every_tile_once_and_evenly(driver, tiles_t, tiles_n, cached, max_band):
         assert worst == (n + 7) // 8
     else:   # whole patches of 32 dealt to the XCDs
         assert worst <= n / 8 * 1.1 + 64
+
+
+@pytest.mark.parametrize("tiles_t,tiles_n,cached,run_tiles,runs", [
+    (128, 16, 1, 4096, False), (16, 224, 0, 4096, False),      # whole patches that go round evenly
+    (64, 16, 1, 4096, True), (12, 224, 0, 4096, True),         # up to 1024 tiles; patches that do not
+    (64, 16, 1, 1023, False), (63, 16, 1, 1023, True), (96, 20, 1, 1023, False), (96, 12, 1, 1023, True)])   # the sparse kernel
+def test_which_order(driver, tiles_t, tiles_n, cached, run_tiles, runs):
+    out = subprocess.run([driver, str(tiles_t), str(tiles_n), str(cached), "4", str(run_tiles)], capture_output=True, text=True)
+    assert out.returncode == 0, out.stdout
+    worst, band = (int(v) for v in out.stdout.split())
+    assert (band > 0) == runs
+    if runs:
+        assert worst == (tiles_t * tiles_n + 7) // 8
