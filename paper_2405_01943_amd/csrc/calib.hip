@@ -962,10 +962,10 @@ static bool split_f32(int64_t T, int64_t d_int)
     return ((T + 2 * F_WT - 1) / (2 * F_WT)) * ((d_int + 2 * F_WT - 1) / (2 * F_WT)) <= 256;
 }
 
-// Whether `matrices` bf16 matrices of this size stay in the 256 MB memory-side cache.
-static bool fits_memory_cache(int64_t matrices, int64_t rows, int64_t cols)
+// Whether `matrices` matrices of this size stay in the 256 MB memory-side cache.
+static bool fits_memory_cache(int64_t matrices, int64_t rows, int64_t cols, int dt)
 {
-    return matrices * rows * cols * 2 <= (256LL << 20);
+    return matrices * rows * cols * elem_bytes(dt) <= (256LL << 20);
 }
 
 }  // namespace dass
@@ -1020,7 +1020,7 @@ extern "C" dass_status dass_calib_norms(const void *X, int64_t T, int64_t ldx, c
     const TileShape shape = pipe64 ? tile_shape(T, d_int, true) : TileShape{};
     const int64_t tiles_t = pipe64 ? shape.tiles_t : bf16 ? (T + BM - 1) / BM : (T + f_tile - 1) / f_tile;
     const int64_t tiles_n = pipe64 ? shape.tiles_n : bf16 ? (d_int + BN - 1) / BN : (d_int + f_tile - 1) / f_tile;
-    const TileOrder order = make_tile_order(tiles_t, tiles_n, fits_memory_cache(2, d_int, d),
+    const TileOrder order = make_tile_order(tiles_t, tiles_n, fits_memory_cache(2, d_int, d, dt),
                                             pipe64 && shape.which == 1 ? 8 : kPatchT);
     const int64_t blocks = pipe64 || !bf16 ? order.blocks : (tiles_t * tiles_n + 7) / 8 * 8;
     if (blocks <= 0 || blocks > 0x7fffffffLL)
@@ -1113,7 +1113,7 @@ extern "C" dass_status dass_mlp_forward(const void *X, int64_t T, int64_t ldx, c
     // Eq. 2: y = act(X Wgate^T) * (X Wup^T), tiles of up to 256 tokens x 128 neurons
     {
         const TileShape shape = tile_shape(T, d_int, true);
-        const TileOrder order = make_tile_order(shape.tiles_t, shape.tiles_n, fits_memory_cache(2, d_int, d),
+        const TileOrder order = make_tile_order(shape.tiles_t, shape.tiles_n, fits_memory_cache(2, d_int, d, dt),
                                                 shape.which == 1 ? 8 : kPatchT);
         if (order.blocks == 0)
             return fail(DASS_ERR_SHAPE, "%s: too many tiles for one launch; split the tokens", fn);
@@ -1130,7 +1130,7 @@ extern "C" dass_status dass_mlp_forward(const void *X, int64_t T, int64_t ldx, c
     // Eq. 3: out = y Wdown^T, tiles of up to 256 tokens x 256 output features, K = d_int
     {
         const TileShape shape = tile_shape(T, d, false);
-        const TileOrder order = make_tile_order(shape.tiles_t, shape.tiles_n, fits_memory_cache(1, d_int, d),
+        const TileOrder order = make_tile_order(shape.tiles_t, shape.tiles_n, fits_memory_cache(1, d_int, d, dt),
                                                 shape.which == 1 ? 8 : kPatchT);
         if (order.blocks == 0)
             return fail(DASS_ERR_SHAPE, "%s: too many tiles for one launch; split the tokens", fn);

@@ -6,8 +6,8 @@
 // tiles.  Two orders:
 //
 //   runs (band > 0)   every XCD takes one contiguous run of ceil(N / 8) tiles of a list in which the
-//       token tiles are cut into bands of at most 4 and a band's tiles are listed column of tiles by
-//       column of tiles, so 32 neighbours of the list are about a 4 x 8 patch.  The XCDs get equal
+//       token tiles are cut into bands of at most 4 (8: max_band) and a band's tiles are listed column of
+//       tiles by column of tiles, so 32 neighbours of the list are about a 4 x 8 patch.  The XCDs get equal
 //       shares whatever the shape of the grid.
 //   patches (band = 0)   the grid is cut into patches of 4 token tiles x 8 column tiles, each taken
 //       by one XCD (its L2 serves 13/16 of their reads), and the patches are dealt round-robin from a
@@ -65,10 +65,11 @@ __device__ __forceinline__ bool tile_of_block(const TileOrder &o, uint32_t block
 
 // Runs up to this many tiles (16 rounds of the chip).  Measured on calib_pipe64_kernel, patches -> runs:
 // 6 x 192 tiles 1390 us (super-rows of 8: two of the eight XCDs had work) -> 345, 366 with even
-// super-rows; 2 x 86 tiles 87 -> 75 us, 4 x 86 170 -> 157; the plain product with 4 x 16 tiles 251 -> 207 us.
-// From about 4000 tiles on either order is within 1 % (22 x the chip: patches 0.5 % ahead), with one
-// exception: an even number of patch columns of which the last is not whole gives the XCDs of one
-// parity all the short patches (12 column tiles, 128 token tiles: 4.6 ms against 3.6).
+// super-rows; 2 x 86 tiles 87 -> 75 us, 4 x 86 170 -> 157; the plain product with 4 x 16 tiles 251 -> 207 us;
+// from about 1000 tiles on either order is within 2.5 % (12 x 86 and 24 x 86 tiles patches 2 % ahead, 12 x 112 and
+// 24 x 112 even), with two exceptions: an even number of patch columns of which the last is not whole gives
+// the XCDs of one parity all the short patches (12 column tiles, 128 token tiles: 4.6 ms against 3.6), and grids
+// narrower than a patch leave most of every patch empty (calib_f32_kernel, 4096 x 1 tiles: 320 us against 127).
 constexpr int64_t kRunTiles = 4096;
 
 // weights_cached: the operand that the column tiles read fits the 256 MB memory-side cache.
@@ -81,25 +82,28 @@ inline TileOrder make_tile_order(int64_t tiles_t, int64_t tiles_n, bool weights_
 {
     TileOrder o = {0, 0, 0, 0, 0, 0};
     const int64_t np_t = (tiles_t + kPatchT - 1) / kPatchT, np_n = (tiles_n + kPatchN - 1) / kPatchN;
-    const int64_t patches = np_t * np_n, patch_blocks = (patches + kXcds - 1) / kXcds * kXcds * kXcdSlots;
-    if (patch_blocks > 0x7fffffffLL)
+    const int64_t n = tiles_t * tiles_n, patches = np_t * np_n;
+    const bool short_patches_meet = weights_cached && tiles_n % kPatchN != 0 && np_n % 2 == 0;
+    // Whole patches that go round evenly leave no XCD idle, and are then ahead, on weights that stay cached and on
+    // others.  Taken in turn, patches against runs: stage 1 with d = 4096, 16 to 32 x 64 tiles 0.7 to 1.4 %, 12 to 20 x
+    // 128 0.7 to 1.2 %, 16 x 112 0.6 %; uncached 8 to 20 x 192 (d = 3072) 0.8 to 1.5 %, 8 and 16 x 224 0.5 %, with d =
+    // 8192 1.4 and 0.3 %; dass_mlp_forward of 16384 to 32768 tokens of 4096 x 14336 0.2 to 0.8 %, but of 8192 x 8192
+    // 2 % behind.
+    const bool even_patches = n > 1024 && tiles_t % kPatchT == 0 && tiles_n % kPatchN == 0 && patches % kXcds == 0;
+    const bool runs = (n <= run_tiles && !even_patches) || short_patches_meet || tiles_n < kPatchN;
+    const int64_t blocks = runs ? (n + kXcds - 1) / kXcds * kXcds : (patches + kXcds - 1) / kXcds * kXcds * kXcdSlots;
+    if (blocks > 0x7fffffffLL)
         return o;
     o.tiles_t = (uint32_t)tiles_t;
     o.tiles_n = (uint32_t)tiles_n;
-    const int64_t n = tiles_t * tiles_n;
-    const bool short_patches_meet = weights_cached && tiles_n % kPatchN != 0 && np_n % 2 == 0;
-    // Whole patches that go round evenly leave no XCD idle, and from some rounds on their order is ahead
-    // (down projection of 32768 tokens of 4096 x 14336, 128 x 16 tiles: dass_mlp_forward 7.59 -> 7.52 ms).
-    const bool even_patches = n > 1024 && tiles_t % kPatchT == 0 && tiles_n % kPatchN == 0 && patches % kXcds == 0;
-    if ((n <= run_tiles && !even_patches) || short_patches_meet) {
+    o.blocks = (uint32_t)blocks;
+    if (runs) {
         const int64_t bands = (tiles_t + max_band - 1) / max_band;
         o.band = (uint32_t)((tiles_t + bands - 1) / bands);   // even bands of at most max_band
         o.per_xcd = (uint32_t)((n + kXcds - 1) / kXcds);
-        o.blocks = o.per_xcd * kXcds;
     } else {
         const int64_t supers = weights_cached ? np_t : (np_t + 7) / 8;
         o.super_rows = (uint32_t)((np_t + supers - 1) / supers);
-        o.blocks = (uint32_t)patch_blocks;
     }
     return o;
 }

@@ -73,7 +73,8 @@ def test_every_tile_once_and_evenly(driver, tiles_t, tiles_n, cached, max_band):
 @pytest.mark.parametrize("tiles_t,tiles_n,cached,run_tiles,runs", [
     (128, 16, 1, 4096, False), (16, 224, 0, 4096, False),      # whole patches that go round evenly
     (64, 16, 1, 4096, True), (12, 224, 0, 4096, True),         # up to 1024 tiles; patches that do not
-    (64, 16, 1, 1023, False), (63, 16, 1, 1023, True), (96, 20, 1, 1023, False), (96, 12, 1, 1023, True)])   # the sparse kernel
+    (64, 16, 1, 1023, False), (63, 16, 1, 1023, True), (96, 20, 1, 1023, False), (96, 12, 1, 1023, True),
+    (16384, 1, 1, 4096, True), (5000, 7, 1, 4096, True)])      # grids narrower than a patch
 def test_which_order(driver, tiles_t, tiles_n, cached, run_tiles, runs):
     out = subprocess.run([driver, str(tiles_t), str(tiles_n), str(cached), "4", str(run_tiles)], capture_output=True, text=True)
     assert out.returncode == 0, out.stdout
