@@ -126,9 +126,16 @@ def _ptr(t: Optional[torch.Tensor]):
     return None if t is None else ctypes.c_void_p(t.data_ptr())
 
 
+# The raw handle of the current stream: building a torch.cuda.Stream takes 2.9 us a call, this 0.3.  It is
+# none of torch's public functions, so that a torch without it goes by the public one.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> int:
-    if stream is None:   # the raw handle: building a torch.cuda.Stream takes 2.9 us a call, this 0.3
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if stream is None:
+        if _raw_stream is not None:
+            return _raw_stream(torch.cuda.current_device())
+        stream = torch.cuda.current_stream()
     return stream.cuda_stream
 
 

@@ -54,6 +54,20 @@ def test_workspace_queries(lib):
     assert lib.dass_unstructured_workspace_bytes(24576, 3072, 1, 1, 0) >= 24576 * 3072 * 2
 
 
+def test_current_stream_without_the_raw_handle(monkeypatch):
+    """torch's function for the raw handle of the current stream is private: without it the public one serves,
+    and a stream that is passed is taken as it is."""
+    class Stream:
+        cuda_stream = 0x77
+
+    monkeypatch.setattr(binding, "_raw_stream", None)
+    monkeypatch.setattr(binding.torch.cuda, "current_stream", lambda: Stream)
+    assert binding._stream(None) == 0x77
+    monkeypatch.setattr(binding, "_raw_stream", lambda device: 0x99 + device)
+    monkeypatch.setattr(binding.torch.cuda, "current_device", lambda: 2)
+    assert binding._stream(None) == 0x9b and binding._stream(Stream) == 0x77
+
+
 FAKE = ctypes.c_void_p(0x1000)      # aligned, never dereferenced: every call below is rejected first
 ODD = ctypes.c_void_p(0x1004)
 FAKE2 = ctypes.c_void_p(0x10000000)  # aligned, far from FAKE
