@@ -273,10 +273,12 @@ static dass_status launch_e(const char *fn, bool col_lines, const Args &a)
                            a.norms, a.fmode, a.along, a.n_keep, a.mask);
         return check_launch("short-line unstructured kernel");
     }
-    const size_t lds = 8 * kWords * 8 + 8 * ((size_t)(a.rows + 15) / 16 * 16 + 8) * (DT == DASS_BF16 ? 2 : 4);
+    auto lds_of = [](int64_t rows) { return 8 * kWords * 8 + 8 * (size_t)((rows + 15) / 16 * 16 + 8) * (DT == DASS_BF16 ? 2 : 4); };
+    const size_t lds = lds_of(a.rows);
+    // the same for every call: another thread may set it between this and the launch
     if (hipFuncSetAttribute(reinterpret_cast<const void *>(short_cols_kernel<DT, E>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-        return fail(DASS_ERR_HIP, "%s: cannot reserve %zu bytes of LDS", fn, lds);
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_of(64 * E)) != hipSuccess)
+        return fail(DASS_ERR_HIP, "%s: cannot reserve %zu bytes of LDS", fn, lds_of(64 * E));
     hipLaunchKernelGGL((short_cols_kernel<DT, E>), dim3((unsigned)((a.cols / 8 + 63) / 64 * 64)), dim3(512), lds, a.stream,
                        a.W, a.rows, a.cols, a.ld, a.norms, a.fmode, a.along, a.n_keep, a.mask);
     return check_launch("short-line unstructured kernel");
