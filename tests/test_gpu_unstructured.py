@@ -53,17 +53,23 @@ def _run_case(gpu_device, rows, cols, dtype, axes, alpha, n_prune, seed, ties=Fa
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("axes", AXES)
 @pytest.mark.parametrize("ties", [False, True])
-def test_unstructured_half(gpu_device, dtype, axes, ties):
+@pytest.mark.parametrize("long", [False, True])    # a wavefront's line, a workgroup's
+def test_unstructured_half(gpu_device, dtype, axes, ties, long):
     # line lengths that are not multiples of the block's stride; several column slabs
     rows, cols = 331, 8 * 37
+    if long:
+        rows, cols = (2311, 8 * 37) if axes[1] == "rows" else (331, 8 * 297)
     length = rows if axes[1] == "rows" else cols
     alpha = 0.5 if axes[0] == axes[1] else 1.0
     _run_case(gpu_device, rows, cols, dtype, axes, alpha, length // 2, seed=3, ties=ties)
 
 
 @pytest.mark.parametrize("axes", [("rows", "rows"), ("cols", "cols")])
-def test_unstructured_quota_edges(gpu_device, axes):
+@pytest.mark.parametrize("long", [False, True])
+def test_unstructured_quota_edges(gpu_device, axes, long):
     rows, cols = 70, 72
+    if long:
+        rows, cols = (2070, 72) if axes[1] == "rows" else (70, 2072)
     length = rows if axes[1] == "rows" else cols
     for n_prune in (0, 1, length - 1, length):
         for ties in (False, True):
@@ -86,10 +92,13 @@ def test_unstructured_magnitude_ties_on_long_lines(gpu_device, dtype):
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("axes", [("rows", "rows"), ("cols", "cols"), ("rows", "cols")])
-def test_unstructured_extreme_magnitudes(gpu_device, dtype, axes):
+@pytest.mark.parametrize("long", [False, True])    # a wavefront's line, a workgroup's
+def test_unstructured_extreme_magnitudes(gpu_device, dtype, axes, long):
     """Scores near the bottom and the top of the f32 range (subnormal weights, tiny and huge norms,
     products that underflow or overflow in f32) and exact zeros: the selection must stay exact."""
     rows, cols = 200, 256
+    if long:
+        rows, cols = (2200, 256) if axes[1] == "rows" else (200, 2256)
     g = torch.Generator(device="cpu").manual_seed(78)
     mant = torch.rand((rows, cols), generator=g) + 1.0
     expo = torch.randint(-140, -100, (rows, cols), generator=g).to(torch.float32)
@@ -115,11 +124,12 @@ def test_unstructured_extreme_magnitudes(gpu_device, dtype, axes):
 
 
 @pytest.mark.parametrize("axes", [("rows", "rows"), ("cols", "cols")])
-def test_unstructured_scores_equal_to_f32_precision(gpu_device, axes):
+@pytest.mark.parametrize("length", [1536, 4096])    # a wavefront's line, a workgroup's
+def test_unstructured_scores_equal_to_f32_precision(gpu_device, axes, length):
     """Position k of a line has weight 1 + (k mod 64)/128 and norm fl32(P / weight): all products
     are P up to an f32 rounding error, so their leading f32 terms tie in large numbers and the
     exact remainders (then the indices) must rank them like the oracle."""
-    length, lines = 1536, 40
+    lines = 40
     g = torch.Generator(device="cpu").manual_seed(11)
     k = torch.arange(length) % 64
     k = k[torch.randperm(length, generator=g)]
@@ -140,11 +150,13 @@ def test_unstructured_scores_equal_to_f32_precision(gpu_device, axes):
 
 @pytest.mark.parametrize("axes", [("rows", "rows"), ("cols", "cols")])
 @pytest.mark.parametrize("cluster", [48, 300])
-def test_unstructured_threshold_inside_a_cluster_of_close_scores(gpu_device, axes, cluster):
+@pytest.mark.parametrize("length", [1536, 2048, 4096])
+def test_unstructured_threshold_inside_a_cluster_of_close_scores(gpu_device, axes, cluster, length):
     """The threshold falls among scores that differ only in the last 10 bits of their f32 form, some
     of them equal: 48 of them (ranked directly after two digit passes) or 300 (more than the
-    direct ranking holds, so the last digit pass runs too).  Norms are 1: scores are |w|, f32."""
-    length, lines, big = 2048, 16, 900
+    direct ranking holds, so the last digit pass runs too).  Norms are 1: scores are |w|, f32.  Lines of a
+    wavefront, either side of its limit for columns, and of a workgroup."""
+    lines, big = 16, length * 900 // 2048
     g = torch.Generator(device="cpu").manual_seed(23 + cluster)
     steps = torch.randint(0, cluster // 2, (lines, cluster), generator=g)       # about 2 weights per value
     close = (torch.full((lines, cluster), 0x3F800000, dtype=torch.int64) + steps).to(torch.int32).view(torch.float32)
@@ -502,9 +514,14 @@ def test_unstructured_calls_overlap_on_several_streams(gpu_device):
 @pytest.mark.parametrize("dtype,rows,cols,axes", [
     (torch.bfloat16, 2056, 1032, ("rows", "rows")),    # passes over column tiles
     (torch.float32, 1040, 2048, ("cols", "cols")),     # whole rows per workgroup
-    (torch.float32, 688, 72, ("rows", "rows")),        # line-resident, column lines
-    (torch.bfloat16, 72, 696, ("cols", "cols")),       # line-resident, row lines
-    (torch.bfloat16, 136, 264, ("rows", "cols")),      # line-resident, one factor per line
+    (torch.float32, 688, 72, ("rows", "rows")),        # a wavefront per line, column lines
+    (torch.bfloat16, 72, 696, ("cols", "cols")),       # a wavefront per line, row lines
+    (torch.bfloat16, 136, 264, ("rows", "cols")),      # a wavefront per line, one factor per line
+    (torch.float32, 2064, 72, ("rows", "rows")),       # line-resident, column lines
+    (torch.bfloat16, 2064, 72, ("cols", "rows")),      # line-resident, column lines, one factor per line
+    (torch.bfloat16, 20, 8200, ("cols", "cols")),      # line-resident, row lines
+    (torch.bfloat16, 136, 2056, ("rows", "cols")),     # line-resident, row lines, one factor per line
+    (torch.float32, 72, 2056, ("cols", "cols")),       # multi-pass, row lines
     (torch.bfloat16, 16392, 72, ("rows", "rows")),     # transposed copy (without mask), multi-pass (with it)
 ])
 def test_unstructured_other_exponents(gpu_device, dtype, rows, cols, axes):
