@@ -377,7 +377,7 @@ __device__ __forceinline__ uint32_t bf16_pair(float lo, float hi)
 //
 // The tile is MI x NI blocks of 16 x 16 per wavefront and {gate, up}: 8 x 4 is the one described above;
 // 4 x 4 (128 tokens) and 4 x 2 (128 tokens x 64 neurons) are for grids that leave compute units idle,
-// where a slab's time is that of its loads on one compute unit (tile_shape() chooses).  They keep the
+// where a slab's time is that of its loads on one compute unit (tile_order.h chooses).  They keep the
 // ring's five units and its schedule, with units partly filled.
 template <int ACT, int EPI, int MI, int NI>
 __global__ __launch_bounds__(256) void calib_pipe64_kernel(
@@ -877,34 +877,6 @@ static void launch_mfma(int act, dim3 grid, hipStream_t stream, const uint16_t *
     }
 }
 
-// The tile of calib_pipe64_kernel for T tokens and n output columns (of each of two matrices for the gated
-// forms, so their tiles are half as wide in columns).  A workgroup fills a compute unit, and on grids that
-// do not run for many rounds a slab takes about as long as its rows take to load, so a shape's time goes as
-// rounds x rows of a tile's slab.  Large tiles load least in all and win wherever they fill the chip; small
-// ones win where large ones leave compute units idle.  256 x 256 against the tile chosen here, whole calls:
-// dass_mlp_forward 128 tokens of 1024 x 4096 98 -> 49 us, 1024 of 4096 x 11008 (64 tiles in the down
-// projection) 397 -> 293, 2048 of it (128 tiles) 451 -> 439; dass_calib_norms 300 of 4096 x 1024 73 -> 36.
-struct TileShape {
-    int which;              // 0: 8 x 4, 1: 4 x 4, 2: 4 x 2
-    int64_t tiles_t, tiles_n;
-};
-static TileShape tile_shape(int64_t T, int64_t n, bool gated)
-{
-    constexpr int kTokens[3] = {256, 128, 128}, kCols[3] = {256, 256, 128};
-    TileShape best{};
-    int64_t best_cost = 0;
-    for (int k = 0; k < 3; ++k) {
-        const int cols = gated ? kCols[k] / 2 : kCols[k];
-        const TileShape s{k, (T + kTokens[k] - 1) / kTokens[k], (n + cols - 1) / cols};
-        const int64_t cost = (s.tiles_t * s.tiles_n + 255) / 256 * (kTokens[k] + kCols[k]);
-        if (k == 0 || cost < best_cost) {
-            best = s;
-            best_cost = cost;
-        }
-    }
-    return best;
-}
-
 template <int ACT, int EPI, int MI, int NI>
 static hipError_t launch_pipe64_tile(hipStream_t stream, const uint16_t *X, int64_t T, int64_t ldx,
                                      const uint16_t *Wg, const uint16_t *Wu, int64_t ldw, int64_t d, int64_t d_int,
@@ -1017,7 +989,7 @@ extern "C" dass_status dass_calib_norms(const void *X, int64_t T, int64_t ldx, c
     // tile's rows.
     const bool pipe64 = bf16 && d % 64 == 0 && (int64_t)BM * ldx * 2 < 0x7fffffffLL &&
                         (int64_t)BN * ldw * 2 < 0x7fffffffLL;
-    const TileShape shape = pipe64 ? tile_shape(T, d_int, true) : TileShape{};
+    const TileShape shape = pipe64 ? dense_tile_shape(T, d_int, true) : TileShape{};
     const int64_t tiles_t = pipe64 ? shape.tiles_t : bf16 ? (T + BM - 1) / BM : (T + f_tile - 1) / f_tile;
     const int64_t tiles_n = pipe64 ? shape.tiles_n : bf16 ? (d_int + BN - 1) / BN : (d_int + f_tile - 1) / f_tile;
     const TileOrder order = make_tile_order(tiles_t, tiles_n, fits_memory_cache(2, d_int, d, dt),
@@ -1112,7 +1084,7 @@ extern "C" dass_status dass_mlp_forward(const void *X, int64_t T, int64_t ldx, c
     uint16_t *Y = static_cast<uint16_t *>(workspace);
     // Eq. 2: y = act(X Wgate^T) * (X Wup^T), tiles of up to 256 tokens x 128 neurons
     {
-        const TileShape shape = tile_shape(T, d_int, true);
+        const TileShape shape = dense_tile_shape(T, d_int, true);
         const TileOrder order = make_tile_order(shape.tiles_t, shape.tiles_n, fits_memory_cache(2, d_int, d, dt),
                                                 shape.which == 1 ? 8 : kPatchT);
         if (order.blocks == 0)
@@ -1129,7 +1101,7 @@ extern "C" dass_status dass_mlp_forward(const void *X, int64_t T, int64_t ldx, c
     }
     // Eq. 3: out = y Wdown^T, tiles of up to 256 tokens x 256 output features, K = d_int
     {
-        const TileShape shape = tile_shape(T, d, false);
+        const TileShape shape = dense_tile_shape(T, d, false);
         const TileOrder order = make_tile_order(shape.tiles_t, shape.tiles_n, fits_memory_cache(1, d_int, d, dt),
                                                 shape.which == 1 ? 8 : kPatchT);
         if (order.blocks == 0)

@@ -359,31 +359,16 @@ extern "C" dass_status dass_down_proj_sparse24(const void *Y, int64_t T, int64_t
     if ((int64_t)sp::kTN * ldy * 2 >= 0x7fffffffLL || (int64_t)sp::kFM * ldv * 2 >= 0x7fffffffLL ||
         (int64_t)sp::kFM * ldm >= 0x7fffffffLL)
         return fail(DASS_ERR_SHAPE, "%s: rows too long for the tile addressing", fn);
-    // A workgroup fills a compute unit and a slab takes about as long as its rows take to load, so a tile's
-    // time goes as rounds x bytes of a slab (64 a feature, 128 a token): small tiles where large ones leave
-    // compute units idle.  256 x 256 against the tile chosen here: 2048 tokens of 4096 x 11008 (128 tiles)
-    // 176 -> 128 us; with the compression 1024 tokens 219 -> 103, 128 tokens of 1024 x 4096 65 -> 33 us;
-    // 4096 tokens (256 tiles) and more stay with 256 x 256.
-    constexpr int kFeatures[3] = {256, 256, 128}, kTokens[3] = {256, 128, 128};
-    int which = 0;
-    int64_t tiles_t = 0, tiles_f = 0, cost = 0;
-    for (int k = 0; k < 3; ++k) {
-        const int64_t nt = (T + kTokens[k] - 1) / kTokens[k], nf = (d + kFeatures[k] - 1) / kFeatures[k];
-        const int64_t c = (nt * nf + 255) / 256 * (kFeatures[k] + 2 * kTokens[k]);
-        if (k == 0 || c < cost) {
-            which = k;
-            tiles_t = nt;
-            tiles_f = nf;
-            cost = c;
-        }
-    }
+    const TileShape shape = sparse_tile_shape(T, d);
     // Patches from 1024 tiles on, us, taken in turn with runs: 64 and 128 x 16 tiles (4096 x 14336) 1052 1095, 2118
     // 2173; 64 and 96 x 20 (5120 x 13824) 1274 1304, 1972 2033; 4096 x 11008 and 8192 x 8192 within 0.7 %.
-    const TileOrder order = make_tile_order(tiles_t, tiles_f, true, which == 1 ? 8 : kPatchT, 1023);
+    const TileOrder order = make_tile_order(shape.tiles_t, shape.tiles_n, true, shape.which == 1 ? 8 : kPatchT, 1023);
     if (order.blocks == 0)
         return fail(DASS_ERR_SHAPE, "%s: too many tiles for one launch; split the tokens", fn);
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    const auto launch = which == 0 ? sp::launch_tile<4, 4> : which == 1 ? sp::launch_tile<4, 2> : sp::launch_tile<2, 2>;
+    const auto launch = shape.which == 0   ? sp::launch_tile<4, 4>
+                        : shape.which == 1 ? sp::launch_tile<4, 2>
+                                           : sp::launch_tile<2, 2>;
     const hipError_t e = launch(stream, static_cast<const uint16_t *>(Y), T, ldy, static_cast<const uint16_t *>(values), ldv,
                                 meta, ldm, d, d_int, static_cast<uint16_t *>(out), ldo, order);
     if (e != hipSuccess)

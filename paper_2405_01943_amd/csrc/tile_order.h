@@ -1,4 +1,5 @@
-// Which output tile a workgroup of the matrix-core kernels (calib.hip, sparse_down.hip) computes.
+// Which output tile a workgroup of the matrix-core kernels (calib.hip, sparse_down.hip) computes, and how
+// large the tiles are.
 //
 // Consecutive workgroup ids go to different XCDs (8 of them, each with its own L2), and an XCD
 // runs about 32 of these workgroups at a time, one per compute unit.  Tiles that share rows of X
@@ -106,6 +107,49 @@ inline TileOrder make_tile_order(int64_t tiles_t, int64_t tiles_n, bool weights_
         o.super_rows = (uint32_t)((np_t + supers - 1) / supers);
     }
     return o;
+}
+
+// The tile of a workgroup.  It fills a compute unit, and on grids that do not run for many rounds a slab of
+// K takes about as long as its rows take to load, so a shape's time goes as rounds x bytes of a tile's slab.
+// Large tiles load least in all and win wherever they fill the chip; small ones win where large ones leave
+// compute units idle.
+struct TileShape {
+    int which;   // 0: the largest, 1: half as many tokens, 2: half of both
+    int64_t tiles_t, tiles_n;
+};
+
+// tokens, cols: of the three tiles; token_bytes, col_bytes: of a slab, in any unit
+inline TileShape cheapest_tile(int64_t T, int64_t n, const int (&tokens)[3], const int (&cols)[3], int token_bytes, int col_bytes)
+{
+    TileShape best = {0, 0, 0};
+    int64_t best_cost = 0;
+    for (int k = 0; k < 3; ++k) {
+        const TileShape s = {k, (T + tokens[k] - 1) / tokens[k], (n + cols[k] - 1) / cols[k]};
+        const int64_t cost = (s.tiles_t * s.tiles_n + 255) / 256 * (tokens[k] * token_bytes + cols[k] * col_bytes);
+        if (k == 0 || cost < best_cost) {
+            best = s;
+            best_cost = cost;
+        }
+    }
+    return best;
+}
+
+// calib_pipe64_kernel for T tokens and n output columns (of each of two matrices for the gated forms, so
+// their tiles are half as wide in columns).  256 x 256 against the tile chosen here, whole calls:
+// dass_mlp_forward 128 tokens of 1024 x 4096 98 -> 49 us, 1024 of 4096 x 11008 (64 tiles in the down
+// projection) 397 -> 293, 2048 of it (128 tiles) 451 -> 439; dass_calib_norms 300 of 4096 x 1024 73 -> 36.
+inline TileShape dense_tile_shape(int64_t T, int64_t n, bool gated)
+{
+    return gated ? cheapest_tile(T, n, {256, 128, 128}, {128, 128, 64}, 1, 2)
+                 : cheapest_tile(T, n, {256, 128, 128}, {256, 256, 128}, 1, 1);
+}
+
+// down_sparse24_kernel: 64 bytes a feature, 128 a token.  256 x 256 against the tile chosen here: 2048 tokens of
+// 4096 x 11008 (128 tiles) 176 -> 128 us; with the compression 1024 tokens 219 -> 103, 128 tokens of 1024 x 4096
+// 65 -> 33 us; 4096 tokens (256 tiles) and more stay with 256 x 256.
+inline TileShape sparse_tile_shape(int64_t T, int64_t d)
+{
+    return cheapest_tile(T, d, {256, 128, 128}, {256, 256, 128}, 2, 1);
 }
 
 }  // namespace dass

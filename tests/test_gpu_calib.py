@@ -73,10 +73,13 @@ def test_calib_activations_ragged_shapes(gpu_device, dtype, act):
     _check(X, Wg, Wu, act, gpu_device)
 
 
+# T, d, d_int of the direct-to-LDS kernel and its tile: 0 the largest, 1 half as many tokens, 2 half of both
+PIPE_SHAPES = [(300, 64, 150, 2), (515, 192, 257, 2), (1100, 448, 130, 2), (4225, 192, 530, 1), (16700, 64, 530, 0)]
+TILE_SHAPES = [(T, d_int, tile) for T, _, d_int, tile in PIPE_SHAPES]
+
+
 @pytest.mark.parametrize("act", ACTS)
-@pytest.mark.parametrize("T,d,I", [(300, 64, 150), (515, 192, 257), (1100, 448, 130),
-                                     # tiles of 128 tokens x 128 neurons, then of 256 x 128
-                                     (4225, 192, 530), (16700, 64, 530)])
+@pytest.mark.parametrize("T,d,I", [shape[:3] for shape in PIPE_SHAPES])
 def test_calib_pipelined_kernel_every_activation(gpu_device, act, T, d, I):
     """bf16 with d a multiple of 64: the direct-to-LDS kernel (1, 3 and 7 K slabs, so the prologue,
     the steady state and the peeled last slabs all run), ragged T and d_int, every activation's

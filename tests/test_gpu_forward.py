@@ -58,24 +58,29 @@ def test_forward_small_shapes(gpu_device, act, T, d, d_int, pad):
         assert torch.all(out._base[:, d:] == 7.0)   # nothing written past a row's end
 
 
-@pytest.mark.parametrize("T,d,d_int", [(8200, 512, 64), (4225, 192, 1088), (33100, 512, 128)])
-def test_forward_tile_shapes(gpu_device, T, d, d_int):
-    """Grids that take each tile of the two launches: 128 tokens where 256 x 256 tiles are about half
-    the compute units (first the down projection, then the gated launch), the largest tile beyond
-    them; each result is, bit for bit, that of token chunks small enough for the smallest tile (an
-    output's K order does not depend on the tile), and one chunk is the oracle's."""
+# T, d, d_int and the tiles of the gated and of the down launch: 0 the largest, 1 half as many tokens, 2 half of both
+TILE_SHAPES = [(8200, 512, 64, 2, 1), (4225, 192, 1088, 0, 2), (33100, 512, 128, 0, 0), (4000, 128, 1024, 1, 2),
+               (3970, 192, 960, 1, 2)]
+
+
+@pytest.mark.parametrize("act", ["silu", "gelu_tanh", "relu", "gelu_erf"])
+@pytest.mark.parametrize("T,d,d_int,gated,down", TILE_SHAPES)
+def test_forward_tile_shapes(gpu_device, T, d, d_int, gated, down, act):
+    """Grids that take each tile of the two launches; each result is, bit for bit, that of token chunks
+    small enough for the smallest gated tile (an output's K order does not depend on the tile), and one
+    chunk is the oracle's."""
     g = torch.Generator(device="cpu").manual_seed(T)
     X = torch.randn((T, d), generator=g).to(torch.bfloat16).to(gpu_device)
     Wg, Wu = ((torch.randn((d_int, d), generator=g) * 0.1).to(torch.bfloat16).to(gpu_device) for _ in range(2))
     Wd = (torch.randn((d, d_int), generator=g) * 0.1).to(torch.bfloat16).to(gpu_device)
     whole = torch.empty((T, d), dtype=torch.bfloat16, device=gpu_device)
     parts = torch.empty_like(whole)
-    dass.mlp_forward(X, Wg, Wu, Wd, "silu", whole)
+    dass.mlp_forward(X, Wg, Wu, Wd, act, whole)
     for lo in range(0, T, 700):
-        dass.mlp_forward(X[lo:lo + 700], Wg, Wu, Wd, "silu", parts[lo:lo + 700])
+        dass.mlp_forward(X[lo:lo + 700], Wg, Wu, Wd, act, parts[lo:lo + 700])
     torch.cuda.synchronize()
     assert torch.equal(whole.view(torch.int16), parts.view(torch.int16))
-    ref, ab = oracle.mlp_forward(to_np32(X[-300:]), to_np32(Wg), to_np32(Wu), to_np32(Wd), "silu", want_abs=True)
+    ref, ab = oracle.mlp_forward(to_np32(X[-300:]), to_np32(Wg), to_np32(Wu), to_np32(Wd), act, want_abs=True)
     _check(to_np32(whole[-300:]), ref, ab, f"T={T} d={d} d_int={d_int}")
 
 

@@ -37,10 +37,13 @@ def _sparse_weights(d, d_int, seed):
     return torch.from_numpy(W).to(torch.bfloat16)
 
 
-@pytest.mark.parametrize("T,d,d_int,pad", [(300, 192, 320, 0), (513, 264, 448, 8), (256, 256, 64, 0), (70, 8, 704, 16),
-                                           (1, 520, 128, 0),
-                                           # tiles of 256 features x 128 tokens, then of 256 x 256
-                                           (8200, 520, 192, 8), (4225, 1032, 576, 0), (33100, 512, 128, 0)])
+# T, d, d_int, padding and the kernel's tile: 0 the largest, 1 half as many tokens, 2 half of both
+SHAPES = [(300, 192, 320, 0, 2), (513, 264, 448, 8, 2), (256, 256, 64, 0, 2), (70, 8, 704, 16, 2), (1, 520, 128, 0, 2),
+          (8200, 520, 192, 8, 1), (4225, 1032, 576, 0, 1), (33100, 512, 128, 0, 0)]
+TILE_SHAPES = [(T, d, tile) for T, d, _, _, tile in SHAPES]
+
+
+@pytest.mark.parametrize("T,d,d_int,pad", [shape[:4] for shape in SHAPES])
 def test_sparse_down_small_shapes(gpu_device, T, d, d_int, pad):
     W = _sparse_weights(d, d_int, T + d)
     # the compressed form comes from the oracle, so the test does not lean on the GPU's compressor

@@ -18,6 +18,12 @@ DRIVER = r"""
 using namespace dass;
 int main(int argc, char **argv)
 {
+    if (argc == 4) {   // tokens, columns, kernel: which tile
+        const int64_t T = atoll(argv[1]), n = atoll(argv[2]);
+        const char k = argv[3][0];
+        printf("%d", (k == 's' ? sparse_tile_shape(T, n) : dense_tile_shape(T, n, k == 'g')).which);
+        return 0;
+    }
     const uint32_t tt = atoi(argv[1]), tn = atoi(argv[2]);
     const TileOrder o = argc > 5 ? make_tile_order(tt, tn, atoi(argv[3]) != 0, atoi(argv[4]), atoi(argv[5]))
                                  : make_tile_order(tt, tn, atoi(argv[3]) != 0, atoi(argv[4]));
@@ -82,3 +88,23 @@ def test_which_order(driver, tiles_t, tiles_n, cached, run_tiles, runs):
     assert (band > 0) == runs
     if runs:
         assert worst == (tiles_t * tiles_n + 7) // 8
+
+
+def _which(driver, tokens, columns, kernel):
+    return int(subprocess.run([driver, str(tokens), str(columns), kernel], capture_output=True, text=True, check=True).stdout)
+
+
+def test_gpu_tests_take_every_tile(driver):
+    """The shapes of the GPU tests that are meant for the tiles of the matrix-core kernels take them."""
+    import test_gpu_calib
+    import test_gpu_forward
+    import test_gpu_sparse_down
+    for T, d, d_int, gated, down in test_gpu_forward.TILE_SHAPES:
+        assert (_which(driver, T, d_int, "gated"), _which(driver, T, d, "down")) == (gated, down), (T, d, d_int)
+        assert _which(driver, 700, d_int, "gated") == 2     # its chunks
+    for shapes, kernel in ((test_gpu_calib.TILE_SHAPES, "gated"), (test_gpu_sparse_down.TILE_SHAPES, "sparse")):
+        for T, columns, which in shapes:
+            assert _which(driver, T, columns, kernel) == which, (kernel, T, columns)
+    for taken in ([s[3] for s in test_gpu_forward.TILE_SHAPES], [s[4] for s in test_gpu_forward.TILE_SHAPES],
+                  [s[2] for s in test_gpu_calib.TILE_SHAPES], [s[2] for s in test_gpu_sparse_down.TILE_SHAPES]):
+        assert set(taken) == {0, 1, 2}
