@@ -362,10 +362,14 @@ constexpr int P_BM = 256, P_BN = 128;
 // The two storing forms go through LDS (free after the last barrier of the main loop): lanes
 // pair neighbouring columns into 32-bit words, the workgroup then writes whole 16-byte chunks
 // of output rows.
+//
+// The tile is MI x NI blocks of 16 x 16 per wavefront and {gate, up}: 8 x 4 is the one described above;
+// 4 x 4 (128 tokens) and 4 x 2 (128 tokens x 64 neurons) are for grids that leave compute units idle,
+// where a slab's time is that of its loads on one compute unit (tile_order.h chooses).  They keep the
+// ring's five units and its schedule, with units partly filled.
 constexpr int P64_LDS = 5 * 32768;
 enum { kEpiNorms = 0, kEpiGlu = 1, kEpiGemm = 2 };
 
-// float -> bf16 bits, round to nearest even (finite inputs)
 // Two f32 rounded to bf16 (nearest even), `lo` in the low half of the word: one v_cvt_pk_bf16_f32.
 typedef __attribute__((ext_vector_type(2))) float f32x2_t;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
@@ -374,11 +378,6 @@ __device__ __forceinline__ uint32_t bf16_pair(float lo, float hi)
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{lo, hi}, bf16x2_t));
 }
 
-//
-// The tile is MI x NI blocks of 16 x 16 per wavefront and {gate, up}: 8 x 4 is the one described above;
-// 4 x 4 (128 tokens) and 4 x 2 (128 tokens x 64 neurons) are for grids that leave compute units idle,
-// where a slab's time is that of its loads on one compute unit (tile_order.h chooses).  They keep the
-// ring's five units and its schedule, with units partly filled.
 template <int ACT, int EPI, int MI, int NI>
 __global__ __launch_bounds__(256) void calib_pipe64_kernel(
     const uint16_t *__restrict__ X, int64_t T, int64_t ldx, const uint16_t *__restrict__ Wg,
@@ -412,7 +411,7 @@ __global__ __launch_bounds__(256) void calib_pipe64_kernel(
     // register, the K offset a scalar, and a read outside the buffer returns 0 instead of faulting.
     const int wl_row = lane >> 3, wl_slot = lane & 7;
     const int64_t rows_x = T - t0 < BM ? T - t0 : BM, rows_w = d_int - n0 < BN ? d_int - n0 : BN;
-    // kEpiGemm: the second 128 rows of the tile may be fewer, or none (then an empty buffer:
+    // kEpiGemm: the second half of the tile's rows may be fewer, or none (then an empty buffer:
     // its reads fetch nothing and return 0; clamped rows beyond its end do the same)
     const int64_t left_u = d_int - n0 - BN;
     const int64_t rows_u = EPI != kEpiGemm ? rows_w : left_u < 0 ? 0 : left_u < BN ? left_u : BN;
@@ -546,12 +545,13 @@ __global__ __launch_bounds__(256) void calib_pipe64_kernel(
         read_one(f0, 0, 1, 0, q);
 
     // ---- main loop.  One slab = 2 K steps of N_PAIRS gate/up MFMA pairs, the first on f0, the second
-    // on f1.  (The spacings below are those of the 8 x 4 tile.)  During K step 0 a wavefront reads the fragments of K step 1 (one read every second
-    // pair); during the second half of K step 1, after the slab's one barrier, those of K step 0
-    // of the next slab (one read a pair).  One global->LDS wave-load goes out every fourth pair:
-    // the rest of the B part of slab s + 1 (first half of K step 0), then the A part of slab s + 2
-    // (up to the barrier), then the first half of the B part of slab s + 2 into the A unit of
-    // slab s, which is free once every wavefront holds its last fragments of slab s.  B1, A2, B2:
+    // on f1.  During K step 0 a wavefront reads the fragments of K step 1, evenly between the pairs (8 x 4
+    // tile: one read every second pair); during the second half of K step 1, after the slab's one barrier,
+    // those of K step 0 of the next slab (one read a pair).  One global->LDS wave-load goes out every
+    // A_GAP or B_GAP pairs (fourth pair): the rest of the B part of slab s + 1 (first half of K step 0),
+    // then the A part of slab s + 2 (up to the barrier), then the first half of the B part of slab s + 2
+    // into the A unit of slab s, which is free once every wavefront holds its last fragments of slab s.
+    // B1, A2, B2:
     // whether these parts exist and were not issued by the prologue; NEXT: whether a slab follows.
     // All four are compile-time, so the steady state has no branch between its MFMAs.
     int ua = 0, ub = 1;   // ring units of slab s

@@ -223,6 +223,7 @@ __global__ __launch_bounds__(256) void down_sparse24_kernel(
         constexpr int PAR = decltype(par_tag)::value;
         constexpr int kAhead = PAR == 0 ? kLoadsEven : kLoadsOdd;                    // loads of slab s + 2
         constexpr int kIssue = PAR == 1 ? kLoadsEven : kLoadsOdd;                    // loads of slab s + 3
+        static_assert(kAhead < 16, "the low four bits of the wait's counter hold it");
         const char *st = lds + (s % kStages) * kStage, *st_next = lds + ((s + 1) % kStages) * kStage;
 #pragma unroll
         for (int q = 0; q < kMfmas; ++q) {   // K step 0
@@ -232,8 +233,8 @@ __global__ __launch_bounds__(256) void down_sparse24_kernel(
             mfma(fa, codes, 0, q);
             __builtin_amdgcn_sched_barrier(0);
         }
-        // slab s + 1 has landed (only slab s + 2 may be in flight) and this wavefront holds its last
-        // fragments of slab s: vmcnt(14 or 0), lgkmcnt(0)
+        // slab s + 1 has landed (only slab s + 2, kAhead loads, may be in flight) and this wavefront holds
+        // its last fragments of slab s: vmcnt(kAhead or 0), lgkmcnt(0)
         if (AHEAD)
             __builtin_amdgcn_s_waitcnt(0x0070 | kAhead);
         else
