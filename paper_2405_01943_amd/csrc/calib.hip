@@ -365,8 +365,13 @@ constexpr int P_BM = 256, P_BN = 128;
 //
 // The tile is MI x NI blocks of 16 x 16 per wavefront and {gate, up}: 8 x 4 is the one described above;
 // 4 x 4 (128 tokens) and 4 x 2 (128 tokens x 64 neurons) are for grids that leave compute units idle,
-// where a slab's time is that of its loads on one compute unit (tile_order.h chooses).  They keep the
-// ring's five units and its schedule, with units partly filled.
+// where a slab's time is that of its loads on one compute unit (tile_order.h chooses).  A slab's MFMAs
+// (0.2 to 0.4 us) are then shorter than its loads are on their way (0.8 us out of the memory-side cache, 2.5 us
+// out of HBM), so these tiles keep a ring of whole parts for each operand and request a part as soon as
+// its place is free, two to four slabs ahead, instead of the half to one slab of the schedule above.  Whole
+// dass_mlp_forward calls, that schedule with its units partly filled against this one: 2048 tokens of 4096 x 11008
+// 451-465 -> 428-436 us, 512 of it 203-207 -> 178-181, 1500 of 3072 x 24576 695-718 -> 636-640, 128 of 2048 x 8192
+// 85-87 -> 76, 128 of 1024 x 4096 46-47 -> 40; dass_calib_norms of 512 tokens of 11008 x 2048 90 -> 68.
 constexpr int P64_LDS = 5 * 32768;
 enum { kEpiNorms = 0, kEpiGlu = 1, kEpiGemm = 2 };
 
@@ -389,8 +394,12 @@ __global__ __launch_bounds__(256) void calib_pipe64_kernel(
     constexpr int BN_TILE = EPI == kEpiGemm ? 2 * BN : BN;   // rows of W (output columns) per tile
     constexpr int TM = 16 * MI, TN = 16 * NI;   // wavefront tile
     constexpr int CH = BK / 8;               // 16-byte chunks per tile row
-    constexpr int UNIT = 32768;              // A part, or gate half + up half of the B part
     constexpr int B_HALF = BN * BK * 2;      // 16 KB at most
+    constexpr bool DEEP = MI < 8;
+    constexpr int NA = !DEEP ? 5 : NI == 4 ? 4 : 5, NB = !DEEP ? 5 : NI == 4 ? 3 : 5;   // ring units
+    constexpr int A_UNIT = DEEP ? BM * BK * 2 : 32768, B_UNIT = DEEP ? 2 * B_HALF : 32768;
+    constexpr int B_BASE = DEEP ? NA * A_UNIT : 0;   // 8 x 4: one ring for both parts
+    static_assert(!DEEP || NA * A_UNIT + NB * B_UNIT <= P64_LDS, "the rings fit");
     constexpr int A_WL = MI, B_WL = NI;      // wave-loads (8 rows x 128 B) per wavefront per slab: MI + NI + NI
 
     extern __shared__ __attribute__((aligned(1024))) char lds64[];   // P64_LDS bytes
@@ -442,14 +451,14 @@ __global__ __launch_bounds__(256) void calib_pipe64_kernel(
 
     // q-th of this wavefront's A_WL loads of an A part (slab at byte offset kb) into ring unit `unit`
     auto issue_a = [&](int unit, int kb, int q) {
-        load_to_lds(rx, lds64 + unit * UNIT + (wave * A_WL + q) * 1024, a_off[q], kb);
+        load_to_lds(rx, lds64 + unit * A_UNIT + (wave * A_WL + q) * 1024, a_off[q], kb);
     };
     // q-th of its 2 B_WL loads of a B part: B_WL of Wgate, then B_WL of Wup
     auto issue_b = [&](int unit, int kb, int q) {
         if (q < B_WL)
-            load_to_lds(rg, lds64 + unit * UNIT + (wave * B_WL + q) * 1024, b_off[q], kb);
+            load_to_lds(rg, lds64 + B_BASE + unit * B_UNIT + (wave * B_WL + q) * 1024, b_off[q], kb);
         else
-            load_to_lds(ru, lds64 + unit * UNIT + B_HALF + (wave * B_WL + q - B_WL) * 1024, b_off[q - B_WL], kb);
+            load_to_lds(ru, lds64 + B_BASE + unit * B_UNIT + B_HALF + (wave * B_WL + q - B_WL) * 1024, b_off[q - B_WL], kb);
     };
 
     f32x4 acc_g[MI][NI], acc_u[MI][NI];
@@ -472,7 +481,7 @@ __global__ __launch_bounds__(256) void calib_pipe64_kernel(
     // q-th fragment of K step kk of the slab in units (ua, ub), in the order the MFMAs need them:
     // a0 a1 g0 u0 g1 u1 .. a2 a3 ..
     auto read_one = [&](Frags &f, int ua, int ub, int kk, int q) {
-        const char *pa = lds64 + ua * UNIT + (a_frag0 ^ (kk * 64)), *pb = lds64 + ub * UNIT + (b_frag0 ^ (kk * 64));
+        const char *pa = lds64 + ua * A_UNIT + (a_frag0 ^ (kk * 64)), *pb = lds64 + B_BASE + ub * B_UNIT + (b_frag0 ^ (kk * 64));
         if (q < 2) {
             f.a[q] = *reinterpret_cast<const bf16x8 *>(pa + q * 2048);
         } else if (q < 2 + 2 * NI) {
@@ -502,8 +511,118 @@ __global__ __launch_bounds__(256) void calib_pipe64_kernel(
         }
     };
 
-    // ---- prologue: A0 B0 A1 B1 A2 fill the five units
     const int S = (int)(d / BK);   // slabs; the host guarantees d % 64 == 0
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                acc_g[i][j][r] = 0.0f;
+                acc_u[i][j][r] = 0.0f;
+            }
+    if constexpr (DEEP) {
+    // ---- small tiles.  Under the MFMAs of K step 0 go the fragment reads of K step 1; the second half of K step
+    // 1, after the slab's one barrier, carries those of K step 0 of the next slab.  The loads of the B part of
+    // slab s + NB and the A part of slab s + NA, into the units of slab s, go out one a pair from that barrier on,
+    // the last ones under K step 0 of slab s + 1 (all in the second half, 1 to 3 us more of every figure above).
+    // Parts past the last slab are requested from an empty buffer (nothing is fetched), so that every slab waits
+    // for the same number of loads.
+    constexpr int N_LOADS = A_WL + 2 * B_WL;
+    // q-th load of the B part of slab s + NB and the A part of slab s + NA, into the units ub and ua; the B part first
+    auto issue = [&](int s, int ua, int ub, int q) {
+        const bool is_b = q < 2 * B_WL, g = q < B_WL;
+        const int slab = s + (is_b ? NB : NA);
+        const int span = slab < S ? is_b ? g ? span_w : span_u : span_x : 0;
+        const uint16_t *rows = is_b ? g ? Wg + n0 * ldw : up_rows : X + t0 * ldx;
+        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(rows), 0, span, kRawBuffer);
+        if (is_b)
+            load_to_lds(r, lds64 + B_BASE + ub * B_UNIT + (g ? 0 : B_HALF) + (wave * B_WL + q % B_WL) * 1024, b_off[q % B_WL],
+                        slab * BK * 2);
+        else
+            load_to_lds(r, lds64 + ua * A_UNIT + (wave * A_WL + q - 2 * B_WL) * 1024, a_off[q - 2 * B_WL], slab * BK * 2);
+    };
+    // As if slabs -NB, -NB + 1, .. had been read: two of them here, the others under the MFMAs of slab 0.  A parts
+    // that run further ahead than the B parts come first.
+#pragma unroll
+    for (int p = -NA; p < -NB; ++p)
+#pragma unroll
+        for (int q = 2 * B_WL; q < N_LOADS; ++q)
+            issue(p, p + NA, 0, q);
+#pragma unroll
+    for (int p = -NB; p < 2 - NB; ++p)
+#pragma unroll
+        for (int q = 0; q < N_LOADS; ++q)
+            issue(p, p + NA, p + NB, q);
+    constexpr int A_MORE = NA > NB ? A_WL : 0;   // the A part requested with a B part is due a slab later
+    wait_vmcnt<N_LOADS + A_MORE>();              // slab 0 has landed
+    block_barrier();
+    Frags f0, f1;
+#pragma unroll
+    for (int q = 0; q < N_READS; ++q)
+        read_one(f0, 0, 0, 0, q);
+    int ua = 0, ub = 0, pa = 0, pb = 0;   // ring units of slab s, of slab s - 1
+    constexpr int N_NOW = N_LOADS < N_HALF ? N_LOADS : N_HALF, N_LATE = N_LOADS - N_NOW;
+    auto slab_body = [&](int s, auto first_tag) {
+        constexpr bool FIRST = decltype(first_tag)::value;
+        constexpr int N_REST = FIRST ? (NB - 2) * N_LOADS : 0, N_FREE = N_PAIRS + N_HALF;
+        auto rest = [&](int q) {   // the prologue's other loads, spread over the pairs before the barrier
+#pragma unroll
+            for (int x = q * N_REST / N_FREE; x < (q + 1) * N_REST / N_FREE; ++x)
+                issue(2 - NB + x / N_LOADS, 2 - NB + x / N_LOADS + NA, 2 + x / N_LOADS, x % N_LOADS);
+        };
+        const int ua1 = ua + 1 == NA ? 0 : ua + 1, ub1 = ub + 1 == NB ? 0 : ub + 1;
+#pragma unroll
+        for (int q = 0; q < N_PAIRS; ++q) {   // K step 0
+            rest(q);
+            if constexpr (!FIRST) {
+#pragma unroll
+                for (int x = q * N_LATE / N_PAIRS; x < (q + 1) * N_LATE / N_PAIRS; ++x)
+                    issue(s - 1, pa, pb, N_NOW + x);
+            }
+#pragma unroll
+            for (int x = (q * N_READS + N_PAIRS - 1) / N_PAIRS; x < ((q + 1) * N_READS + N_PAIRS - 1) / N_PAIRS; ++x)
+                read_one(f1, ua, ub, 1, x);
+            mfma_pair(f0, q);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int q = 0; q < N_HALF; ++q) {   // K step 1, first half
+            rest(N_PAIRS + q);
+            mfma_pair(f1, q);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        // slab s + 1 has landed and this wavefront holds its last fragments of slab s: lgkmcnt(0) and vmcnt of
+        // what was requested after the B part of slab s + 1
+        constexpr int AHEAD = (NB - 2) * N_LOADS + A_MORE;
+        static_assert(AHEAD < 64, "vmcnt is a 6-bit counter");
+        __builtin_amdgcn_s_waitcnt(0x0070 | (AHEAD & 15) | ((AHEAD >> 4) << 14));
+        block_barrier();
+#pragma unroll
+        for (int q = 0; q < N_HALF; ++q) {   // K step 1, second half; past the last slab the reads are of no use
+#pragma unroll
+            for (int x = q * N_NOW / N_HALF; x < (q + 1) * N_NOW / N_HALF; ++x)
+                issue(s, ua, ub, x);
+#pragma unroll
+            for (int x = (q * N_READS + N_HALF - 1) / N_HALF; x < ((q + 1) * N_READS + N_HALF - 1) / N_HALF; ++x)
+                read_one(f0, ua1, ub1, 0, x);
+            mfma_pair(f1, N_HALF + q);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        pa = ua;
+        pb = ub;
+        ua = ua1;
+        ub = ub1;
+    };
+    // (the first slab on its own: with one loop the compiler gave the accumulators other registers in every slab and
+    // moved them back)
+    slab_body(0, std::true_type{});
+    for (int s = 1; s < S; ++s)
+        slab_body(s, std::false_type{});
+    wait_vmcnt<0>();   // the rings are about to be used again, and the empty parts would be written over that
+    block_barrier();
+    } else {
+    // ---- prologue: A0 B0 A1 B1 A2 fill the five units
 #pragma unroll
     for (int q = 0; q < A_WL; ++q)
         issue_a(0, 0, q);
@@ -523,15 +642,6 @@ __global__ __launch_bounds__(256) void calib_pipe64_kernel(
         for (int q = 0; q < A_WL; ++q)
             issue_a(4, 2 * BK * 2, q);
     }
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int j = 0; j < NI; ++j)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                acc_g[i][j][r] = 0.0f;
-                acc_u[i][j][r] = 0.0f;
-            }
     if (S > 2)
         wait_vmcnt<2 * A_WL + 2 * B_WL>();   // slab 0 has landed
     else if (S > 1)
@@ -618,6 +728,7 @@ __global__ __launch_bounds__(256) void calib_pipe64_kernel(
         slab_body(1, No{}, No{}, No{}, No{});
     } else {
         slab_body(0, No{}, No{}, No{}, No{});
+    }
     }
 
     if constexpr (EPI == kEpiNorms) {

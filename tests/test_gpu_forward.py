@@ -84,6 +84,22 @@ def test_forward_tile_shapes(gpu_device, T, d, d_int, gated, down, act):
     _check(to_np32(whole[-300:]), ref, ab, f"T={T} d={d} d_int={d_int}")
 
 
+@pytest.mark.parametrize("slabs", range(1, 9))
+def test_forward_ring_ends(gpu_device, slabs):
+    """K of one to eight 64-column slabs around the depths of the small tiles' rings (3 to 5 parts): the smallest
+    tile in both launches, half as many tokens in the gated one, then in the down projection."""
+    for T, d, d_int in ((90, 64 * slabs, 64 * (9 - slabs)), (3970, 64 * slabs, 960), (8200, 512, 64 * slabs)):
+        g = torch.Generator(device="cpu").manual_seed(slabs)
+        X = torch.randn((T, d), generator=g).to(torch.bfloat16).to(gpu_device)
+        Wg, Wu = ((torch.randn((d_int, d), generator=g) * 0.1).to(torch.bfloat16).to(gpu_device) for _ in range(2))
+        Wd = (torch.randn((d, d_int), generator=g) * 0.1).to(torch.bfloat16).to(gpu_device)
+        out = torch.empty((T, d), dtype=torch.bfloat16, device=gpu_device)
+        dass.mlp_forward(X, Wg, Wu, Wd, "silu", out)
+        torch.cuda.synchronize()
+        ref, ab = oracle.mlp_forward(to_np32(X[-90:]), to_np32(Wg), to_np32(Wu), to_np32(Wd), "silu", want_abs=True)
+        _check(to_np32(out[-90:]), ref, ab, f"T={T} d={d} d_int={d_int}")
+
+
 def test_forward_token_chunks_are_independent(gpu_device):
     """Rows of the output depend on their own token only: two halves equal the whole, bit for bit."""
     T, d, d_int = 700, 128, 256
