@@ -12,9 +12,15 @@
 //
 // K slabs of 64 dense columns go from global memory straight into a ring of three LDS stages
 // (buffer_load ... lds): 256 rows x 64 B of values and 256 tokens x 128 B of y = 48 KB a stage;
-// the codes come two slabs at a time (256 rows x 16 B, two 4 KB blocks behind the ring), so that
-// a lane fetches 16 bytes of them, not 4.  Rows are XOR-swizzled in 16-byte chunks so that the fragment reads spread
-// over the banks.  One barrier per slab; the loads of slab s + 2 are issued right after it.
+// the codes come eight slabs at a time (64 bytes of a row; four in the largest tile, whose ring leaves 16 KB),
+// a quarter of them with every second slab.  The tiles that do not fill the chip are bound by the number of
+// row pieces they request: with codes of two slabs (16 bytes of a row) these were 128 of 512 requests a slab of the
+// 256 x 128 tile, now 32 of 416, and a slab takes 0.66 us instead of 0.76 (0.47 without any loads, 0.66
+// before with nothing but the loads).  2048 tokens of 4096 x 11008 132 -> 118 us, 1024 of it 88 -> 79, 1024 of 8192 x
+// 28672 384 -> 328, 300 of 2048 x 5632 39 -> 34; 128 of 1024 x 4096 23 -> 24, and the largest tile within 1 %.
+// (A ring of four or six stages, more bytes in flight, gave nothing: 0 to 4 us slower.)  Rows are XOR-swizzled in
+// 16-byte chunks so that the fragment reads spread over the banks.  One barrier per slab; the loads of slab s + 3
+// are issued right after it.
 #include "dass_internal.h"
 #include "tile_order.h"
 
@@ -39,14 +45,16 @@ struct Tile {
     static constexpr int kABytes = kFM * (kBK / 2) * 2;           // 16 KB of values
     static constexpr int kBBytes = kTN * kBK * 2;                 // 32 KB of y
     static constexpr int kStage = kABytes + kBBytes;              // 48 KB
-    // codes of two slabs (128 dense K): 16 B a row, 4 KB.  A wave-load is 64 rows, so 128 features
-    // are two: wavefronts 2 and 3 then load the same rows into a copy that nobody reads, so that every
-    // wavefront waits for the same number of loads.
-    static constexpr int kMBlock = 4 * 1024;
+    // codes of kMSlabs slabs, 8 B a row each: a block of 256 rows, fetched one wave-load (1 KB) a wavefront with
+    // every even slab.  Of 128 features the other half of the loads lie past the buffer's end: nothing is
+    // fetched, and every wavefront waits for the same number of loads.
+    static constexpr int kMSlabs = FB * NB >= 16 ? 4 : 8;
+    static constexpr int kMRow = 8 * kMSlabs, kMChunks = kMRow / 16;   // bytes and 16-byte chunks of a row of codes
+    static constexpr int kMBlock = 256 * kMRow;
     static constexpr int kMBase = kStages * kStage;               // two such blocks behind the ring
-    static constexpr int kLds = kMBase + 2 * kMBlock;             // 152 KB
-    // wave-loads a wavefront issues for slab s: FB of values, 2 NB of y, and with every even slab the
-    // codes of that slab and the next
+    static constexpr int kLds = kMBase + 2 * kMBlock;             // 160, 128 and 104 KB
+    // wave-loads a wavefront issues for slab s: FB of values, 2 NB of y, and with every even slab a part of the
+    // codes of a later block
     static constexpr int kLoadsOdd = FB + 2 * NB, kLoadsEven = kLoadsOdd + 1;
 };
 
@@ -84,7 +92,7 @@ __global__ __launch_bounds__(256) void down_sparse24_kernel(
 {
     using P = Tile<FB, NB>;
     constexpr int kFM = P::kFM, kTN = P::kTN, kABytes = P::kABytes, kStage = P::kStage, kMBlock = P::kMBlock,
-                  kMBase = P::kMBase, kLoadsOdd = P::kLoadsOdd, kLoadsEven = P::kLoadsEven;
+                  kMBase = P::kMBase, kMSlabs = P::kMSlabs, kMRow = P::kMRow, kLoadsOdd = P::kLoadsOdd, kLoadsEven = P::kLoadsEven;
     extern __shared__ __attribute__((aligned(1024))) char lds[];   // P::kLds bytes
 
     uint32_t tile_t, tile_f;   // tile_order.h
@@ -108,21 +116,35 @@ __global__ __launch_bounds__(256) void down_sparse24_kernel(
     const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint16_t *>(Y + t0 * ldy), 0, (int)((rows_t - 1) * ldy * 2 + d_int * 2), kRawBuffer);
     // values: a wave-load is 16 rows x 64 B; lane l fills slot l % 4 of row l / 4 with chunk slot ^ (row / 4 & 3)
-    uint32_t a_off[FB], m_off, b_off[2 * NB];
+    uint32_t a_off[FB], m_off, m_row_bytes, b_off[2 * NB];
 #pragma unroll
     for (int q = 0; q < FB; ++q) {
         const int r = (wave * FB + q) * 16 + (lane >> 2);
         a_off[q] = (uint32_t)((int64_t)r * ldv * 2 + (((lane & 3) ^ ((r >> 2) & 3)) * 16));
     }
-    // codes: a wave-load is 64 rows x 16 B (two slabs), one row a lane
-    m_off = (uint32_t)((int64_t)((wave * 64 + lane) % kFM) * ldm);
+    // codes: a wave-load is 1024 / kMRow rows; lane l fills slot l % kMChunks of row l / kMChunks with a chunk of
+    // that row that changes every 256 bytes of rows.  Part i of a block is the rows from i x 4 wave-loads on.
+    constexpr int kMRows = 1024 / kMRow;
+    auto m_swizzle = [](int r) { return (r / (256 / P::kMRow)) & (P::kMChunks - 1); };
+    {
+        const int r = wave * kMRows + lane / P::kMChunks;
+        m_off = (uint32_t)((int64_t)r * ldm + ((lane % P::kMChunks) ^ m_swizzle(r)) * 16);
+        m_row_bytes = (uint32_t)(4 * kMRows * ldm);
+    }
+    static_assert((4 * kMRows / (256 / P::kMRow)) % P::kMChunks == 0, "every part of a block has the same swizzle");
     // y: a wave-load is 8 rows x 128 B; lane l fills slot l % 8 of row l / 8 with chunk slot ^ (row / 2 & 7)
 #pragma unroll
     for (int q = 0; q < 2 * NB; ++q) {
         const int r = (wave * 2 * NB + q) * 8 + (lane >> 3);
         b_off[q] = (uint32_t)((int64_t)r * ldy * 2 + (((lane & 7) ^ ((r >> 1) & 7)) * 16));
     }
-    // q-th wave-load of slab s: FB of values, 2 NB of y, the last (even slabs only) the codes of slabs s, s + 1
+    // Part i of block b of the codes.  Rows past the last feature lie past the buffer's end.
+    auto load_codes = [&](int b, int i) {
+        load_to_lds(rm, lds + kMBase + (b & 1) * kMBlock + (i * 4 + wave) * 1024, m_off + (uint32_t)i * m_row_bytes, b * kMRow);
+    };
+    // q-th wave-load of slab s: FB of values, 2 NB of y, the last (even slabs only) a part of the codes.  The block
+    // after the one of slab s' = s - 2: its place is free when slab s' - 1, the last that reads the codes there, has
+    // read them, and its last part lands with the first slab that needs it.
     auto load_one = [&](int s, int q) {
         char *st = lds + (s % kStages) * kStage;
         if (q < FB)
@@ -130,13 +152,13 @@ __global__ __launch_bounds__(256) void down_sparse24_kernel(
         else if (q < kLoadsOdd)
             load_to_lds(ry, st + kABytes + (wave * 2 * NB + q - FB) * 1024, b_off[q - FB], s * kBK * 2);
         else
-            load_to_lds(rm, lds + kMBase + ((s >> 1) & 1) * kMBlock + wave * 1024, m_off, (s >> 1) * 16);
+            load_codes((s - 2) / kMSlabs + 1, (s - 2) % kMSlabs / 2);
     };
     auto issue_slab = [&](int s) {   // prologue only
 #pragma unroll
         for (int q = 0; q < kLoadsOdd; ++q)
             load_one(s, q);
-        if ((s & 1) == 0)
+        if (s == 2)
             load_one(s, kLoadsOdd);
     };
 
@@ -168,8 +190,9 @@ __global__ __launch_bounds__(256) void down_sparse24_kernel(
         }
     };
     u32x2 codes[FB], codes_next[FB];   // the 16 nibbles of a slab of each of this lane's FB rows
-    auto read_codes = [&](u32x2 *c, int s, int i) {   // slab s: half s % 2 of the row's 16 bytes in block s / 2
-        c[i] = *reinterpret_cast<const u32x2 *>(lds + kMBase + ((s >> 1) & 1) * kMBlock + a_row[i] * 16 + (s & 1) * 8);
+    auto read_codes = [&](u32x2 *c, int s, int i) {   // slab s: half s % 2 of a 16-byte chunk of the row
+        c[i] = *reinterpret_cast<const u32x2 *>(lds + kMBase + ((s / kMSlabs) & 1) * kMBlock + a_row[i] * kMRow +
+                                              ((s % kMSlabs / 2) ^ m_swizzle(a_row[i])) * 16 + (s & 1) * 8);
     };
 
     f32x16 acc[FB][NB];
@@ -193,6 +216,9 @@ __global__ __launch_bounds__(256) void down_sparse24_kernel(
     // s from LDS any more, so its stage takes slab s + 3 - and under the MFMAs of K step 1 go those
     // loads and the fragment reads of K step 0 of slab s + 1.
     const int S = (int)(d_int / kBK);   // the host guarantees d_int % 64 == 0
+#pragma unroll
+    for (int i = 0; i < kMSlabs / 2; ++i)
+        load_codes(0, i);
     issue_slab(0);
     if (S > 1)
         issue_slab(1);

@@ -67,6 +67,22 @@ def test_sparse_down_small_shapes(gpu_device, T, d, d_int, pad):
         assert torch.all(out._base[:, d:] == 7.0)
 
 
+@pytest.mark.parametrize("T,d", [(90, 136), (8200, 520), (33100, 512)])
+@pytest.mark.parametrize("slabs", [1, 2, 3, 4, 5, 7, 8, 9, 11, 12, 16, 17])
+def test_sparse_down_code_blocks(gpu_device, T, d, slabs):
+    """K around the ends of the blocks that the position codes come in (4 and 8 slabs of 64), all three tiles."""
+    d_int = 64 * slabs
+    W = _sparse_weights(d, d_int, slabs)
+    ov, om, _ = oracle.compress_24(W.float().numpy(), "cols")
+    values, meta = torch.from_numpy(ov).to(torch.bfloat16).to(gpu_device), torch.from_numpy(om).to(gpu_device)
+    Y = torch.randn((T, d_int), generator=torch.Generator(device="cpu").manual_seed(d_int)).to(torch.bfloat16).to(gpu_device)
+    out = torch.empty((T, d), dtype=torch.bfloat16, device=gpu_device)
+    dass.down_proj_sparse24(Y, values, meta, out)
+    torch.cuda.synchronize()
+    ref, ab = oracle.down_sparse24(to_np32(Y[-80:]), ov, om, want_abs=True)
+    _check(to_np32(out[-80:]), ref, ab, f"T={T} d={d} d_int={d_int}")
+
+
 def test_sparse_down_equals_dense_route(gpu_device):
     """Prune, compress and multiply on the GPU, and compare with the dense down projection of
     dass_mlp_forward's second launch on the same pruned matrix: the same sums in another order."""
