@@ -21,58 +21,22 @@
 // two-term score, a threshold outside the window, more scores in the bin than the list holds)
 // leaves all 8 rows untouched and marks the block in `todo`; the caller's next launch, gated
 // per block, redoes those rows.
-#include "select.h"
-#include "unstructured_tiled.h"
+#include "unstructured_rows.h"
 
 #include <type_traits>
 
 namespace dass {
 namespace rowl {
 
-constexpr int kRows = kRowlinesBlock;   // rows per workgroup
-constexpr int kThreads = 1024;
-constexpr int kBins = 256;
-// Counters of a row: [0 .. 255] the bins ascending, then 64 counters for scores above the window and 64
-// for scores below it, one per lane: a fifth of a row's scores lies on either side, and 64 lanes
-// adding to one LDS word take turns.
-constexpr int kAbove = kBins, kBelow = kBins + 64;
-constexpr int kStride = kBins + 128;
-constexpr int kSamples = 128;
-constexpr int kCap = 256;               // listed scores per row
 constexpr int kU = 4;                   // vectors a thread has in flight while counting
 constexpr int kUD = 2;                  // and in the apply pass (two workgroups share a compute unit only
                                         // if a thread takes at most 64 registers; four vectors there take 72)
-constexpr uint32_t kInfBits = 0x7f800000u;
 
-struct Window {
-    uint32_t lo, sh;
-};
 // The columns are taken in `count` chunks of `vecs` 16-byte vectors (the last one `last_vecs`); the
 // magic numbers are ceil(2^32 / vecs) and ceil(2^32 / last_vecs) for the division by multiply-high.
 struct Chunks {
     uint32_t count, vecs, last_vecs, magic, last_magic;
 };
-struct Select {
-    uint32_t lo, width, need, inside;
-};
-
-__device__ __forceinline__ uint32_t mono(float q)   // unsigned integer that grows with q
-{
-    const uint32_t b = __float_as_uint(q);
-    return b ^ ((uint32_t)((int32_t)b >> 31) | 0x80000000u);
-}
-
-// The 128 sampled positions of a row are 16 runs of 8 consecutive columns (a sample spread one by one
-// would touch 128 of the row's 172 memory lines: most of the matrix, just to sample it): run k
-// lies in the k-th sixteenth of the row, at an offset that changes from run to run.  Returns the
-// run's first column, a multiple of 8.
-constexpr int kRuns = kSamples / 8;
-__device__ __forceinline__ uint32_t sample_run(uint32_t k, uint32_t cols)
-{
-    const uint32_t octets = cols / 8, stratum = octets / kRuns;   // cols >= 1024: stratum >= 8
-    const uint32_t o = (uint32_t)(((uint64_t)k * octets) / kRuns) + ((k * 2654435761u) >> 8) % stratum;
-    return (o < octets ? o : octets - 1) * 8;
-}
 
 // Layout of the dynamic LDS, in bytes from its start.
 struct Smem {
@@ -501,6 +465,16 @@ RowlinesPlan plan_rowlines(int64_t rows, int64_t cols, int64_t ld, int dt, const
     p.blocks = (rows + kRows - 1) / kRows;
     if (p.blocks > 0x7fffffffLL)
         return p;
+    // Held in registers or read twice, us, back to back with the copy of the dense weights.  Up to 1024 rows (256
+    // workgroups of 4 rows; of 8 they leave half of the compute units idle) held: bf16 1024 x 5400 25 read twice, 22
+    // held, 1024 x 11008 36 31, 1024 x 28672 85 63, 768 x 14336 50 38, 256 x 16384 48 33, 64 x 32768 85 57, f32 1024 x
+    // 4096 24 19.5.  Beyond, the phases of fewer wavefronts are longer than the second read, which comes out of the
+    // memory-side cache: 1280 x 28672 87 107, 1536 x 11008 37 41, 4096 x 11008 62 74.  Except with a mask on short lines
+    // of many rows, where rowlines_kernel's workgroups do not share a compute unit: 4096 x 2048 28 24, 8192 x 2048
+    // 49 36, 16384 x 2048 88 58, 8192 x 3000 58 49, but 2048 x 2048 20 22 and 8192 x 7000 99 117.
+    const int64_t vpl = cols / vec_elems(dt);
+    const bool held = rows <= 1024 || (mask_out && rows >= 4096 && vpl <= 512);
+    p.held_slots = !held || vpl > 4096 ? 0 : vpl <= 1024 ? 1 : vpl <= 2048 ? 2 : 4;
     p.todo_bytes = round_up((size_t)p.blocks * sizeof(uint32_t), 256);
     p.fits = true;
     return p;
@@ -511,6 +485,8 @@ dass_status launch_rowlines(const char *fn, const RowlinesPlan &p, void *W, int6
                             const uint8_t *out_of_range, hipStream_t stream)
 {
     using namespace rowl;
+    if (p.held_slots)
+        return launch_held_rows(p, W, rows, cols, ld, dt, norms, fmode, n_keep, mask_out, todo, out_of_range, stream);
     const bool bf16 = dt == DASS_BF16;
     auto pick = [&](auto early_tag) {
         constexpr bool E = decltype(early_tag)::value;

@@ -44,6 +44,7 @@ struct RowlinesPlan {
     int64_t chunk_cols;  // ... of so many columns (a multiple of 8; the last chunk may be shorter)
     size_t smem;         // dynamic LDS of the kernel
     size_t todo_bytes;   // one word per block in the caller's workspace
+    int held_slots;      // > 0: the weights stay in registers, so many column slots of four rows a thread
 };
 
 // Row lines of W [rows, cols] with the factor varying along the line (fmode: factor = norm or its square root).
@@ -55,6 +56,11 @@ RowlinesPlan plan_rowlines(int64_t rows, int64_t cols, int64_t ld, int dt, const
 dass_status launch_rowlines(const char *fn, const RowlinesPlan &p, void *W, int64_t rows, int64_t cols, int64_t ld, int dt,
                             const float *norms, int fmode, uint32_t n_keep, uint8_t *mask_out, uint32_t *todo,
                             const uint8_t *out_of_range, hipStream_t stream);
+
+// Its part for p.held_slots > 0 (unstructured_held.hip); todo has a byte for every two rows there.
+dass_status launch_held_rows(const RowlinesPlan &p, void *W, int64_t rows, int64_t cols, int64_t ld, int dt, const float *norms,
+                             int fmode, uint32_t n_keep, uint8_t *mask_out, uint32_t *todo, const uint8_t *out_of_range,
+                             hipStream_t stream);
 
 // ---- lines of at most 2048 weights (unstructured_short.hip): one launch, a wavefront per line ----
 // Whether the lines are at most `longest` (<= 2048) weights long and the launch is possible.

@@ -431,6 +431,33 @@ def test_unstructured_row_lines_streamed(gpu_device, dtype, rows, cols, pad):
             assert not todo.any(), f"alpha={alpha}: ordinary rows must be decided by the streaming kernel ({todo.sum()} blocks left)"
 
 
+@pytest.mark.parametrize("dtype,rows,cols,masked", [
+    (torch.bfloat16, 1024, 2056, False), (torch.bfloat16, 1025, 2056, False),       # held in registers; read twice
+    (torch.bfloat16, 257, 8192, False), (torch.bfloat16, 258, 8200, True),          # one and two column slots a thread
+    (torch.bfloat16, 131, 16384, True), (torch.bfloat16, 133, 16392, False),        # two and four
+    (torch.bfloat16, 67, 32768, True), (torch.bfloat16, 70, 32776, True),           # four; read twice
+    (torch.float32, 518, 4096, True), (torch.float32, 513, 4104, False), (torch.float32, 258, 8200, True),
+    (torch.float32, 129, 16384, False), (torch.bfloat16, 4096, 1032, True), (torch.bfloat16, 4102, 4096, True),
+    (torch.bfloat16, 4097, 4104, True), (torch.float32, 4099, 1032, True)])
+def test_unstructured_row_lines_held(gpu_device, dtype, rows, cols, masked):
+    """Both sides of the limits of the kernel that holds its rows in registers, ragged last blocks of 4 and of 8
+    rows, and rows of equal scores that it leaves to the launch behind it."""
+    g = torch.Generator(device="cpu").manual_seed(rows + cols)
+    W = (torch.randn((rows, cols), generator=g) * 0.02).to(dtype)
+    W[3] = 0.5
+    W[-1] = -0.25
+    W, nrm = W.to(gpu_device), synth.make_norms(cols, "cpu", 5)
+    nrm[8:] = nrm[:-8].clone()
+    nrm = nrm.to(gpu_device)
+    want, want_mask = oracle.mask_unstructured(to_np32(W), nrm.cpu().numpy(), "cols", "cols", 0.5, cols * 2 // 5, want_mask=True)
+    mask = torch.full((rows, cols // 8), 0x55, dtype=torch.uint8, device=gpu_device) if masked else None
+    dass.score_mask_unstructured(W, nrm, "cols", "cols", 0.5, cols * 2 // 5, mask_out=mask)
+    torch.cuda.synchronize()
+    assert bits_equal(W, want), first_mismatch(W, want)
+    if masked:
+        assert np.array_equal(mask.cpu().numpy(), want_mask)
+
+
 def test_unstructured_row_lines_streamed_undecided_cases(gpu_device):
     """Blocks of rows that the streaming kernel cannot decide are left to the other kernels, block by
     block, and the result is the oracle's all the same: rows of thousands of equal scores beside
