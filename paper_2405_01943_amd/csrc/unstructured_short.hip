@@ -8,7 +8,8 @@
 // search ends at the first bit at which the count is the wanted one (about 20 of 31 bits).  Ties at the
 // threshold go on with the error terms and then the indexes in the same way.
 // Three matrices a call each, copies of the dense weights and the host's calls included, against the
-// workgroup-wide kernel: f32 256 x 688 with mask 63 -> 43 us; bf16 8192 x 1000 261 -> 125.  A bit's cost grows
+// workgroup-wide kernel: f32 256 x 688 with mask 63 -> 34 us; bf16 8192 x 1000 261 -> 125 (before the loads of
+// short_cols_kernel went out at once).  A bit's cost grows
 // with the line: at 4096 the other kernels are ahead (256 x 4096 112 -> 144, 4096 x 4096 161 -> 425).  Which
 // lines come here is decided in unstructured.hip.
 //
@@ -205,26 +206,44 @@ __global__ __launch_bounds__(512) void short_cols_kernel(void *__restrict__ Wv, 
     char *W = static_cast<char *>(Wv) + octet * 8 * EB;
     const int tid = threadIdx.x, lane = tid & 63, col = tid >> 6;
 
-    for (int v = tid; v < len * VR; v += 512) {
-        const int r = v / VR, c = (v % VR) * EPV;
-        const u32x4 x = *reinterpret_cast<const u32x4 *>(W + (int64_t)r * ld * EB + c * EB);
-#pragma unroll
-        for (int e = 0; e < EPV; ++e)
-            tile[(c + e) * stride + r] = DT == DASS_BF16 ? (elem_t)(x[e / 2] >> (16 * (e % 2))) : (elem_t)x[e % 4];
-    }
-    __syncthreads();
-    elem_t *mine = tile + col * stride;
-    const float f_col = along ? 0.0f : factor_of(norms[octet * 8 + col], fmode);
     auto valid = [&](int k) { return lane + 64 * k < len; };
     // positions beyond the line read its last one: a load behind a branch would be waited for on its own
     auto place = [&](int k) { return valid(k) ? lane + 64 * k : len - 1; };
+    // Norms and weights are all requested before anything is waited for: a matrix this small costs trips to memory, not
+    // bytes.  Against a loop of loads and the norms behind the barrier, a call with mask: f32 688 x 256 21 -> 13 us, 1500 x
+    // 512 24 -> 20.5, bf16 1000 x 8192 44 -> 37, 512 x 2048 17.6 -> 16.
+    float f[E];
+#pragma unroll
+    for (int k = 0; k < E; ++k)
+        f[k] = norms[along ? place(k) : octet * 8 + col];
+    constexpr int NV = (64 * E * VR + 511) / 512;   // vectors of a thread
+    u32x4 in[NV];
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+        const int v = tid + 512 * q < len * VR ? tid + 512 * q : len * VR - 1;
+        in[q] = *reinterpret_cast<const u32x4 *>(W + (int64_t)(v / VR) * ld * EB + (v % VR) * 16);
+    }
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+        const int v = tid + 512 * q, r = v / VR, c = (v % VR) * EPV;
+        if (v < len * VR) {
+#pragma unroll
+            for (int e = 0; e < EPV; ++e)
+                tile[(c + e) * stride + r] = DT == DASS_BF16 ? (elem_t)(in[q][e / 2] >> (16 * (e % 2))) : (elem_t)in[q][e % 4];
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < E; ++k)
+        f[k] = factor_of(f[k], fmode);
+    __syncthreads();
+    elem_t *mine = tile + col * stride;
     const uint32_t kept = keep_bits<E>(
         n_keep,
         [&](int k) {
             const uint32_t w = mine[place(k)];
             return fabsf(__uint_as_float(DT == DASS_BF16 ? w << 16 : w));
         },
-        [&](int k) { return along ? factor_of(norms[place(k)], fmode) : f_col; },
+        [&](int k) { return f[k]; },
         [&](int k) { return (uint32_t)(lane + 64 * k); }, valid);
 #pragma unroll
     for (int k = 0; k < E; ++k) {
@@ -290,6 +309,8 @@ static dass_status launch_dt(const char *fn, bool col_lines, int64_t per_lane, c
 {
     if (per_lane <= 8)
         return launch_e<DT, 8>(fn, col_lines, a);
+    if (DT == DASS_F32 && per_lane <= 12)
+        return launch_e<DT, DT == DASS_F32 ? 12 : 16>(fn, col_lines, a);
     if (per_lane <= 16)
         return launch_e<DT, 16>(fn, col_lines, a);
     if (per_lane <= 24)
