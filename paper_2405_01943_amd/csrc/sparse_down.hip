@@ -12,15 +12,16 @@
 //
 // K slabs of 64 dense columns go from global memory straight into a ring of three LDS stages
 // (buffer_load ... lds): 256 rows x 64 B of values and 256 tokens x 128 B of y = 48 KB a stage;
-// the codes come eight slabs at a time (64 bytes of a row; four in the largest tile, whose ring leaves 16 KB),
-// a quarter of them with every second slab.  The tiles that do not fill the chip are bound by the number of
-// row pieces they request: with codes of two slabs (16 bytes of a row) these were 128 of 512 requests a slab of the
-// 256 x 128 tile, now 32 of 416, and a slab takes 0.66 us instead of 0.76 (0.47 without any loads, 0.66
-// before with nothing but the loads).  2048 tokens of 4096 x 11008 132 -> 118 us, 1024 of it 88 -> 79, 1024 of 8192 x
-// 28672 384 -> 328, 300 of 2048 x 5632 39 -> 34; 128 of 1024 x 4096 23 -> 24, and the largest tile within 1 %.
-// (A ring of four or six stages, more bytes in flight, gave nothing: 0 to 4 us slower.)  Rows are XOR-swizzled in
-// 16-byte chunks so that the fragment reads spread over the banks.  One barrier per slab; the loads of slab s + 3
-// are issued right after it.
+// the codes come eight slabs at a time (64 bytes of a row; four where the ring leaves 16 KB), a part of them with
+// every second slab.  The tiles that do not fill the chip are bound by the number of row pieces they request: with
+// codes of two slabs (16 bytes of a row) these were 128 of 512 requests a slab of the 256 x 128 tile, and the loads
+// alone took 0.66 of the slab's 0.76 us (the rest alone: 0.47).  That tile takes the values two slabs at a time as
+// well, 128 bytes of a row: 320 requests, 0.64 us.  2048 tokens of 4096 x 11008 132 -> 118 us by the codes, 114 by
+// the values; 1024 of 8192 x 28672 384 -> 328, 310.  The 128 x 128 tile
+// by the codes alone (by the values within 2 % either way): 1024 of 4096 x 11008 88 -> 77, 300 of 2048 x 5632 39 -> 34.
+// The largest tile is within 1 % of before.  (A ring of four or six stages, more bytes in flight, gave nothing: 0 to 4
+// us slower.)  Rows are XOR-swizzled in 16-byte chunks so that the fragment reads spread over the banks.  One barrier
+// per slab; the loads of slab s + 3 are issued right after it.
 #include "dass_internal.h"
 #include "tile_order.h"
 
@@ -45,14 +46,17 @@ struct Tile {
     static constexpr int kABytes = kFM * (kBK / 2) * 2;           // 16 KB of values
     static constexpr int kBBytes = kTN * kBK * 2;                 // 32 KB of y
     static constexpr int kStage = kABytes + kBBytes;              // 48 KB
+    // The middle tile takes the values two slabs at a time, whole 128-byte lines of a row: three units of those,
+    // behind three of y.
+    static constexpr bool kWide = FB * NB == 8;
     // codes of kMSlabs slabs, 8 B a row each: a block of 256 rows, fetched one wave-load (1 KB) a wavefront with
     // every even slab.  Of 128 features the other half of the loads lie past the buffer's end: nothing is
     // fetched, and every wavefront waits for the same number of loads.
-    static constexpr int kMSlabs = FB * NB >= 16 ? 4 : 8;
+    static constexpr int kMSlabs = FB * NB >= 8 ? 4 : 8;
     static constexpr int kMRow = 8 * kMSlabs, kMChunks = kMRow / 16;   // bytes and 16-byte chunks of a row of codes
     static constexpr int kMBlock = 256 * kMRow;
-    static constexpr int kMBase = kStages * kStage;               // two such blocks behind the ring
-    static constexpr int kLds = kMBase + 2 * kMBlock;             // 160, 128 and 104 KB
+    static constexpr int kMBase = kWide ? 3 * kBBytes + 6 * kABytes : kStages * kStage;   // two such blocks behind the ring
+    static constexpr int kLds = kMBase + 2 * kMBlock;             // 160, 160 and 128 KB
     // wave-loads a wavefront issues for slab s: FB of values, 2 NB of y, and with every even slab a part of the
     // codes of a later block
     static constexpr int kLoadsOdd = FB + 2 * NB, kLoadsEven = kLoadsOdd + 1;
@@ -63,6 +67,13 @@ __device__ __forceinline__ void wait_vmcnt()
 {
     static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
     __builtin_amdgcn_s_waitcnt(0x0f70 | (N & 15) | ((N >> 4) << 14));
+}
+// The same, and no LDS access.
+template <int N>
+__device__ __forceinline__ void wait_loads()
+{
+    static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
+    __builtin_amdgcn_s_waitcnt(0x0070 | (N & 15) | ((N >> 4) << 14));
 }
 // One wave-load of 16 bytes a lane from a buffer straight into LDS.  (Not a template: with arguments that
 // depend on one, the compiler's host pass rejects the builtin and drops the kernel's stub without a word.)
@@ -115,12 +126,19 @@ __global__ __launch_bounds__(256) void down_sparse24_kernel(
         const_cast<uint8_t *>(meta + f0 * ldm), 0, (int)((rows_f - 1) * ldm + d_int / 8), kRawBuffer);
     const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint16_t *>(Y + t0 * ldy), 0, (int)((rows_t - 1) * ldy * 2 + d_int * 2), kRawBuffer);
-    // values: a wave-load is 16 rows x 64 B; lane l fills slot l % 4 of row l / 4 with chunk slot ^ (row / 4 & 3)
-    uint32_t a_off[FB], m_off, m_row_bytes, b_off[2 * NB];
+    // values: a wave-load is 16 rows x 64 B; lane l fills slot l % 4 of row l / 4 with chunk slot ^ (row / 4 & 3).
+    // Two slabs at a time: 8 rows x 128 B, as y below.
+    constexpr bool kWide = P::kWide;
+    uint32_t a_off[kWide ? 2 * FB : FB], m_off, m_row_bytes, b_off[2 * NB];
 #pragma unroll
-    for (int q = 0; q < FB; ++q) {
-        const int r = (wave * FB + q) * 16 + (lane >> 2);
-        a_off[q] = (uint32_t)((int64_t)r * ldv * 2 + (((lane & 3) ^ ((r >> 2) & 3)) * 16));
+    for (int q = 0; q < (kWide ? 2 * FB : FB); ++q) {
+        if constexpr (kWide) {
+            const int r = (wave * 2 * FB + q) * 8 + (lane >> 3);
+            a_off[q] = (uint32_t)((int64_t)r * ldv * 2 + (((lane & 7) ^ ((r >> 1) & 7)) * 16));
+        } else {
+            const int r = (wave * FB + q) * 16 + (lane >> 2);
+            a_off[q] = (uint32_t)((int64_t)r * ldv * 2 + (((lane & 3) ^ ((r >> 2) & 3)) * 16));
+        }
     }
     // codes: a wave-load is 1024 / kMRow rows; lane l fills slot l % kMChunks of row l / kMChunks with a chunk of
     // that row that changes every 256 bytes of rows.  Part i of a block is the rows from i x 4 wave-loads on.
@@ -190,9 +208,13 @@ __global__ __launch_bounds__(256) void down_sparse24_kernel(
         }
     };
     u32x2 codes[FB], codes_next[FB];   // the 16 nibbles of a slab of each of this lane's FB rows
+    int code_row[FB];   // a row of codes and its first chunk; the chunk's other places differ in bits that are 0 in the row's
+#pragma unroll
+    for (int i = 0; i < FB; ++i)
+        code_row[i] = a_row[i] * kMRow + m_swizzle(a_row[i]) * 16;
     auto read_codes = [&](u32x2 *c, int s, int i) {   // slab s: half s % 2 of a 16-byte chunk of the row
-        c[i] = *reinterpret_cast<const u32x2 *>(lds + kMBase + ((s / kMSlabs) & 1) * kMBlock + a_row[i] * kMRow +
-                                              ((s % kMSlabs / 2) ^ m_swizzle(a_row[i])) * 16 + (s & 1) * 8);
+        c[i] = *reinterpret_cast<const u32x2 *>(lds + (kMBase + ((s / kMSlabs) & 1) * kMBlock + (s & 1) * 8) +
+                                              (code_row[i] ^ (s % kMSlabs / 2 * 16)));
     };
 
     f32x16 acc[FB][NB];
@@ -210,12 +232,128 @@ __global__ __launch_bounds__(256) void down_sparse24_kernel(
     };
 
     constexpr int kMfmas = FB * NB;
+    const int S = (int)(d_int / kBK);   // the host guarantees d_int % 64 == 0
 
+    if constexpr (kWide) {
+        // ---- main loop of the middle tile.  Step s, the time from the barrier of slab s to that of the next one,
+        // requests a part of the codes (odd s), the y of slab s + 3 and half of the rows of a unit of values: of
+        // unit (s + 5) / 2 with s odd, whose place is free since slab s is read, the other half in the step after.
+        // What lies past the last slab is requested from an empty buffer (nothing is fetched).
+        constexpr int kUnit = 2 * kABytes, kUnits = 3 * P::kBBytes;   // values of two slabs; where the units begin
+        auto buffer = [&](const void *rows, int64_t bytes, bool any) {
+            return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(rows), 0, any ? (int)bytes : 0, kRawBuffer);
+        };
+        auto load_y = [&](int s, int q) {
+            load_to_lds(buffer(Y + t0 * ldy, (rows_t - 1) * ldy * 2 + d_int * 2, s < S),
+                        lds + s % 3 * P::kBBytes + (wave * 2 * NB + q) * 1024, b_off[q], s * kBK * 2);
+        };
+        auto load_values = [&](int unit, int q) {   // q-th of 2 FB
+            load_to_lds(buffer(values + f0 * ldv, (rows_f - 1) * ldv * 2 + d_int, 2 * unit < S),
+                        lds + kUnits + unit % 3 * kUnit + (wave * 2 * FB + q) * 1024, a_off[q], unit * 128);
+        };
+        auto step_load = [&](int s, bool odd, int q) {   // q-th of a step's loads: the codes first
+            if (odd) {
+                if (q == 0) {
+                    load_codes((s + 1) / kMSlabs + 1, (s + 1) % kMSlabs / 2);
+                    return;
+                }
+                --q;
+            }
+            if (q < 2 * NB)
+                load_y(s + 3, q);
+            else
+                load_values(odd ? (s + 5) / 2 : (s + 4) / 2, q - 2 * NB + (odd ? 0 : FB));
+        };
+        auto read_wide = [&](Frags &f, int s, int kk, int q) {
+            const char *ys = lds + s % 3 * P::kBBytes, *vs = lds + kUnits + s / 2 % 3 * kUnit;
+            if (q < FB) {
+                const int r = a_row[q];
+                f.a[q] = *reinterpret_cast<const bf16x8 *>(vs + r * 128 + (((4 * (s & 1) + 2 * kk + fc) ^ ((r >> 1) & 7)) * 16));
+            } else {
+                const int j = (q - FB) >> 1, r = b_row[j], c = 4 * kk + fc + ((q - FB) & 1 ? 2 : 0);
+                const bf16x8 v = *reinterpret_cast<const bf16x8 *>(ys + r * 128 + ((c ^ ((r >> 1) & 7)) * 16));
+                if (((q - FB) & 1) == 0)
+                    f.lo[j] = v;
+                else
+                    f.hi[j] = v;
+            }
+        };
+        // Steps -5 to -1, as far as there is something in them.
+#pragma unroll
+        for (int i = 0; i < kMSlabs / 2; ++i)
+            load_codes(0, i);
+#pragma unroll
+        for (int q = 0; q < 2 * FB; ++q)
+            load_values(0, q);
+#pragma unroll
+        for (int s = -3; s < 0; ++s) {
+            if (s == -1)
+                load_codes(1, 0);
+#pragma unroll
+            for (int q = 0; q < 2 * NB; ++q)
+                load_y(s + 3, q);
+#pragma unroll
+            for (int q = 0; q < FB; ++q)
+                load_values(s == -1 ? 2 : 1, q + (s == -2 ? FB : 0));
+        }
+        wait_loads<FB + 2 * (2 * NB + FB) + 1>();   // the codes, unit 0 and the y of slab 0
+        block_barrier();
+        Frags fa, fb;
+#pragma unroll
+        for (int q = 0; q < kReads; ++q)
+            read_wide(fa, 0, 0, q);
+#pragma unroll
+        for (int i = 0; i < FB; ++i)
+            read_codes(codes, 0, i);
+        auto body = [&](int s, auto odd_tag) {
+            constexpr bool ODD = decltype(odd_tag)::value;
+            constexpr int kLoads = 2 * NB + FB + (ODD ? 1 : 0);
+#pragma unroll
+            for (int q = 0; q < kMfmas; ++q) {   // K step 0
+#pragma unroll
+                for (int x = q; x < kReads; x += kMfmas)
+                    read_wide(fb, s, 1, x);
+                mfma(fa, codes, 0, q);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            // The y of slab s + 1, requested in step s - 2 behind the codes, has landed, and the values, which are
+            // requested earlier; the values of step s - 2 and what step s - 1 requested may be in flight.
+            wait_loads<FB + 2 * NB + FB>();
+            block_barrier();
+#pragma unroll
+            for (int q = 0; q < kMfmas; ++q) {   // K step 1; past the last slab the reads are of no use
+#pragma unroll
+                for (int x = q * kLoads / kMfmas; x < (q + 1) * kLoads / kMfmas; ++x) {   // in this order
+                    step_load(s, ODD, x);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+#pragma unroll
+                for (int x = q; x < kReads + FB; x += kMfmas) {
+                    if (x < kReads)
+                        read_wide(fa, s + 1, 0, x);
+                    else
+                        read_codes(codes_next, s + 1, x - kReads);
+                }
+                mfma(fb, codes, 1, q);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int i = 0; i < FB; ++i)
+                codes[i] = codes_next[i];
+        };
+        int s = 0;
+        for (; s + 1 < S; s += 2) {
+            body(s, std::false_type{});
+            body(s + 1, std::true_type{});
+        }
+        if (s < S)
+            body(s, std::false_type{});
+        wait_loads<0>();   // the empty parts would be written over the finished tile
+    } else {
     // ---- main loop.  A slab is two K steps of FB NB sparse MFMAs (16).  Under the MFMAs of K step 0 go
     // the fragment reads of K step 1; then one barrier - slab s + 1 has landed, nobody reads slab
     // s from LDS any more, so its stage takes slab s + 3 - and under the MFMAs of K step 1 go those
     // loads and the fragment reads of K step 0 of slab s + 1.
-    const int S = (int)(d_int / kBK);   // the host guarantees d_int % 64 == 0
 #pragma unroll
     for (int i = 0; i < kMSlabs / 2; ++i)
         load_codes(0, i);
@@ -310,6 +448,8 @@ __global__ __launch_bounds__(256) void down_sparse24_kernel(
     if (s + 1 < S)
         slab_body(s++, Yes{}, No{}, No{}, Any{});     // slab S - 2
     slab_body(s, No{}, No{}, No{}, Any{});            // slab S - 1
+
+    }
 
     // ---- epilogue: the tile goes to LDS as bf16 [token][feature] (row stride 528 B) and leaves it
     // in whole 16-byte chunks of output rows.  A lane holds, per block, 4 x 4 consecutive features
