@@ -137,7 +137,8 @@ inline TileShape cheapest_tile(int64_t T, int64_t n, const int (&tokens)[3], con
 // calib_pipe64_kernel for T tokens and n output columns (of each of two matrices for the gated forms, so
 // their tiles are half as wide in columns).  256 x 256 against the tile chosen here, whole calls:
 // dass_mlp_forward 128 tokens of 1024 x 4096 98 -> 49 us, 1024 of 4096 x 11008 (64 tiles in the down
-// projection) 397 -> 293, 2048 of it (128 tiles) 451 -> 439; dass_calib_norms 300 of 4096 x 1024 73 -> 36.
+// projection) 397 -> 293, 2048 of it (128 tiles) 451 -> 439; dass_calib_norms 300 of 4096 x 1024 73 -> 36.  (Since then the
+// smaller tiles have rings of their own, calib.hip: the second figures are now 40, 268, 424 and 31.)
 inline TileShape dense_tile_shape(int64_t T, int64_t n, bool gated)
 {
     return gated ? cheapest_tile(T, n, {256, 128, 128}, {128, 128, 64}, 1, 2)
@@ -146,7 +147,8 @@ inline TileShape dense_tile_shape(int64_t T, int64_t n, bool gated)
 
 // down_sparse24_kernel: 64 bytes a feature, 128 a token.  256 x 256 against the tile chosen here: 2048 tokens of
 // 4096 x 11008 (128 tiles) 176 -> 128 us; with the compression 1024 tokens 219 -> 103, 128 tokens of 1024 x 4096
-// 65 -> 33 us; 4096 tokens (256 tiles) and more stay with 256 x 256.
+// 65 -> 33 us; 4096 tokens (256 tiles) and more stay with 256 x 256.  (With fewer requests a slab, sparse_down.hip, the
+// first is now 114.)
 inline TileShape sparse_tile_shape(int64_t T, int64_t d)
 {
     return cheapest_tile(T, d, {256, 128, 128}, {256, 256, 128}, 2, 1);

@@ -1236,7 +1236,8 @@ namespace dass {
 //   row lines                  128 x 32768 lines bf16 335 38, 1024 x 8192 99 27, 2048 x 4096 58 32, f32 52 34
 //     bf16, one factor         1536 x 4096 64 57, 2048 x 2048 38 40, 2048 x 4096 67 73: equal scores (bf16
 //                              magnitudes tie all the time) cost a second and a third search
-//   column lines               bf16 512 x 2048 24 12, 1000 x 8192 71 40, 1536 x 4096 47 47, 2048 x 4096 53 72;
+//   column lines (the wavefronts' figures are from before their loads went out at once, which takes 1 to 8 us off)
+//                              bf16 512 x 2048 24 12, 1000 x 8192 71 40, 1536 x 4096 47 47, 2048 x 4096 53 72;
 //                              f32 1536 x 4096 55 38, 2048 x 4096 67 72
 //     f32, one factor a line   2048 x 1024 29 25, 2048 x 8192 123 88
 //     bf16, one factor         512 x 2048 23 22, 688 x 2048 24 31, 1000 x 4096 46 46, 1000 x 8192 85 81, 1032 x
