@@ -13,12 +13,16 @@
 // K slabs of 64 dense columns go from global memory straight into a ring of three LDS stages
 // (buffer_load ... lds): 256 rows x 64 B of values and 256 tokens x 128 B of y = 48 KB a stage;
 // the codes come eight slabs at a time (64 bytes of a row; four where the ring leaves 16 KB), a part of them with
-// every second slab.  The tiles that do not fill the chip are bound by the number of row pieces they request: with
-// codes of two slabs (16 bytes of a row) these were 128 of 512 requests a slab of the 256 x 128 tile, and the loads
-// alone took 0.66 of the slab's 0.76 us (the rest alone: 0.47).  That tile takes the values two slabs at a time as
-// well, 128 bytes of a row: 320 requests, 0.64 us.  2048 tokens of 4096 x 11008 132 -> 118 us by the codes, 114 by
-// the values; 1024 of 8192 x 28672 384 -> 328, 310.  The 128 x 128 tile
-// by the codes alone (by the values within 2 % either way): 1024 of 4096 x 11008 88 -> 77, 300 of 2048 x 5632 39 -> 34.
+// every second or fourth slab.  The tiles that do not fill the chip are bound by the number of row pieces they request:
+// with codes of two slabs (16 bytes of a row) these were 128 of 512 requests a slab of the 256 x 128 tile, and the
+// loads alone took 0.66 of the slab's 0.76 us (the rest alone: 0.47).  That tile takes the values two slabs at a time
+// as well, 128 bytes of a row: 320 requests, 0.64 us.  Back to back, 2048 tokens of 4096 x 11008 132 -> 118 us by the
+// codes, 114 by the values; 1024 of 8192 x 28672 384 -> 328, 310.  The 128 x 128 tile by the codes alone (by the values
+// within 2 % either way): 1024 of 4096 x 11008 87 -> 75, 300 of 2048 x 5632 39 -> 34.  A grid of few such tiles, each
+// compute unit with one wavefront per SIMD, is bound by the number of instructions a slab, so its loop is unrolled by the
+// four slabs between two parts of the codes: what a part is and where a chunk lies then costs next to nothing (with a
+// part every second slab, half of them rows past the last feature, and places computed for each slab, 128 tokens of 1024
+// x 4096 took 24.0 us, now 22.8; codes of two slabs 22.7).
 // The largest tile is within 1 % of before.  (A ring of four or six stages, more bytes in flight, gave nothing: 0 to 4
 // us slower.)  Rows are XOR-swizzled in 16-byte chunks so that the fragment reads spread over the banks.  One barrier
 // per slab; the loads of slab s + 3 are issued right after it.
@@ -49,17 +53,17 @@ struct Tile {
     // The middle tile takes the values two slabs at a time, whole 128-byte lines of a row: three units of those,
     // behind three of y.
     static constexpr bool kWide = FB * NB == 8;
-    // codes of kMSlabs slabs, 8 B a row each: a block of 256 rows, fetched one wave-load (1 KB) a wavefront with
-    // every even slab.  Of 128 features the other half of the loads lie past the buffer's end: nothing is
-    // fetched, and every wavefront waits for the same number of loads.
+    // codes of kMSlabs slabs, 8 B a row each: a block of kMParts parts, one wave-load (1 KB) a wavefront each, fetched
+    // a part every kMEvery slabs.
     static constexpr int kMSlabs = FB * NB >= 8 ? 4 : 8;
     static constexpr int kMRow = 8 * kMSlabs, kMChunks = kMRow / 16;   // bytes and 16-byte chunks of a row of codes
-    static constexpr int kMBlock = 256 * kMRow;
+    static constexpr int kMBlock = kFM * kMRow, kMParts = kMBlock / 4096, kMEvery = kMSlabs / kMParts;
     static constexpr int kMBase = kWide ? 3 * kBBytes + 6 * kABytes : kStages * kStage;   // two such blocks behind the ring
-    static constexpr int kLds = kMBase + 2 * kMBlock;             // 160, 160 and 128 KB
-    // wave-loads a wavefront issues for slab s: FB of values, 2 NB of y, and with every even slab a part of the
+    static constexpr int kLds = kMBase + 2 * kMBlock;
+    static_assert(kLds == (FB * NB >= 8 ? 160 : 88) * 1024, "160 KB is what a compute unit has");
+    // wave-loads a wavefront issues for slab s: FB of values, 2 NB of y, and with slabs 2, 2 + kMEvery, .. a part of the
     // codes of a later block
-    static constexpr int kLoadsOdd = FB + 2 * NB, kLoadsEven = kLoadsOdd + 1;
+    static constexpr int kLoads = FB + 2 * NB;
 };
 
 template <int N>
@@ -103,7 +107,8 @@ __global__ __launch_bounds__(256) void down_sparse24_kernel(
 {
     using P = Tile<FB, NB>;
     constexpr int kFM = P::kFM, kTN = P::kTN, kABytes = P::kABytes, kStage = P::kStage, kMBlock = P::kMBlock,
-                  kMBase = P::kMBase, kMSlabs = P::kMSlabs, kMRow = P::kMRow, kLoadsOdd = P::kLoadsOdd, kLoadsEven = P::kLoadsEven;
+                  kMBase = P::kMBase, kMSlabs = P::kMSlabs, kMRow = P::kMRow, kMParts = P::kMParts, kMEvery = P::kMEvery,
+                  kLoads = P::kLoads;
     extern __shared__ __attribute__((aligned(1024))) char lds[];   // P::kLds bytes
 
     uint32_t tile_t, tile_f;   // tile_order.h
@@ -160,24 +165,24 @@ __global__ __launch_bounds__(256) void down_sparse24_kernel(
     auto load_codes = [&](int b, int i) {
         load_to_lds(rm, lds + kMBase + (b & 1) * kMBlock + (i * 4 + wave) * 1024, m_off + (uint32_t)i * m_row_bytes, b * kMRow);
     };
-    // q-th wave-load of slab s: FB of values, 2 NB of y, the last (even slabs only) a part of the codes.  The block
-    // after the one of slab s' = s - 2: its place is free when slab s' - 1, the last that reads the codes there, has
-    // read them, and its last part lands with the first slab that needs it.
+    // q-th wave-load of slab s: FB of values, 2 NB of y, the last (slabs 2, 2 + kMEvery, ..) a part of the codes.  The
+    // block after the one of slab s' = s - 2: its place is free when slab s' - 1, the last that reads the codes there, has
+    // read them, and its last part lands with the first slab that needs it or before.
     auto load_one = [&](int s, int q) {
         char *st = lds + (s % kStages) * kStage;
         if (q < FB)
             load_to_lds(rv, st + (wave * FB + q) * 1024, a_off[q], s * kBK);
-        else if (q < kLoadsOdd)
+        else if (q < kLoads)
             load_to_lds(ry, st + kABytes + (wave * 2 * NB + q - FB) * 1024, b_off[q - FB], s * kBK * 2);
         else
-            load_codes((s - 2) / kMSlabs + 1, (s - 2) % kMSlabs / 2);
+            load_codes((s - 2) / kMSlabs + 1, (s - 2) % kMSlabs / kMEvery);
     };
     auto issue_slab = [&](int s) {   // prologue only
 #pragma unroll
-        for (int q = 0; q < kLoadsOdd; ++q)
+        for (int q = 0; q < kLoads; ++q)
             load_one(s, q);
         if (s == 2)
-            load_one(s, kLoadsOdd);
+            load_one(s, kLoads);
     };
 
     // ---- LDS -> registers
@@ -254,7 +259,7 @@ __global__ __launch_bounds__(256) void down_sparse24_kernel(
         auto step_load = [&](int s, bool odd, int q) {   // q-th of a step's loads: the codes first
             if (odd) {
                 if (q == 0) {
-                    load_codes((s + 1) / kMSlabs + 1, (s + 1) % kMSlabs / 2);
+                    load_codes((s + 1) / kMSlabs + 1, (s + 1) % kMSlabs / kMEvery);
                     return;
                 }
                 --q;
@@ -280,7 +285,7 @@ __global__ __launch_bounds__(256) void down_sparse24_kernel(
         };
         // Steps -5 to -1, as far as there is something in them.
 #pragma unroll
-        for (int i = 0; i < kMSlabs / 2; ++i)
+        for (int i = 0; i < kMParts; ++i)
             load_codes(0, i);
 #pragma unroll
         for (int q = 0; q < 2 * FB; ++q)
@@ -355,7 +360,7 @@ __global__ __launch_bounds__(256) void down_sparse24_kernel(
     // s from LDS any more, so its stage takes slab s + 3 - and under the MFMAs of K step 1 go those
     // loads and the fragment reads of K step 0 of slab s + 1.
 #pragma unroll
-    for (int i = 0; i < kMSlabs / 2; ++i)
+    for (int i = 0; i < kMParts; ++i)
         load_codes(0, i);
     issue_slab(0);
     if (S > 1)
@@ -363,9 +368,9 @@ __global__ __launch_bounds__(256) void down_sparse24_kernel(
     if (S > 2)
         issue_slab(2);
     if (S > 2)
-        wait_vmcnt<kLoadsOdd + kLoadsEven>();   // slabs 1 and 2 may be in flight
+        wait_vmcnt<2 * kLoads + 1>();   // slabs 1 and 2 may be in flight
     else if (S > 1)
-        wait_vmcnt<kLoadsOdd>();
+        wait_vmcnt<kLoads>();
     else
         wait_vmcnt<0>();
     block_barrier();
@@ -376,17 +381,29 @@ __global__ __launch_bounds__(256) void down_sparse24_kernel(
 #pragma unroll
     for (int i = 0; i < FB; ++i)
         read_codes(codes, 0, i);
+    // read_codes of slab s + 1; a chunk holds an even slab and the next, whose place is then known.
+    int code_at[FB];
+    auto next_codes = [&](int s, int i, auto phase_tag) {
+        constexpr int PHASE = decltype(phase_tag)::value;
+        if (PHASE % 2 == 1 || PHASE == kMEvery)
+            code_at[i] = ((s + 1) / kMSlabs & 1) * kMBlock + (code_row[i] ^ ((s + 1) % kMSlabs / 2 * 16));
+        codes_next[i] = *reinterpret_cast<const u32x2 *>(
+            lds + (kMBase + (PHASE == kMEvery ? ((s + 1) & 1) : 1 - PHASE % 2) * 8) + code_at[i]);
+    };
+#pragma unroll
+    for (int i = 0; i < FB; ++i)
+        code_at[i] = code_row[i];
     // MORE: a slab follows; LOAD: slab s + 3 exists; AHEAD: slab s + 2 exists (it may be in flight
     // at the barrier).  All three are compile-time: the steady state has no branch between MFMAs.
-    // PAR: the parity of s (0, 1), which says how many loads slabs s + 2 and s + 3 are, or 2 when it
-    // is only known at run time (the last slabs): then the barrier waits as if slab s + 2 were the
-    // shorter kind (one load more has to land, harmless) and the codes' load is a run-time test.
-    auto slab_body = [&](int s, auto more_tag, auto load_tag, auto ahead_tag, auto par_tag) {
+    // PHASE: s modulo kMEvery, which says whether slabs s + 2 and s + 3 bring a part of the codes, or kMEvery when
+    // it is only known at run time (the last slabs): then the barrier waits as if slab s + 2 brought none (one
+    // load more has to land, harmless).
+    auto slab_body = [&](int s, auto more_tag, auto load_tag, auto ahead_tag, auto phase_tag) {
         constexpr bool MORE = decltype(more_tag)::value, LOAD = decltype(load_tag)::value,
                        AHEAD = decltype(ahead_tag)::value;
-        constexpr int PAR = decltype(par_tag)::value;
-        constexpr int kAhead = PAR == 0 ? kLoadsEven : kLoadsOdd;                    // loads of slab s + 2
-        constexpr int kIssue = PAR == 1 ? kLoadsEven : kLoadsOdd;                    // loads of slab s + 3
+        constexpr int PHASE = decltype(phase_tag)::value;
+        constexpr int kAhead = kLoads + (PHASE == 0 ? 1 : 0);                        // loads of slab s + 2
+        constexpr int kIssue = kLoads + (PHASE == kMEvery - 1 ? 1 : 0);              // loads of slab s + 3
         static_assert(kAhead < 16, "the low four bits of the wait's counter hold it");
         const char *st = lds + (s % kStages) * kStage, *st_next = lds + ((s + 1) % kStages) * kStage;
 #pragma unroll
@@ -411,15 +428,13 @@ __global__ __launch_bounds__(256) void down_sparse24_kernel(
                 for (int x = q; x < kIssue; x += kMfmas)
                     load_one(s + 3, x);
             }
-            if (LOAD && PAR == 2 && q == kLoadsOdd % kMfmas && ((s + 3) & 1) == 0)   // uniform
-                load_one(s + 3, kLoadsOdd);
             if (MORE) {
 #pragma unroll
                 for (int x = q; x < kReads + FB; x += kMfmas) {
                     if (x < kReads)
                         read_one(fa, st_next, 0, x);
                     else
-                        read_codes(codes_next, s + 1, x - kReads);
+                        next_codes(s, x - kReads, phase_tag);
                 }
             }
             mfma(fb, codes, 1, q);
@@ -433,16 +448,26 @@ __global__ __launch_bounds__(256) void down_sparse24_kernel(
     };
     using Yes = std::true_type;
     using No = std::false_type;
-    using Even = std::integral_constant<int, 0>;
-    using Odd = std::integral_constant<int, 1>;
-    using Any = std::integral_constant<int, 2>;
+    using Any = std::integral_constant<int, kMEvery>;
+    auto at_phase = [&](int s, auto phase_tag) { slab_body(s, Yes{}, Yes{}, Yes{}, phase_tag); };
+    static_assert(kMEvery == 2 || kMEvery == 4 || kWide, "the loop below");
     int s = 0;
-    for (; s + 4 < S; s += 2) {   // s is even here
-        slab_body(s, Yes{}, Yes{}, Yes{}, Even{});
-        slab_body(s + 1, Yes{}, Yes{}, Yes{}, Odd{});
+    for (; s + kMEvery + 2 < S; s += kMEvery) {   // s is a multiple of kMEvery here
+        at_phase(s, std::integral_constant<int, 0>{});
+        at_phase(s + 1, std::integral_constant<int, 1>{});
+        if constexpr (kMEvery == 4) {
+            at_phase(s + 2, std::integral_constant<int, 2>{});
+            at_phase(s + 3, std::integral_constant<int, 3>{});
+        }
     }
-    if (s + 3 < S)
-        slab_body(s++, Yes{}, Yes{}, Yes{}, Any{});   // slab S - 4 when the loop left it
+    if (s + 3 < S)   // the slabs before S - 3 that the loop left
+        at_phase(s++, std::integral_constant<int, 0>{});
+    if constexpr (kMEvery == 4) {
+        if (s + 3 < S)
+            at_phase(s++, std::integral_constant<int, 1>{});
+        if (s + 3 < S)
+            at_phase(s++, std::integral_constant<int, 2>{});
+    }
     if (s + 2 < S)
         slab_body(s++, Yes{}, No{}, Yes{}, Any{});    // slab S - 3
     if (s + 1 < S)

@@ -68,19 +68,26 @@ def test_sparse_down_small_shapes(gpu_device, T, d, d_int, pad):
 
 
 @pytest.mark.parametrize("T,d", [(90, 136), (8200, 520), (33100, 512)])
-@pytest.mark.parametrize("slabs", [1, 2, 3, 4, 5, 7, 8, 9, 11, 12, 16, 17])
-def test_sparse_down_code_blocks(gpu_device, T, d, slabs):
-    """K around the ends of the blocks that the position codes come in (4 and 8 slabs of 64), all three tiles."""
+@pytest.mark.parametrize("slabs", [1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15, 16, 17])
+@pytest.mark.parametrize("pad", [0, 8])
+def test_sparse_down_code_blocks(gpu_device, T, d, slabs, pad):
+    """K around the ends of the blocks that the position codes come in (4 and 8 slabs of 64) and of the loops that are
+    unrolled by 2 and 4 slabs, all three tiles; rows longer than K too (the last unit of an odd number of slabs then
+    reaches into what lies between two rows)."""
     d_int = 64 * slabs
     W = _sparse_weights(d, d_int, slabs)
     ov, om, _ = oracle.compress_24(W.float().numpy(), "cols")
     values, meta = torch.from_numpy(ov).to(torch.bfloat16).to(gpu_device), torch.from_numpy(om).to(gpu_device)
     Y = torch.randn((T, d_int), generator=torch.Generator(device="cpu").manual_seed(d_int)).to(torch.bfloat16).to(gpu_device)
     out = torch.empty((T, d), dtype=torch.bfloat16, device=gpu_device)
+    if pad:
+        Y, values, out = padded(Y, pad), padded(values, pad), padded(out, pad)
+        meta = torch.nn.functional.pad(meta, (0, 4), value=0xEE)[:, :d_int // 8]
     dass.down_proj_sparse24(Y, values, meta, out)
     torch.cuda.synchronize()
     ref, ab = oracle.down_sparse24(to_np32(Y[-80:]), ov, om, want_abs=True)
-    _check(to_np32(out[-80:]), ref, ab, f"T={T} d={d} d_int={d_int}")
+    _check(to_np32(out[-80:]), ref, ab, f"T={T} d={d} d_int={d_int} pad={pad}")
+    assert not pad or torch.all(out._base[:, d:] == 7.0)
 
 
 def test_sparse_down_equals_dense_route(gpu_device):
