@@ -158,7 +158,12 @@ __device__ __forceinline__ void rank_list(const uint32_t *mine_list, uint32_t li
 
 constexpr int kHeldRows = 4;
 
-template <int DT, int J, bool MASK>
+// EARLY: the rows are left to the next launch as soon as their samples or a factor say that they will be, before any of
+// their weights is requested.  bf16, half of the weights 0, alpha 0.75, mean of eight matrices a size, us: weights
+// requested first, behind the decision, and rowlines_kernel: 768 x 8000 148 147 158, 256 x 16384 135 133 135, 512 x 28672
+// 345 339 328, 64 x 32768 201 196 197, 1024 x 4096 107 105 113.  (Whether a block's samples lie beyond the two deviations
+// is chance, and one block that stays costs all its phases: single matrices differ by 30 % either way.)
+template <int DT, int J, bool MASK, bool EARLY>
 __global__ __launch_bounds__(kThreads) void held_rows_kernel(void *__restrict__ Wv, uint32_t rows, uint32_t cols, int64_t ld,
                                                              const float *__restrict__ norms, int fmode, uint32_t n_keep,
                                                              uint8_t *__restrict__ mask, uint8_t *__restrict__ todo,
@@ -190,8 +195,8 @@ __global__ __launch_bounds__(kThreads) void held_rows_kernel(void *__restrict__ 
         return;
     }
 
-    // ---- requests, in the order in which they are wanted: samples, factors, weights.  A row or slot past the end
-    // takes the last one: a load behind a branch could not be counted, and nothing is done with it.
+    // ---- requests, in the order in which they are wanted: samples, factors, weights (EARLY: behind phase A).  A row or
+    // slot past the end takes the last one: a load behind a branch could not be counted, and nothing is done with it.
     constexpr int S = J == 1 ? (R + 1) / 2 : 1;   // rows a wavefront samples: there are two wavefronts or more, R with J > 1
     float smp_w[S][2], smp_n[2];
     const uint32_t smp_c = sample_run(lane / 4, cols) + 2 * (lane % 4);   // lane l: columns 2 (l % 4), + 1 of run l / 4
@@ -219,31 +224,35 @@ __global__ __launch_bounds__(kThreads) void held_rows_kernel(void *__restrict__ 
     uint32_t slot[J];
     float f[J][EPV];
     u32x4 x[J][R];
+    auto request = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = 0; j < J; ++j) {
-        const uint32_t cv = tid + j * nt;
-        slot[j] = cv < vpl ? cv : vpl - 1;
-    }
-#pragma unroll
-    for (int j = 0; j < J; ++j)
-#pragma unroll
-        for (int q = 0; q < EPV / 4; ++q) {
-            const u32x4 n4 = *reinterpret_cast<const u32x4 *>(norms + slot[j] * EPV + 4 * q);
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                f[j][4 * q + i] = __uint_as_float(n4[i]);
+        for (int j = 0; j < J; ++j) {
+            const uint32_t cv = tid + j * nt;
+            slot[j] = cv < vpl ? cv : vpl - 1;
         }
-    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int j = 0; j < J; ++j)
+        for (int j = 0; j < J; ++j)
 #pragma unroll
-        for (int r = 0; r < R; ++r)
-            x[j][r] = __builtin_nontemporal_load(
-                reinterpret_cast<const u32x4 *>(W + (r < (int)n_rows ? r : (int)n_rows - 1) * row_bytes + slot[j] * 16));
-    __builtin_amdgcn_sched_barrier(0);
+            for (int q = 0; q < EPV / 4; ++q) {
+                const u32x4 n4 = *reinterpret_cast<const u32x4 *>(norms + slot[j] * EPV + 4 * q);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    f[j][4 * q + i] = __uint_as_float(n4[i]);
+            }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < J; ++j)
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                x[j][r] = __builtin_nontemporal_load(
+                    reinterpret_cast<const u32x4 *>(W + (r < (int)n_rows ? r : (int)n_rows - 1) * row_bytes + slot[j] * 16));
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    if constexpr (!EARLY)
+        request();
 
-    bool leave = false;   // the rows are left to the next launch
-    if (out_of_range)
+    bool leave = false;   // EARLY: the rows are left to the next launch
+    if constexpr (EARLY)
         for (uint32_t i = tid; i * kFactorBlock < cols; i += nt)
             leave |= out_of_range[i] != 0;
 
@@ -266,7 +275,7 @@ __global__ __launch_bounds__(kThreads) void held_rows_kernel(void *__restrict__ 
 #pragma unroll
         for (int q = 0; q < 2; ++q)
             s[q] = __float_as_uint(fabsf(smp_w[k][q]) * (factor_of(smp_n[q], fmode) * kFactorScale));
-        if (out_of_range) {
+        if constexpr (EARLY) {
             const int n = __popcll(__ballot(s[0] == 0)) + __popcll(__ballot(s[1] == 0));
             if (lane == 0)
                 atomicAdd(&zeros, (uint32_t)n);
@@ -276,13 +285,14 @@ __global__ __launch_bounds__(kThreads) void held_rows_kernel(void *__restrict__ 
             win[r] = w;
     }
     lds_barrier();
-    if (out_of_range) {   // uniform
+    if constexpr (EARLY) {
         const float taken = (float)(n_rows * kSamples), pruned = (float)(cols - n_keep) / (float)cols;
         leave |= (float)zeros >= taken * pruned - 2.0f * sqrtf(taken * pruned * (1.0f - pruned));
         if (__syncthreads_or(leave)) {
             mark(true);
             return;
         }
+        request();
     }
 
     // ---- B: counts
@@ -438,17 +448,20 @@ dass_status launch_held_rows(const RowlinesPlan &p, void *W, int64_t rows, int64
 {
     using namespace rowl;
     const bool bf16 = dt == DASS_BF16;
-    auto held = [&](auto dt_tag, auto mask_tag) {
+    auto held = [&](auto dt_tag, auto mask_tag, auto early_tag) {
         constexpr int D = decltype(dt_tag)::value;
-        constexpr bool M = decltype(mask_tag)::value;
-        return p.held_slots == 4   ? held_rows_kernel<D, 4, M>
-               : p.held_slots == 2 ? held_rows_kernel<D, 2, M>
-                                   : held_rows_kernel<D, 1, M>;
+        constexpr bool M = decltype(mask_tag)::value, E = decltype(early_tag)::value;
+        return p.held_slots == 4   ? held_rows_kernel<D, 4, M, E>
+               : p.held_slots == 2 ? held_rows_kernel<D, 2, M, E>
+                                   : held_rows_kernel<D, 1, M, E>;
     };
-    using Bf16 = std::integral_constant<int, DASS_BF16>;
-    using F32 = std::integral_constant<int, DASS_F32>;
-    auto hk = bf16 ? (mask_out ? held(Bf16{}, std::true_type{}) : held(Bf16{}, std::false_type{}))
-                   : (mask_out ? held(F32{}, std::true_type{}) : held(F32{}, std::false_type{}));
+    auto pick = [&](auto early_tag) {
+        using Bf16 = std::integral_constant<int, DASS_BF16>;
+        using F32 = std::integral_constant<int, DASS_F32>;
+        return bf16 ? (mask_out ? held(Bf16{}, std::true_type{}, early_tag) : held(Bf16{}, std::false_type{}, early_tag))
+                    : (mask_out ? held(F32{}, std::true_type{}, early_tag) : held(F32{}, std::false_type{}, early_tag));
+    };
+    auto hk = out_of_range ? pick(std::true_type{}) : pick(std::false_type{});
     const int64_t slots = cols / vec_elems(dt), threads = ((slots + p.held_slots - 1) / p.held_slots + 63) / 64 * 64;
     hipLaunchKernelGGL(hk, dim3((unsigned)(p.blocks * (kRows / kHeldRows))), dim3((unsigned)threads), 0, stream, W,
                        (uint32_t)rows, (uint32_t)cols, ld, norms, fmode, n_keep, mask_out,

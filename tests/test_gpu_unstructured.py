@@ -393,6 +393,21 @@ def _rowline_todo(workspace, n_norms, rows):
     return workspace[off:off + 4 * ((rows + 7) // 8)].view(torch.int32).cpu().numpy()
 
 
+def _rowline_workspace(rows, cols, dtype, device):
+    """A workspace filled with a value that no row-line kernel leaves in the words of its blocks: after a call
+    _rowline_left tells a call that went past those kernels from one that they decided."""
+    return torch.full((dass.unstructured_workspace_bytes(rows, cols, dtype, "cols", "cols"),), 0x5A, dtype=torch.uint8,
+                      device=device)
+
+
+def _rowline_left(workspace, cols, rows):
+    """The rows that the row-line kernel left, as the bytes of its words: byte i is 1 for rows 2 i, 2 i + 1 in the
+    form that holds 4 rows in registers; the form that reads 8 rows twice sets byte 0 of a block's 4 only."""
+    left = _rowline_todo(workspace, cols, rows).view(np.uint8)
+    assert left.max() <= 1, "the call did not go through the row-line kernels"
+    return left
+
+
 @pytest.mark.parametrize("dtype,rows,cols,pad", [(torch.bfloat16, 1032, 2048, 0), (torch.bfloat16, 520, 4104, 8),
                                                  (torch.float32, 837, 2504, 4), (torch.bfloat16, 2052, 1024, 0),
                                                  (torch.bfloat16, 84, 28672, 0), (torch.float32, 132, 16392, 4),
@@ -574,7 +589,9 @@ def test_unstructured_other_exponents(gpu_device, dtype, rows, cols, axes):
 @pytest.mark.parametrize("dtype,rows,cols,group_axis", [
     (torch.bfloat16, 1040, 2056, "rows"), (torch.float32, 1032, 8200, "rows"),     # redone in the registers of a workgroup; by the multi-pass kernels
     (torch.bfloat16, 1032, 12296, "rows"),
-    (torch.bfloat16, 1030, 2056, "cols"), (torch.float32, 201, 11272, "cols")])    # row lines, one chunk of factors and two
+    (torch.bfloat16, 1028, 2056, "cols"), (torch.float32, 1028, 11272, "cols"),    # rows read twice, one chunk of factors and two
+    (torch.bfloat16, 1020, 2064, "cols"), (torch.bfloat16, 132, 16384, "cols"), (torch.bfloat16, 68, 32768, "cols"),
+    (torch.float32, 524, 4096, "cols"), (torch.float32, 260, 8192, "cols"), (torch.float32, 204, 11272, "cols")])  # rows held
 @pytest.mark.parametrize("undecided", ["zeros", "some zeros", "range", "neither"])
 def test_unstructured_other_exponents_undecided(gpu_device, dtype, rows, cols, group_axis, undecided):
     """What the streaming passes leave with other exponents: thresholds that tie at 0, in all lines or in
@@ -593,10 +610,16 @@ def test_unstructured_other_exponents_undecided(gpu_device, dtype, rows, cols, g
     W, n_prune = W0.to(dtype).to(gpu_device), length // 2
     want, want_mask = oracle.mask_unstructured(to_np32(W), nrm.numpy(), group_axis, group_axis, 0.75, n_prune, want_mask=True)
     mask = torch.full((rows, cols // 8), 0x55, dtype=torch.uint8, device=gpu_device)
-    dass.score_mask_unstructured(W, nrm.to(gpu_device), group_axis, group_axis, 0.75, n_prune, mask_out=mask)
+    ws = _rowline_workspace(rows, cols, dtype, gpu_device) if group_axis == "cols" else None
+    dass.score_mask_unstructured(W, nrm.to(gpu_device), group_axis, group_axis, 0.75, n_prune, mask_out=mask, workspace=ws)
     torch.cuda.synchronize()
     assert bits_equal(W, want), first_mismatch(W, want)
     assert np.array_equal(mask.cpu().numpy(), want_mask)
+    if group_axis == "cols":
+        left = np.add.reduceat(_rowline_left(ws, cols, rows), np.arange(0, (rows + 7) // 8 * 4, 4)) > 0
+        blocks = (rows + 7) // 8
+        lines = {"zeros": range(blocks), "some zeros": range(40 // 8, -(-60 // 8)), "range": range(blocks), "neither": ()}
+        assert np.flatnonzero(left).tolist() == list(lines[undecided])
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
