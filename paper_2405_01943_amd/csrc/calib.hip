@@ -526,21 +526,23 @@ __global__ __launch_bounds__(256) void calib_pipe64_kernel(
     // 1, after the slab's one barrier, carries those of K step 0 of the next slab.  The loads of the B part of
     // slab s + NB and the A part of slab s + NA, into the units of slab s, go out one a pair from that barrier on,
     // the last ones under K step 0 of slab s + 1 (all in the second half, 1 to 3 us more of every figure above).
-    // Parts past the last slab are requested from an empty buffer (nothing is fetched), so that every slab waits
-    // for the same number of loads.
+    // Parts past the last slab are requested from an empty buffer, so that every slab waits for the same number of
+    // loads.  A raw buffer's lane is out of range, and its load fetches nothing, if its offset is not below the
+    // buffer's length less the scalar offset: the empty ones have scalar offset 0, so that this is never negative.
     constexpr int N_LOADS = A_WL + 2 * B_WL;
     // q-th load of the B part of slab s + NB and the A part of slab s + NA, into the units ub and ua; the B part first
     auto issue = [&](int s, int ua, int ub, int q) {
         const bool is_b = q < 2 * B_WL, g = q < B_WL;
         const int slab = s + (is_b ? NB : NA);
-        const int span = slab < S ? is_b ? g ? span_w : span_u : span_x : 0;
+        const bool there = slab < S;
+        const int span = there ? is_b ? g ? span_w : span_u : span_x : 0, off = there ? slab * BK * 2 : 0;
         const uint16_t *rows = is_b ? g ? Wg + n0 * ldw : up_rows : X + t0 * ldx;
         const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(rows), 0, span, kRawBuffer);
         if (is_b)
             load_to_lds(r, lds64 + B_BASE + ub * B_UNIT + (g ? 0 : B_HALF) + (wave * B_WL + q % B_WL) * 1024, b_off[q % B_WL],
-                        slab * BK * 2);
+                        off);
         else
-            load_to_lds(r, lds64 + ua * A_UNIT + (wave * A_WL + q - 2 * B_WL) * 1024, a_off[q - 2 * B_WL], slab * BK * 2);
+            load_to_lds(r, lds64 + ua * A_UNIT + (wave * A_WL + q - 2 * B_WL) * 1024, a_off[q - 2 * B_WL], off);
     };
     // As if slabs -NB, -NB + 1, .. had been read: two of them here, the others under the MFMAs of slab 0.  A parts
     // that run further ahead than the B parts come first.

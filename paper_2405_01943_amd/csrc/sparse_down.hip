@@ -122,7 +122,9 @@ __global__ __launch_bounds__(256) void down_sparse24_kernel(
     const int fr = lane & 31, fc = lane >> 5;
 
     // ---- global -> LDS.  Rows past the end of a matrix lie beyond the end of its buffer
-    // descriptor and read as zeros.
+    // descriptor and read as zeros.  (A raw buffer's lane is out of range if its offset is not below the buffer's
+    // length less the scalar offset.  That is never negative here: the last block of codes asked for begins at 8 S + 40
+    // bytes of a row at most, the values end with their row, and there are 8 features or more, 64 S bytes of codes.)
     const int64_t rows_f = d - f0 < kFM ? d - f0 : kFM, rows_t = T - t0 < kTN ? T - t0 : kTN;
     constexpr int kRawBuffer = 0x00020000;
     const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(
@@ -243,18 +245,19 @@ __global__ __launch_bounds__(256) void down_sparse24_kernel(
         // ---- main loop of the middle tile.  Step s, the time from the barrier of slab s to that of the next one,
         // requests a part of the codes (odd s), the y of slab s + 3 and half of the rows of a unit of values: of
         // unit (s + 5) / 2 with s odd, whose place is free since slab s is read, the other half in the step after.
-        // What lies past the last slab is requested from an empty buffer (nothing is fetched).
+        // What lies past the last slab is requested from an empty buffer, at scalar offset 0 (see above): nothing is
+        // fetched.
         constexpr int kUnit = 2 * kABytes, kUnits = 3 * P::kBBytes;   // values of two slabs; where the units begin
         auto buffer = [&](const void *rows, int64_t bytes, bool any) {
             return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(rows), 0, any ? (int)bytes : 0, kRawBuffer);
         };
         auto load_y = [&](int s, int q) {
             load_to_lds(buffer(Y + t0 * ldy, (rows_t - 1) * ldy * 2 + d_int * 2, s < S),
-                        lds + s % 3 * P::kBBytes + (wave * 2 * NB + q) * 1024, b_off[q], s * kBK * 2);
+                        lds + s % 3 * P::kBBytes + (wave * 2 * NB + q) * 1024, b_off[q], s < S ? s * kBK * 2 : 0);
         };
         auto load_values = [&](int unit, int q) {   // q-th of 2 FB
             load_to_lds(buffer(values + f0 * ldv, (rows_f - 1) * ldv * 2 + d_int, 2 * unit < S),
-                        lds + kUnits + unit % 3 * kUnit + (wave * 2 * FB + q) * 1024, a_off[q], unit * 128);
+                        lds + kUnits + unit % 3 * kUnit + (wave * 2 * FB + q) * 1024, a_off[q], 2 * unit < S ? unit * 128 : 0);
         };
         auto step_load = [&](int s, bool odd, int q) {   // q-th of a step's loads: the codes first
             if (odd) {
