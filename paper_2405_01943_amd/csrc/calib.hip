@@ -545,17 +545,21 @@ __global__ __launch_bounds__(256) void calib_pipe64_kernel(
             load_to_lds(r, lds64 + ua * A_UNIT + (wave * A_WL + q - 2 * B_WL) * 1024, a_off[q - 2 * B_WL], off);
     };
     // As if slabs -NB, -NB + 1, .. had been read: two of them here, the others under the MFMAs of slab 0.  A parts
-    // that run further ahead than the B parts come first.
+    // that run further ahead than the B parts come first.  In this order: the waits count.
 #pragma unroll
     for (int p = -NA; p < -NB; ++p)
 #pragma unroll
-        for (int q = 2 * B_WL; q < N_LOADS; ++q)
+        for (int q = 2 * B_WL; q < N_LOADS; ++q) {
             issue(p, p + NA, 0, q);
+            __builtin_amdgcn_sched_barrier(0);
+        }
 #pragma unroll
     for (int p = -NB; p < 2 - NB; ++p)
 #pragma unroll
-        for (int q = 0; q < N_LOADS; ++q)
+        for (int q = 0; q < N_LOADS; ++q) {
             issue(p, p + NA, p + NB, q);
+            __builtin_amdgcn_sched_barrier(0);
+        }
     constexpr int A_MORE = NA > NB ? A_WL : 0;   // the A part requested with a B part is due a slab later
     wait_vmcnt<N_LOADS + A_MORE>();              // slab 0 has landed
     block_barrier();
@@ -570,8 +574,10 @@ __global__ __launch_bounds__(256) void calib_pipe64_kernel(
         constexpr int N_REST = FIRST ? (NB - 2) * N_LOADS : 0, N_FREE = N_PAIRS + N_HALF;
         auto rest = [&](int q) {   // the prologue's other loads, spread over the pairs before the barrier
 #pragma unroll
-            for (int x = q * N_REST / N_FREE; x < (q + 1) * N_REST / N_FREE; ++x)
+            for (int x = q * N_REST / N_FREE; x < (q + 1) * N_REST / N_FREE; ++x) {
+                __builtin_amdgcn_sched_barrier(0);
                 issue(2 - NB + x / N_LOADS, 2 - NB + x / N_LOADS + NA, 2 + x / N_LOADS, x % N_LOADS);
+            }
         };
         const int ua1 = ua + 1 == NA ? 0 : ua + 1, ub1 = ub + 1 == NB ? 0 : ub + 1;
 #pragma unroll
@@ -624,13 +630,14 @@ __global__ __launch_bounds__(256) void calib_pipe64_kernel(
     wait_vmcnt<0>();   // the rings are about to be used again, and the empty parts would be written over that
     block_barrier();
     } else {
-    // ---- prologue: A0 B0 A1 B1 A2 fill the five units
+    // ---- prologue: A0 B0 A1 B1 A2 fill the five units, in this order: the waits count
 #pragma unroll
     for (int q = 0; q < A_WL; ++q)
         issue_a(0, 0, q);
 #pragma unroll
     for (int q = 0; q < 2 * B_WL; ++q)
         issue_b(1, 0, q);
+    __builtin_amdgcn_sched_barrier(0);
     if (S > 1) {
 #pragma unroll
         for (int q = 0; q < A_WL; ++q)
@@ -639,6 +646,7 @@ __global__ __launch_bounds__(256) void calib_pipe64_kernel(
         for (int q = 0; q < 2 * B_WL; ++q)
             issue_b(3, BK * 2, q);
     }
+    __builtin_amdgcn_sched_barrier(0);
     if (S > 2) {
 #pragma unroll
         for (int q = 0; q < A_WL; ++q)

@@ -179,12 +179,14 @@ __global__ __launch_bounds__(256) void down_sparse24_kernel(
         else
             load_codes((s - 2) / kMSlabs + 1, (s - 2) % kMSlabs / kMEvery);
     };
-    auto issue_slab = [&](int s) {   // prologue only
+    auto issue_slab = [&](int s) {   // prologue only; slab by slab, the waits count
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int q = 0; q < kLoads; ++q)
             load_one(s, q);
         if (s == 2)
             load_one(s, kLoads);
+        __builtin_amdgcn_sched_barrier(0);
     };
 
     // ---- LDS -> registers
@@ -286,23 +288,27 @@ __global__ __launch_bounds__(256) void down_sparse24_kernel(
                     f.hi[j] = v;
             }
         };
-        // Steps -5 to -1, as far as there is something in them.
+        // Steps -5 to -1, as far as there is something in them; in this order, the waits count.
 #pragma unroll
         for (int i = 0; i < kMParts; ++i)
             load_codes(0, i);
 #pragma unroll
         for (int q = 0; q < 2 * FB; ++q)
             load_values(0, q);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int s = -3; s < 0; ++s) {
             if (s == -1)
                 load_codes(1, 0);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int q = 0; q < 2 * NB; ++q)
                 load_y(s + 3, q);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int q = 0; q < FB; ++q)
                 load_values(s == -1 ? 2 : 1, q + (s == -2 ? FB : 0));
+            __builtin_amdgcn_sched_barrier(0);
         }
         wait_loads<FB + 2 * (2 * NB + FB) + 1>();   // the codes, unit 0 and the y of slab 0
         block_barrier();
