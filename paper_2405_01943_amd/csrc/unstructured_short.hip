@@ -188,10 +188,13 @@ __global__ __launch_bounds__(64) void short_rows_kernel(void *__restrict__ Wv, i
 // Lines are columns: a workgroup of eight wavefronts takes 8 neighbouring columns through LDS, column by
 // column there, so that a wavefront reads its own without bank conflicts and the global accesses stay
 // 16 bytes a lane.  The 8 workgroups that share 64 columns run on one XCD, as in unstructured.hip.
-template <int DT, int E>
+// ALONG: a factor a position; else one a line, in one register.  Calls with one factor a line, from the norm behind the
+// barrier, a copy of it a position, one register, us: f32 2048 x 8192 97 101 89, 1000 x 8192 37 38 31, 1000 x 1024 16 17
+// 15; bf16 1000 x 8192 71 72 63.
+template <int DT, int E, bool ALONG>
 __global__ __launch_bounds__(512) void short_cols_kernel(void *__restrict__ Wv, int64_t rows, int64_t cols, int64_t ld,
-                                                         const float *__restrict__ norms, int fmode, int along,
-                                                         uint32_t n_keep, uint8_t *__restrict__ mask)
+                                                         const float *__restrict__ norms, int fmode, uint32_t n_keep,
+                                                         uint8_t *__restrict__ mask)
 {
     constexpr int EPV = DT == DASS_BF16 ? 8 : 4, EB = DT == DASS_BF16 ? 2 : 4, VR = 8 / EPV;
     using elem_t = std::conditional_t<DT == DASS_BF16, uint16_t, uint32_t>;
@@ -212,10 +215,10 @@ __global__ __launch_bounds__(512) void short_cols_kernel(void *__restrict__ Wv, 
     // Norms and weights are all requested before anything is waited for: a matrix this small costs trips to memory, not
     // bytes.  Against a loop of loads and the norms behind the barrier, a call with mask: f32 688 x 256 21 -> 13 us, 1500 x
     // 512 24 -> 20.5, bf16 1000 x 8192 44 -> 37, 512 x 2048 17.6 -> 16.
-    float f[E];
+    float f[ALONG ? E : 1];
 #pragma unroll
-    for (int k = 0; k < E; ++k)
-        f[k] = norms[along ? place(k) : octet * 8 + col];
+    for (int k = 0; k < (ALONG ? E : 1); ++k)
+        f[k] = norms[ALONG ? place(k) : octet * 8 + col];
     constexpr int NV = (64 * E * VR + 511) / 512;   // vectors of a thread
     u32x4 in[NV];
 #pragma unroll
@@ -233,7 +236,7 @@ __global__ __launch_bounds__(512) void short_cols_kernel(void *__restrict__ Wv, 
         }
     }
 #pragma unroll
-    for (int k = 0; k < E; ++k)
+    for (int k = 0; k < (ALONG ? E : 1); ++k)
         f[k] = factor_of(f[k], fmode);
     __syncthreads();
     elem_t *mine = tile + col * stride;
@@ -243,7 +246,7 @@ __global__ __launch_bounds__(512) void short_cols_kernel(void *__restrict__ Wv, 
             const uint32_t w = mine[place(k)];
             return fabsf(__uint_as_float(DT == DASS_BF16 ? w << 16 : w));
         },
-        [&](int k) { return f[k]; },
+        [&](int k) { return f[ALONG ? k : 0]; },
         [&](int k) { return (uint32_t)(lane + 64 * k); }, valid);
 #pragma unroll
     for (int k = 0; k < E; ++k) {
@@ -295,11 +298,12 @@ static dass_status launch_e(const char *fn, bool col_lines, const Args &a)
     auto lds_of = [](int64_t rows) { return 8 * kWords * 8 + 8 * (size_t)((rows + 15) / 16 * 16 + 8) * (DT == DASS_BF16 ? 2 : 4); };
     const size_t lds = lds_of(a.rows);
     // the same for every call: another thread may set it between this and the launch
-    if (hipFuncSetAttribute(reinterpret_cast<const void *>(short_cols_kernel<DT, E>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_of(64 * E)) != hipSuccess)
+    auto k = a.along ? short_cols_kernel<DT, E, true> : short_cols_kernel<DT, E, false>;
+    if (hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)lds_of(64 * E)) != hipSuccess)
         return fail(DASS_ERR_HIP, "%s: cannot reserve %zu bytes of LDS", fn, lds_of(64 * E));
-    hipLaunchKernelGGL((short_cols_kernel<DT, E>), dim3((unsigned)((a.cols / 8 + 63) / 64 * 64)), dim3(512), lds, a.stream,
-                       a.W, a.rows, a.cols, a.ld, a.norms, a.fmode, a.along, a.n_keep, a.mask);
+    hipLaunchKernelGGL(k, dim3((unsigned)((a.cols / 8 + 63) / 64 * 64)), dim3(512), lds, a.stream, a.W, a.rows, a.cols, a.ld,
+                       a.norms, a.fmode, a.n_keep, a.mask);
     return check_launch("short-line unstructured kernel");
 }
 
