@@ -1236,12 +1236,11 @@ namespace dass {
 //   row lines                  128 x 32768 lines bf16 335 38, 1024 x 8192 99 27, 2048 x 4096 58 32, f32 52 34
 //     bf16, one factor         1536 x 4096 64 57, 2048 x 2048 38 40, 2048 x 4096 67 73: equal scores (bf16
 //                              magnitudes tie all the time) cost a second and a third search
-//   column lines (the wavefronts' figures are from before their loads went out at once, which takes 1 to 8 us off)
-//                              bf16 512 x 2048 24 12, 1000 x 8192 71 40, 1536 x 4096 47 47, 2048 x 4096 53 72;
-//                              f32 1536 x 4096 55 38, 2048 x 4096 67 72
-//     f32, one factor a line   2048 x 1024 29 25, 2048 x 8192 123 88
-//     bf16, one factor         512 x 2048 23 22, 688 x 2048 24 31, 1000 x 4096 46 46, 1000 x 8192 85 81, 1032 x
-//                              8192 87 155
+//   column lines               bf16 512 x 2048 23 11, 1000 x 8192 73 34, 1536 x 1024 23 19, 1800 x 1024 25 23, 2048 x 1024
+//                              31 31; f32 1536 x 1024 25 20, 1800 x 1024 28 24, 2048 x 1024 31 31
+//     f32, one factor a line   2048 x 1024 29 23, 2048 x 8192 124 78
+//     bf16, one factor         512 x 2048 21 19, 688 x 2048 22 26, 1000 x 2048 24 27, 1000 x 4096 45 39, 1000 x 8192 81
+//                              62, 1032 x 4096 48 52, 1032 x 8192 84 88
 static int64_t short_line_limit(int dt, bool col_lines, bool along, bool one_factor, int64_t lines)
 {
     if (!col_lines)
@@ -1288,7 +1287,7 @@ static dass_status score_mask_unstructured_impl(const char *fn, void *W, int64_t
 
     // Short lines take the wavefront-per-line kernel, ahead of the streaming passes up to 1024 weights.  Of the
     // column lines that those take, 1024 long and more, it keeps up to 8192 of 1024 (us, wavefronts and
-    // passes: bf16 1024 x 4096 25 36, x 8192 40 40, x 32768 126 86; f32 28 35, 42 42, 155 114).
+    // passes: bf16 1024 x 4096 21 32, x 8192 34 38, x 16384 58 55, x 32768 104 86; f32 22 31, 35 42, 61 65, 122 114).
     const bool col_lines = group_axis == DASS_AXIS_ROWS, along = norm_axis == group_axis, one_factor = !along || alpha == 0.0;
     const int64_t short_limit = short_line_limit(dt, col_lines, along, one_factor, lines);
     const bool short_first = short_lines_fit(rows, cols, col_lines, short_limit < 1024 ? short_limit : 1024) &&

@@ -313,6 +313,9 @@ static dass_status launch_dt(const char *fn, bool col_lines, int64_t per_lane, c
 {
     if (per_lane <= 8)
         return launch_e<DT, 8>(fn, col_lines, a);
+    // Lines of 513 to 768 f32 weights, us with 16 positions a lane and with 12: down the rows 520 x 8192 32 26, 768 x 8192
+    // 34 28, 688 x 2048 15 13, along them 640 x 4096 lines 18 15, 768 x 8192 lines 28 23.  (bf16 column lines gain as
+    // much, 520 x 8192 31 26, and have no such instance; a bf16 row vector has 8 weights, 12 are no whole number.)
     if (DT == DASS_F32 && per_lane <= 12)
         return launch_e<DT, DT == DASS_F32 ? 12 : 16>(fn, col_lines, a);
     if (per_lane <= 16)
