@@ -135,20 +135,22 @@ inline TileShape cheapest_tile(int64_t T, int64_t n, const int (&tokens)[3], con
 }
 
 // calib_pipe64_kernel for T tokens and n output columns (of each of two matrices for the gated forms, so
-// their tiles are half as wide in columns).  256 x 256 against the tile chosen here, whole calls:
-// dass_mlp_forward 128 tokens of 1024 x 4096 98 -> 49 us, 1024 of 4096 x 11008 (64 tiles in the down
-// projection) 397 -> 293, 2048 of it (128 tiles) 451 -> 439; dass_calib_norms 300 of 4096 x 1024 73 -> 36.  (Since then the
-// smaller tiles have rings of their own, calib.hip: the second figures are now 40, 268, 424 and 31.)
+// their tiles are half as wide in columns).  256 x 256 against the tile chosen here, whole calls, back to back:
+// dass_mlp_forward 128 tokens of 1024 x 4096 98 -> 40 us, 1024 of 4096 x 11008 (64 tiles in the down
+// projection) 362 -> 271, 2048 of it (128 tiles) 465 -> 430; dass_calib_norms 300 of 4096 x 1024 73 -> 29, 1024 of 4096 x
+// 4096 75 -> 55.  256 x 256 chosen and, in brackets, half as many tokens: 512 of 4096 x 11008 81 (94), 1024 of 4096 x
+// 8192 95 (104), 2048 of 4096 x 8192 182 (203); but where its second round is nearly empty the smaller tile is ahead by
+// now: 1024 of 4096 x 11008 160 (144), 2048 of 4096 x 5632 159 (143), 3000 of 2048 x 5632 131 (127).
 inline TileShape dense_tile_shape(int64_t T, int64_t n, bool gated)
 {
     return gated ? cheapest_tile(T, n, {256, 128, 128}, {128, 128, 64}, 1, 2)
                  : cheapest_tile(T, n, {256, 128, 128}, {256, 256, 128}, 1, 1);
 }
 
-// down_sparse24_kernel: 64 bytes a feature, 128 a token.  256 x 256 against the tile chosen here: 2048 tokens of
-// 4096 x 11008 (128 tiles) 176 -> 128 us; with the compression 1024 tokens 219 -> 103, 128 tokens of 1024 x 4096
-// 65 -> 33 us; 4096 tokens (256 tiles) and more stay with 256 x 256.  (With fewer requests a slab, sparse_down.hip, the
-// first is now 114.)
+// down_sparse24_kernel: 64 bytes a feature, 128 a token.  256 x 256 against the tile chosen here, back to back: 2048
+// tokens of 4096 x 11008 (128 tiles) 162 -> 107 us, 1024 of it 155 -> 70, 4096 of 2048 x 5632 90 -> 58, 128 of 1024 x
+// 4096 58 -> 23.  256 x 256 chosen and, in brackets, half as many tokens: 4096 of 4096 x 11008 (256 tiles) 200 (212), 8192
+// of 2048 x 5632 109 (118), 3000 of 4096 x 11008 172 (190); but 6000 of it, whose second round is half empty, 353 (306).
 inline TileShape sparse_tile_shape(int64_t T, int64_t d)
 {
     return cheapest_tile(T, d, {256, 128, 128}, {256, 256, 128}, 2, 1);
