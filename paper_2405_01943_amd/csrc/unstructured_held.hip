@@ -1,12 +1,13 @@
-// Stage 2, unstructured, row lines: the phases of unstructured_rows.hip for matrices of few rows and lines of at most 4096 vectors, with the weights in registers
-// between counting and writing: the matrix is read once, and nothing waits for 44 KB of factors to be in LDS.  A
-// workgroup owns 4 rows; a thread owns the same J column slots of 16 bytes in each of them (slots tid, tid +
-// blockDim, ..; the host makes blockDim J just cover the line).  A slot's factors are then read once for 4 rows,
-// straight from the norms into registers, and a row's window and threshold are the same for the whole workgroup:
-// scalar registers.  What bounds it is the chain of the phases, with 2 to 11 wavefronts a workgroup: 1024 x 5400 bf16
-// 25 -> 22 us a call with the copy of the dense weights, 768 x 14336 50 -> 38, 333 x 16000 f32 58 -> 41.
-// (rowlines_kernel keeps its own text of the window, the bin and the ranking: made of the functions below, its compiled
-// form was 2 to 3 us slower on 4096 x 11008.)
+// Stage 2, unstructured, row lines: the phases of unstructured_rows.hip for matrices of few rows and lines of at most
+// 4096 vectors, with the weights in registers between counting and writing: the matrix is read once, and nothing
+// waits for 44 KB of factors to be in LDS.  A workgroup owns 4 rows; a thread owns the same J column slots of 16 bytes
+// in each of them (slots tid, tid + blockDim, ..; the host makes blockDim J just cover the line).  A slot's factors are
+// then read once for 4 rows, straight from the norms into registers, and a row's window and threshold are the same for
+// the whole workgroup: scalar registers.  What bounds it is the chain of the phases, with 2 to 16 wavefronts a workgroup:
+// 1024 x 5400 bf16 25 -> 22 us a call with the copy of the dense weights, 768 x 14336 50 -> 38, 333 x 16000 f32 58 -> 41.
+// (The window, the bin and the ranking stand here and in rowlines_kernel, whose compiled form was 2 to 3 us slower on
+// 4096 x 11008 when it called the functions below.  Both texts have to select the same bins: a change to one is made to
+// both, and a test runs the same rows through the two kernels.)
 #include "unstructured_rows.h"
 
 #include <type_traits>
@@ -58,45 +59,46 @@ __device__ __forceinline__ Window window_of(uint32_t s0, uint32_t s1, uint32_t n
     return Window{lo, (uint32_t)(width > 8 ? width - 8 : 0)};
 }
 
-// The bin of a row that holds the n_keep-th largest score: the lane whose `out` says so, or -1 if it is outside the window or
-// holds more than a list does.  Lane l owns bins 255 - 4 l .. 252 - 4 l, a prefix sum over the lanes counts from the top.
+// The bin of a row that holds the n_keep-th largest score: the lane whose `out` says so, or -1 if it is outside the
+// window or holds more than a list does.  Lane l owns bins 255 - 4 l .. 252 - 4 l, a prefix sum over the lanes counts
+// from the top.
 __device__ __forceinline__ int bin_of(const uint32_t *h_row, const Window w, uint32_t n_keep, Select &out)
 {
     const int lane = threadIdx.x & 63;
-            uint32_t h[4];
-    #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                h[j] = h_row[255 - 4 * lane - j];
-            uint32_t above = h_row[kAbove + lane];
-    #pragma unroll
-            for (int o = 32; o > 0; o >>= 1)
-                above += __shfl_xor(above, o, 64);
-            const uint32_t sum = h[0] + h[1] + h[2] + h[3];
-            uint32_t incl = sum;
-    #pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const uint32_t t = __shfl_up(incl, o, 64);
-                if (lane >= o)
-                    incl += t;
-            }
-            uint32_t excl = incl - sum;
-            bool found = false;
-            uint32_t bin = 0, need = 0, inside = 0;
-            if (n_keep > above) {
-                const uint32_t want = n_keep - above;
-                if (excl < want && want <= incl) {
-    #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        if (!found && want <= excl + h[j]) {
-                            found = true;
-                            bin = 255 - 4 * lane - j;
-                            need = want - excl;
-                            inside = h[j];
-                        }
-                        excl += h[j];
-                    }
+    uint32_t h[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        h[j] = h_row[255 - 4 * lane - j];
+    uint32_t above = h_row[kAbove + lane];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+        above += __shfl_xor(above, o, 64);
+    const uint32_t sum = h[0] + h[1] + h[2] + h[3];
+    uint32_t incl = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t t = __shfl_up(incl, o, 64);
+        if (lane >= o)
+            incl += t;
+    }
+    uint32_t excl = incl - sum;
+    bool found = false;
+    uint32_t bin = 0, need = 0, inside = 0;
+    if (n_keep > above) {
+        const uint32_t want = n_keep - above;
+        if (excl < want && want <= incl) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (!found && want <= excl + h[j]) {
+                    found = true;
+                    bin = 255 - 4 * lane - j;
+                    need = want - excl;
+                    inside = h[j];
                 }
+                excl += h[j];
             }
+        }
+    }
     const uint64_t who = __ballot(found);
     if (who == 0 || __shfl(inside, __ffsll((long long)who) - 1, 64) > (uint32_t)kCap)
         return -1;
@@ -107,53 +109,53 @@ __device__ __forceinline__ int bin_of(const uint32_t *h_row, const Window w, uin
 
 // Ranks a row's list with one wavefront; an entry with `need` or more entries above it is pruned after all.
 template <int DT, bool MASK>
-__device__ __forceinline__ void rank_list(const uint32_t *mine_list, uint32_t listed, uint32_t need, char *row, uint32_t row_index,
-                                          uint32_t cols, uint8_t *__restrict__ mask)
+__device__ __forceinline__ void rank_list(const uint32_t *mine_list, uint32_t listed, uint32_t need, char *row,
+                                          uint32_t row_index, uint32_t cols, uint8_t *__restrict__ mask)
 {
     const int lane = threadIdx.x & 63;
-            const uint32_t n = __builtin_amdgcn_readfirstlane(listed < (uint32_t)kCap ? listed : (uint32_t)kCap);
-            need = __builtin_amdgcn_readfirstlane(need);
-            uint32_t ma[kCap / 64], mb[kCap / 64], mc[kCap / 64];
-            uint64_t key[kCap / 64];
-    #pragma unroll
-            for (int j = 0; j < kCap / 64; ++j) {
-                const uint32_t k = lane + 64 * j;
-                ma[j] = k < n ? mine_list[k * 3] : 0u;
-                mb[j] = k < n ? mine_list[k * 3 + 1] : 0u;
-                mc[j] = k < n ? mine_list[k * 3 + 2] : 0u;
-                key[j] = (uint64_t)ma[j] << 32 | mb[j];
+    const uint32_t n = __builtin_amdgcn_readfirstlane(listed < (uint32_t)kCap ? listed : (uint32_t)kCap);
+    need = __builtin_amdgcn_readfirstlane(need);
+    uint32_t ma[kCap / 64], mb[kCap / 64], mc[kCap / 64];
+    uint64_t key[kCap / 64];
+#pragma unroll
+    for (int j = 0; j < kCap / 64; ++j) {
+        const uint32_t k = lane + 64 * j;
+        ma[j] = k < n ? mine_list[k * 3] : 0u;
+        mb[j] = k < n ? mine_list[k * 3 + 1] : 0u;
+        mc[j] = k < n ? mine_list[k * 3 + 2] : 0u;
+        key[j] = (uint64_t)ma[j] << 32 | mb[j];
+    }
+    uint32_t above[kCap / 64] = {0, 0, 0, 0};
+    const int slots = (int)((n + 63) / 64);
+#pragma unroll
+    for (int src = 0; src < kCap / 64; ++src) {
+        if (src >= slots)
+            break;
+        const int in_slot = (int)n - 64 * src < 64 ? (int)n - 64 * src : 64;
+        for (int k = 0; k < in_slot; ++k) {
+            const uint64_t o = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)ma[src], k) << 32 |
+                               (uint32_t)__builtin_amdgcn_readlane((int)mb[src], k);
+            const uint32_t oc = (uint32_t)__builtin_amdgcn_readlane((int)mc[src], k);
+#pragma unroll
+            for (int j = 0; j < kCap / 64; ++j)
+                if (j < slots)
+                    above[j] += (o > key[j]) | ((o == key[j]) & (oc > mc[j]));
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < kCap / 64; ++j) {
+        if (lane + 64 * j < n && above[j] >= need) {
+            const uint32_t c = 0xFFFFu - mc[j];
+            if constexpr (DT == DASS_BF16)
+                *reinterpret_cast<uint16_t *>(row + c * 2) = 0;
+            else
+                *reinterpret_cast<uint32_t *>(row + c * 4) = 0;
+            if constexpr (MASK) {
+                const size_t byte = (size_t)row_index * (cols / 8) + c / 8;
+                atomicAnd(reinterpret_cast<uint32_t *>(mask) + byte / 4, ~(1u << ((byte % 4) * 8 + c % 8)));
             }
-            uint32_t above[kCap / 64] = {0, 0, 0, 0};
-            const int slots = (int)((n + 63) / 64);
-    #pragma unroll
-            for (int src = 0; src < kCap / 64; ++src) {
-                if (src >= slots)
-                    break;
-                const int in_slot = (int)n - 64 * src < 64 ? (int)n - 64 * src : 64;
-                for (int k = 0; k < in_slot; ++k) {
-                    const uint64_t o = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)ma[src], k) << 32 |
-                                       (uint32_t)__builtin_amdgcn_readlane((int)mb[src], k);
-                    const uint32_t oc = (uint32_t)__builtin_amdgcn_readlane((int)mc[src], k);
-    #pragma unroll
-                    for (int j = 0; j < kCap / 64; ++j)
-                        if (j < slots)
-                            above[j] += (o > key[j]) | ((o == key[j]) & (oc > mc[j]));
-                }
-            }
-    #pragma unroll
-            for (int j = 0; j < kCap / 64; ++j) {
-                if (lane + 64 * j < n && above[j] >= need) {
-                    const uint32_t c = 0xFFFFu - mc[j];
-                    if constexpr (DT == DASS_BF16)
-                        *reinterpret_cast<uint16_t *>(row + c * 2) = 0;
-                    else
-                        *reinterpret_cast<uint32_t *>(row + c * 4) = 0;
-                    if constexpr (MASK) {
-                        const size_t byte = (size_t)row_index * (cols / 8) + c / 8;
-                        atomicAnd(reinterpret_cast<uint32_t *>(mask) + byte / 4, ~(1u << ((byte % 4) * 8 + c % 8)));
-                    }
-                }
-            }
+        }
+    }
 }
 
 constexpr int kHeldRows = 4;
@@ -197,7 +199,8 @@ __global__ __launch_bounds__(kThreads) void held_rows_kernel(void *__restrict__ 
 
     // ---- requests, in the order in which they are wanted: samples, factors, weights (EARLY: behind phase A).  A row or
     // slot past the end takes the last one: a load behind a branch could not be counted, and nothing is done with it.
-    constexpr int S = J == 1 ? (R + 1) / 2 : 1;   // rows a wavefront samples: there are two wavefronts or more, R with J > 1
+    // rows a wavefront samples: there are two wavefronts or more, R or more with J > 1
+    constexpr int S = J == 1 ? (R + 1) / 2 : 1;
     float smp_w[S][2], smp_n[2];
     const uint32_t smp_c = sample_run(lane / 4, cols) + 2 * (lane % 4);   // lane l: columns 2 (l % 4), + 1 of run l / 4
     {
@@ -309,7 +312,8 @@ __global__ __launch_bounds__(kThreads) void held_rows_kernel(void *__restrict__ 
         const bool in = tid + j * nt < (int)vpl;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const Window w = {(uint32_t)__builtin_amdgcn_readfirstlane(win[r].lo), (uint32_t)__builtin_amdgcn_readfirstlane(win[r].sh)};
+            const Window w = {(uint32_t)__builtin_amdgcn_readfirstlane(win[r].lo),
+                              (uint32_t)__builtin_amdgcn_readfirstlane(win[r].sh)};
             __builtin_amdgcn_sched_barrier(0);
             if (in && r < (int)n_rows) {
                 uint32_t *const mine = hist + r * kStride;
@@ -360,7 +364,8 @@ __global__ __launch_bounds__(kThreads) void held_rows_kernel(void *__restrict__ 
         }
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const uint32_t lo = __builtin_amdgcn_readfirstlane(sel[r].lo), width = __builtin_amdgcn_readfirstlane(sel[r].width);
+            const uint32_t lo = __builtin_amdgcn_readfirstlane(sel[r].lo);
+            const uint32_t width = __builtin_amdgcn_readfirstlane(sel[r].width);
             __builtin_amdgcn_sched_barrier(0);
             const bool live = in && r < (int)n_rows;
             uint32_t kept = 0;

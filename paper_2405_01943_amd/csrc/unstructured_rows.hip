@@ -21,6 +21,8 @@
 // two-term score, a threshold outside the window, more scores in the bin than the list holds)
 // leaves all 8 rows untouched and marks the block in `todo`; the caller's next launch, gated
 // per block, redoes those rows.
+// The window (A), the bin (B, C) and the ranking (E) stand in unstructured_held.hip as well, as functions: a change to
+// one text is made to both.
 #include "unstructured_rows.h"
 
 #include <type_traits>
