@@ -409,15 +409,15 @@ def _rowline_left(workspace, cols, rows):
 
 
 @pytest.mark.parametrize("dtype,rows,cols,pad", [(torch.bfloat16, 1032, 2048, 0), (torch.bfloat16, 520, 4104, 8),
-                                                 (torch.float32, 837, 2504, 4), (torch.bfloat16, 2052, 1024, 0),
+                                                 (torch.float32, 844, 2504, 4), (torch.bfloat16, 2052, 1032, 0),
                                                  (torch.bfloat16, 84, 28672, 0), (torch.float32, 132, 16392, 4),
                                                  (torch.bfloat16, 68, 40000, 8), (torch.bfloat16, 188, 11272, 0)])
 def test_unstructured_row_lines_streamed(gpu_device, dtype, rows, cols, pad):
-    """Row lines of matrices large enough for the one-launch streaming kernel (a workgroup owns 8 whole
-    rows: window, counts, bin, apply with the bin's scores listed, ranking): a ragged last block of
-    rows, lines that are no multiple of the workgroup's stride, lines so long that their factors are
-    staged in two, three or four chunks of columns, a leading dimension, both exponents, quotas from
-    a tenth to nine tenths and one from either end; mask bits as well."""
+    """Row lines of matrices large enough for the one-launch kernels (a workgroup owns 8 whole rows and reads
+    them twice, or 4 and holds them: window, counts, bin, apply with the bin's scores listed, ranking): a
+    ragged last block of rows, lines that are no multiple of the workgroup's stride, lines of f32 that are
+    staged in two chunks of columns and of bf16 in four, a leading dimension, both exponents, quotas from a
+    tenth to nine tenths and one from either end; mask bits as well."""
     g = torch.Generator(device="cpu").manual_seed(rows * 7 + cols)
     W0 = (torch.randn((rows, cols), generator=g) * 0.02).to(dtype)
     W0[5, :] *= 40.0                                  # rows of very different scale
@@ -426,8 +426,7 @@ def test_unstructured_row_lines_streamed(gpu_device, dtype, rows, cols, pad):
     nrm = synth.make_norms(cols, "cpu", 21)
     nrm[::97] = 0.0                                   # dead neurons: their scores are 0
     nrm = nrm.to(gpu_device)
-    ws = torch.zeros(dass.unstructured_workspace_bytes(rows, cols, dtype, "cols", "cols"), dtype=torch.uint8,
-                     device=gpu_device)
+    ws = _rowline_workspace(rows, cols, dtype, gpu_device)
     for alpha, n_prune in ((1.0, cols // 2), (0.5, cols // 10), (1.0, cols * 9 // 10), (0.5, cols - 1), (1.0, 1)):
         W = W0.to(gpu_device)
         if pad:
@@ -441,46 +440,124 @@ def test_unstructured_row_lines_streamed(gpu_device, dtype, rows, cols, pad):
         assert np.array_equal(mask.cpu().numpy(), want_mask)
         if pad:
             assert torch.all(W._base[:, cols:] == 7.0)
+        left = _rowline_left(ws, cols, rows)
         if n_prune == cols // 2:
-            todo = _rowline_todo(ws, cols, rows)
-            assert not todo.any(), f"alpha={alpha}: ordinary rows must be decided by the streaming kernel ({todo.sum()} blocks left)"
+            assert not left.any(), f"alpha={alpha}: ordinary rows must be decided ({left.sum()} left)"
 
 
-@pytest.mark.parametrize("dtype,rows,cols,masked", [
-    (torch.bfloat16, 1024, 2056, False), (torch.bfloat16, 1025, 2056, False),       # held in registers; read twice
-    (torch.bfloat16, 257, 8192, False), (torch.bfloat16, 258, 8200, True),          # one and two column slots a thread
-    (torch.bfloat16, 131, 16384, True), (torch.bfloat16, 133, 16392, False),        # two and four
-    (torch.bfloat16, 67, 32768, True), (torch.bfloat16, 70, 32776, True),           # four; read twice
-    (torch.float32, 518, 4096, True), (torch.float32, 513, 4104, False), (torch.float32, 258, 8200, True),
-    (torch.float32, 129, 16384, False), (torch.bfloat16, 4096, 1032, True), (torch.bfloat16, 4102, 4096, True),
-    (torch.bfloat16, 4097, 4104, True), (torch.float32, 4099, 1032, True)])
-def test_unstructured_row_lines_held(gpu_device, dtype, rows, cols, masked):
-    """Both sides of the limits of the kernel that holds its rows in registers, ragged last blocks of 4 and of 8
-    rows, and rows of equal scores that it leaves to the launch behind it."""
-    g = torch.Generator(device="cpu").manual_seed(rows + cols)
+def _tied_rows(rows, cols, dtype, seed, tied):
+    """Weights and norms such that the rows `tied` tie at a quota of 0.4 (half of the norms are equal, and so are those
+    rows' weights: half a line at the threshold, more than a list holds) and the others do not."""
+    g = torch.Generator(device="cpu").manual_seed(seed)
     W = (torch.randn((rows, cols), generator=g) * 0.02).to(dtype)
-    W[3] = 0.5
-    W[-1] = -0.25
-    W, nrm = W.to(gpu_device), synth.make_norms(cols, "cpu", 5)
-    nrm[8:] = nrm[:-8].clone()
-    nrm = nrm.to(gpu_device)
+    for r in tied:
+        W[r] = 0.5 if r % 2 else -0.25
+    nrm = synth.make_norms(cols, "cpu", 5)
+    nrm[:cols // 2] = nrm[cols // 2:].median()
+    return W, nrm
+
+
+def _expected_left(rows, held, tied):
+    """What _rowline_left gives when just the rows `tied` are undecided."""
+    want = np.zeros((rows + 7) // 8 * 4, dtype=np.uint8)
+    for r in tied:
+        if held:
+            want[r // 4 * 2:r // 4 * 2 + 2] = 1
+        else:
+            want[r // 8 * 4] = 1
+    return want
+
+
+@pytest.mark.parametrize("dtype,rows,cols,masked,held", [
+    (torch.bfloat16, 1024, 2056, False, True), (torch.bfloat16, 1025, 2056, False, False),   # the limit of rows
+    (torch.bfloat16, 257, 8192, False, True), (torch.bfloat16, 260, 8200, True, True),       # one and two column slots a thread
+    (torch.bfloat16, 132, 16384, True, True), (torch.bfloat16, 133, 16392, False, True),     # two and four
+    (torch.bfloat16, 68, 32768, True, True), (torch.bfloat16, 72, 32776, True, False),       # the limit of the line
+    (torch.float32, 518, 4096, True, True), (torch.float32, 518, 4112, True, True),          # f32: one and two slots
+    (torch.float32, 258, 8192, True, True), (torch.float32, 260, 8200, True, True),          # two and four
+    (torch.float32, 130, 16384, True, True), (torch.float32, 129, 16384, False, True),
+    (torch.float32, 128, 16392, True, False),
+    (torch.bfloat16, 4096, 1032, True, True), (torch.bfloat16, 4092, 1032, True, False),     # masks on many short lines
+    (torch.bfloat16, 4102, 4096, True, True), (torch.bfloat16, 4100, 4104, True, False),
+    (torch.float32, 4100, 1032, True, True), (torch.float32, 4100, 2048, True, True),
+    (torch.float32, 4100, 2056, True, False)])
+def test_unstructured_row_lines_held(gpu_device, dtype, rows, cols, masked, held):
+    """Both sides of the limits of the kernel that holds its rows in registers, ragged last blocks of 4 and of 8
+    rows, and rows of equal scores that it leaves to the launch behind it: one group of 4 of a block, the other
+    group, both, and the last rows."""
+    tied = (3, 13, 17, 22, rows - 1)
+    W, nrm = _tied_rows(rows, cols, dtype, rows + cols, tied)
+    W, nrm = W.to(gpu_device), nrm.to(gpu_device)
     want, want_mask = oracle.mask_unstructured(to_np32(W), nrm.cpu().numpy(), "cols", "cols", 0.5, cols * 2 // 5, want_mask=True)
     mask = torch.full((rows, cols // 8), 0x55, dtype=torch.uint8, device=gpu_device) if masked else None
-    dass.score_mask_unstructured(W, nrm, "cols", "cols", 0.5, cols * 2 // 5, mask_out=mask)
+    ws = _rowline_workspace(rows, cols, dtype, gpu_device)
+    dass.score_mask_unstructured(W, nrm, "cols", "cols", 0.5, cols * 2 // 5, mask_out=mask, workspace=ws)
     torch.cuda.synchronize()
     assert bits_equal(W, want), first_mismatch(W, want)
     if masked:
         assert np.array_equal(mask.cpu().numpy(), want_mask)
+    assert np.array_equal(_rowline_left(ws, cols, rows), _expected_left(rows, held, tied))
 
 
-def test_unstructured_row_lines_streamed_undecided_cases(gpu_device):
+@pytest.mark.parametrize("dtype,rows,cols,pad", [(torch.bfloat16, 1028, 11272, 8), (torch.bfloat16, 1028, 28672, 0),
+                                                 (torch.float32, 1028, 12296, 4), (torch.bfloat16, 1036, 40000, 8)])
+def test_unstructured_row_lines_in_chunks(gpu_device, dtype, rows, cols, pad):
+    """Rows that are read twice, with factors staged in two, three and four chunks of columns, a leading dimension, a
+    ragged last block and rows that are left.  The oracle has some of the rows: the first and last blocks and every 29th."""
+    tied = (20, rows - 2)
+    W, nrm = _tied_rows(rows, cols, dtype, rows + cols, tied)
+    some = sorted({*range(24), *range(24, rows - 12, 29), *range(rows - 12, rows)})
+    want, want_mask = oracle.mask_unstructured(to_np32(W[some]), nrm.numpy(), "cols", "cols", 1.0, cols * 2 // 5, want_mask=True)
+    W = padded(W.to(gpu_device), pad) if pad else W.to(gpu_device)
+    mask = torch.full((rows, cols // 8), 0x55, dtype=torch.uint8, device=gpu_device)
+    ws = _rowline_workspace(rows, cols, dtype, gpu_device)
+    dass.score_mask_unstructured(W, nrm.to(gpu_device), "cols", "cols", 1.0, cols * 2 // 5, mask_out=mask, workspace=ws)
+    torch.cuda.synchronize()
+    assert bits_equal(W[some], want), first_mismatch(W[some], want)
+    assert np.array_equal(mask[some].cpu().numpy(), want_mask)
+    assert not pad or torch.all(W._base[:, cols:] == 7.0)
+    assert np.array_equal(_rowline_left(ws, cols, rows), _expected_left(rows, False, tied))
+
+
+@pytest.mark.parametrize("dtype,cols", [(torch.bfloat16, 4096), (torch.bfloat16, 11272), (torch.float32, 4096),
+                                        (torch.float32, 12296)])
+def test_unstructured_row_lines_alike_held_and_read_twice(gpu_device, dtype, cols):
+    """The same rows as part of a matrix whose rows are held and of one whose rows are read twice: the same bits, the
+    same blocks left.  Weights of few values and many zeros: lists up to their limit and beyond; quotas near both ends."""
+    rows, more = 1024, 1040
+    g = torch.Generator(device="cpu").manual_seed(cols)
+    W0 = torch.randn((more, cols), generator=g) * 0.02
+    W0[:256] = (W0[:256] * 2000).round() / 2000                       # ties by the dozen and by the hundred
+    W0[256:384] *= (torch.rand((128, cols), generator=g) < 0.55).to(torch.float32)
+    W0[384:512] *= (torch.rand((128, cols), generator=g) < 0.45).to(torch.float32)   # more zeros than half
+    W0 = W0.to(dtype).to(gpu_device)
+    nrm = synth.make_norms(cols, "cpu", 5)
+    nrm[:cols // 4] = 3.0
+    nrm = nrm.to(gpu_device)
+    for alpha, n_prune in ((0.5, cols // 2), (1.0, cols * 2 // 5), (0.5, cols // 20), (1.0, cols - 40), (0.75, cols // 2)):
+        got = []
+        for n in (rows, more):
+            W = W0[:n].clone()
+            mask = torch.full((n, cols // 8), 0x55, dtype=torch.uint8, device=gpu_device)
+            ws = _rowline_workspace(n, cols, dtype, gpu_device)
+            dass.score_mask_unstructured(W, nrm, "cols", "cols", alpha, n_prune, mask_out=mask, workspace=ws)
+            torch.cuda.synchronize()
+            left = np.add.reduceat(_rowline_left(ws, cols, n), np.arange(0, n // 2, 4))[:rows // 8] > 0
+            got.append((W[:rows].view(torch.int16), mask[:rows], left))
+        assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1]), f"alpha={alpha} n_prune={n_prune}"
+        if alpha != 0.75:   # there the samples of 4 and of 8 rows decide whether a block leaves early
+            assert np.array_equal(got[0][2], got[1][2]), f"alpha={alpha} n_prune={n_prune}"
+            assert n_prune != cols // 2 or 0 < got[0][2].sum() < rows // 8
+
+
+@pytest.mark.parametrize("rows", [1024, 1032])   # rows held, rows read twice
+def test_unstructured_row_lines_streamed_undecided_cases(gpu_device, rows):
     """Blocks of rows that the streaming kernel cannot decide are left to the other kernels, block by
     block, and the result is the oracle's all the same: rows of thousands of equal scores beside
     ordinary ones, a product that overflows f32, a factor below the range of the two-term score."""
-    rows, cols = 1024, 2048
+    cols = 2048
     g = torch.Generator(device="cpu").manual_seed(5)
-    ws = torch.zeros(dass.unstructured_workspace_bytes(rows, cols, torch.bfloat16, "cols", "cols"), dtype=torch.uint8,
-                     device=gpu_device)
+    ws = _rowline_workspace(rows, cols, torch.bfloat16, gpu_device)
 
     def check(W, nrm, alpha, n_prune, what, expect_left):
         want, want_mask = oracle.mask_unstructured(to_np32(W), nrm.cpu().numpy(), "cols", "cols", alpha, n_prune,
