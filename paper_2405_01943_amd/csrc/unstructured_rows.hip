@@ -467,15 +467,18 @@ RowlinesPlan plan_rowlines(int64_t rows, int64_t cols, int64_t ld, int dt, const
     p.blocks = (rows + kRows - 1) / kRows;
     if (p.blocks > 0x7fffffffLL)
         return p;
-    // Held in registers or read twice, us, back to back with the copy of the dense weights.  Up to 1024 rows (256
-    // workgroups of 4 rows; of 8 they leave half of the compute units idle) held: bf16 1024 x 5400 25 read twice, 22
-    // held, 1024 x 11008 36 31, 1024 x 28672 85 63, 768 x 14336 50 38, 256 x 16384 48 33, 64 x 32768 85 57, f32 1024 x
-    // 4096 24 19.5.  Beyond, the phases of fewer wavefronts are longer than the second read, which comes out of the
-    // memory-side cache: 1280 x 28672 87 107, 1536 x 11008 37 41, 4096 x 11008 62 74.  Except with a mask on short lines
-    // of many rows, where rowlines_kernel's workgroups do not share a compute unit: 4096 x 2048 28 24, 8192 x 2048
-    // 49 36, 16384 x 2048 88 58, 8192 x 3000 58 49, but 2048 x 2048 20 22 and 8192 x 7000 99 117.
+    // Read twice or held in registers, us, back to back with the copy of the dense weights.  Up to 1024 rows (256
+    // workgroups of 4 rows; of 8 they leave half of the compute units idle) held: bf16 1024 x 5400 25 read twice, 21
+    // held, 1024 x 11008 36 30, 1024 x 28672 85 62, 768 x 14336 50 38, 256 x 16384 47 32, 64 x 32768 84 57, f32 1024 x
+    // 4096 22 18, 333 x 16000 48 35; 1020 x 2064 16 16.  Beyond, the phases of fewer wavefronts are longer than the second
+    // read, which comes out of the memory-side cache: 1280 x 11008 37 40, 1280 x 28672 87 105, 4096 x 11008 61 73, f32 1280
+    // x 12288 51 56 (1032 x 5400 24 23).
+    // Except with a mask on short lines of many rows, where rowlines_kernel's workgroups do not share a compute unit: bf16
+    // 4096 x 2048 29 24, 8192 x 2048 49 36, 28672 x 1032 122 81, 28672 x 4096 221 152, f32 4096 x 2048 25.2 24.2, 8192 x
+    // 1032 31 31, 28672 x 2048 131 110.  Longer lines: bf16 8192 x 4600 74 74, 8192 x 5400 83 84, 8192 x 7000 98
+    // 119, f32 8192 x 2400 47 56, 28672 x 2400 149 171.  Below 10 MB: bf16 4096 x 1032 23.6 24.3, 4096 x 1400 25.2 25.5 (2048 x 2048 17 18, but 3000 x 2048 27 21).
     const int64_t vpl = cols / vec_elems(dt);
-    const bool held = rows <= 1024 || (mask_out && rows >= 4096 && vpl <= 512);
+    const bool held = rows <= 1024 || (mask_out && rows >= 4096 && vpl <= 512 && rows * vpl >= 640 << 10);
     p.held_slots = !held || vpl > 4096 ? 0 : vpl <= 1024 ? 1 : vpl <= 2048 ? 2 : 4;
     p.todo_bytes = round_up((size_t)p.blocks * sizeof(uint32_t), 256);
     p.fits = true;

@@ -477,7 +477,8 @@ def _expected_left(rows, held, tied):
     (torch.float32, 258, 8192, True, True), (torch.float32, 260, 8200, True, True),          # two and four
     (torch.float32, 130, 16384, True, True), (torch.float32, 129, 16384, False, True),
     (torch.float32, 128, 16392, True, False),
-    (torch.bfloat16, 4096, 1032, True, True), (torch.bfloat16, 4092, 1032, True, False),     # masks on many short lines
+    (torch.bfloat16, 5084, 1032, True, True), (torch.bfloat16, 5080, 1032, True, False),     # masks on many short lines
+    (torch.bfloat16, 4096, 2048, True, True), (torch.bfloat16, 4092, 2048, True, False),
     (torch.bfloat16, 4102, 4096, True, True), (torch.bfloat16, 4100, 4104, True, False),
     (torch.float32, 4100, 1032, True, True), (torch.float32, 4100, 2048, True, True),
     (torch.float32, 4100, 2056, True, False)])
