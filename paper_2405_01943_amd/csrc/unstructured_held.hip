@@ -4,7 +4,9 @@
 // in each of them (slots tid, tid + blockDim, ..; the host makes blockDim J just cover the line).  A slot's factors are
 // then read once for 4 rows, straight from the norms into registers, and a row's window and threshold are the same for
 // the whole workgroup: scalar registers.  What bounds it is the chain of the phases, with 2 to 16 wavefronts a workgroup:
-// 1024 x 5400 bf16 25 -> 22 us a call with the copy of the dense weights, 768 x 14336 50 -> 38, 333 x 16000 f32 58 -> 41.
+// 1024 x 5400 bf16 25 -> 21 us a call with the copy of the dense weights, 768 x 14336 50 -> 38, 333 x 16000 f32 48 -> 35.
+// Four slots take all of the 128 registers that 16 wavefronts leave each: bf16 keeps 8 of a thread's values in scratch, f32
+// with a mask 2 (64 x 32768 bf16 is 57 us all the same, read twice 84).
 // (The window, the bin and the ranking stand here and in rowlines_kernel, whose compiled form was 2 to 3 us slower on
 // 4096 x 11008 when it called the functions below.  Both texts have to select the same bins: a change to one is made to
 // both, and a test runs the same rows through the two kernels.)
