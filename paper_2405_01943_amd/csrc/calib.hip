@@ -523,70 +523,72 @@ __global__ __launch_bounds__(256) void calib_pipe64_kernel(
             }
     if constexpr (DEEP) {
     // ---- small tiles.  Under the MFMAs of K step 0 go the fragment reads of K step 1; the second half of K step
-    // 1, after the slab's one barrier, carries those of K step 0 of the next slab.  The loads of the B part of
-    // slab s + NB and the A part of slab s + NA, into the units of slab s, go out one a pair from that barrier on,
-    // the last ones under K step 0 of slab s + 1 (all in the second half, 1 to 3 us more of every figure above).
-    // Parts past the last slab are requested from an empty buffer, so that every slab waits for the same number of
-    // loads.  A raw buffer's lane is out of range, and its load fetches nothing, if its offset is not below the
-    // buffer's length less the scalar offset: the empty ones have scalar offset 0, so that this is never negative.
-    constexpr int N_LOADS = A_WL + 2 * B_WL;
-    // q-th load of the B part of slab s + NB and the A part of slab s + NA, into the units ub and ua; the B part first
-    auto issue = [&](int s, int ua, int ub, int q) {
-        const bool is_b = q < 2 * B_WL, g = q < B_WL;
-        const int slab = s + (is_b ? NB : NA);
-        const bool there = slab < S;
-        const int span = there ? is_b ? g ? span_w : span_u : span_x : 0, off = there ? slab * BK * 2 : 0;
-        const uint16_t *rows = is_b ? g ? Wg + n0 * ldw : up_rows : X + t0 * ldx;
-        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(rows), 0, span, kRawBuffer);
-        if (is_b)
-            load_to_lds(r, lds64 + B_BASE + ub * B_UNIT + (g ? 0 : B_HALF) + (wave * B_WL + q % B_WL) * 1024, b_off[q % B_WL],
-                        off);
-        else
-            load_to_lds(r, lds64 + ua * A_UNIT + (wave * A_WL + q - 2 * B_WL) * 1024, a_off[q - 2 * B_WL], off);
+    // 1, after the slab's one barrier, carries those of K step 0 of the next slab.  The B part of slab s + NB goes into
+    // the unit of slab s from that barrier on, one load a pair, and the A part of slab s + NA under K step 0 of slab
+    // s + 1 (all in the second half, 1 to 3 us more of every figure above).  Only slabs that exist are requested: the
+    // last NB slabs have bodies of their own with fewer loads to wait for, and K of up to NB slabs begins with those.
+    // (Requests from an empty buffer instead, with one count for every wait, keep the load path as busy as real ones.  A
+    // launch with those and now: one slab of 64 5.5 -> 5.0 us, two 6.1 -> 5.6, twelve 8.9 -> 8.5, 32 15.3 -> 14.9.)
+    constexpr int N_LOADS = A_WL + 2 * B_WL, A_LEAD = NA - NB;   // the A parts run A_LEAD slabs further ahead
+    static_assert(N_HALF == 2 * B_WL && N_PAIRS >= A_WL && (A_LEAD == 0 || A_LEAD == 1), "every load has its place");
+    auto request_a = [&](int slab, int unit, int q) {
+        issue_a(unit, slab * BK * 2, q);
+        __builtin_amdgcn_sched_barrier(0);   // in this order: the waits count
     };
-    // As if slabs -NB, -NB + 1, .. had been read: two of them here, the others under the MFMAs of slab 0.  A parts
-    // that run further ahead than the B parts come first.  In this order: the waits count.
+    auto request_b = [&](int slab, int unit, int q) {
+        issue_b(unit, slab * BK * 2, q);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // A0 first where the A parts lead, then B0, A0 or A1, B1, ..: two of each before the first wait and the others of
+    // the rings under the MFMAs of slab 0, or all there are of a K that the B ring holds whole.
+    const bool many = S > NB;
+    auto request_b_of = [&](int p) {
 #pragma unroll
-    for (int p = -NA; p < -NB; ++p)
+        for (int q = 0; q < 2 * B_WL; ++q)
+            request_b(p, p, q);
+    };
+    auto request_a_of = [&](int p) {
 #pragma unroll
-        for (int q = 2 * B_WL; q < N_LOADS; ++q) {
-            issue(p, p + NA, 0, q);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-#pragma unroll
-    for (int p = -NB; p < 2 - NB; ++p)
-#pragma unroll
-        for (int q = 0; q < N_LOADS; ++q) {
-            issue(p, p + NA, p + NB, q);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    constexpr int A_MORE = NA > NB ? A_WL : 0;   // the A part requested with a B part is due a slab later
-    wait_vmcnt<N_LOADS + A_MORE>();              // slab 0 has landed
-    block_barrier();
+        for (int q = 0; q < A_WL; ++q)
+            request_a(p, p, q);
+    };
+    if (A_LEAD > 0)
+        request_a_of(0);
     Frags f0, f1;
+    auto begin = [&]() __attribute__((always_inline)) {   // slab 0 has landed
+        block_barrier();
 #pragma unroll
-    for (int q = 0; q < N_READS; ++q)
-        read_one(f0, 0, 0, 0, q);
-    int ua = 0, ub = 0, pa = 0, pb = 0;   // ring units of slab s, of slab s - 1
-    constexpr int N_NOW = N_LOADS < N_HALF ? N_LOADS : N_HALF, N_LATE = N_LOADS - N_NOW;
-    auto slab_body = [&](int s, auto first_tag) {
+        for (int q = 0; q < N_READS; ++q)
+            read_one(f0, 0, 0, 0, q);
+    };
+    int ua = 0, ub = 0, pa = 0;   // ring units of slab s, of the A part of slab s - 1
+    // LEFT: how many slabs follow; NB stands for NB and more.
+    auto slab_body = [&](int s, auto first_tag, auto left_tag) {
         constexpr bool FIRST = decltype(first_tag)::value;
+        constexpr int LEFT = decltype(left_tag)::value;
+        constexpr bool LATE_A = !FIRST && LEFT >= NA - 1, NEXT_B = LEFT >= NB;
         constexpr int N_REST = FIRST ? (NB - 2) * N_LOADS : 0, N_FREE = N_PAIRS + N_HALF;
         auto rest = [&](int q) {   // the prologue's other loads, spread over the pairs before the barrier
 #pragma unroll
             for (int x = q * N_REST / N_FREE; x < (q + 1) * N_REST / N_FREE; ++x) {
+                const int p = 2 + x / N_LOADS, y = x % N_LOADS;
                 __builtin_amdgcn_sched_barrier(0);
-                issue(2 - NB + x / N_LOADS, 2 - NB + x / N_LOADS + NA, 2 + x / N_LOADS, x % N_LOADS);
+                if (y < 2 * B_WL)
+                    request_b(p, p, y);
+                else
+                    request_a(p + A_LEAD, p + A_LEAD, y - 2 * B_WL);
             }
         };
         const int ua1 = ua + 1 == NA ? 0 : ua + 1, ub1 = ub + 1 == NB ? 0 : ub + 1;
 #pragma unroll
         for (int q = 0; q < N_PAIRS; ++q) {   // K step 0
             rest(q);
-            if constexpr (!FIRST) {
+            if constexpr (LATE_A) {
+                if (LEFT == NB || many) {   // (the prologue of a K of NB slabs has requested it)
 #pragma unroll
-                for (int x = q * N_LATE / N_PAIRS; x < (q + 1) * N_LATE / N_PAIRS; ++x)
-                    issue(s - 1, pa, pb, N_NOW + x);
+                    for (int x = q * A_WL / N_PAIRS; x < (q + 1) * A_WL / N_PAIRS; ++x)
+                        issue_a(pa, (s - 1 + NA) * BK * 2, x);
+                }
             }
 #pragma unroll
             for (int x = (q * N_READS + N_PAIRS - 1) / N_PAIRS; x < ((q + 1) * N_READS + N_PAIRS - 1) / N_PAIRS; ++x)
@@ -600,35 +602,85 @@ __global__ __launch_bounds__(256) void calib_pipe64_kernel(
             mfma_pair(f1, q);
             __builtin_amdgcn_sched_barrier(0);
         }
-        // slab s + 1 has landed and this wavefront holds its last fragments of slab s: lgkmcnt(0) and vmcnt of
-        // what was requested after the B part of slab s + 1
-        constexpr int AHEAD = (NB - 2) * N_LOADS + A_MORE;
-        static_assert(AHEAD < 64, "vmcnt is a 6-bit counter");
-        __builtin_amdgcn_s_waitcnt(0x0070 | (AHEAD & 15) | ((AHEAD >> 4) << 14));
-        block_barrier();
+        if constexpr (LEFT > 0) {
+            // slab s + 1 has landed and this wavefront holds its last fragments of slab s: lgkmcnt(0) and vmcnt of
+            // what was requested after both parts of slab s + 1
+            constexpr int B_AHEAD = LEFT < NB - 1 ? LEFT : NB - 1, A_AHEAD = LEFT < NA - 1 ? LEFT : NA - 1;
+            constexpr int AHEAD = (B_AHEAD - 1) * 2 * B_WL + (A_AHEAD - 1) * A_WL;
+            static_assert(AHEAD < 64, "vmcnt is a 6-bit counter");
+            __builtin_amdgcn_s_waitcnt(0x0070 | (AHEAD & 15) | ((AHEAD >> 4) << 14));
+            block_barrier();
+        }
 #pragma unroll
-        for (int q = 0; q < N_HALF; ++q) {   // K step 1, second half; past the last slab the reads are of no use
+        for (int q = 0; q < N_HALF; ++q) {   // K step 1, second half
+            if constexpr (NEXT_B)
+                issue_b(ub, (s + NB) * BK * 2, q);
+            if constexpr (LEFT > 0) {
 #pragma unroll
-            for (int x = q * N_NOW / N_HALF; x < (q + 1) * N_NOW / N_HALF; ++x)
-                issue(s, ua, ub, x);
-#pragma unroll
-            for (int x = (q * N_READS + N_HALF - 1) / N_HALF; x < ((q + 1) * N_READS + N_HALF - 1) / N_HALF; ++x)
-                read_one(f0, ua1, ub1, 0, x);
+                for (int x = (q * N_READS + N_HALF - 1) / N_HALF; x < ((q + 1) * N_READS + N_HALF - 1) / N_HALF; ++x)
+                    read_one(f0, ua1, ub1, 0, x);
+            }
             mfma_pair(f1, N_HALF + q);
             __builtin_amdgcn_sched_barrier(0);
         }
         pa = ua;
-        pb = ub;
         ua = ua1;
         ub = ub1;
     };
-    // (the first slab on its own: with one loop the compiler gave the accumulators other registers in every slab and
-    // moved them back)
-    slab_body(0, std::true_type{});
-    for (int s = 1; s < S; ++s)
-        slab_body(s, std::false_type{});
-    wait_vmcnt<0>();   // the rings are about to be used again, and the empty parts would be written over that
-    block_barrier();
+    using Many = std::integral_constant<int, NB>;
+    int s = 0;
+    if (many) {
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            request_b_of(p);
+            request_a_of(p + A_LEAD);
+        }
+        wait_vmcnt<N_LOADS + A_LEAD * A_WL>();
+        begin();
+        // (the first slab on its own: with one loop the compiler gave the accumulators other registers in every slab
+        // and moved them back)
+        slab_body(s++, std::true_type{}, Many{});
+        for (; s + NB < S; ++s)
+            slab_body(s, std::false_type{}, Many{});
+    } else {
+#pragma unroll
+        for (int p = 0; p < NB; ++p) {
+            if (p < S)
+                request_b_of(p);
+            if (p + A_LEAD < S)
+                request_a_of(p + A_LEAD);
+        }
+        // The sums are cleared while the loads are on their way; left to itself the compiler does it behind the wait.
+        // (Slab 0 above begins with constant ones.)
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int j = 0; j < NI; ++j)
+                asm volatile("" : "+a"(acc_g[i][j]), "+a"(acc_u[i][j]));
+        static_assert(NB <= 5, "the waits below");
+        if (S == 1)
+            wait_vmcnt<0>();
+        else if (S == 2)
+            wait_vmcnt<N_LOADS>();
+        else if (S == 3)
+            wait_vmcnt<2 * N_LOADS>();
+        else if (S == 4)
+            wait_vmcnt<3 * N_LOADS>();
+        else
+            wait_vmcnt<4 * N_LOADS>();
+        begin();
+    }
+    auto last = [&](auto left_tag) {
+        constexpr int LEFT = decltype(left_tag)::value;
+        if (LEFT < NB && s + LEFT < S)
+            slab_body(s++, std::false_type{}, std::integral_constant<int, LEFT < NB ? LEFT : 0>{});
+    };
+    last(std::integral_constant<int, 4>{});
+    last(std::integral_constant<int, 3>{});
+    last(std::integral_constant<int, 2>{});
+    last(std::integral_constant<int, 1>{});
+    last(std::integral_constant<int, 0>{});
+    block_barrier();   // the rings are about to be used again
     } else {
     // ---- prologue: A0 B0 A1 B1 A2 fill the five units, in this order: the waits count
 #pragma unroll
