@@ -526,7 +526,7 @@ __global__ __launch_bounds__(256) void calib_pipe64_kernel(
     // 1, after the slab's one barrier, carries those of K step 0 of the next slab.  The B part of slab s + NB goes into
     // the unit of slab s from that barrier on, one load a pair, and the A part of slab s + NA under K step 0 of slab
     // s + 1 (all in the second half, 1 to 3 us more of every figure above).  Only slabs that exist are requested: the
-    // last NB slabs have bodies of their own with fewer loads to wait for, and K of up to NB slabs begins with those.
+    // last NB slabs have bodies of their own with fewer loads to wait for, and so have the first of a K of 3 to NB.
     // (Requests from an empty buffer instead, with one count for every wait, keep the load path as busy as real ones.  A
     // launch with those and now: one slab of 64 5.5 -> 5.0 us, two 6.1 -> 5.6, twelve 8.9 -> 8.5, 32 15.3 -> 14.9.)
     constexpr int N_LOADS = A_WL + 2 * B_WL, A_LEAD = NA - NB;   // the A parts run A_LEAD slabs further ahead
@@ -540,8 +540,7 @@ __global__ __launch_bounds__(256) void calib_pipe64_kernel(
         __builtin_amdgcn_sched_barrier(0);
     };
     // A0 first where the A parts lead, then B0, A0 or A1, B1, ..: two of each before the first wait and the others of
-    // the rings under the MFMAs of slab 0, or all there are of a K that the B ring holds whole.
-    const bool many = S > NB;
+    // the rings under the MFMAs of slab 0 (all five of K = 320 before the first wait, 0.4 us more).
     auto request_b_of = [&](int p) {
 #pragma unroll
         for (int q = 0; q < 2 * B_WL; ++q)
@@ -567,7 +566,8 @@ __global__ __launch_bounds__(256) void calib_pipe64_kernel(
         constexpr bool FIRST = decltype(first_tag)::value;
         constexpr int LEFT = decltype(left_tag)::value;
         constexpr bool LATE_A = !FIRST && LEFT >= NA - 1, NEXT_B = LEFT >= NB;
-        constexpr int N_REST = FIRST ? (NB - 2) * N_LOADS : 0, N_FREE = N_PAIRS + N_HALF;
+        constexpr int N_REST = !FIRST ? 0 : LEFT < NB ? (LEFT - 1) * N_LOADS - A_LEAD * A_WL : (NB - 2) * N_LOADS;
+        constexpr int N_FREE = N_PAIRS + N_HALF;
         auto rest = [&](int q) {   // the prologue's other loads, spread over the pairs before the barrier
 #pragma unroll
             for (int x = q * N_REST / N_FREE; x < (q + 1) * N_REST / N_FREE; ++x) {
@@ -584,11 +584,9 @@ __global__ __launch_bounds__(256) void calib_pipe64_kernel(
         for (int q = 0; q < N_PAIRS; ++q) {   // K step 0
             rest(q);
             if constexpr (LATE_A) {
-                if (LEFT == NB || many) {   // (the prologue of a K of NB slabs has requested it)
 #pragma unroll
-                    for (int x = q * A_WL / N_PAIRS; x < (q + 1) * A_WL / N_PAIRS; ++x)
-                        issue_a(pa, (s - 1 + NA) * BK * 2, x);
-                }
+                for (int x = q * A_WL / N_PAIRS; x < (q + 1) * A_WL / N_PAIRS; ++x)
+                    issue_a(pa, (s - 1 + NA) * BK * 2, x);
             }
 #pragma unroll
             for (int x = (q * N_READS + N_PAIRS - 1) / N_PAIRS; x < ((q + 1) * N_READS + N_PAIRS - 1) / N_PAIRS; ++x)
@@ -627,9 +625,8 @@ __global__ __launch_bounds__(256) void calib_pipe64_kernel(
         ua = ua1;
         ub = ub1;
     };
-    using Many = std::integral_constant<int, NB>;
     int s = 0;
-    if (many) {
+    if (S > 2) {
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
             request_b_of(p);
@@ -639,16 +636,29 @@ __global__ __launch_bounds__(256) void calib_pipe64_kernel(
         begin();
         // (the first slab on its own: with one loop the compiler gave the accumulators other registers in every slab
         // and moved them back)
-        slab_body(s++, std::true_type{}, Many{});
-        for (; s + NB < S; ++s)
-            slab_body(s, std::false_type{}, Many{});
+        if (S > NB) {
+            slab_body(s++, std::true_type{}, std::integral_constant<int, NB>{});
+            for (; s + NB < S; ++s)
+                slab_body(s, std::false_type{}, std::integral_constant<int, NB>{});
+        } else if (S == 3) {
+            slab_body(s++, std::true_type{}, std::integral_constant<int, 2>{});
+        } else if constexpr (NB == 5) {
+            if (S == 4)
+                slab_body(s++, std::true_type{}, std::integral_constant<int, 3>{});
+            else
+                slab_body(s++, std::true_type{}, std::integral_constant<int, 4>{});
+        }
+        static_assert(NB == 3 || NB == 5, "every S has its first slab");
     } else {
-#pragma unroll
-        for (int p = 0; p < NB; ++p) {
-            if (p < S)
-                request_b_of(p);
-            if (p + A_LEAD < S)
-                request_a_of(p + A_LEAD);
+        request_b_of(0);
+        if (A_LEAD == 0)
+            request_a_of(0);
+        if (S == 2) {
+            if (A_LEAD > 0)
+                request_a_of(1);
+            request_b_of(1);
+            if (A_LEAD == 0)
+                request_a_of(1);
         }
         // The sums are cleared while the loads are on their way; left to itself the compiler does it behind the wait.
         // (Slab 0 above begins with constant ones.)
@@ -657,23 +667,18 @@ __global__ __launch_bounds__(256) void calib_pipe64_kernel(
 #pragma unroll
             for (int j = 0; j < NI; ++j)
                 asm volatile("" : "+a"(acc_g[i][j]), "+a"(acc_u[i][j]));
-        static_assert(NB <= 5, "the waits below");
-        if (S == 1)
-            wait_vmcnt<0>();
-        else if (S == 2)
+        if (S == 2)
             wait_vmcnt<N_LOADS>();
-        else if (S == 3)
-            wait_vmcnt<2 * N_LOADS>();
-        else if (S == 4)
-            wait_vmcnt<3 * N_LOADS>();
         else
-            wait_vmcnt<4 * N_LOADS>();
+            wait_vmcnt<0>();
         begin();
     }
     auto last = [&](auto left_tag) {
         constexpr int LEFT = decltype(left_tag)::value;
-        if (LEFT < NB && s + LEFT < S)
-            slab_body(s++, std::false_type{}, std::integral_constant<int, LEFT < NB ? LEFT : 0>{});
+        if constexpr (LEFT < NB) {
+            if (s + LEFT < S)
+                slab_body(s++, std::false_type{}, left_tag);
+        }
     };
     last(std::integral_constant<int, 4>{});
     last(std::integral_constant<int, 3>{});
