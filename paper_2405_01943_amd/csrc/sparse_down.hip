@@ -247,19 +247,15 @@ __global__ __launch_bounds__(256) void down_sparse24_kernel(
         // ---- main loop of the middle tile.  Step s, the time from the barrier of slab s to that of the next one,
         // requests a part of the codes (odd s), the y of slab s + 3 and half of the rows of a unit of values: of
         // unit (s + 5) / 2 with s odd, whose place is free since slab s is read, the other half in the step after.
-        // What lies past the last slab is requested from an empty buffer, at scalar offset 0 (see above): nothing is
-        // fetched.
+        // Only slabs and units that exist are requested, so the last slabs have bodies of their own.  (With requests
+        // from an empty buffer instead, which keep the load path as busy as real ones, 2048 tokens of 4096 x 256 took
+        // 8.5 us, now 8.1, 8200 of 512 x 256 7.7, now 7.3, 2048 of 4096 x 1024 15.5, now 15.2.)
         constexpr int kUnit = 2 * kABytes, kUnits = 3 * P::kBBytes;   // values of two slabs; where the units begin
-        auto buffer = [&](const void *rows, int64_t bytes, bool any) {
-            return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(rows), 0, any ? (int)bytes : 0, kRawBuffer);
-        };
         auto load_y = [&](int s, int q) {
-            load_to_lds(buffer(Y + t0 * ldy, (rows_t - 1) * ldy * 2 + d_int * 2, s < S),
-                        lds + s % 3 * P::kBBytes + (wave * 2 * NB + q) * 1024, b_off[q], s < S ? s * kBK * 2 : 0);
+            load_to_lds(ry, lds + s % 3 * P::kBBytes + (wave * 2 * NB + q) * 1024, b_off[q], s * kBK * 2);
         };
         auto load_values = [&](int unit, int q) {   // q-th of 2 FB
-            load_to_lds(buffer(values + f0 * ldv, (rows_f - 1) * ldv * 2 + d_int, 2 * unit < S),
-                        lds + kUnits + unit % 3 * kUnit + (wave * 2 * FB + q) * 1024, a_off[q], 2 * unit < S ? unit * 128 : 0);
+            load_to_lds(rv, lds + kUnits + unit % 3 * kUnit + (wave * 2 * FB + q) * 1024, a_off[q], unit * 128);
         };
         auto step_load = [&](int s, bool odd, int q) {   // q-th of a step's loads: the codes first
             if (odd) {
@@ -295,22 +291,36 @@ __global__ __launch_bounds__(256) void down_sparse24_kernel(
 #pragma unroll
         for (int q = 0; q < 2 * FB; ++q)
             load_values(0, q);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int s = -3; s < 0; ++s) {
-            if (s == -1)
-                load_codes(1, 0);
+        auto y_and_values = [&](int slab, int unit, int half) {
             __builtin_amdgcn_sched_barrier(0);
+            if (slab < S) {
 #pragma unroll
-            for (int q = 0; q < 2 * NB; ++q)
-                load_y(s + 3, q);
+                for (int q = 0; q < 2 * NB; ++q)
+                    load_y(slab, q);
+            }
             __builtin_amdgcn_sched_barrier(0);
+            if (2 * unit < S) {
 #pragma unroll
-            for (int q = 0; q < FB; ++q)
-                load_values(s == -1 ? 2 : 1, q + (s == -2 ? FB : 0));
+                for (int q = 0; q < FB; ++q)
+                    load_values(unit, q + half * FB);
+            }
             __builtin_amdgcn_sched_barrier(0);
-        }
-        wait_loads<FB + 2 * (2 * NB + FB) + 1>();   // the codes, unit 0 and the y of slab 0
+        };
+        y_and_values(0, 1, 0);
+        y_and_values(1, 1, 1);
+        if (S > kMSlabs)
+            load_codes(1, 0);
+        y_and_values(2, 2, 0);
+        // the codes, unit 0 and the y of slab 0 have landed
+        if (S > 4)
+            wait_loads<FB + 2 * (2 * NB + FB) + 1>();
+        else if (S > 2)
+            wait_loads<2 * (2 * NB + FB)>();
+        else if (S == 2)
+            wait_loads<2 * NB>();
+        else
+            wait_loads<0>();
+        static_assert(kMSlabs == 4, "the first of these waits counts a part of the codes");
         block_barrier();
         Frags fa, fb;
 #pragma unroll
@@ -319,9 +329,13 @@ __global__ __launch_bounds__(256) void down_sparse24_kernel(
 #pragma unroll
         for (int i = 0; i < FB; ++i)
             read_codes(codes, 0, i);
-        auto body = [&](int s, auto odd_tag) {
+        // LEFT: how many slabs follow, 5 for all that request a half unit of values (an even slab does that with four
+        // left too).  Below 4 the slab may be an even or an odd one.
+        auto body = [&](int s, auto odd_tag, auto left_tag) {
             constexpr bool ODD = decltype(odd_tag)::value;
-            constexpr int kLoads = 2 * NB + FB + (ODD ? 1 : 0);
+            constexpr int LEFT = decltype(left_tag)::value;
+            constexpr int kCodes = LEFT >= 4 && ODD ? 1 : 0;
+            constexpr int kLoads = LEFT >= 5 ? 2 * NB + FB + kCodes : LEFT >= 3 ? 2 * NB + kCodes : 0;
 #pragma unroll
             for (int q = 0; q < kMfmas; ++q) {   // K step 0
 #pragma unroll
@@ -330,39 +344,62 @@ __global__ __launch_bounds__(256) void down_sparse24_kernel(
                 mfma(fa, codes, 0, q);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            // The y of slab s + 1, requested in step s - 2 behind the codes, has landed, and the values, which are
-            // requested earlier; the values of step s - 2 and what step s - 1 requested may be in flight.
-            wait_loads<FB + 2 * NB + FB>();
-            block_barrier();
+            if constexpr (LEFT > 0) {
+                // The y of slab s + 1, requested in step s - 2 behind the codes, has landed, and the values, which are
+                // requested earlier; the values of step s - 2 and what step s - 1 requested may be in flight: both
+                // halves of a unit and the y of slab s + 2, or as much of that as is there whatever slab this is.
+                wait_loads<LEFT >= 4 ? FB + 2 * NB + FB : LEFT == 3 ? FB + 2 * NB : LEFT == 2 ? 2 * NB : 0>();
+                block_barrier();
+            }
+            if constexpr (LEFT == 3) {
+                if (s & 1)
+                    step_load(s, true, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
 #pragma unroll
-            for (int q = 0; q < kMfmas; ++q) {   // K step 1; past the last slab the reads are of no use
+            for (int q = 0; q < kMfmas; ++q) {   // K step 1
 #pragma unroll
                 for (int x = q * kLoads / kMfmas; x < (q + 1) * kLoads / kMfmas; ++x) {   // in this order
-                    step_load(s, ODD, x);
+                    step_load(s, kCodes != 0, x);
                     __builtin_amdgcn_sched_barrier(0);
                 }
+                if constexpr (LEFT > 0) {
 #pragma unroll
-                for (int x = q; x < kReads + FB; x += kMfmas) {
-                    if (x < kReads)
-                        read_wide(fa, s + 1, 0, x);
-                    else
-                        read_codes(codes_next, s + 1, x - kReads);
+                    for (int x = q; x < kReads + FB; x += kMfmas) {
+                        if (x < kReads)
+                            read_wide(fa, s + 1, 0, x);
+                        else
+                            read_codes(codes_next, s + 1, x - kReads);
+                    }
                 }
                 mfma(fb, codes, 1, q);
                 __builtin_amdgcn_sched_barrier(0);
             }
+            if constexpr (LEFT > 0) {
 #pragma unroll
-            for (int i = 0; i < FB; ++i)
-                codes[i] = codes_next[i];
+                for (int i = 0; i < FB; ++i)
+                    codes[i] = codes_next[i];
+            }
         };
+        using Even = std::false_type;
+        using Odd = std::true_type;
+        using Steady = std::integral_constant<int, 5>;
         int s = 0;
-        for (; s + 1 < S; s += 2) {
-            body(s, std::false_type{});
-            body(s + 1, std::true_type{});
+        for (; s + 6 < S; s += 2) {
+            body(s, Even{}, Steady{});
+            body(s + 1, Odd{}, Steady{});
         }
-        if (s < S)
-            body(s, std::false_type{});
-        wait_loads<0>();   // the empty parts would be written over the finished tile
+        if (s + 4 < S)
+            body(s++, Even{}, Steady{});
+        if (s + 4 < S)
+            body(s++, Odd{}, std::integral_constant<int, 4>{});
+        if (s + 3 < S)
+            body(s++, Even{}, std::integral_constant<int, 3>{});
+        if (s + 2 < S)
+            body(s++, Even{}, std::integral_constant<int, 2>{});
+        if (s + 1 < S)
+            body(s++, Even{}, std::integral_constant<int, 1>{});
+        body(s, Even{}, std::integral_constant<int, 0>{});
     } else {
     // ---- main loop.  A slab is two K steps of FB NB sparse MFMAs (16).  Under the MFMAs of K step 0 go
     // the fragment reads of K step 1; then one barrier - slab s + 1 has landed, nobody reads slab
