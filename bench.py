@@ -45,8 +45,8 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 # of its kernel is the one the counters were taken on; otherwise `traffic` is null.
 MEASURED_TRAFFIC = {
     "stage1": {"sources": ("calib.hip", "tile_order.h"),
-               "sha256": "d28a5b73bf547201ce7d682dee56ea4fdc71a7170f9bcc6d6353eeca20d508dd",
-               "bytes": (37496601 * 2.0 + 88064) * 1024},
+               "sha256": "84931e6a59fa4bffb1b2cd62e398d8640fe910f7e3b001f4de554d0b4daf2489",
+               "bytes": (38209297 * 2.0 + 88064) * 1024},
     # the step's two batched launches: Gate + Up, Down
     "stage2": {"sources": ("nm.hip", "select.h"), "sha256": "6e0c1d7b4feaa3f4533cbef910c1dec8f06fc37d7cf336a813278e5259bdbcc9",
                "bytes": ((88450.5 * 2.0 + 176132.6) + (44504.0 * 2.0 + 88070.4)) * 1024},
