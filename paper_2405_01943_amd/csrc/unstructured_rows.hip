@@ -476,7 +476,8 @@ RowlinesPlan plan_rowlines(int64_t rows, int64_t cols, int64_t ld, int dt, const
     // Except with a mask on short lines of many rows, where rowlines_kernel's workgroups do not share a compute unit: bf16
     // 4096 x 2048 29 24, 8192 x 2048 49 36, 28672 x 1032 122 81, 28672 x 4096 221 152, f32 4096 x 2048 25.2 24.2, 8192 x
     // 1032 31 31, 28672 x 2048 131 110.  Longer lines: bf16 8192 x 4600 74 74, 8192 x 5400 83 84, 8192 x 7000 98
-    // 119, f32 8192 x 2400 47 56, 28672 x 2400 149 171.  Below 10 MB: bf16 4096 x 1032 23.6 24.3, 4096 x 1400 25.2 25.5 (2048 x 2048 17 18, but 3000 x 2048 27 21).
+    // 119, f32 8192 x 2400 47 56, 28672 x 2400 149 171.  Below 10 MB: bf16 4096 x 1032 23.6 24.3, 4096 x 1400
+    // 25.2 25.5 (2048 x 2048 17 18, but 3000 x 2048 27 21).
     const int64_t vpl = cols / vec_elems(dt);
     const bool held = rows <= 1024 || (mask_out && rows >= 4096 && vpl <= 512 && rows * vpl >= 640 << 10);
     p.held_slots = !held || vpl > 4096 ? 0 : vpl <= 1024 ? 1 : vpl <= 2048 ? 2 : 4;
